@@ -426,6 +426,13 @@ hipError_t launch_chain(const Dims& d, const double* nodes, const double* densit
   return hipGetLastError();
 }
 
+hipError_t launch_source_finalize(const Dims& d, int parts, const double4* geo,
+                                  const double2* spart, double* sg, hipStream_t s) {
+  hipLaunchKernelGGL(k_source_finalize, dim3((d.N + 255) / 256), dim3(256), 0, s, d.N, d.kind,
+                     parts, geo, spart, sg);
+  return hipGetLastError();
+}
+
 hipError_t launch_make_G(const Dims& d, const double* cot, double2* G, hipStream_t s) {
   const int n = d.Mc * d.nk;
   hipLaunchKernelGGL(k_make_G, dim3((n + 255) / 256), dim3(256), 0, s, d.Mc, d.T, d.nk, cot, G);

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/qbx.h"
+#include "qbx_far.h"
 #include "qbx_internal.h"
 #include "qbx_special.h"
 
@@ -180,7 +181,9 @@ Layout make_layout(const Dims& d) {
   L.tape = take(sizeof(double2) * (size_t)d.Mc * d.nk * 4);
   L.G = take(sizeof(double2) * (size_t)d.nk * d.Mc);
   L.cg = take(sizeof(double) * (size_t)d.Mc * 8);
-  L.spart = take(sizeof(double2) * (size_t)std::max(d.n_csplit, d.n_cb) * src_slots(d.kind) * d.N);
+  int n_sp = std::max(d.n_csplit, d.n_cb);
+  if (far_applies(d)) n_sp = std::max(n_sp, 8);   // the near source passes' shares
+  L.spart = take(sizeof(double2) * (size_t)n_sp * src_slots(d.kind) * d.N);
   L.cpart = take(sizeof(double) * (size_t)d.n_sb * d.Mc * 4);
   L.sg = take(sizeof(double) * (size_t)d.N * 8);
   L.scratch = take(sizeof(double) * (16 + (size_t)d.Mc));
@@ -196,6 +199,12 @@ Layout make_layout(const Dims& d) {
   L.apart = take(sizeof(double2) * (size_t)d.n_asplit * (d.nk + 2) * d.T);
   L.gtw = take(sizeof(double) * (size_t)d.T * 2);
   L.gde = take(sizeof(double2) * (size_t)d.nk * d.T);
+  L.far = 0;
+  if (far_applies(d)) {
+    L.far = take(sizeof(FarItem));
+    FarItem it;
+    far_layout(d, true, take, &it);
+  }
   L.total = o;
   return L;
 }
@@ -203,7 +212,7 @@ Layout make_layout(const Dims& d) {
 // The arrays the plain forward alone uses (tables, source grid, centers, J
 // tables without the order-weighted block, forward partial sums), packed; the
 // other offsets are left at 0 and must not be used.
-Layout make_forward_layout(const Dims& d) {
+Layout make_forward_layout(const Dims& d, bool far) {
   Layout L{};
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -219,6 +228,11 @@ Layout make_forward_layout(const Dims& d) {
   L.ctr = take(sizeof(CenterRec) * (size_t)d.Mc);
   L.jtab = take(sizeof(double) * (size_t)d.Mc * d.NJ);
   L.partial = take(sizeof(double2) * (size_t)d.n_split * d.nk * d.Mc);
+  if (far && far_applies(d)) {
+    L.far = take(sizeof(FarItem));
+    FarItem it;
+    far_layout(d, false, take, &it);
+  }
   L.total = o;
   return L;
 }
@@ -297,14 +311,40 @@ static void timer_clear() {
   }
 }
 
-// tables + source grid + centers into the workspace
+// the item of a call's far sums: the offsets of layout L (full: make_layout's, else
+// make_forward_layout's), for plain pairs
+static FarItem far_item_of(const Dims& d, const Layout& L, bool full, bool fwd, bool bwd) {
+  size_t o = align256(L.far + sizeof(FarItem));
+  auto take = [&](size_t bytes) {
+    const size_t a = o;
+    o = align256(o + bytes);
+    return a;
+  };
+  FarItem it;
+  far_layout(d, full, take, &it);
+  it.k = d.k;
+  it.geo = it.fgeo = L.geo / sizeof(double);
+  it.dens = it.fdens = L.dens / sizeof(double);
+  it.ctr = L.ctr / sizeof(double);
+  it.jtab = L.jtab / sizeof(double);
+  it.G = it.fG = L.G / sizeof(double);
+  it.bnd = L.bnd / sizeof(double);
+  it.partial = L.partial / sizeof(double);
+  it.cg = L.cg / sizeof(double);
+  it.spart = L.spart / sizeof(double);
+  far_shape(&it, fwd, bwd);
+  return it;
+}
+
+// tables + source grid + centers into the workspace (it: and the far sums' item)
 static int prepare(const Dims& d, const Layout& L, const double* nodes, const double* density,
-                   void* ws, hipStream_t stream) {
+                   void* ws, hipStream_t stream, const FarItem* it = nullptr) {
   hipError_t e = launch_tables(d, at<double>(ws, L.tables), stream);
   if (e != hipSuccess) return device_fail(e, "tables kernel");
   e = launch_upsample(d, nodes, density, at<double>(ws, L.tables), at<double4>(ws, L.geo),
                       at<double2>(ws, L.dens), at<double>(ws, L.wgt), at<double>(ws, L.h),
-                      at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab), stream);
+                      at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab), stream, it,
+                      at<FarItem>(ws, L.far));
   if (e != hipSuccess) return device_fail(e, "upsample kernel");
   return QBX_OK;
 }
@@ -337,8 +377,64 @@ const NodeDiff& node_diff() {
   return D;
 }
 
+// the adjoint without a tape, far pairs through panel expansions: the density's gradient
+// needs the cotangents' field at the sources, the nodes' also the densities' field at
+// the centers
+static int run_adjoint_far(const Dims& d, const Layout& L, const double* nodes,
+                           const double* density, const double* cotangent, double* grad_density,
+                           double* grad_nodes, void* ws, hipStream_t stream) {
+  const bool geom = grad_nodes != nullptr;
+  const FarItem it = far_item_of(d, L, true, geom, true);
+  int rc = prepare(d, L, nodes, density, ws, stream, &it);
+  if (rc) return rc;
+  double* w = static_cast<double*>(ws);
+  const FarItem* dev = at<FarItem>(ws, L.far);
+  const FarBlocks one{dev, nullptr, 1};
+  hipError_t e = launch_make_G(d, cotangent, at<double2>(ws, L.G), stream);
+  if (e != hipSuccess) return device_fail(e, "cotangent kernel");
+  e = far_fields(far_single(it, dev), nodes, w, geom, true, geom ? 2 : -1, true, geom, true,
+                 stream);
+  if (e != hipSuccess) return device_fail(e, "panel expansion kernels");
+  timer_begin(geom ? 4 : 1, stream);
+  if (geom)
+    e = launch_near(kNearCenters, d.p, d.kind, one, far_blocks(it, kStepCenters), w, nullptr,
+                    stream);
+  if (e == hipSuccess)
+    e = launch_near(geom ? kNearSources : kNearDensity, d.p, d.kind, one,
+                    far_blocks(it, kStepChunks), w, nullptr, stream);
+  timer_end(geom ? 4 : 1, stream);
+  if (e != hipSuccess) return device_fail(e, "near adjoint kernels");
+  e = launch_source_finalize(d, it.nsrc, at<double4>(ws, L.geo), at<double2>(ws, L.spart),
+                             at<double>(ws, L.sg), stream);
+  if (e == hipSuccess)
+    e = launch_chain(d, nodes, density, at<double>(ws, L.tables), at<double>(ws, L.sg),
+                     at<double>(ws, L.cg), nullptr, nullptr, grad_density, grad_nodes, stream);
+  return e == hipSuccess ? QBX_OK : device_fail(e, "adjoint chain kernels");
+}
+
+// the forward with the far pairs through panel expansions, the near ones one by one
+static int run_forward_far(const Dims& d, const Layout& L, const double* nodes,
+                           const double* density, double* out, void* ws, hipStream_t stream,
+                           bool timed) {
+  const bool full = L.tape != 0;   // make_layout's offsets
+  const FarItem it = far_item_of(d, L, full, true, false);
+  int rc = prepare(d, L, nodes, density, ws, stream, &it);
+  if (rc) return rc;
+  double* w = static_cast<double*>(ws);
+  const FarItem* dev = at<FarItem>(ws, L.far);
+  hipError_t e = far_fields(far_single(it, dev), nodes, w, true, false, 0, false, false, true,
+                            stream);
+  if (e != hipSuccess) return device_fail(e, "panel expansion kernels");
+  if (timed) timer_begin(0, stream);
+  e = launch_near(kNearForward, d.p, d.kind, FarBlocks{dev, nullptr, 1},
+                  far_blocks(it, kStepCenters), w, out, stream);
+  if (timed) timer_end(0, stream);
+  return e == hipSuccess ? QBX_OK : device_fail(e, "near forward kernel");
+}
+
 int run_forward(const Dims& d, const Layout& L, const double* nodes, const double* density,
                 double* out, void* ws, hipStream_t stream, bool timed) {
+  if (L.far) return run_forward_far(d, L, nodes, density, out, ws, stream, timed);
   int rc = prepare(d, L, nodes, density, ws, stream);
   if (rc) return rc;
   if (timed) timer_begin(0, stream);
@@ -422,17 +518,7 @@ int qbx_layer_potential_ext(const qbx_geometry* g, const double* density, double
   const Layout L = make_layout(d);
   if (ws_bytes < L.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
-  rc = prepare(d, L, g->nodes, density, ws, stream);
-  if (rc) return rc;
-  timer_begin(0, stream);
-  hipError_t e = launch_forward(d, at<double4>(ws, L.geo), at<double2>(ws, L.dens),
-                                at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab),
-                                at<double2>(ws, L.partial), stream);
-  timer_end(0, stream);
-  if (e != hipSuccess) return device_fail(e, "forward kernel");
-  e = launch_finalize(d, at<double2>(ws, L.partial), out, stream);
-  if (e != hipSuccess) return device_fail(e, "finalize kernel");
-  return QBX_OK;
+  return run_forward(d, L, g->nodes, density, out, ws, stream);
 }
 
 }  // extern "C"
@@ -588,6 +674,27 @@ int qbx_layer_potential_gradient(const qbx_geometry* g, const double* density, d
   const Layout L = make_layout(d);
   if (ws_bytes < L.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
+  if (L.far) {
+    const FarItem it = far_item_of(d, L, true, true, false);
+    rc = prepare(d, L, g->nodes, density, ws, stream, &it);
+    if (rc) return rc;
+    double* w = static_cast<double*>(ws);
+    const FarItem* dev = at<FarItem>(ws, L.far);
+    hipError_t e = launch_order_weighted(d, at<double>(ws, L.jtab), stream);
+    if (e != hipSuccess) return device_fail(e, "order-weighted table kernel");
+    e = far_fields(far_single(it, dev), g->nodes, w, true, false, 1, false, false, true, stream);
+    if (e != hipSuccess) return device_fail(e, "panel expansion kernels");
+    timer_begin(5, stream);
+    e = launch_near(kNearGradient, d.p, d.kind, FarBlocks{dev, nullptr, 1},
+                    far_blocks(it, kStepCenters), w, nullptr, stream);
+    timer_end(5, stream);
+    if (e != hipSuccess) return device_fail(e, "near target-derivative kernel");
+    Dims one = d;   // a single partial sum per center
+    one.n_tsplit = 1;
+    e = launch_finalize_gradient(one, at<CenterRec>(ws, L.ctr), at<double2>(ws, L.partial), grad,
+                                 dn, stream);
+    return e == hipSuccess ? QBX_OK : device_fail(e, "gradient finalize kernel");
+  }
   rc = prepare(d, L, g->nodes, density, ws, stream);
   if (rc) return rc;
   hipError_t e = launch_order_weighted(d, at<double>(ws, L.jtab), stream);
@@ -619,6 +726,9 @@ int qbx_layer_potential_adjoint(const qbx_geometry* g, const double* density, do
   if (ws_bytes < L.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
   if (!grad_density && !grad_nodes) return QBX_OK;
+  if (L.far && !tape)
+    return run_adjoint_far(d, L, g->nodes, density, cotangent, grad_density, grad_nodes, ws,
+                           stream);
   rc = prepare(d, L, g->nodes, density, ws, stream);
   if (rc) return rc;
   hipError_t e;

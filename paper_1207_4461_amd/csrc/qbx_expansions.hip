@@ -294,7 +294,7 @@ struct ExpLayout {
 
 ExpLayout make_expansion_layout(const Dims& d) {
   ExpLayout E;
-  E.base = make_forward_layout(d);
+  E.base = make_forward_layout(d, false);
   size_t o = E.base.total;
   auto take = [&](size_t bytes) {
     size_t at = o;

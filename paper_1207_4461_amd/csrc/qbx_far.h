@@ -1,0 +1,255 @@
+// Far sums of the pair kernels through panel expansions: shared declarations of
+// qbx_far.hip (the expansions) and qbx_near.hip (the pairs that stay pairs).
+//
+// The truncated expansion of Section 2 at a center c is linear in the field of the
+// sources near c: its coefficients a_n, |n| <= p, are those of the local expansion of
+// that field about c.  For a source panel far from a target panel that field is
+// smooth, and three exact translations (Graf's addition theorem, eq. graf-addition)
+// carry it from the sources of the one to the centers of the other at a cost per pair
+// of panels instead of per pair of points:
+//
+//   M_m = sum_j q_j J_m(k r_j) e^{-i m alpha_j}        about the source panel's mean b_A,
+//   L_l = sum_A sum_m M_m F_{m-l}(b_B - b_A)           F_n(D) = H_n(k|D|) e^{i n arg D},
+//   a_n = sum_l L_l J_{l-n}(k|tau|) e^{i(l-n) arg tau}  tau = c - b_B,
+//
+// and the value is sum_n a_n J_n(k R) e^{i n theta} over |n| <= p, the truncation of
+// the pair kernels.  The double layer takes the normal derivative of the regular
+// waves in M_m.  Orders |m|, |l| <= kFarQ are kept; two panels are taken this way only
+// where the terms beyond are below 1e-17 of the leading one (far_adm), so that the
+// sums differ from the pair sums by rounding.  The same holds for groups of kFarGroup
+// consecutive panels, which take the pairs of groups that are far enough as one pair.
+// Every other pair of panels is near, and its pairs are evaluated one by one.
+//
+// The adjoint is the transpose: T_l = sum_c G_c E_l(c) over the centers of a panel
+// (E_l the value of the wave l at the center's target), carried by the same
+// translation to the source panels, where the field's value and derivatives at each
+// source are its gradients.
+#pragma once
+
+#include "qbx_internal.h"
+
+namespace qbx {
+
+constexpr int kFarQ = 24;        // order of the expansions
+constexpr int kFarLo = 12;       // order where every lane's panel is farther still
+constexpr int kFarW = 2 * kFarQ + 1;
+constexpr int kFarGroup = 8;     // panels of a group
+
+// One cluster (a panel or a group): mean of its nodes, radius of its sources (rs) and
+// of its centers with their disks (rt), the distances from which an expansion of order
+// kFarQ (ds, dt) and kFarLo (dsl, dtl) resolves them, and, for the near/far split's
+// groups, the radius of the panel means (rb) and gamma times the largest node radius
+// (gr): groups at least that far hold no pair of panels within gamma radii.
+struct FarRec {
+  double bx, by, rs, rt, ds, dt, dsl, dtl, rb, gr;
+};
+
+// Symmetric in its arguments bit for bit (no contraction; maxima and sums of two), so
+// every kernel and both directions take the same decision.  False for NaN positions.
+__device__ __forceinline__ bool far_adm(const FarRec& a, const FarRec& b) {
+#pragma clang fp contract(off)
+  const double dx = a.bx - b.bx, dy = a.by - b.by;
+  const double d2 = dx * dx + dy * dy;
+  const double t0 = fmax(fmax(a.ds + b.rt, b.ds + a.rt), fmax(a.dt + b.rs, b.dt + a.rs));
+  const double t = fmax(t0, (a.rb + b.rb) + fmax(a.gr, b.gr));
+  return d2 >= t * t;
+}
+// the same for the order kFarLo
+__device__ __forceinline__ bool far_adm_lo(const FarRec& a, const FarRec& b) {
+#pragma clang fp contract(off)
+  const double dx = a.bx - b.bx, dy = a.by - b.by;
+  const double d2 = dx * dx + dy * dy;
+  const double t = fmax(fmax(a.dsl + b.rt, b.dsl + a.rt), fmax(a.dtl + b.rs, b.dtl + a.rs));
+  return d2 >= t * t;
+}
+
+// gamma relation of the near/far split (qbx_split.hip): every operation rounded on
+// its own, the same decision for any IEEE evaluation of the formula
+__device__ __forceinline__ bool panels_near(double4 a, double4 b, double g2) {
+#pragma clang fp contract(off)
+  const double dx = a.x - b.x;
+  const double dy = a.y - b.y;
+  const double d2 = dx * dx + dy * dy;
+  return d2 < g2 * fmax(a.z, b.z);
+}
+
+// Which pairs of panels go through expansions: the pairs of far groups at once, the
+// remaining far pairs of panels one by one.  With the gamma relation (bnd set) only
+// pairs that it calls far.
+struct FarRel {
+  const FarRec* r0;    // panels
+  const FarRec* r1;    // groups, or null
+  const double4* bnd;  // gamma relation's panels, or null
+  double g2;
+};
+__device__ __forceinline__ bool far_panels(const FarRel& R, int a, int b) {
+  if (R.r1 && far_adm(R.r1[a / kFarGroup], R.r1[b / kFarGroup])) return true;
+  if (R.bnd && panels_near(R.bnd[a], R.bnd[b], R.g2)) return false;
+  return far_adm(R.r0[a], R.r0[b]);
+}
+
+// One contour of a call.  Offsets count doubles from the workspace base.
+struct FarItem {
+  int P, C1;            // panels, groups (0: none)
+  int T, N, qs, Mc, n_sides, nk, kind, p, NJ, side;
+  int fqs;              // far sources per panel (qs; the split: 16, the nodes)
+  int pt;               // far targets are points (the split: the nodes)
+  int V;                // vectors translated: kinds forward, then kinds backward
+  int vf;               // of them forward (0 or nk)
+  int nsrc;             // waves per 64-source chunk in the near source passes
+  int n0, n1;           // blocks of sources per 64 target panels / groups
+  double k, g2;         // g2: the split's gamma squared, or 0
+  size_t node_off;      // doubles into the nodes
+  size_t out_off;       // doubles into out
+  size_t geo, dens, ctr, jtab, G;      // pair sources, centers, cotangent weights
+  size_t fgeo, fdens, fG;              // far sources and far targets' weights
+  size_t bnd, rec0, rec1;
+  size_t ncount, nlist;                // int arrays (still offsets in doubles)
+  size_t rows0, rows1;                 // double2 [V][2][C][kFarW]
+  size_t lp0, lp1;                     // double2 [n][V][2][kFarQ + 1][C]
+  size_t ls0, ls1;                     // double2 [V][C][kFarW]
+  size_t tp0, tp1;                     // double2 [n_sides or 2 n_sides][nk][C][kFarW]
+  size_t fu;                           // double2 [nk][Mc][2] far sums per center
+  size_t fc;                           // double [Mc][4] far center gradients
+  size_t fs;                           // double2 [nk + 2][far sources]
+  size_t partial, cg, spart;           // near outputs: gradient sums, center / source gradients
+};
+
+// item of a block: prefix sums of the items' block counts, or a single item
+struct FarBlocks {
+  const FarItem* items;
+  const int* pre;   // null: one item
+  int n;
+};
+__device__ __forceinline__ const FarItem* far_item(const FarBlocks& B, int block, int* local) {
+  int s = 0;
+  if (B.pre) {
+    int hi = B.n;   // pre[s] <= block < pre[hi]
+    while (hi - s > 1) {
+      const int mid = (s + hi) >> 1;
+      if (B.pre[mid] <= block) s = mid;
+      else hi = mid;
+    }
+    block -= B.pre[s];
+  }
+  *local = block;
+  return B.items + s;
+}
+
+// the grids of the steps, per item
+enum FarStep {
+  kStepClusters,   // panels and groups, one wave each
+  kStepM2L, kStepSum,
+  kStepTargets,    // 64 targets of one side
+  kStepRows, kStepSources, kStepLists,
+  kStepCenters,    // four centers, one wave each (qbx_near.hip)
+  kStepChunks,     // four chunks of 64 sources (qbx_near.hip)
+};
+int far_blocks(const FarItem& it, FarStep step);
+
+// the near pairs' passes (qbx_near.hip); out: kNearForward's result
+enum NearPass { kNearForward, kNearGradient, kNearCenters, kNearSources, kNearDensity };
+hipError_t launch_near(NearPass pass, int p, int kind, const FarBlocks& B, int blocks,
+                       double* ws, double* out, hipStream_t s);
+
+// A call's items on the device and the grids of its steps.  One contour: the item in the
+// workspace and no prefix arrays; a batch: every step's prefix sums of block counts.
+struct FarPlan {
+  FarBlocks at[kStepLists + 1];
+  int blocks[kStepLists + 1];
+};
+// the plan of one item (device copy at `dev`)
+FarPlan far_single(const FarItem& it, const FarItem* dev);
+// records and near lists, multipoles (fwd) and their transpose (bwd), translations, and
+// what the caller wants of them: values or sums at the targets (eval: the mode of
+// launch_far_eval, or -1), gradients at the sources (src; geom: position and normal too)
+hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fwd, bool bwd,
+                      int eval, bool src, bool geom, bool lists, hipStream_t s);
+// the offsets of an item's far arrays from take(bytes) (returning a byte offset), with
+// bwd those of the adjoint too; V, n0, n1 are then set per call (far_shape)
+template <typename Take>
+inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it);
+// vectors and translation shares of a call: fwd / bwd as in far_fields
+void far_shape(FarItem* it, bool fwd, bool bwd);
+
+hipError_t launch_far_recs(const FarBlocks& B, int blocks, const double* nodes, double* ws,
+                           hipStream_t s);
+hipError_t launch_far_lists(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+hipError_t launch_far_p2m(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+hipError_t launch_far_m2l(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+hipError_t launch_far_lsum(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+// mode 0 values, 1 target derivatives, 2 center gradients contracted with G
+hipError_t launch_far_eval(int mode, const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+hipError_t launch_far_t(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+hipError_t launch_far_rows(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+hipError_t launch_far_src(const FarBlocks& B, int blocks, double* ws, bool geom, hipStream_t s);
+
+
+// fewest panels that are worth the expansions, largest center distance r taken (a disk
+// that reaches over many panels leaves every panel near)
+constexpr int kFarMinPanels = 96;
+constexpr int kFarGroupPanels = 512;   // from here on groups too
+inline bool far_applies(const Dims& d) {
+  return d.P >= kFarMinPanels && d.center_rule == 0 && d.r <= 1.0;
+}
+// blocks of the translation aimed for (256 compute units, two blocks each resident)
+constexpr int kFarM2LBlocks = 512;
+inline int far_share(int C, int V) {
+  const int tb = (C + kWave - 1) / kWave;
+  int n = (kFarM2LBlocks + tb * V * 2 - 1) / (tb * V * 2);
+  const int most = (C + 3) / 4;
+  if (n > most) n = most;
+  return n < 1 ? 1 : n;
+}
+inline size_t far_lp_doubles(int C, int Vmax) {
+  size_t most = 0;   // over the vector counts a call may have
+  for (int V = 1; V <= Vmax; ++V) {
+    const size_t n = (size_t)far_share(C, V) * V * 2 * (kFarQ + 1) * C * 2;
+    if (n > most) most = n;
+  }
+  return most;
+}
+
+template <typename Take>
+inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it) {
+  auto at = [&](size_t doubles) { return take(sizeof(double) * doubles) / sizeof(double); };
+  *it = FarItem{};
+  it->P = d.P;
+  it->C1 = d.P >= kFarGroupPanels ? (d.P + kFarGroup - 1) / kFarGroup : 0;
+  it->T = d.T;
+  it->N = d.N;
+  it->qs = d.qs;
+  it->fqs = d.qs;
+  it->Mc = d.Mc;
+  it->n_sides = d.n_sides;
+  it->nk = d.nk;
+  it->kind = d.kind;
+  it->p = d.p;
+  it->NJ = d.NJ;
+  it->side = d.side;
+  const int Vmax = d.nk * (bwd ? 2 : 1);
+  const size_t C0 = d.P, C1 = it->C1;
+  it->rec0 = at(sizeof(FarRec) / sizeof(double) * C0);
+  it->rec1 = at(sizeof(FarRec) / sizeof(double) * C1);
+  it->ncount = at((C0 + 1) / 2);
+  it->nlist = at(C0 * kNearCap / 2);
+  it->rows0 = at((size_t)Vmax * 2 * C0 * kFarW * 2);
+  it->rows1 = at((size_t)Vmax * 2 * C1 * kFarW * 2);
+  it->lp0 = at(far_lp_doubles(d.P, Vmax));
+  it->lp1 = at(it->C1 ? far_lp_doubles(it->C1, Vmax) : 0);
+  it->ls0 = at((size_t)Vmax * C0 * kFarW * 2);
+  it->ls1 = at((size_t)Vmax * C1 * kFarW * 2);
+  it->fu = at((size_t)d.nk * d.Mc * (bwd ? 4 : 2));
+  if (bwd) {
+    it->tp0 = at((size_t)d.n_sides * d.nk * C0 * kFarW * 2);
+    it->tp1 = at((size_t)2 * d.n_sides * d.nk * C1 * kFarW * 2);
+    it->fc = at((size_t)d.Mc * 4);
+    it->fs = at((size_t)(d.nk + 2) * d.N * 2);
+  }
+  // waves of the near source passes: about 8192, a chunk's list cut into at most eight
+  const int chunks = (d.N + kWave - 1) / kWave;
+  int ns = (8192 + chunks - 1) / chunks;
+  it->nsrc = ns > 8 ? 8 : ns;
+}
+
+}  // namespace qbx

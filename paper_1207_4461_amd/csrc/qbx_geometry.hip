@@ -9,6 +9,7 @@
 //    n = (y', -x') / |X'| for a counter-clockwise curve (Section 3.2).
 //  * Section 3.3 step 4(a): c = x + s r h_m n with h_m the panel length,
 //    radius R = r h_m, and theta = arg(x - c) = arg(-s n).
+#include "qbx_far.h"
 #include "qbx_internal.h"
 #include "qbx_panel.h"
 #include "qbx_special.h"
@@ -93,7 +94,11 @@ hipError_t launch_order_weighted(const Dims& d, double* jtab, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(128) void k_upsample(Dims d, const double* __restrict__ nodes,
+// item_dev (or null): where the call's item of the far sums goes, which every later
+// kernel reads from memory
+__global__ __launch_bounds__(128) void k_upsample(Dims d, FarItem item,
+                                                  FarItem* __restrict__ item_dev,
+                                                  const double* __restrict__ nodes,
                                                   const double* __restrict__ density,
                                                   const double* __restrict__ tab,
                                                   double4* __restrict__ geo,
@@ -102,14 +107,17 @@ __global__ __launch_bounds__(128) void k_upsample(Dims d, const double* __restri
                                                   double* __restrict__ hpan,
                                                   CenterRec* __restrict__ ctr,
                                                   double* __restrict__ jtab) {
+  if (item_dev && blockIdx.x == 0 && threadIdx.x == 0) *item_dev = item;
   upsample_panel(d, blockIdx.x, nodes, density, tab, geo, dens, wgt, hpan, ctr, jtab);
 }
 
 hipError_t launch_upsample(const Dims& d, const double* nodes, const double* density,
                            const double* tables, double4* geo, double2* dens, double* wgt,
-                           double* h, CenterRec* ctr, double* jtab, hipStream_t s) {
-  hipLaunchKernelGGL(k_upsample, dim3(d.P), dim3(128), 0, s, d, nodes, density, tables, geo, dens,
-                     wgt, h, ctr, jtab);
+                           double* h, CenterRec* ctr, double* jtab, hipStream_t s,
+                           const FarItem* item, FarItem* item_dev) {
+  hipLaunchKernelGGL(k_upsample, dim3(d.P), dim3(128), 0, s, d, item ? *item : FarItem{},
+                     item ? item_dev : nullptr, nodes, density, tables, geo, dens, wgt, h, ctr,
+                     jtab);
   return hipGetLastError();
 }
 

@@ -18,6 +18,8 @@ constexpr int kNearCap = 64;
 
 // per-panel near lists of the split: count[m] and, when count[m] <= kNearCap,
 // list[m * kNearCap + i], i < count[m], the panels near m in ascending order
+struct FarItem;   // qbx_far.h
+
 struct NearLists {
   const int* count;
   const int* list;
@@ -108,6 +110,7 @@ struct Layout {
                    // (density; with the node gradient also position and normal)
   size_t gtw;      // double[T][2] split node adjoint: far weights' tangent gradients
   size_t gde;      // double2[nk][T] split node adjoint: far node density gradients
+  size_t far;      // panel expansions (FarItem, then its arrays), or 0: the pair kernels alone
   size_t total;
 };
 
@@ -143,8 +146,9 @@ int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 int device_fail(hipError_t e, const char* where);
 size_t align256(size_t x);
 Layout make_layout(const Dims& d);
-// the plain forward's arrays only (tables ... partial), packed from offset 0
-Layout make_forward_layout(const Dims& d);
+// the plain forward's arrays only (tables ... partial), packed from offset 0; far: with
+// those of the panel expansions where they apply
+Layout make_forward_layout(const Dims& d, bool far);
 // tables, source grid and centers, then the plain forward and its finalize
 // into out, with the arrays of L (make_layout or make_forward_layout) in ws;
 // timed: bracket the pair kernel with the kernel timer's events when it is on
@@ -155,7 +159,8 @@ int run_forward(const Dims& d, const Layout& L, const double* nodes, const doubl
 hipError_t launch_tables(const Dims& d, double* tables, hipStream_t s);
 hipError_t launch_upsample(const Dims& d, const double* nodes, const double* density,
                            const double* tables, double4* geo, double2* dens, double* wgt,
-                           double* h, CenterRec* ctr, double* jtab, hipStream_t s);
+                           double* h, CenterRec* ctr, double* jtab, hipStream_t s,
+                           const FarItem* item = nullptr, FarItem* item_dev = nullptr);
 hipError_t launch_forward(const Dims& d, const double4* geo, const double2* dens,
                           const CenterRec* ctr, const double* jtab, double2* partial,
                           hipStream_t s);
@@ -237,6 +242,9 @@ hipError_t launch_chain(const Dims& d, const double* nodes, const double* densit
                         const double* tables, const double* sg, const double* cg,
                         const double* gtw, const double* gde, double* grad_density,
                         double* grad_nodes, hipStream_t s);
+// per-source gradients sg from the parts of the source-side sums
+hipError_t launch_source_finalize(const Dims& d, int parts, const double4* geo,
+                                  const double2* spart, double* sg, hipStream_t s);
 hipError_t launch_forward_tape(const Dims& d, const double4* geo, const double2* dens,
                                const CenterRec* ctr, const double* jtab, double2* partial,
                                hipStream_t s);

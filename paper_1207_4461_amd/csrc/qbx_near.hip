@@ -1,0 +1,470 @@
+// Near pairs: the pairs of a center and a source that are evaluated one by one when
+// the far ones are summed otherwise (the panel expansions of qbx_far.hip, the direct rule
+// of the near/far split).  One wave per center walks its target panel's near list, one
+// wave per 64-source chunk the lists of its panels; panels with more than kNearCap near
+// panels are served by a scan of all panels.  The pair bodies are those of the plain
+// kernels (qbx_pair.h).
+#include "qbx_far.h"
+#include "qbx_pair.h"
+#include "qbx_panel.h"
+
+// compiled once per kind, so that the template instances build in parallel
+#ifndef QBX_NEAR_KIND
+#error "compile with -DQBX_NEAR_KIND=1, 2 or 3"
+#endif
+
+namespace qbx {
+
+// near relation of an item: the split's gamma relation, or every pair of panels that no
+// expansion takes; symmetric
+struct NearRel {
+  FarRel R;
+  bool gamma;
+};
+__device__ __forceinline__ NearRel near_rel(const FarItem& it, const double* ro) {
+  NearRel n;
+  n.gamma = it.g2 > 0.0;
+  n.R.r0 = reinterpret_cast<const FarRec*>(ro + it.rec0);
+  n.R.r1 = it.C1 > 0 ? reinterpret_cast<const FarRec*>(ro + it.rec1) : nullptr;
+  n.R.bnd = reinterpret_cast<const double4*>(ro + it.bnd);
+  n.R.g2 = it.g2;
+  return n;
+}
+__device__ __forceinline__ bool is_near(const NearRel& n, int a, int b) {
+  if (n.gamma) return panels_near(n.R.bnd[a], n.R.bnd[b], n.R.g2);
+  FarRel R = n.R;
+  R.bnd = nullptr;
+  return !far_panels(R, a, b);
+}
+
+__device__ __forceinline__ NearLists near_lists(const FarItem& it, const double* ro) {
+  NearLists l;
+  l.count = reinterpret_cast<const int*>(ro + it.ncount);
+  l.list = reinterpret_cast<const int*>(ro + it.nlist);
+  return l;
+}
+
+// f(pan) for every panel near panel m (wave-uniform), in ascending order: from m's list
+// when it fits, else by the wave's scan of all NP panels
+template <typename F>
+__device__ __forceinline__ void for_near_panels(int m, const NearRel& R, int NP, NearLists nl,
+                                                int lane, F&& f) {
+  const int cnt = nl.count[m];
+  if (cnt <= kNearCap) {
+    const int* __restrict__ L = nl.list + (size_t)m * kNearCap;
+    for (int i = 0; i < cnt; ++i) f(L[i]);
+    return;
+  }
+  for (int w0 = 0; w0 < NP; w0 += kWave) {
+    const int mp = w0 + lane;
+    const bool nr = mp < NP && is_near(R, m, mp);
+    unsigned long long mask = __ballot(nr);
+    while (mask) {
+      const int pan = w0 + __builtin_ctzll(mask);
+      mask &= mask - 1;
+      f(pan);
+    }
+  }
+}
+
+// f(m) once for every panel m near any of the panels pa..pb (a 64-source chunk's
+// panels), of those every ns-th starting at the sp-th: from their lists, each m at the
+// first list that holds it, when every list fits; else by the wave's scan (ascending)
+template <typename F>
+__device__ __forceinline__ void for_near_any(int pa, int pb, const NearRel& R, int NP,
+                                             NearLists nl, int lane, int sp, int ns, F&& f) {
+  bool fits = true;
+  for (int ps = pa; ps <= pb; ++ps) fits = fits && nl.count[ps] <= kNearCap;
+  int n = 0;
+  if (fits) {
+    for (int ps = pa; ps <= pb; ++ps) {
+      const int* __restrict__ L = nl.list + (size_t)ps * kNearCap;
+      const int cnt = nl.count[ps];
+      for (int i = 0; i < cnt; ++i) {
+        const int m = L[i];
+        bool seen = false;
+        for (int pq = pa; pq < ps; ++pq) seen = seen || is_near(R, m, pq);
+        if (!seen && n++ % ns == sp) f(m);
+      }
+    }
+    return;
+  }
+  for (int w0 = 0; w0 < NP; w0 += kWave) {
+    const int mt = w0 + lane;
+    bool any = false;
+    if (mt < NP)
+      for (int ps = pa; ps <= pb; ++ps) any = any || is_near(R, mt, ps);
+    unsigned long long mask = __ballot(any);
+    while (mask) {
+      const int m = w0 + __builtin_ctzll(mask);
+      mask &= mask - 1;
+      if (n++ % ns == sp) f(m);
+    }
+  }
+}
+
+// Values.  Plain: out = (i/4) (near + far), the far sums of k_far_eval; split: the near
+// sums alone into partial[kk][ci] (its finalize adds the far rule's).
+template <int P, int KIND>
+__global__ __launch_bounds__(256) void k_near_forward(FarBlocks B, const double* __restrict__ ro,
+                                                      double* __restrict__ wo,
+                                                      double* __restrict__ out) {
+  constexpr bool kS = (KIND & 1) != 0;
+  constexpr bool kD = (KIND & 2) != 0;
+  constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int ci = b * 4 + wave;
+  if (ci >= it.Mc) return;
+  const int m = (ci % it.T) / kQ;                 // the target's panel
+  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
+  const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
+  const CenterRec* C = reinterpret_cast<const CenterRec*>(ro + it.ctr) + ci;
+  const double cx = C->cx, cy = C->cy, ct = C->ct, st = C->st;
+  const double k = it.k, inv_k = 1.0 / k;
+  const int N = it.N, qs = it.qs;
+  const double* Jtab = ro + it.jtab + (size_t)ci * it.NJ;
+  double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
+  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
+    for (int s0 = 0; s0 < qs; s0 += kWave) {
+      if (s0 + lane < qs)
+        forward_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k,
+                                Jtab, sr, si, dr, di);
+    }
+  });
+  Cplx S = {sr, si}, Dd = {k * dr, k * di};
+  if (kS) wave_sum(S);
+  if (kD) wave_sum(Dd);
+  if (lane == 0) {
+    Cplx v[2];
+    v[0] = kS ? S : Dd;
+    v[1] = Dd;
+    if (it.g2 > 0.0) {
+      double2* partial = reinterpret_cast<double2*>(wo + it.partial);
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk)
+        partial[(size_t)kk * it.Mc + ci] = make_double2(v[kk].r, v[kk].i);
+    } else {
+      const double2* fu = reinterpret_cast<const double2*>(ro + it.fu);
+      const int s = ci / it.T, t = ci - s * it.T;
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) {
+        const double2 f = fu[(size_t)kk * it.Mc + ci];
+        double* o = out + it.out_off + 2 * (((size_t)s * NK + kk) * it.T + t);
+        o[0] = -0.25 * (v[kk].i + f.y);   // (i/4)(near + far)
+        o[1] = 0.25 * (v[kk].r + f.x);
+      }
+    }
+  }
+}
+
+// Target derivatives: partial[kk][ci][0..1] = F_R, F_theta over the near sources; plain:
+// with the far ones.
+template <int P, int KIND>
+__global__ __launch_bounds__(256) void k_near_grad(FarBlocks B, const double* __restrict__ ro,
+                                                   double* __restrict__ wo) {
+  constexpr bool kS = (KIND & 1) != 0;
+  constexpr bool kD = (KIND & 2) != 0;
+  constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int ci = b * 4 + wave;
+  const int Mc = it.Mc, NJ = it.NJ;
+  if (ci >= Mc) return;
+  const int m = (ci % it.T) / kQ;
+  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
+  const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
+  const CenterRec* C = reinterpret_cast<const CenterRec*>(ro + it.ctr) + ci;
+  const double cx = C->cx, cy = C->cy, ct = C->ct, st = C->st;
+  const double k = it.k, inv_k = 1.0 / k;
+  const int N = it.N, qs = it.qs;
+  const double* Jtab = ro + it.jtab + (size_t)ci * NJ;
+  const double* Ltab = ro + it.jtab + (size_t)Mc * NJ + (size_t)ci * (NJ / 2);   // l J_l
+  Cplx A[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) A[a][0] = A[a][1] = {0.0, 0.0};
+  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
+    for (int s0 = 0; s0 < qs; s0 += kWave) {
+      if (s0 + lane < qs)
+        grad_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k, Jtab,
+                             NJ / 2, Ltab, A);
+    }
+  });
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) {
+    wave_sum(A[kk][0]);
+    wave_sum(A[kk][1]);
+  }
+  if (lane == 0) {
+    const bool add = !(it.g2 > 0.0);
+    const double2* fu = reinterpret_cast<const double2*>(ro + it.fu);
+    double2* partial = reinterpret_cast<double2*>(wo + it.partial);
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const size_t o = ((size_t)kk * Mc + ci) * 2 + q;
+        const double2 f = add ? fu[o] : make_double2(0.0, 0.0);
+        partial[o] = make_double2(A[kk][q].r + f.x, A[kk][q].i + f.y);
+      }
+  }
+}
+
+// Adjoint, center side: the tape sums over the near sources (K_R, K_theta, grad_v K)
+// contracted with G, plain: plus the far ones (fc); then center_grad_from_sums.
+template <int P, int KIND>
+__global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double* __restrict__ ro,
+                                                      double* __restrict__ wo) {
+  constexpr bool kS = (KIND & 1) != 0;
+  constexpr bool kD = (KIND & 2) != 0;
+  constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int ci = b * 4 + wave;
+  const int Mc = it.Mc;
+  if (ci >= Mc) return;
+  const int m = (ci % it.T) / kQ;
+  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
+  const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
+  const CenterRec* ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
+  const CenterRec* C = ctr + ci;
+  const double cx = C->cx, cy = C->cy, ct = C->ct, st = C->st;
+  const double k = it.k, inv_k = 1.0 / k;
+  const int N = it.N, qs = it.qs;
+  const double* Jtab = ro + it.jtab + (size_t)ci * it.NJ;
+  const int nj = it.NJ / 2;
+  Cplx A[2][5];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int q = 0; q < 5; ++q) A[a][q] = {0.0, 0.0};
+  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
+    for (int s0 = 0; s0 < qs; s0 += kWave) {
+      if (s0 + lane < qs)
+        tape_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k, Jtab,
+                             nj, A);
+    }
+  });
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+    for (int q = 1; q < 5; ++q) wave_sum(A[kk][q]);
+  if (lane == 0) {
+    const double2* G = reinterpret_cast<const double2*>(ro + it.G);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    if (!(it.g2 > 0.0)) {
+      const double* fc = ro + it.fc + (size_t)ci * 4;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] = fc[q];
+    }
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+      const double2 g = G[(size_t)kk * Mc + ci];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] += g.x * A[kk][q + 1].r - g.y * A[kk][q + 1].i;   // Re(G a)
+    }
+    center_grad_from_sums(ci, it.side, it.T, ctr, s[0], s[1], s[2], s[3], wo + it.cg);
+  }
+}
+
+// Adjoint, source side: spart[sp][b][j], b < src_slots(KIND), the plain adjoint's
+// source-side sums over the centers of the target panels near j's panel (every ns-th
+// panel of the chunk's a wave); plain: the first share adds the far sums (fs).
+template <int P, int KIND>
+__global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double* __restrict__ ro,
+                                                      double* __restrict__ wo) {
+  constexpr bool kS = (KIND & 1) != 0;
+  constexpr bool kD = (KIND & 2) != 0;
+  constexpr int NK = kS && kD ? 2 : 1;
+  constexpr int NA = src_slots(KIND);
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int w = b * 4 + wave;
+  const int ns = it.nsrc;
+  const int c = w / ns, sp = w - c * ns;
+  const int N = it.N, qs = it.qs, T = it.T, Mc = it.Mc, NJ = it.NJ;
+  if (c * kWave >= N) return;
+  const int j = c * kWave + lane;
+  const bool valid = j < N;
+  const int jj = valid ? j : N - 1;
+  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
+  const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
+  const CenterRec* __restrict__ ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
+  const double* __restrict__ jtab = ro + it.jtab;
+  const double2* __restrict__ G = reinterpret_cast<const double2*>(ro + it.G);
+  const int mj = jj / qs;
+  const int pa = (c * kWave) / qs;
+  const int pb = min(c * kWave + kWave - 1, N - 1) / qs;
+  const double4 g = geo[jj];
+  double2 q[2];
+  q[0] = dens[jj];
+  q[1] = dens[(size_t)(NK - 1) * N + jj];
+  const double k = it.k, inv_k = 1.0 / k;
+  const int nj = NJ / 2, n_sides = it.n_sides;
+  const NearRel R = near_rel(it, ro);
+  Cplx A[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) A[a] = {0.0, 0.0};
+  for_near_any(pa, pb, R, it.P, near_lists(it, ro), lane, sp, ns, [&](int m) {
+    if (valid && (pa == pb || is_near(R, m, mj))) {
+      for (int si = 0; si < n_sides; ++si) {
+        for (int a = 0; a < kQ; ++a) {
+          const int ci = si * T + m * kQ + a;
+          const int z0 = opaque_zero();
+          const double2 GS = G[(size_t)ci + z0];
+          const double2 GD = NK == 2 ? G[(size_t)Mc + ci + z0] : GS;
+          adjoint_pair<P, KIND>(g, q, ctr + ci + z0, jtab + (size_t)ci * NJ + z0,
+                                g_seed_table + z0, GS, GD, k, inv_k, nj, A);
+        }
+      }
+    }
+  });
+  if (valid) {
+    double2* part = reinterpret_cast<double2*>(wo + it.spart) + (size_t)sp * NA * N;
+    const double2* fs = reinterpret_cast<const double2*>(ro + it.fs);
+    const bool add = sp == 0 && !(it.g2 > 0.0);
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      const double2 f = add ? fs[(size_t)a * N + j] : make_double2(0.0, 0.0);
+      part[(size_t)a * N + j] = make_double2(A[a].r + f.x, A[a].i + f.y);
+    }
+  }
+}
+
+// Adjoint with respect to the density alone: sum_i G_i K_ij over the near centers, into
+// spart[sp][kk][j]; plain: conjugated and with the far sums (fs), as the source passes
+// keep it.
+template <int P, int KIND>
+__global__ __launch_bounds__(256) void k_near_density(FarBlocks B, const double* __restrict__ ro,
+                                                      double* __restrict__ wo) {
+  constexpr bool kS = (KIND & 1) != 0;
+  constexpr bool kD = (KIND & 2) != 0;
+  constexpr int NA = src_slots(KIND);
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int w = b * 4 + wave;
+  const int ns = it.nsrc;
+  const int c = w / ns, sp = w - c * ns;
+  const int N = it.N, qs = it.qs, T = it.T, Mc = it.Mc, NJ = it.NJ;
+  if (c * kWave >= N) return;
+  const int j = c * kWave + lane;
+  const bool valid = j < N;
+  const int jj = valid ? j : N - 1;
+  const CenterRec* __restrict__ ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
+  const double* __restrict__ jtab = ro + it.jtab;
+  const double2* __restrict__ G = reinterpret_cast<const double2*>(ro + it.G);
+  const int mj = jj / qs;
+  const int pa = (c * kWave) / qs;
+  const int pb = min(c * kWave + kWave - 1, N - 1) / qs;
+  const double4 g = reinterpret_cast<const double4*>(ro + it.geo)[jj];
+  const double k = it.k, inv_k = 1.0 / k;
+  const int n_sides = it.n_sides;
+  const NearRel R = near_rel(it, ro);
+  double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
+  for_near_any(pa, pb, R, it.P, near_lists(it, ro), lane, sp, ns, [&](int m) {
+    if (valid && (pa == pb || is_near(R, m, mj))) {
+      for (int si_ = 0; si_ < n_sides; ++si_) {
+        for (int a = 0; a < kQ; ++a) {
+          const int ci = si_ * T + m * kQ + a;
+          const int z0 = opaque_zero();
+          const double* __restrict__ J = jtab + (size_t)ci * NJ + z0;
+          const double* __restrict__ cf = g_seed_table + z0;
+          const CenterRec* C = ctr + ci;
+          const double vx = g.x - C->cx, vy = g.y - C->cy;
+          const double rho2 = fma(vx, vx, vy * vy);
+          const double ir = rsqrt_refined(rho2);
+          const double rho = rho2 * ir;
+          const double cd = (C->ct * vx + C->st * vy) * ir;
+          const double sd = (C->st * vx - C->ct * vy) * ir;
+          double cps = 0.0, sps = 0.0;
+          if (kD) {
+            cps = C->ct * g.z + C->st * g.w;
+            sps = C->st * g.z - C->ct * g.w;
+          }
+          double ks_r, ks_i, kd_r, kd_i;
+          pair_kernel<P, KIND>(k * rho, ir * inv_k, cd, sd, cps, sps, J, cf, ks_r, ks_i, kd_r,
+                               kd_i);
+          int kk = 0;
+          if (kS) {
+            const double2 Gi = G[(size_t)(kk++) * Mc + ci];
+            sr = fma(Gi.x, ks_r, fma(-Gi.y, ks_i, sr));
+            si = fma(Gi.x, ks_i, fma(Gi.y, ks_r, si));
+          }
+          if (kD) {
+            const double2 Gi = G[(size_t)kk * Mc + ci];
+            dr = fma(Gi.x, kd_r, fma(-Gi.y, kd_i, dr));
+            di = fma(Gi.x, kd_i, fma(Gi.y, kd_r, di));
+          }
+        }
+      }
+    }
+  });
+  if (valid) {
+    const bool plain = !(it.g2 > 0.0);
+    // the split sums near parts itself, [kk][j]; plain parts lie in the source-pass layout
+    double2* part = reinterpret_cast<double2*>(wo + it.spart) +
+                    (size_t)sp * (plain ? NA : (kS && kD ? 2 : 1)) * N;
+    const double2* fs = reinterpret_cast<const double2*>(ro + it.fs);
+    const double sg = plain ? -1.0 : 1.0;
+    int kk = 0;
+    if (kS) {
+      const double2 f = plain && sp == 0 ? fs[j] : make_double2(0.0, 0.0);
+      part[j] = make_double2(sr + f.x, sg * si + f.y);
+      ++kk;
+    }
+    if (kD) {
+      const double2 f = plain && sp == 0 ? fs[(size_t)kk * N + j] : make_double2(0.0, 0.0);
+      part[(size_t)kk * N + j] = make_double2(k * dr + f.x, sg * k * di + f.y);
+    }
+  }
+}
+
+template <int P, int KIND>
+static hipError_t launch_near_pk(NearPass pass, const FarBlocks& B, int blocks, double* ws,
+                                 double* out, hipStream_t s) {
+  const dim3 grid((unsigned)blocks), block(256);
+  switch (pass) {
+    case kNearForward:
+      hipLaunchKernelGGL((k_near_forward<P, KIND>), grid, block, 0, s, B, ws, ws, out);
+      break;
+    case kNearGradient:
+      hipLaunchKernelGGL((k_near_grad<P, KIND>), grid, block, 0, s, B, ws, ws);
+      break;
+    case kNearCenters:
+      hipLaunchKernelGGL((k_near_centers<P, KIND>), grid, block, 0, s, B, ws, ws);
+      break;
+    case kNearSources:
+      hipLaunchKernelGGL((k_near_sources<P, KIND>), grid, block, 0, s, B, ws, ws);
+      break;
+    case kNearDensity:
+      hipLaunchKernelGGL((k_near_density<P, KIND>), grid, block, 0, s, B, ws, ws);
+      break;
+  }
+  return hipGetLastError();
+}
+
+template <int P>
+static hipError_t launch_near_p(NearPass pass, const FarBlocks& B, int blocks, double* ws,
+                                double* out, hipStream_t s) {
+  return launch_near_pk<P, QBX_NEAR_KIND>(pass, B, blocks, ws, out, s);
+}
+
+#define QBX_CAT2(a, b) a##b
+#define QBX_CAT(a, b) QBX_CAT2(a, b)
+hipError_t QBX_CAT(launch_near_, QBX_NEAR_KIND)(NearPass pass, int p, const FarBlocks& B,
+                                                int blocks, double* ws, double* out,
+                                                hipStream_t s) {
+  QBX_P_SWITCH(p, launch_near_p, pass, B, blocks, ws, out, s)
+}
+
+}  // namespace qbx

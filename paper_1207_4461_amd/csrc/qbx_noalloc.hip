@@ -63,7 +63,9 @@ extern "C" int qbx_layer_potential_noalloc(const qbx_geometry* g, const double* 
   if (rc) return rc;
   if (!density) return fail(QBX_EINVAL, "density is NULL");
   if (!out) return fail(QBX_EINVAL, "out is NULL");
-  const Layout L = make_forward_layout(d);
+  // the expansions where their arrays fit too (they add rounding differences only)
+  Layout L = make_forward_layout(d, true);
+  if (L.total > (size_t)QBX_STATIC_SCRATCH_BYTES) L = make_forward_layout(d, false);
   if (L.total > (size_t)QBX_STATIC_SCRATCH_BYTES)
     return fail(QBX_EWORKSPACE,
                 "this forward needs %zu bytes of scratch; the static scratch holds %zu",

@@ -22,18 +22,12 @@
 // fixed order and applies i/4.
 #include <type_traits>
 
+#include "qbx_far.h"
 #include "qbx_pair.h"
 #include "qbx_panel.h"
 
 namespace qbx {
 
-__device__ __forceinline__ bool panels_near(double4 a, double4 b, double g2) {
-#pragma clang fp contract(off)
-  const double dx = a.x - b.x;
-  const double dy = a.y - b.y;
-  const double d2 = dx * dx + dy * dy;
-  return d2 < g2 * fmax(a.z, b.z);
-}
 
 // Near lists: one wave per panel m scans all panels (64 per ballot) and writes
 // the near ones in ascending order, at most kNearCap of them, and their count.

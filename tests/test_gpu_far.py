@@ -1,0 +1,72 @@
+"""Far pairs through panel expansions against the same sums taken pair by pair.
+
+The pair-by-pair path is the one that writes or reads a tape (forward, adjoint) or, for the
+target derivatives, the near/far split with every panel near; both are held to the oracle
+elsewhere.  Expansions drop terms below 1e-17 of a pair's leading one, so the paths differ by
+rounding: sums of up to 1e5 terms of both signs, a few 1e-14 of the largest value; the
+bars allow 1e-12 (values, densities, derivatives) and 1e-11 (node gradients, which cancel
+about ten times more).
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_1207_4461_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# panels around the threshold (96), the 64-cluster blocks, the groups of eight (from 512 on) and
+# their remainders; every kind and side; smallest and largest order and oversampling;
+# wavenumbers that no distance resolves (every pair near) and that reach the table's lower end
+CASES = [
+    dict(P=95, k=5.0, p=8, side=1, kind=1, os=4),
+    dict(P=96, k=5.0, p=8, side=1, kind=1, os=4),
+    dict(P=97, k=20.0, p=12, side=0, kind=3, os=1),
+    dict(P=128, k=0.003, p=4, side=-1, kind=2, os=3),
+    dict(P=129, k=150.0, p=10, side=0, kind=2, os=2),
+    dict(P=193, k=12.0, p=0, side=0, kind=3, os=8),
+    dict(P=511, k=30.0, p=24, side=1, kind=3, os=1),
+    dict(P=512, k=30.0, p=3, side=-1, kind=1, os=5),
+    dict(P=513, k=60.0, p=16, side=0, kind=2, os=1),
+    dict(P=580, k=8.0, p=7, side=0, kind=3, os=3),
+]
+
+
+def rel(a, b):
+    return float((a - b).abs().max() / b.abs().max())
+
+
+@pytest.mark.parametrize("c", CASES, ids=lambda c: "P{P}-k{k}-p{p}-s{side}-{kind}-o{os}".format(**c))
+def test_far_matches_pairs(c):
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), c["P"], c["k"], c["p"], c["side"],
+                        c["kind"], 17, oversample=c["os"], with_cotangent=True)
+    nodes, dens, cot = (torch.from_numpy(np.ascontiguousarray(a)).cuda()
+                        for a in (pb.nodes, pb.density, pb.cotangent))
+    kw = dict(k=pb.k, p=pb.p, oversample=pb.oversample, side=pb.side, kind=pb.kind)
+    tape = torch.empty(qbx.tape_bytes(c["P"], c["p"], c["side"], c["kind"]), dtype=torch.uint8,
+                       device="cuda")
+    ref = qbx.layer_potential(nodes, dens, tape=tape, **kw)
+    rd, rn = qbx.layer_potential_vjp(nodes, dens, cot, tape=tape, **kw)
+    u = qbx.layer_potential(nodes, dens, **kw)
+    gd, gn = qbx.layer_potential_vjp(nodes, dens, cot, **kw)
+    only, _ = qbx.layer_potential_vjp(nodes, dens, cot, want_nodes=False, **kw)
+    assert rel(u, ref) < 1e-12
+    assert rel(gd, rd) < 1e-12 and rel(only, rd) < 1e-12
+    assert rel(gn, rn) < 1e-11
+    assert torch.equal(u, qbx.layer_potential(nodes, dens, **kw))
+    grad, dn = qbx.layer_potential_gradient(nodes, dens, **kw)
+    pg, pd = qbx.layer_potential_split_gradient(nodes, dens, gamma=1e6, **kw)
+    assert rel(grad, pg) < 1e-12 and rel(dn, pd) < 1e-12
+
+
+def test_far_nan_density_reaches_every_target():
+    """A NaN in one density value spoils every target, near or far, as the pair sums do."""
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), 128, 5.0, 6, 1, 1, 3)
+    dens = torch.from_numpy(pb.density).cuda()
+    dens[0, 40] = float("nan")
+    u = qbx.layer_potential(torch.from_numpy(pb.nodes).cuda(), dens, pb.k, pb.p)
+    assert bool(torch.isnan(u.real).all())
