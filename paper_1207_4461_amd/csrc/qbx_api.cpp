@@ -182,7 +182,7 @@ Layout make_layout(const Dims& d) {
   L.G = take(sizeof(double2) * (size_t)d.nk * d.Mc);
   L.cg = take(sizeof(double) * (size_t)d.Mc * 8);
   int n_sp = std::max(d.n_csplit, d.n_cb);
-  if (far_applies(d)) n_sp = std::max(n_sp, 8);   // the near source passes' shares
+  if (far_applies(d)) n_sp = std::max(n_sp, kFarMaxShares);   // of the near source passes
   L.spart = take(sizeof(double2) * (size_t)n_sp * src_slots(d.kind) * d.N);
   L.cpart = take(sizeof(double) * (size_t)d.n_sb * d.Mc * 4);
   L.sg = take(sizeof(double) * (size_t)d.N * 8);
@@ -396,12 +396,14 @@ static int run_adjoint_far(const Dims& d, const Layout& L, const double* nodes,
                  stream);
   if (e != hipSuccess) return device_fail(e, "panel expansion kernels");
   timer_begin(geom ? 4 : 1, stream);
-  if (geom)
+  e = launch_near(geom ? kNearSources : kNearDensity, d.p, d.kind, one,
+                  far_blocks(it, kStepChunks), w, nullptr, stream);
+  if (geom && e == hipSuccess)
+    e = launch_near(kNearCenterSums, d.p, d.kind, one, far_blocks(it, kStepCenterSums), w, nullptr,
+                    stream);
+  if (geom && e == hipSuccess)
     e = launch_near(kNearCenters, d.p, d.kind, one, far_blocks(it, kStepCenters), w, nullptr,
                     stream);
-  if (e == hipSuccess)
-    e = launch_near(geom ? kNearSources : kNearDensity, d.p, d.kind, one,
-                    far_blocks(it, kStepChunks), w, nullptr, stream);
   timer_end(geom ? 4 : 1, stream);
   if (e != hipSuccess) return device_fail(e, "near adjoint kernels");
   e = launch_source_finalize(d, it.nsrc, at<double4>(ws, L.geo), at<double2>(ws, L.spart),

@@ -2,6 +2,7 @@
 // descriptor, the task lookup and the per-task bodies of the persistent kernels.
 #pragma once
 
+#include "qbx_far.h"
 #include "qbx_pair.h"
 #include "qbx_panel.h"
 
@@ -21,6 +22,8 @@ struct BatchItemDev {
   long long spart_off;   // double2 into the source-pass sums
   long long panel_off;   // first panel of this contour in the batch
   long long cpart_off;   // doubles into the fused adjoint's center-side partial sums
+  int far_parts;         // > 0: the call takes this contour's far pairs through panel expansions,
+                         // and its source sums come in so many parts
 };
 
 __device__ __forceinline__ int find_slot(const long long* __restrict__ pre, int n, long long t) {

@@ -15,9 +15,15 @@
 // Every wavefront leaves once the counter passes the task count.  Geometry,
 // per-center and per-source steps run as ordinary grids over all contours'
 // panels, centers or sources.
+//
+// Contours that panel expansions apply to (far_applies) take their far pairs that way
+// (qbx_far.hip, one grid per step over all of them) and their near pairs in one ordinary
+// grid per class (qbx_near.hip); the persistent kernels keep the small contours, and every
+// contour of a call with a tape.
 #include <algorithm>
 #include <mutex>
 #include <cmath>
+#include <cstring>
 #include <numeric>
 #include <vector>
 
@@ -32,6 +38,7 @@ struct BatchClass {
   int kind, p, n;
   int ord_at, pre_at;
   long long tasks_f, tasks_a, tasks_x;   // forward, adjoint source pass, fused adjoint tiles
+  int far_at, far_n;                     // its slice of the far items
 };
 
 struct BatchPlan {
@@ -44,7 +51,14 @@ struct BatchPlan {
   std::vector<long long> pre_panel, pre_ctr, pre_src, pre_G;  // prefix sums in item order
   long long n_panels = 0, n_ctr = 0, n_src = 0, n_G = 0, n_densw = 0, n_jtab = 0, n_tape = 0,
             n_spart = 0, n_cpart = 0;
+  // contours with panel expansions, class by class, the grids of the steps over all of them and
+  // the near passes' over each class's (prefix sums in `far_pre`, far_step[i] entries in)
+  std::vector<FarItem> far;
+  std::vector<int> far_pre;
+  int far_step[kStepCenterSums + 1];
+  int far_total[kStepLists + 1];
   // workspace offsets
+  size_t o_far, o_far_pre, plan_bytes;
   size_t o_items, o_ord_f, o_ord_a, o_ord_x, o_pre_f, o_pre_a, o_pre_x, o_pre_panel, o_pre_ctr, o_pre_src, o_pre_G,
       o_counter, o_tables, o_geo, o_densw, o_wgt, o_h, o_ctr, o_jtab, o_tape, o_G, o_cg, o_spart, o_cpart,
       o_sg, total;
@@ -55,7 +69,10 @@ static double g_batch_grid_scale = 1.0;       // persistent grid = resident bloc
 static double g_batch_adjoint_tasks = 16384;  // adjoint tasks per (kind, p) class
 static int g_batch_fused_chunks = 4;          // 64-source chunks per fused adjoint tile
 
-static bool build_plan(const qbx_batch_item* items, int n, int oversample, BatchPlan* P) {
+// use_far: contours that panel expansions apply to leave the persistent kernels' tasks;
+// fwd, bwd: what their expansions carry in this call (far_fields)
+static bool build_plan(const qbx_batch_item* items, int n, int oversample, BatchPlan* P,
+                       bool use_far, bool fwd = true, bool bwd = false) {
   if (!items || n < 1 || oversample < 1 || oversample > QBX_OVERSAMPLE_MAX) return false;
   P->n = n;
   P->qs = kQ * oversample;
@@ -107,7 +124,7 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     size_t c = 0;
     while (c < P->cls.size() && !(P->cls[c].kind == d.kind && P->cls[c].p == d.p)) ++c;
     if (c == P->cls.size()) {
-      P->cls.push_back(BatchClass{d.kind, d.p, 0, 0, 0, 0, 0, 0});
+      P->cls.push_back(BatchClass{d.kind, d.p, 0, 0, 0, 0, 0, 0, 0, 0});
       cls_cost.push_back(0.0);
       members.emplace_back();
     }
@@ -130,9 +147,18 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
   P->pre_x.clear();
   P->pre_f.clear();
   P->pre_a.clear();
+  std::vector<std::vector<int>> far_members(P->cls.size());
+  int n_far = 0;
   for (size_t c = 0; c < P->cls.size(); ++c) {
     BatchClass& C = P->cls[c];
-    const std::vector<int>& mem = sorted_members[c];
+    std::vector<int> mem;
+    for (int i : sorted_members[c]) {
+      BatchItemDev& B = P->items[i];
+      B.far_parts = 0;
+      if (far_applies(B.d)) far_members[c].push_back(i);
+      if (!use_far || !far_applies(B.d)) mem.push_back(i);
+    }
+    n_far += (int)far_members[c].size();
     C.n = (int)mem.size();
     C.ord_at = (int)P->order_f.size();
     C.pre_at = (int)P->pre_f.size();
@@ -153,9 +179,9 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     // adjoint tasks: (center split, 64-source chunk); the class's work is cut
     // into about g_batch_adjoint_tasks tasks of at least 16 centers each
     double work = 0.0;
-    for (int i : mem) work += (double)P->items[i].d.chunks * P->items[i].d.Mc;
+    for (int i : sorted_members[c]) work += (double)P->items[i].d.chunks * P->items[i].d.Mc;
     const long long g = std::max<long long>(16, (long long)std::ceil(work / g_batch_adjoint_tasks));
-    for (int i : mem) {
+    for (int i : sorted_members[c]) {
       Dims& d = P->items[i].d;
       d.centers_per_split = (int)std::min<long long>(d.Mc, g);
       d.n_csplit = (d.Mc + d.centers_per_split - 1) / d.centers_per_split;
@@ -164,7 +190,7 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     C.tasks_a = append(cost_a, P->order_a, P->pre_a, false);
     // fused adjoint tiles: fused_tile_height centers x g_batch_fused_chunks
     // 64-source chunks; tile cost ~ centers of the tile
-    for (int i : mem) {
+    for (int i : sorted_members[c]) {
       Dims& d = P->items[i].d;
       d.fused_cblock = fused_tile_height(d.Mc, d.N, d.kind);
       d.n_cb = (d.Mc + d.fused_cblock - 1) / d.fused_cblock;
@@ -189,7 +215,9 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
   for (int i = 0; i < n; ++i) {
     BatchItemDev& B = P->items[i];
     B.spart_off = P->n_spart;
-    P->n_spart += (long long)std::max(B.d.n_csplit, B.d.n_cb) * src_slots(B.d.kind) * B.d.N;
+    const int parts = std::max(std::max(B.d.n_csplit, B.d.n_cb),
+                               far_applies(B.d) ? kFarMaxShares : 1);
+    P->n_spart += (long long)parts * src_slots(B.d.kind) * B.d.N;
     B.cpart_off = P->n_cpart;
     P->n_cpart += (long long)B.d.n_sb * B.d.Mc * 4;
   }
@@ -199,17 +227,23 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     o = align256(o + bytes);
     return at;
   };
+  // the host's tables first, in the order of upload_plan
   P->o_items = take(sizeof(BatchItemDev) * n);
   P->o_ord_f = take(sizeof(int) * n);
   P->o_ord_a = take(sizeof(int) * n);
   P->o_ord_x = take(sizeof(int) * n);
-  P->o_pre_f = take(sizeof(long long) * P->pre_f.size());
-  P->o_pre_a = take(sizeof(long long) * P->pre_a.size());
-  P->o_pre_x = take(sizeof(long long) * P->pre_x.size());
+  const size_t n_pre = (size_t)n + P->cls.size();   // at most, over the classes' tasks
+  P->o_pre_f = take(sizeof(long long) * n_pre);
+  P->o_pre_a = take(sizeof(long long) * n_pre);
+  P->o_pre_x = take(sizeof(long long) * n_pre);
   P->o_pre_panel = take(sizeof(long long) * (n + 1));
   P->o_pre_ctr = take(sizeof(long long) * (n + 1));
   P->o_pre_src = take(sizeof(long long) * (n + 1));
   P->o_pre_G = take(sizeof(long long) * (n + 1));
+  P->o_far = take(sizeof(FarItem) * n_far);
+  P->o_far_pre = take(sizeof(int) * ((size_t)(kStepLists + 1) * (n_far + 1) +
+                                     3 * ((size_t)n_far + P->cls.size())));
+  P->plan_bytes = o;
   P->o_counter = take(sizeof(int) * 3 * P->cls.size());
   P->o_tables = take(sizeof(double) * table_layout(P->qs).total);
   P->o_geo = take(sizeof(double4) * P->n_src);
@@ -224,7 +258,53 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
   P->o_spart = take(sizeof(double2) * P->n_spart);
   P->o_cpart = take(sizeof(double) * P->n_cpart);
   P->o_sg = take(sizeof(double) * 8 * P->n_src);
+  // the far items, class by class, and their arrays
+  P->far.clear();
+  P->far_pre.clear();
+  for (size_t c = 0; c < P->cls.size(); ++c) {
+    P->cls[c].far_at = (int)P->far.size();
+    P->cls[c].far_n = use_far ? (int)far_members[c].size() : 0;
+    for (int i : far_members[c]) {
+      BatchItemDev& B = P->items[i];
+      FarItem it;
+      far_layout(B.d, true, take, &it, n_far);
+      it.k = B.d.k;
+      it.node_off = B.node_off;
+      it.out_off = B.out_off;
+      it.geo = it.fgeo = P->o_geo / 8 + 4 * B.src_off;
+      it.dens = it.fdens = P->o_densw / 8 + 2 * B.densw_off;
+      it.ctr = P->o_ctr / 8 + 8 * B.ctr_off;
+      it.jtab = P->o_jtab / 8 + B.jtab_off;
+      it.G = it.fG = P->o_G / 8 + 2 * B.G_off;
+      it.cg = P->o_cg / 8 + 8 * B.ctr_off;
+      it.spart = P->o_spart / 8 + 2 * B.spart_off;
+      far_shape(&it, fwd, bwd);
+      if (use_far) {
+        B.far_parts = it.nsrc;
+        P->far.push_back(it);
+      }
+    }
+  }
   P->total = o;
+  for (int st = 0; st <= kStepCenterSums; ++st) P->far_step[st] = 0;
+  if (P->far.empty()) return true;
+  auto prefix = [&](FarStep st, int at, int cnt) {
+    int acc = 0;
+    P->far_pre.push_back(0);
+    for (int i = at; i < at + cnt; ++i) {
+      acc += far_blocks(P->far[i], st);
+      P->far_pre.push_back(acc);
+    }
+    return acc;
+  };
+  for (int st = 0; st <= kStepLists; ++st) {
+    P->far_step[st] = (int)P->far_pre.size();
+    P->far_total[st] = prefix((FarStep)st, 0, (int)P->far.size());
+  }
+  for (int st : {kStepCenters, kStepChunks, kStepCenterSums}) {
+    P->far_step[st] = (int)P->far_pre.size();
+    for (const BatchClass& C : P->cls) prefix((FarStep)st, C.far_at, C.far_n);
+  }
   return true;
 }
 
@@ -292,6 +372,7 @@ __global__ __launch_bounds__(256) void k_fused_center_grads_batched(
   if (e >= total) return;
   const int it = find_slot(pre_ctr, n, e);
   const BatchItemDev& B = items[it];
+  if (B.far_parts > 0) return;   // written by k_near_centers
   const Dims& d = B.d;
   const int ci = (int)(e - pre_ctr[it]);
   double s[4] = {0.0, 0.0, 0.0, 0.0};
@@ -312,9 +393,10 @@ __global__ __launch_bounds__(256) void k_source_finalize_batched(
   if (e >= total) return;
   const int it = find_slot(pre_src, n, e);
   const BatchItemDev& B = items[it];
-  // the source sums come in n_cb parts from the fused pass, n_csplit otherwise
+  // the source sums come in far_parts parts from the near passes, n_cb from the fused pass,
+  // n_csplit otherwise
   source_finalize_elem((int)(e - pre_src[it]), B.d.N, B.d.kind,
-                       fused ? B.d.n_cb : B.d.n_csplit, geo + B.src_off, spart + B.spart_off,
+                       B.far_parts > 0 ? B.far_parts : fused ? B.d.n_cb : B.d.n_csplit, geo + B.src_off, spart + B.spart_off,
                        sg + B.src_off * 8);
 }
 
@@ -337,30 +419,27 @@ __global__ __launch_bounds__(128) void k_chain_batched(
 // host side
 // ---------------------------------------------------------------------------
 
+// the plan's tables in one copy (staged by the runtime before the call returns)
 static int upload_plan(const BatchPlan& P, void* ws, hipStream_t s) {
-  struct Up {
-    size_t off;
-    const void* src;
-    size_t bytes;
-  } ups[] = {
-      {P.o_items, P.items.data(), sizeof(BatchItemDev) * P.n},
-      {P.o_ord_f, P.order_f.data(), sizeof(int) * P.n},
-      {P.o_ord_a, P.order_a.data(), sizeof(int) * P.n},
-      {P.o_ord_x, P.order_x.data(), sizeof(int) * P.n},
-      {P.o_pre_f, P.pre_f.data(), sizeof(long long) * P.pre_f.size()},
-      {P.o_pre_a, P.pre_a.data(), sizeof(long long) * P.pre_a.size()},
-      {P.o_pre_x, P.pre_x.data(), sizeof(long long) * P.pre_x.size()},
-      {P.o_pre_panel, P.pre_panel.data(), sizeof(long long) * (P.n + 1)},
-      {P.o_pre_ctr, P.pre_ctr.data(), sizeof(long long) * (P.n + 1)},
-      {P.o_pre_src, P.pre_src.data(), sizeof(long long) * (P.n + 1)},
-      {P.o_pre_G, P.pre_G.data(), sizeof(long long) * (P.n + 1)},
+  std::vector<char> h(P.plan_bytes, 0);
+  auto put = [&](size_t off, const void* src, size_t bytes) {
+    if (bytes) std::memcpy(h.data() + off, src, bytes);
   };
-  for (const Up& u : ups) {
-    hipError_t e = hipMemcpyAsync(static_cast<char*>(ws) + u.off, u.src, u.bytes,
-                                  hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return device_fail(e, "upload of the batch plan");
-  }
-  return QBX_OK;
+  put(P.o_items, P.items.data(), sizeof(BatchItemDev) * P.n);
+  put(P.o_ord_f, P.order_f.data(), sizeof(int) * P.order_f.size());
+  put(P.o_ord_a, P.order_a.data(), sizeof(int) * P.order_a.size());
+  put(P.o_ord_x, P.order_x.data(), sizeof(int) * P.order_x.size());
+  put(P.o_pre_f, P.pre_f.data(), sizeof(long long) * P.pre_f.size());
+  put(P.o_pre_a, P.pre_a.data(), sizeof(long long) * P.pre_a.size());
+  put(P.o_pre_x, P.pre_x.data(), sizeof(long long) * P.pre_x.size());
+  put(P.o_pre_panel, P.pre_panel.data(), sizeof(long long) * (P.n + 1));
+  put(P.o_pre_ctr, P.pre_ctr.data(), sizeof(long long) * (P.n + 1));
+  put(P.o_pre_src, P.pre_src.data(), sizeof(long long) * (P.n + 1));
+  put(P.o_pre_G, P.pre_G.data(), sizeof(long long) * (P.n + 1));
+  put(P.o_far, P.far.data(), sizeof(FarItem) * P.far.size());
+  put(P.o_far_pre, P.far_pre.data(), sizeof(int) * P.far_pre.size());
+  hipError_t e = hipMemcpyAsync(ws, h.data(), P.plan_bytes, hipMemcpyHostToDevice, s);
+  return e == hipSuccess ? QBX_OK : device_fail(e, "upload of the batch plan");
 }
 
 static int batch_prepare(const BatchPlan& P, const double* nodes, const double* density, void* ws,
@@ -477,15 +556,44 @@ int class_join(ClassFork* f) {
 }
 }  // namespace
 
-static int batch_forward(const BatchPlan& P, double* out, double2* tape, void* ws, hipStream_t s) {
+// the far items' expansions (far_fields over all of them)
+static int batch_far(const BatchPlan& P, const double* nodes, void* ws, bool fwd, bool bwd,
+                     int eval, bool src, bool geom, hipStream_t s) {
+  if (P.far.empty()) return QBX_OK;
+  FarPlan F;
+  for (int i = 0; i <= kStepLists; ++i) {
+    F.at[i] = FarBlocks{wsp<FarItem>(ws, P.o_far), wsp<int>(ws, P.o_far_pre) + P.far_step[i],
+                        (int)P.far.size()};
+    F.blocks[i] = P.far_total[i];
+  }
+  hipError_t e = far_fields(F, nodes, static_cast<double*>(ws), fwd, bwd, eval, src, geom, true, s);
+  return e == hipSuccess ? QBX_OK : device_fail(e, "batched panel expansion kernels");
+}
+
+// one near pass over the far items of class c
+static hipError_t batch_near(const BatchPlan& P, size_t c, NearPass pass, FarStep step, void* ws,
+                             double* out, hipStream_t s) {
+  const BatchClass& C = P.cls[c];
+  if (C.far_n == 0) return hipSuccess;
+  const int at = P.far_step[step] + C.far_at + (int)c;   // each class's prefix has one entry more
+  const FarBlocks B{wsp<FarItem>(ws, P.o_far) + C.far_at, wsp<int>(ws, P.o_far_pre) + at, C.far_n};
+  return launch_near(pass, C.p, C.kind, B, P.far_pre[at + C.far_n], static_cast<double*>(ws), out,
+                     s);
+}
+
+static int batch_forward(const BatchPlan& P, const double* nodes, double* out, double2* tape,
+                         void* ws, hipStream_t s) {
   int rc = zero_counters(P, ws, s);
   if (rc) return rc;
+  if ((rc = batch_far(P, nodes, ws, true, false, 0, false, false, s))) return rc;
   timer_begin(2, s);
   ClassFork f;
   rc = class_fork(P.cls.size(), s, &f);
   if (rc) return rc;
   hipError_t e = hipSuccess;
   for (size_t c = 0; c < P.cls.size() && e == hipSuccess; ++c) {
+    e = batch_near(P, c, kNearForward, kStepCenters, ws, out, f.stream(c));
+    if (e != hipSuccess || P.cls[c].n == 0) continue;
     const BatchTasks t = class_tasks(P, ws, c, 0);
     e = launch_forward_batched(tape ? 1 : 0, P.cls[c].kind, P.cls[c].p, t,
                                wsp<double4>(ws, P.o_geo), wsp<double2>(ws, P.o_densw),
@@ -532,13 +640,13 @@ extern "C" {
 
 size_t qbx_batched_workspace_bytes(const qbx_batch_item* items, int n_items, int oversample) {
   BatchPlan P;
-  if (!build_plan(items, n_items, oversample, &P)) return 0;
+  if (!build_plan(items, n_items, oversample, &P, true)) return 0;
   return P.total;
 }
 
 size_t qbx_batched_tape_bytes(const qbx_batch_item* items, int n_items) {
   BatchPlan P;
-  if (!build_plan(items, n_items, 1, &P)) return 0;
+  if (!build_plan(items, n_items, 1, &P, false)) return 0;
   return sizeof(double2) * (size_t)P.n_tape;
 }
 
@@ -546,14 +654,14 @@ int qbx_layer_potential_batched(const qbx_batch_item* items, int n_items, const 
                                 const double* density, double* out, double* tape, int oversample,
                                 void* ws, size_t ws_bytes, hipStream_t stream) {
   BatchPlan P;
-  if (!build_plan(items, n_items, oversample, &P))
+  if (!build_plan(items, n_items, oversample, &P, tape == nullptr, true, false))
     return fail(QBX_EINVAL, "invalid batch (an item's parameters, offsets or oversample)");
   if (!nodes || !density || !out || !ws) return fail(QBX_EINVAL, "NULL array argument");
   if (ws_bytes < P.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, P.total);
   int rc = batch_prepare(P, nodes, density, ws, stream);
   if (rc) return rc;
-  return batch_forward(P, out, reinterpret_cast<double2*>(tape), ws, stream);
+  return batch_forward(P, nodes, out, reinterpret_cast<double2*>(tape), ws, stream);
 }
 
 int qbx_layer_potential_batched_adjoint(const qbx_batch_item* items, int n_items,
@@ -562,7 +670,8 @@ int qbx_layer_potential_batched_adjoint(const qbx_batch_item* items, int n_items
                                         double* grad_density, double* grad_nodes, int oversample,
                                         void* ws, size_t ws_bytes, hipStream_t stream) {
   BatchPlan P;
-  if (!build_plan(items, n_items, oversample, &P))
+  const bool geom = grad_nodes != nullptr;
+  if (!build_plan(items, n_items, oversample, &P, tape == nullptr, geom, true))
     return fail(QBX_EINVAL, "invalid batch (an item's parameters, offsets or oversample)");
   if (!nodes || !density || !cotangent || !ws) return fail(QBX_EINVAL, "NULL array argument");
   if (ws_bytes < P.total)
@@ -585,14 +694,21 @@ int qbx_layer_potential_batched_adjoint(const qbx_batch_item* items, int n_items
                        wsp<double2>(ws, P.o_G), wsp<double>(ws, P.o_cg));
   rc = zero_counters(P, ws, stream);
   if (rc) return rc;
+  if ((rc = batch_far(P, nodes, ws, geom, true, geom ? 2 : -1, true, geom, stream))) return rc;
   timer_begin(2, stream);
   ClassFork f;
   rc = class_fork(P.cls.size(), stream, &f);
   if (rc) return rc;
   hipError_t ea = hipSuccess;
   for (size_t c = 0; c < P.cls.size() && ea == hipSuccess; ++c) {
-    const BatchTasks t = class_tasks(P, ws, c, fused ? 2 : 1);
     const hipStream_t sc = f.stream(c);
+    ea = batch_near(P, c, geom ? kNearSources : kNearDensity, kStepChunks, ws, nullptr, sc);
+    if (geom && ea == hipSuccess)
+      ea = batch_near(P, c, kNearCenterSums, kStepCenterSums, ws, nullptr, sc);
+    if (geom && ea == hipSuccess)
+      ea = batch_near(P, c, kNearCenters, kStepCenters, ws, nullptr, sc);
+    if (ea != hipSuccess || P.cls[c].n == 0) continue;
+    const BatchTasks t = class_tasks(P, ws, c, fused ? 2 : 1);
     ea = fused ? launch_adjoint_fused_batched(P.cls[c].kind, P.cls[c].p, t,
                                               wsp<double4>(ws, P.o_geo),
                                               wsp<double2>(ws, P.o_densw),

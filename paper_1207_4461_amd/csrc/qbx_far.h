@@ -16,8 +16,8 @@
 // the pair kernels.  The double layer takes the normal derivative of the regular
 // waves in M_m.  Orders |m|, |l| <= kFarQ are kept; two panels are taken this way only
 // where the terms beyond are below 1e-17 of the leading one (far_adm), so that the
-// sums differ from the pair sums by rounding.  The same holds for groups of kFarGroup
-// consecutive panels, which take the pairs of groups that are far enough as one pair.
+// sums differ from the pair sums by rounding.  The same holds for groups of consecutive
+// panels (FarItem::g), which take the pairs of groups that are far enough as one pair.
 // Every other pair of panels is near, and its pairs are evaluated one by one.
 //
 // The adjoint is the transpose: T_l = sum_c G_c E_l(c) over the centers of a panel
@@ -31,17 +31,15 @@
 namespace qbx {
 
 constexpr int kFarQ = 24;        // order of the expansions
-constexpr int kFarLo = 12;       // order where every lane's panel is farther still
 constexpr int kFarW = 2 * kFarQ + 1;
-constexpr int kFarGroup = 8;     // panels of a group
 
 // One cluster (a panel or a group): mean of its nodes, radius of its sources (rs) and
 // of its centers with their disks (rt), the distances from which an expansion of order
-// kFarQ (ds, dt) and kFarLo (dsl, dtl) resolves them, and, for the near/far split's
+// kFarQ resolves them (ds, dt), and, for the near/far split's
 // groups, the radius of the panel means (rb) and gamma times the largest node radius
 // (gr): groups at least that far hold no pair of panels within gamma radii.
 struct FarRec {
-  double bx, by, rs, rt, ds, dt, dsl, dtl, rb, gr;
+  double bx, by, rs, rt, ds, dt, rb, gr;
 };
 
 // Symmetric in its arguments bit for bit (no contraction; maxima and sums of two), so
@@ -52,14 +50,6 @@ __device__ __forceinline__ bool far_adm(const FarRec& a, const FarRec& b) {
   const double d2 = dx * dx + dy * dy;
   const double t0 = fmax(fmax(a.ds + b.rt, b.ds + a.rt), fmax(a.dt + b.rs, b.dt + a.rs));
   const double t = fmax(t0, (a.rb + b.rb) + fmax(a.gr, b.gr));
-  return d2 >= t * t;
-}
-// the same for the order kFarLo
-__device__ __forceinline__ bool far_adm_lo(const FarRec& a, const FarRec& b) {
-#pragma clang fp contract(off)
-  const double dx = a.bx - b.bx, dy = a.by - b.by;
-  const double d2 = dx * dx + dy * dy;
-  const double t = fmax(fmax(a.dsl + b.rt, b.dsl + a.rt), fmax(a.dtl + b.rs, b.dtl + a.rs));
   return d2 >= t * t;
 }
 
@@ -78,19 +68,20 @@ __device__ __forceinline__ bool panels_near(double4 a, double4 b, double g2) {
 // pairs that it calls far.
 struct FarRel {
   const FarRec* r0;    // panels
-  const FarRec* r1;    // groups, or null
+  const FarRec* r1;    // groups of g panels, or null
+  int g;
   const double4* bnd;  // gamma relation's panels, or null
   double g2;
 };
 __device__ __forceinline__ bool far_panels(const FarRel& R, int a, int b) {
-  if (R.r1 && far_adm(R.r1[a / kFarGroup], R.r1[b / kFarGroup])) return true;
+  if (R.r1 && far_adm(R.r1[a / R.g], R.r1[b / R.g])) return true;
   if (R.bnd && panels_near(R.bnd[a], R.bnd[b], R.g2)) return false;
   return far_adm(R.r0[a], R.r0[b]);
 }
 
 // One contour of a call.  Offsets count doubles from the workspace base.
 struct FarItem {
-  int P, C1;            // panels, groups (0: none)
+  int P, C1, g;         // panels, groups (0: none), panels of a group (4 or 8)
   int T, N, qs, Mc, n_sides, nk, kind, p, NJ, side;
   int fqs;              // far sources per panel (qs; the split: 16, the nodes)
   int pt;               // far targets are points (the split: the nodes)
@@ -98,6 +89,7 @@ struct FarItem {
   int vf;               // of them forward (0 or nk)
   int nsrc;             // waves per 64-source chunk in the near source passes
   int n0, n1;           // blocks of sources per 64 target panels / groups
+  int m2l_blocks;       // translation blocks aimed for
   double k, g2;         // g2: the split's gamma squared, or 0
   size_t node_off;      // doubles into the nodes
   size_t out_off;       // doubles into out
@@ -108,10 +100,11 @@ struct FarItem {
   size_t rows0, rows1;                 // double2 [V][2][C][kFarW]
   size_t lp0, lp1;                     // double2 [n][V][2][kFarQ + 1][C]
   size_t ls0, ls1;                     // double2 [V][C][kFarW]
-  size_t tp0, tp1;                     // double2 [n_sides or 2 n_sides][nk][C][kFarW]
+  size_t tp0, tp1;                     // double2 [n_sides or n_sides g / 4][nk][C][kFarW]
   size_t fu;                           // double2 [nk][Mc][2] far sums per center
   size_t fc;                           // double [Mc][4] far center gradients
   size_t fs;                           // double2 [nk + 2][far sources]
+  size_t cpart;                        // double [P][kNearSlots subs][n_sides kQ][4]: near center sums
   size_t partial, cg, spart;           // near outputs: gradient sums, center / source gradients
 };
 
@@ -139,16 +132,20 @@ __device__ __forceinline__ const FarItem* far_item(const FarBlocks& B, int block
 // the grids of the steps, per item
 enum FarStep {
   kStepClusters,   // panels and groups, one wave each
-  kStepM2L, kStepSum,
+  kStepM2L, kStepM2LGroups, kStepSum,
   kStepTargets,    // 64 targets of one side
   kStepRows, kStepSources, kStepLists,
   kStepCenters,    // four centers, one wave each (qbx_near.hip)
-  kStepChunks,     // four chunks of 64 sources (qbx_near.hip)
+  kStepChunks,     // four shares of the chunks of 64 sources of a panel (qbx_near.hip)
+  kStepCenterSums, // 64 centers, four lanes each (qbx_near.hip)
 };
 int far_blocks(const FarItem& it, FarStep step);
 
 // the near pairs' passes (qbx_near.hip); out: kNearForward's result
-enum NearPass { kNearForward, kNearGradient, kNearCenters, kNearSources, kNearDensity };
+// kNearCenterSums, kNearCenters: the two halves of the center side (short and long lists)
+enum NearPass {
+  kNearForward, kNearGradient, kNearSources, kNearCenterSums, kNearCenters, kNearDensity
+};
 hipError_t launch_near(NearPass pass, int p, int kind, const FarBlocks& B, int blocks,
                        double* ws, double* out, hipStream_t s);
 
@@ -166,9 +163,10 @@ FarPlan far_single(const FarItem& it, const FarItem* dev);
 hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fwd, bool bwd,
                       int eval, bool src, bool geom, bool lists, hipStream_t s);
 // the offsets of an item's far arrays from take(bytes) (returning a byte offset), with
-// bwd those of the adjoint too; V, n0, n1 are then set per call (far_shape)
+// bwd those of the adjoint too; V, n0, n1 are then set per call (far_shape).  n_items: the
+// items that share the call's launches.
 template <typename Take>
-inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it);
+inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_items = 1);
 // vectors and translation shares of a call: fwd / bwd as in far_fields
 void far_shape(FarItem* it, bool fwd, bool bwd);
 
@@ -176,7 +174,7 @@ hipError_t launch_far_recs(const FarBlocks& B, int blocks, const double* nodes, 
                            hipStream_t s);
 hipError_t launch_far_lists(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
 hipError_t launch_far_p2m(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
-hipError_t launch_far_m2l(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+hipError_t launch_far_m2l(bool groups, const FarBlocks& B, int blocks, double* ws, hipStream_t s);
 hipError_t launch_far_lsum(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
 // mode 0 values, 1 target derivatives, 2 center gradients contracted with G
 hipError_t launch_far_eval(int mode, const FarBlocks& B, int blocks, double* ws, hipStream_t s);
@@ -185,37 +183,57 @@ hipError_t launch_far_rows(const FarBlocks& B, int blocks, double* ws, hipStream
 hipError_t launch_far_src(const FarBlocks& B, int blocks, double* ws, bool geom, hipStream_t s);
 
 
+// Near adjoint: a source panel's chunks of 64 (one partial), and the near lists up to which the
+// fused pass also forms the center side (13 panels are near at most sizes; past kNearSlots the
+// centers of a panel are summed by a wave each)
+constexpr int kNearSlots = 32;
+__host__ __device__ inline int near_subs(int qs) { return (qs + kWave - 1) / kWave; }
+
 // fewest panels that are worth the expansions, largest center distance r taken (a disk
 // that reaches over many panels leaves every panel near)
 constexpr int kFarMinPanels = 96;
-constexpr int kFarGroupPanels = 512;   // from here on groups too
+// From kFarGroupPanels panels on groups of four too, from kFarGroup8Panels on of eight.  The
+// second level costs its own multipoles, sums and evaluation (about 70 us at 256 panels,
+// where it saves less: forward 289 us without, 354 us with groups; at 333 panels 449 and
+// 419 us), so a contour alone takes it later than one of a batch, whose items fill the
+// GPU together (64 contours of 16..512 panels: translations 9.9 ms without, 2.6 ms with).
+constexpr int kFarGroupPanels = 320, kFarGroupPanelsBatch = 128;
+constexpr int kFarGroup8Panels = 2048;
 inline bool far_applies(const Dims& d) {
   return d.P >= kFarMinPanels && d.center_rule == 0 && d.r <= 1.0;
 }
-// blocks of the translation aimed for (256 compute units, two blocks each resident)
-constexpr int kFarM2LBlocks = 512;
-inline int far_share(int C, int V) {
+// blocks of the translation aimed for (256 compute units, three blocks each resident), and
+// the most shares of the sources a panel-level block takes when groups serve the rest
+// (about 110 sources are left per 64 target panels)
+constexpr int kFarM2LBlocks = 1024;
+// waves of the near source passes aimed for
+constexpr int kFarSourceWaves = 8192;
+constexpr int kFarMaxShares = 8;   // parts of a chunk's near source sums at most
+constexpr int kFarMaxPanelShares = 16;
+inline int far_share(int C, int V, int blocks, bool inner) {
   const int tb = (C + kWave - 1) / kWave;
-  int n = (kFarM2LBlocks + tb * V * 2 - 1) / (tb * V * 2);
-  const int most = (C + 3) / 4;
+  int n = (blocks + tb * V * 2 - 1) / (tb * V * 2);
+  int most = (C + 3) / 4;
+  if (inner && most > kFarMaxPanelShares) most = kFarMaxPanelShares;
   if (n > most) n = most;
   return n < 1 ? 1 : n;
 }
-inline size_t far_lp_doubles(int C, int Vmax) {
+inline size_t far_lp_doubles(int C, int Vmax, int blocks, bool inner) {
   size_t most = 0;   // over the vector counts a call may have
   for (int V = 1; V <= Vmax; ++V) {
-    const size_t n = (size_t)far_share(C, V) * V * 2 * (kFarQ + 1) * C * 2;
+    const size_t n = (size_t)far_share(C, V, blocks, inner) * V * 2 * (kFarQ + 1) * C * 2;
     if (n > most) most = n;
   }
   return most;
 }
 
 template <typename Take>
-inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it) {
+inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_items) {
   auto at = [&](size_t doubles) { return take(sizeof(double) * doubles) / sizeof(double); };
   *it = FarItem{};
   it->P = d.P;
-  it->C1 = d.P >= kFarGroupPanels ? (d.P + kFarGroup - 1) / kFarGroup : 0;
+  it->g = d.P >= kFarGroup8Panels ? 8 : 4;
+  it->C1 = d.P >= (n_items > 1 ? kFarGroupPanelsBatch : kFarGroupPanels) ? (d.P + it->g - 1) / it->g : 0;
   it->T = d.T;
   it->N = d.N;
   it->qs = d.qs;
@@ -235,21 +253,24 @@ inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it) {
   it->nlist = at(C0 * kNearCap / 2);
   it->rows0 = at((size_t)Vmax * 2 * C0 * kFarW * 2);
   it->rows1 = at((size_t)Vmax * 2 * C1 * kFarW * 2);
-  it->lp0 = at(far_lp_doubles(d.P, Vmax));
-  it->lp1 = at(it->C1 ? far_lp_doubles(it->C1, Vmax) : 0);
+  // a batch's items share the GPU: four times a single item's blocks between them
+  it->m2l_blocks = n_items > 1 ? (4 * kFarM2LBlocks + n_items - 1) / n_items : kFarM2LBlocks;
+  it->lp0 = at(far_lp_doubles(d.P, Vmax, it->m2l_blocks, it->C1 > 0));
+  it->lp1 = at(it->C1 ? far_lp_doubles(it->C1, Vmax, it->m2l_blocks, false) : 0);
   it->ls0 = at((size_t)Vmax * C0 * kFarW * 2);
   it->ls1 = at((size_t)Vmax * C1 * kFarW * 2);
   it->fu = at((size_t)d.nk * d.Mc * (bwd ? 4 : 2));
   if (bwd) {
     it->tp0 = at((size_t)d.n_sides * d.nk * C0 * kFarW * 2);
-    it->tp1 = at((size_t)2 * d.n_sides * d.nk * C1 * kFarW * 2);
+    it->tp1 = at((size_t)(it->g / 4) * d.n_sides * d.nk * C1 * kFarW * 2);
     it->fc = at((size_t)d.Mc * 4);
+    it->cpart = at((size_t)kNearSlots * near_subs(d.qs) * d.Mc * 4);
     it->fs = at((size_t)(d.nk + 2) * d.N * 2);
   }
-  // waves of the near source passes: about 8192, a chunk's list cut into at most eight
-  const int chunks = (d.N + kWave - 1) / kWave;
-  int ns = (8192 + chunks - 1) / chunks;
-  it->nsrc = ns > 8 ? 8 : ns;
+  // a chunk's list is cut into at most kFarMaxShares
+  const long long chunks = (long long)d.P * near_subs(d.qs) * n_items;
+  const int ns = (int)((kFarSourceWaves + chunks - 1) / chunks);
+  it->nsrc = ns > kFarMaxShares ? kFarMaxShares : ns;
 }
 
 }  // namespace qbx

@@ -5,15 +5,14 @@
 
 namespace qbx {
 
-static __constant__ double g_zmin_hi[fartab::kLen] = {QBX_FAR_ZMIN_24};
-static __constant__ double g_zmin_lo[fartab::kLen] = {QBX_FAR_ZMIN_12};
-static_assert(kFarQ == 24 && kFarLo == 12, "the tables are for these orders");
+static __constant__ double g_zmin[fartab::kLen] = {QBX_FAR_ZMIN_24};
+static_assert(kFarQ == 24, "the table is for this order");
 
 // smallest k d that resolves a cluster of k radius x (rounded up to a table entry)
-__device__ __forceinline__ double far_zmin(const double* tab, double x) {
+__device__ __forceinline__ double far_zmin(double x) {
   const double s = ceil((log2(fmax(x, 1e-30)) - fartab::kI0) * fartab::kSteps);
   if (!(s < (double)fartab::kLen)) return 1e300;
-  return tab[s > 0.0 ? (int)s : 0];
+  return g_zmin[s > 0.0 ? (int)s : 0];
 }
 
 __device__ __forceinline__ double wave_max(double v) {
@@ -36,8 +35,8 @@ __global__ __launch_bounds__(64) void k_far_recs(FarBlocks B, const double* __re
   const int lane = threadIdx.x;
   const bool group = b >= it.P;
   const int c = group ? b - it.P : b;
-  const int m0 = group ? c * kFarGroup : c;
-  const int m1 = group ? min(m0 + kFarGroup, it.P) : c + 1;
+  const int m0 = group ? c * it.g : c;
+  const int m1 = group ? min(m0 + it.g, it.P) : c + 1;
   const double* X = nodes + it.node_off;
   double sx = 0.0, sy = 0.0;
   for (int a = m0 * kQ + lane; a < m1 * kQ; a += kWave) {
@@ -83,10 +82,8 @@ __global__ __launch_bounds__(64) void k_far_recs(FarBlocks B, const double* __re
     r.by = by;
     r.rs = rs;
     r.rt = rt;
-    r.ds = far_zmin(g_zmin_hi, it.k * rs) / it.k;
-    r.dt = far_zmin(g_zmin_hi, it.k * rt) / it.k;
-    r.dsl = far_zmin(g_zmin_lo, it.k * rs) / it.k;
-    r.dtl = far_zmin(g_zmin_lo, it.k * rt) / it.k;
+    r.ds = far_zmin(it.k * rs) / it.k;
+    r.dt = far_zmin(it.k * rt) / it.k;
     r.rb = rb;
     r.gr = gr;
     reinterpret_cast<FarRec*>(wo + (group ? it.rec1 : it.rec0))[c] = r;
@@ -191,8 +188,8 @@ __global__ __launch_bounds__(64) void k_far_p2m(FarBlocks B, const double* __res
   const int c = group ? b - it.P : b;
   const int C = group ? it.C1 : it.P;
   const FarRec rec = reinterpret_cast<const FarRec*>(ro + (group ? it.rec1 : it.rec0))[c];
-  const int j0 = (group ? c * kFarGroup : c) * it.fqs;
-  const int j1 = group ? min(j0 + kFarGroup * it.fqs, it.P * it.fqs) : j0 + it.fqs;
+  const int j0 = (group ? c * it.g : c) * it.fqs;
+  const int j1 = group ? min(j0 + it.g * it.fqs, it.P * it.fqs) : j0 + it.fqs;
   const int Nf = it.P * it.fqs;
   const double4* geo = reinterpret_cast<const double4*>(ro + it.fgeo);
   const double2* dens = reinterpret_cast<const double2*>(ro + it.fdens);
@@ -265,84 +262,120 @@ __global__ __launch_bounds__(64) void k_far_p2m(FarBlocks B, const double* __res
         acc.y += ai;
       }
     }
+    double2* r0 = rows + ((size_t)(kk * 2 + 0) * C + c) * kFarW + kFarQ;
+    double2* r1 = rows + ((size_t)(kk * 2 + 1) * C + c) * kFarW + kFarQ;
     if (lane < kFarW) {
       const int m = lane - kFarQ;
-      rows[((size_t)(kk * 2 + 0) * C + c) * kFarW + lane] = acc;
       const double s = (m & 1) ? -1.0 : 1.0;
-      rows[((size_t)(kk * 2 + 1) * C + c) * kFarW + (kFarQ - m)] =
-          make_double2(s * acc.x, s * acc.y);
+      r0[m] = acc;
+      r1[-m] = make_double2(s * acc.x, s * acc.y);
     }
   }
 }
 
-// State of one pair's translation: H_{n-1}, H_n, 2n/z, e^{i n phi}
+// The translation's inner work.  Per pair of clusters and order n of F, L_l takes M_{l+n} F_n
+// and M_{l-n} F_{-n}, four FMAs a term with M in scalar registers.  The row (49 complex
+// values) does not fit those, so it streams through them in pieces of at most kPiece
+// values: the next piece is requested before the current one's FMAs are issued, and its
+// latency hides behind them (scalar loads return in any order, so a wait is for all of
+// them: the request has to come after the current piece has arrived).  Every order is
+// unrolled (45 KB of code); eight rolled blocks of six orders with rows padded to the
+// widest (7 KB) were measured 10 to 60% slower at 256 to 4096 panels.
+constexpr int kPiece = 8;
+struct FarPiece {
+  double2 m[kPiece];
+};
+// order N: F_N serves l < pos, F_{-N} serves l >= neg0
+template <int N>
+struct FarOrder {
+  static constexpr int pos = N <= kFarQ ? kFarQ - N + 1 : 0;
+  static constexpr int neg0 = N > kFarQ ? N - kFarQ : 0;
+  static constexpr int neg = N == 0 ? 0 : kFarQ + 1 - neg0;
+  static constexpr int pp = (pos + kPiece - 1) / kPiece, np = (neg + kPiece - 1) / kPiece;
+  static constexpr int pieces = pp + np;
+};
+// piece PC of order N: M_{m0} .. M_{m0 + len - 1} for l0 ..
+template <int N, int PC>
+struct FarAt {
+  using O = FarOrder<N>;
+  static constexpr bool is_pos = PC < O::pp;
+  static constexpr int k = is_pos ? PC : PC - O::pp;
+  static constexpr int l0 = (is_pos ? 0 : O::neg0) + k * kPiece;
+  static constexpr int left = (is_pos ? O::pos : O::neg) - k * kPiece;
+  static constexpr int len = left < kPiece ? left : kPiece;
+  static constexpr int m0 = is_pos ? l0 + N : l0 - N;
+};
+
+// state of one pair's translation: H_{n-1}, H_n, 2n/z, e^{i n phi}
 struct FarRun {
   double hm_r, hm_i, hc_r, hc_i, tl, tz;
   double2 E, e;
 };
 
-// the terms F_n and F_{-n}, then n + 1 (the orders unrolled by recursion: their
-// register indices are constants)
-template <int Q, int N>
-__device__ __forceinline__ void far_steps(FarRun& f, const double2* __restrict__ base,
+template <int N, int PC>
+__device__ __forceinline__ void far_steps(FarRun& f, double fr, double fi, double gr, double gi,
+                                          FarPiece cur, const double2* __restrict__ row,
                                           double (&Lr)[kFarQ + 1], double (&Li)[kFarQ + 1]) {
-  if constexpr (N <= 2 * Q) {
-    const double rr = f.hc_r * f.E.x, ii = f.hc_i * f.E.y, ri = f.hc_r * f.E.y,
-                 ir = f.hc_i * f.E.x;
-    const double fp_r = rr - ii, fp_i = ri + ir;                   // F_n
-    constexpr double s = (N & 1) ? -1.0 : 1.0;
-    const double fm_r = s * (rr + ii), fm_i = s * (ir - ri);       // F_{-n}
-    // the row is read again for every order (scalar cache): all of it would not fit the
-    // scalar registers
-    const double2* __restrict__ row = base + opaque_zero();
+  using A = FarAt<N, PC>;
+  constexpr bool last_piece = PC + 1 == FarOrder<N>::pieces;
+  constexpr bool last = last_piece && N == 2 * kFarQ;
+  constexpr int N2 = last_piece ? N + 1 : N, P2 = last_piece ? 0 : PC + 1;
 #pragma unroll
-    for (int l = 0; l <= Q; ++l) {
-      if (l + N <= Q) {
-        const double2 M = row[l + N];
-        Lr[l] = fma(M.x, fp_r, fma(-M.y, fp_i, Lr[l]));
-        Li[l] = fma(M.x, fp_i, fma(M.y, fp_r, Li[l]));
-      }
-      if (l - N >= -Q) {
-        const double2 M = row[l - N];
-        Lr[l] = fma(M.x, fm_r, fma(-M.y, fm_i, Lr[l]));
-        Li[l] = fma(M.x, fm_i, fma(M.y, fm_r, Li[l]));
-      }
+  for (int i = 0; i < A::len; ++i) asm volatile("" : "+s"(cur.m[i].x), "+s"(cur.m[i].y));
+  FarPiece nxt;
+  if constexpr (!last) {
+    using B = FarAt<N2, P2>;
+    const double2* __restrict__ r = row + opaque_zero();
+#pragma unroll
+    for (int i = 0; i < B::len; ++i) nxt.m[i] = r[B::m0 + i];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const double Fr = A::is_pos ? fr : gr, Fi = A::is_pos ? fi : gi;
+#pragma unroll
+  for (int i = 0; i < A::len; ++i) {
+    const double2 M = cur.m[i];
+    Lr[A::l0 + i] = fma(M.x, Fr, fma(-M.y, Fi, Lr[A::l0 + i]));
+    Li[A::l0 + i] = fma(M.x, Fi, fma(M.y, Fr, Li[A::l0 + i]));
+  }
+  if constexpr (!last) {
+    if constexpr (last_piece) {   // F_{n+1}, F_{-n-1}
+      const double rr = f.hc_r * f.E.x, ii = f.hc_i * f.E.y, ri = f.hc_r * f.E.y,
+                   ir = f.hc_i * f.E.x;
+      constexpr double s = (N2 & 1) ? -1.0 : 1.0;
+      fr = rr - ii;
+      fi = ri + ir;
+      gr = s * (rr + ii);
+      gi = s * (ir - ri);
+      const double hn_r = fma(f.tl, f.hc_r, -f.hm_r), hn_i = fma(f.tl, f.hc_i, -f.hm_i);
+      f.hm_r = f.hc_r;
+      f.hm_i = f.hc_i;
+      f.hc_r = hn_r;
+      f.hc_i = hn_i;
+      f.tl += f.tz;
+      const double er = fma(f.E.x, f.e.x, -f.E.y * f.e.y), ei = fma(f.E.x, f.e.y, f.E.y * f.e.x);
+      f.E.x = er;
+      f.E.y = ei;
+      // one order in flight: without it the compiler runs the recurrences ahead
+      asm volatile("" : "+v"(f.hm_r), "+v"(f.hm_i), "+v"(f.hc_r), "+v"(f.hc_i), "+v"(f.E.x),
+                   "+v"(f.E.y));
     }
-    const double hn_r = fma(f.tl, f.hc_r, -f.hm_r), hn_i = fma(f.tl, f.hc_i, -f.hm_i);
-    f.hm_r = f.hc_r;
-    f.hm_i = f.hc_i;
-    f.hc_r = hn_r;
-    f.hc_i = hn_i;
-    f.tl += f.tz;
-    const double er = fma(f.E.x, f.e.x, -f.E.y * f.e.y), ei = fma(f.E.x, f.e.y, f.E.y * f.e.x);
-    f.E.x = er;
-    f.E.y = ei;
-    // one order in flight: without it the compiler keeps every F_n live
-    asm volatile("" : "+v"(f.hm_r), "+v"(f.hm_i), "+v"(f.hc_r), "+v"(f.hc_i), "+v"(f.E.x),
-                 "+v"(f.E.y));
-#pragma unroll
-    for (int l = 0; l <= Q; ++l) asm volatile("" : "+v"(Lr[l]), "+v"(Li[l]));
-    far_steps<Q, N + 1>(f, base, Lr, Li);
+    __builtin_amdgcn_sched_barrier(0);
+    far_steps<N2, P2>(f, fr, fi, gr, gi, nxt, row, Lr, Li);
   }
 }
 
-// L_l += sum_m M_m F_{m-l}, l = 0..Q, for one pair of clusters a lane: row[m] = M_m is
-// wave-uniform (scalar loads, the FMAs read it from scalar registers), F_n runs up from
-// the Hankel seeds.
-template <int Q>
+// L_l += sum_m M_m F_{m-l}, l = 0..kFarQ, for one pair of clusters a lane; row[m] = M_m,
+// wave-uniform
 __device__ __forceinline__ void far_translate(double z, double iz, double2 e,
                                               const double2* __restrict__ row,
                                               const double* __restrict__ cf,
                                               double (&Lr)[kFarQ + 1], double (&Li)[kFarQ + 1]) {
   const H01 h = hankel01(z, iz, cf);
-#pragma unroll
-  for (int l = 0; l <= Q; ++l) {
-    const double2 M = row[l];
-    Lr[l] = fma(M.x, h.h0r, fma(-M.y, h.h0i, Lr[l]));
-    Li[l] = fma(M.x, h.h0i, fma(M.y, h.h0r, Li[l]));
-  }
   FarRun f{h.h0r, h.h0i, h.h1r, h.h1i, 2.0 * iz, 2.0 * iz, e, e};
-  far_steps<Q, 1>(f, row, Lr, Li);
+  FarPiece first;
+#pragma unroll
+  for (int i = 0; i < FarAt<0, 0>::len; ++i) first.m[i] = row[i];
+  far_steps<0, 0>(f, h.h0r, h.h0i, 0.0, 0.0, first, row, Lr, Li);
 }
 
 // Translations: lanes are 64 consecutive target clusters, the source cluster is
@@ -351,62 +384,92 @@ __device__ __forceinline__ void far_translate(double z, double iz, double2 e,
 // so the second half runs the same code on the second set of rows with the angle
 // negated (half the accumulators in registers, twice the waves).  The four waves of a
 // block take every fourth source of the block's share and are added in wave order.
-__global__ __launch_bounds__(256, 2) void k_far_m2l(FarBlocks B, const double* __restrict__ ro,
-                                                 double* __restrict__ wo) {
+template <bool GROUP>
+__global__ __launch_bounds__(256, 3) void k_far_m2l(FarBlocks B, const double* __restrict__ ro,
+                                                    double* __restrict__ wo) {
   __shared__ double2 red[kFarQ + 1][kWave];
   int b;
   const FarItem& it = *far_item(B, blockIdx.x, &b);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int per0 = ((it.P + kWave - 1) / kWave) * it.V * 2 * it.n0;
-  const bool group = b >= per0;
-  if (group) b -= per0;
-  const int C = group ? it.C1 : it.P;
-  const int ns = group ? it.n1 : it.n0;
+  const int C = GROUP ? it.C1 : it.P;
+  const int ns = GROUP ? it.n1 : it.n0;
   // block order: source share fastest, then half, vector, target block
   const int sp = b % ns;
   const int half = (b / ns) & 1;
   const int v = (b / (2 * ns)) % it.V;
   const int tb = b / (2 * ns * it.V);
   const FarRec* __restrict__ rec =
-      reinterpret_cast<const FarRec*>(ro + (group ? it.rec1 : it.rec0));
-  const FarRec* __restrict__ grec =
-      reinterpret_cast<const FarRec*>(ro + it.rec1);
-  const double4* __restrict__ bnd = reinterpret_cast<const double4*>(ro + it.bnd);
+      reinterpret_cast<const FarRec*>(ro + (GROUP ? it.rec1 : it.rec0));
+  const FarRec* __restrict__ grec = reinterpret_cast<const FarRec*>(ro + it.rec1);
   const double2* __restrict__ rows =
-      reinterpret_cast<const double2*>(ro + (group ? it.rows1 : it.rows0)) +
+      reinterpret_cast<const double2*>(ro + (GROUP ? it.rows1 : it.rows0)) +
       (size_t)(v * 2 + half) * C * kFarW + kFarQ;
-  const int t = tb * kWave + lane;
-  const bool valid = t < C;
-  const int tt = valid ? t : C - 1;
-  const FarRec me = rec[tt];
-  const bool inner = !group && it.C1 > 0;
-  const bool gam = !group && it.g2 > 0.0;
-  const double k = it.k, inv_k = 1.0 / k;
+  const bool inner = !GROUP && it.C1 > 0;
+  const bool gam = !GROUP && it.g2 > 0.0;
+  const int g = it.g;
   double Lr[kFarQ + 1], Li[kFarQ + 1];
 #pragma unroll
   for (int l = 0; l <= kFarQ; ++l) Lr[l] = Li[l] = 0.0;
-  for (int A = sp * 4 + wave; A < C; A += 4 * ns) {
-    const FarRec o = rec[A];
-    bool on = valid && far_adm(me, o);
-    if (inner && on) on = !far_adm(grec[tt / kFarGroup], grec[A / kFarGroup]);
-    if (gam && on) on = !panels_near(bnd[tt], bnd[A], it.g2);
-    if (!__any(on)) continue;
+  // One source cluster for the lanes whose pair with it is taken at this level.  The
+  // lane's own record is read again each time: it would take registers from the
+  // accumulators for the whole loop.
+  auto source = [&](int A) {
+    const int z0 = opaque_zero();
+    const int t = tb * kWave + lane + z0;
+    const int tt = t < C ? t : C - 1;
+    const FarRec me = rec[tt], o = rec[A];
+    bool on = t < C && far_adm(me, o);
+    if (inner && on) on = !far_adm(grec[tt / g], grec[A / g]);
+    if (gam && on) {
+      const double4* bnd = reinterpret_cast<const double4*>(ro + it.bnd);
+      on = !panels_near(bnd[tt], bnd[A], it.g2);
+    }
+    if (!__any(on)) return;
     if (on) {
       const double dx = me.bx - o.bx, dy = me.by - o.by;
       const double d2 = fma(dx, dx, dy * dy);
       const double ir = rsqrt_refined(d2);
-      const double z = k * (d2 * ir), iz = ir * inv_k;
+      const double k = it.k;
       const double2 e = make_double2(dx * ir, half ? -dy * ir : dy * ir);
-      const int z0 = opaque_zero();
-      const double2* __restrict__ row = rows + (size_t)A * kFarW + z0;
-      const double* __restrict__ cf = g_seed_table + z0;
-      if (__all(far_adm_lo(me, o)))
-        far_translate<kFarLo>(z, iz, e, row, cf, Lr, Li);
-      else
-        far_translate<kFarQ>(z, iz, e, row, cf, Lr, Li);
+      far_translate(k * (d2 * ir), ir / k, e, rows + (size_t)A * kFarW + z0,
+                           g_seed_table + z0, Lr, Li);
+    }
+  };
+  const int share = sp * 4 + wave, shares = 4 * ns;
+  // Panels whose pairs are mostly taken group by group: a ballot finds the groups that
+  // some group of this block's targets does not take (64 at a time), and their panels
+  // are dealt out to the waves in turn.  Otherwise every source is a candidate.
+  const int end = inner ? it.C1 : C;
+  int turn = 0;
+#pragma unroll 1
+  for (int c0 = inner ? 0 : share; c0 < end; c0 += inner ? kWave : shares) {
+    unsigned long long mask = 1;
+    if (inner) {
+      bool need = false;
+      if (c0 + lane < end) {
+        const FarRec q = grec[c0 + lane];
+        const int t1 = min(tb * kWave + kWave - 1, C - 1) / g;
+#pragma unroll 1
+        for (int tg = tb * kWave / g; tg <= t1; ++tg) need = need || !far_adm(grec[tg], q);
+      }
+      mask = __ballot(need);
+    }
+#pragma unroll 1
+    while (mask) {
+      const int c = c0 + __builtin_ctzll(mask);
+      mask &= mask - 1;
+      int A = inner ? c * g : c;
+      const int a1 = inner ? min(A + g, C) : c + 1;
+#pragma unroll 1
+      for (; A < a1; ++A) {
+        if (inner && turn++ % shares != share) continue;
+        source(A);
+      }
     }
   }
+  const int t = tb * kWave + lane;
+  const bool valid = t < C;
   for (int w = 0; w < 4; ++w) {
     if (wave == w) {
 #pragma unroll
@@ -421,7 +484,7 @@ __global__ __launch_bounds__(256, 2) void k_far_m2l(FarBlocks B, const double* _
     }
     __syncthreads();
   }
-  double2* out = reinterpret_cast<double2*>(wo + (group ? it.lp1 : it.lp0)) +
+  double2* out = reinterpret_cast<double2*>(wo + (GROUP ? it.lp1 : it.lp0)) +
                  ((size_t)(sp * it.V + v) * 2 + half) * (kFarQ + 1) * C;
   if (valid)
     for (int l = wave; l <= kFarQ; l += 4) out[(size_t)l * C + t] = red[l][lane];
@@ -566,7 +629,7 @@ __global__ __launch_bounds__(256, 2) void k_far_eval(FarBlocks B, const double* 
   const int nvec = MODE == 2 ? 1 : it.nk;
   const size_t Mt = (size_t)sides * it.T;
   for (int lev = 0; lev < levels; ++lev) {
-    const int c = lev ? m / kFarGroup : m;
+    const int c = lev ? m / it.g : m;
     const int C = lev ? it.C1 : it.P;
     const FarRec rec = reinterpret_cast<const FarRec*>(ro + (lev ? it.rec1 : it.rec0))[c];
     const double vx = tg.tx - rec.bx, vy = tg.ty - rec.by;
@@ -718,7 +781,8 @@ __global__ __launch_bounds__(256, 2) void k_far_eval(FarBlocks B, const double* 
 
 // Adjoint, target side: T_l = sum_c G_c E_l(c) per kind,
 // E_l = e^{i l beta} sum_m (W_m e^{-i m beta}) J_{l-m}(k|tau|), over the block's targets of
-// each panel (16 lanes) and of the group (64).  tp0[si][kk][panel], tp1[2 si + half][kk][group].
+// each panel (16 lanes) and of the group (64: four panels, a group or half of one).
+// tp0[si][kk][panel], tp1[si (g / 4) + half][kk][group].
 __global__ __launch_bounds__(256) void k_far_t(FarBlocks B, const double* __restrict__ ro,
                                                double* __restrict__ wo) {
   __shared__ double Jt[kFarJ + 1][kWave];
@@ -745,7 +809,7 @@ __global__ __launch_bounds__(256) void k_far_t(FarBlocks B, const double* __rest
   g[1] = valid && it.nk > 1 ? G[Mt + ci] : make_double2(0.0, 0.0);
   const int levels = it.C1 > 0 ? 2 : 1;
   for (int lev = 0; lev < levels; ++lev) {
-    const int c = lev ? m / kFarGroup : m;
+    const int c = lev ? m / it.g : m;
     const int C = lev ? it.C1 : it.P;
     const FarRec rec = reinterpret_cast<const FarRec*>(ro + (lev ? it.rec1 : it.rec0))[c];
     const double vx = tg.tx - rec.bx, vy = tg.ty - rec.by;
@@ -812,7 +876,7 @@ __global__ __launch_bounds__(256) void k_far_t(FarBlocks B, const double* __rest
             if ((lane & 15) == 0 && valid)
               tp[(((size_t)si * it.nk + kk) * C + c) * kFarW + l0 + i + kFarQ] = s;
           } else if (lane == 0) {
-            tp[(((size_t)(2 * si + (tb & 1)) * it.nk + kk) * C + c) * kFarW + l0 + i + kFarQ] = s;
+            tp[(((size_t)(si * (it.g / 4) + tb % (it.g / 4)) * it.nk + kk) * C + c) * kFarW + l0 + i + kFarQ] = s;
           }
         }
       }
@@ -838,10 +902,10 @@ __global__ __launch_bounds__(256) void k_far_rows(FarBlocks B, const double* __r
   const int sides = it.pt ? 1 : it.n_sides;
   double2 s = make_double2(0.0, 0.0);
   for (int si = 0; si < sides; ++si)
-    for (int h = 0; h < (group ? 2 : 1); ++h) {
+    for (int h = 0; h < (group ? it.g / 4 : 1); ++h) {
       // the last group's second block is missing when it has at most four panels
-      if (group && h && c * kFarGroup + kFarGroup / 2 >= it.P) continue;
-      const int part = group ? 2 * si + h : si;
+      if (group && c * it.g + 4 * h >= it.P) continue;
+      const int part = group ? si * (it.g / 4) + h : si;
       const double2 x = tp[(((size_t)part * it.nk + kk) * C + c) * kFarW + m + kFarQ];
       s.x += x.x;
       s.y += x.y;
@@ -881,7 +945,7 @@ __global__ __launch_bounds__(64) void k_far_src(FarBlocks B, const double* __res
     for (int s = 0; s < 5; ++s) P[a][s] = make_double2(0.0, 0.0);
   const int levels = it.C1 > 0 ? 2 : 1;
   for (int lev = 0; lev < levels; ++lev) {
-    const int c = lev ? m / kFarGroup : m;
+    const int c = lev ? m / it.g : m;
     const int C = lev ? it.C1 : it.P;
     const FarRec rec = reinterpret_cast<const FarRec*>(ro + (lev ? it.rec1 : it.rec0))[c];
     if (far_none(rec)) continue;
@@ -998,6 +1062,7 @@ __global__ __launch_bounds__(256) void k_far_lists(FarBlocks B, const double* __
   FarRel R;
   R.r0 = reinterpret_cast<const FarRec*>(ro + it.rec0);
   R.r1 = it.C1 > 0 ? reinterpret_cast<const FarRec*>(ro + it.rec1) : nullptr;
+  R.g = it.g;
   R.bnd = nullptr;
   R.g2 = 0.0;
   int* count = reinterpret_cast<int*>(wo + it.ncount);
@@ -1032,9 +1097,8 @@ int far_blocks(const FarItem& it, FarStep step) {
   const int sides = it.pt ? 1 : it.n_sides;
   switch (step) {
     case kStepClusters: return it.P + it.C1;
-    case kStepM2L:
-      return 2 * it.V * (((it.P + kWave - 1) / kWave) * it.n0 +
-                         ((it.C1 + kWave - 1) / kWave) * it.n1);
+    case kStepM2L: return 2 * it.V * ((it.P + kWave - 1) / kWave) * it.n0;
+    case kStepM2LGroups: return 2 * it.V * ((it.C1 + kWave - 1) / kWave) * it.n1;
     case kStepSum:
       return (it.V * 2 * (kFarQ + 1) * it.P + 255) / 256 +
              (it.V * 2 * (kFarQ + 1) * it.C1 + 255) / 256;
@@ -1044,7 +1108,8 @@ int far_blocks(const FarItem& it, FarStep step) {
     case kStepSources: return it.P * ((it.fqs + kWave - 1) / kWave);
     case kStepLists: return (it.P + 3) / 4;
     case kStepCenters: return (it.Mc + 3) / 4;
-    case kStepChunks: return (((it.N + kWave - 1) / kWave) * it.nsrc + 3) / 4;
+    case kStepChunks: return (it.P * near_subs(it.qs) * it.nsrc + 3) / 4;
+    case kStepCenterSums: return (it.Mc + 63) / 64;
   }
   return 0;
 }
@@ -1062,8 +1127,12 @@ hipError_t launch_far_p2m(const FarBlocks& B, int blocks, double* ws, hipStream_
   hipLaunchKernelGGL(k_far_p2m, dim3(blocks), dim3(64), 0, s, B, ws, ws);
   return hipGetLastError();
 }
-hipError_t launch_far_m2l(const FarBlocks& B, int blocks, double* ws, hipStream_t s) {
-  hipLaunchKernelGGL(k_far_m2l, dim3(blocks), dim3(256), 0, s, B, ws, ws);
+hipError_t launch_far_m2l(bool groups, const FarBlocks& B, int blocks, double* ws,
+                          hipStream_t s) {
+  if (groups)
+    hipLaunchKernelGGL(k_far_m2l<true>, dim3(blocks), dim3(256), 0, s, B, ws, ws);
+  else
+    hipLaunchKernelGGL(k_far_m2l<false>, dim3(blocks), dim3(256), 0, s, B, ws, ws);
   return hipGetLastError();
 }
 hipError_t launch_far_lsum(const FarBlocks& B, int blocks, double* ws, hipStream_t s) {
@@ -1104,8 +1173,8 @@ FarPlan far_single(const FarItem& it, const FarItem* dev) {
 void far_shape(FarItem* it, bool fwd, bool bwd) {
   it->vf = fwd ? it->nk : 0;
   it->V = it->vf + (bwd ? it->nk : 0);
-  it->n0 = far_share(it->P, it->V);
-  it->n1 = it->C1 ? far_share(it->C1, it->V) : 1;
+  it->n0 = far_share(it->P, it->V, it->m2l_blocks, it->C1 > 0);
+  it->n1 = it->C1 ? far_share(it->C1, it->V, it->m2l_blocks, false) : 1;
 }
 
 hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fwd, bool bwd,
@@ -1116,7 +1185,9 @@ hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fw
     e = launch_far_p2m(P.at[kStepClusters], P.blocks[kStepClusters], ws, s);
   if (e == hipSuccess && bwd) e = launch_far_t(P.at[kStepTargets], P.blocks[kStepTargets], ws, s);
   if (e == hipSuccess && bwd) e = launch_far_rows(P.at[kStepRows], P.blocks[kStepRows], ws, s);
-  if (e == hipSuccess) e = launch_far_m2l(P.at[kStepM2L], P.blocks[kStepM2L], ws, s);
+  if (e == hipSuccess) e = launch_far_m2l(false, P.at[kStepM2L], P.blocks[kStepM2L], ws, s);
+  if (e == hipSuccess && P.blocks[kStepM2LGroups] > 0)
+    e = launch_far_m2l(true, P.at[kStepM2LGroups], P.blocks[kStepM2LGroups], ws, s);
   if (e == hipSuccess) e = launch_far_lsum(P.at[kStepSum], P.blocks[kStepSum], ws, s);
   if (e == hipSuccess && eval >= 0)
     e = launch_far_eval(eval, P.at[kStepTargets], P.blocks[kStepTargets], ws, s);

@@ -1,8 +1,8 @@
 // Near pairs: the pairs of a center and a source that are evaluated one by one when
 // the far ones are summed otherwise (the panel expansions of qbx_far.hip, the direct rule
-// of the near/far split).  One wave per center walks its target panel's near list, one
-// wave per 64-source chunk the lists of its panels; panels with more than kNearCap near
-// panels are served by a scan of all panels.  The pair bodies are those of the plain
+// of the near/far split).  One wave per center, or per 64 sources of a panel, walks its
+// panel's near list; panels with more than kNearCap near panels are served by a scan of
+// all panels.  The pair bodies are those of the plain
 // kernels (qbx_pair.h).
 #include "qbx_far.h"
 #include "qbx_pair.h"
@@ -26,6 +26,7 @@ __device__ __forceinline__ NearRel near_rel(const FarItem& it, const double* ro)
   n.gamma = it.g2 > 0.0;
   n.R.r0 = reinterpret_cast<const FarRec*>(ro + it.rec0);
   n.R.r1 = it.C1 > 0 ? reinterpret_cast<const FarRec*>(ro + it.rec1) : nullptr;
+  n.R.g = it.g;
   n.R.bnd = reinterpret_cast<const double4*>(ro + it.bnd);
   n.R.g2 = it.g2;
   return n;
@@ -63,42 +64,6 @@ __device__ __forceinline__ void for_near_panels(int m, const NearRel& R, int NP,
       const int pan = w0 + __builtin_ctzll(mask);
       mask &= mask - 1;
       f(pan);
-    }
-  }
-}
-
-// f(m) once for every panel m near any of the panels pa..pb (a 64-source chunk's
-// panels), of those every ns-th starting at the sp-th: from their lists, each m at the
-// first list that holds it, when every list fits; else by the wave's scan (ascending)
-template <typename F>
-__device__ __forceinline__ void for_near_any(int pa, int pb, const NearRel& R, int NP,
-                                             NearLists nl, int lane, int sp, int ns, F&& f) {
-  bool fits = true;
-  for (int ps = pa; ps <= pb; ++ps) fits = fits && nl.count[ps] <= kNearCap;
-  int n = 0;
-  if (fits) {
-    for (int ps = pa; ps <= pb; ++ps) {
-      const int* __restrict__ L = nl.list + (size_t)ps * kNearCap;
-      const int cnt = nl.count[ps];
-      for (int i = 0; i < cnt; ++i) {
-        const int m = L[i];
-        bool seen = false;
-        for (int pq = pa; pq < ps; ++pq) seen = seen || is_near(R, m, pq);
-        if (!seen && n++ % ns == sp) f(m);
-      }
-    }
-    return;
-  }
-  for (int w0 = 0; w0 < NP; w0 += kWave) {
-    const int mt = w0 + lane;
-    bool any = false;
-    if (mt < NP)
-      for (int ps = pa; ps <= pb; ++ps) any = any || is_near(R, mt, ps);
-    unsigned long long mask = __ballot(any);
-    while (mask) {
-      const int m = w0 + __builtin_ctzll(mask);
-      mask &= mask - 1;
-      if (n++ % ns == sp) f(m);
     }
   }
 }
@@ -214,8 +179,142 @@ __global__ __launch_bounds__(256) void k_near_grad(FarBlocks B, const double* __
   }
 }
 
-// Adjoint, center side: the tape sums over the near sources (K_R, K_theta, grad_v K)
-// contracted with G, plain: plus the far ones (fc); then center_grad_from_sums.
+// A source pass's wave: share sp of ns of the list of chunk (panel, sub), 64 sources of one
+// panel (fewer in the last)
+struct NearChunk {
+  int panel, sub, sp;
+  bool on;
+};
+__device__ __forceinline__ NearChunk near_chunk(const FarItem& it, int w) {
+  NearChunk c;
+  const int subs = near_subs(it.qs), ns = it.nsrc;
+  const int ch = w / ns;
+  c.sp = w - ch * ns;
+  c.panel = ch / subs;
+  c.sub = ch - c.panel * subs;
+  c.on = c.panel < it.P;
+  return c;
+}
+
+// Adjoint, one evaluation per near pair (fused_pair) for both gradient sides.  Lanes are
+// the sources of a chunk; the wave walks its share of the panel's near list and the
+// centers of each panel on it.
+//  * source side, in the lanes: spart[sp][b][j], b < src_slots(KIND); plain: the first
+//    share adds the far sums (fs).
+//  * center side: four reals a pair, summed over the lanes (the reduce-scatter of
+//    fused_tile) into LDS and from there into the chunk's slot of the target panel,
+//    cpart[panel][slot][center][4], slot = position of the chunk's panel in the target
+//    panel's list (times the chunks of a panel).  Panels whose list is longer than
+//    kNearSlots have no slots: k_near_centers sums their centers.
+// Replaces a pass per side (1758 and 1259 flops a pair at p = 20, S + D) by one of 1432.
+template <int P, int KIND>
+__global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double* __restrict__ ro,
+                                                      double* __restrict__ wo) {
+  constexpr bool kS = (KIND & 1) != 0;
+  constexpr bool kD = (KIND & 2) != 0;
+  constexpr int NK = kS && kD ? 2 : 1;
+  constexpr int NA = src_slots(KIND);
+  __shared__ double csum[4][2 * kQ * 4];
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const NearChunk c = near_chunk(it, b * 4 + wave);
+  if (!c.on) return;
+  const int N = it.N, qs = it.qs, T = it.T, Mc = it.Mc, NJ = it.NJ;
+  const bool valid = c.sub * kWave + lane < qs;
+  const int j = c.panel * qs + (valid ? c.sub * kWave + lane : qs - 1);
+  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
+  const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
+  const CenterRec* __restrict__ ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
+  const double* __restrict__ jtab = ro + it.jtab;
+  const double2* __restrict__ G = reinterpret_cast<const double2*>(ro + it.G);
+  const double4 g = geo[j];
+  double2 q[2];   // lanes past the panel's sources take part in the sums with zeros
+  q[0] = valid ? dens[j] : make_double2(0.0, 0.0);
+  q[1] = NK == 2 && valid ? dens[(size_t)N + j] : make_double2(0.0, 0.0);
+  const double k = it.k, inv_k = 1.0 / k;
+  const int nj = NJ / 2, nc = it.n_sides * kQ;
+  const int subs = near_subs(qs);
+  const NearLists nl = near_lists(it, ro);
+  double* __restrict__ cs = csum[wave];
+  Cplx A[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) A[a] = {0.0, 0.0};
+  int turn = 0;
+  for_near_panels(c.panel, near_rel(it, ro), it.P, nl, lane, [&](int m) {
+    if (turn++ % it.nsrc != c.sp) return;
+    const int cnt = nl.count[m];
+    for (int cc = 0; cc < nc; ++cc) {
+      const int si = cc / kQ;
+      const int ci = si * T + m * kQ + (cc - si * kQ);
+      const int z0 = opaque_zero();
+      const CenterRec* __restrict__ C = ctr + ci + z0;
+      double2 Gk[2];
+      Gk[0] = G[(size_t)ci + z0];
+      Gk[1] = NK == 2 ? G[(size_t)Mc + ci + z0] : Gk[0];
+      double cres[4];
+      fused_pair<P, KIND>(g, q, C->cx, C->cy, C->ct, C->st, jtab + (size_t)ci * NJ + z0, nj,
+                          g_seed_table + z0, k, inv_k, Gk, A, cres);
+      const double v = wave_sum4(cres, lane);
+      if ((lane & 15) == 0) cs[cc * 4 + (lane >> 4)] = v;
+    }
+    if (cnt <= kNearSlots) {
+      const int* __restrict__ L = nl.list + (size_t)m * kNearCap;
+      const unsigned long long at = __ballot(lane < cnt && L[lane < cnt ? lane : 0] == c.panel);
+      // (the relation is symmetric, so the panel is on the list)
+      const int slot = (at ? __builtin_ctzll(at) : 0) * subs + c.sub;
+      double* __restrict__ o =
+          wo + it.cpart + (((size_t)m * kNearSlots * subs + slot) * nc) * 4;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (int t = lane; t < nc * 4; t += kWave) o[t] = cs[t];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  });
+  if (valid) {
+    double2* part = reinterpret_cast<double2*>(wo + it.spart) + (size_t)c.sp * NA * N;
+    const double2* fs = reinterpret_cast<const double2*>(ro + it.fs);
+    const bool add = c.sp == 0 && !(it.g2 > 0.0);
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      const double2 f = add ? fs[(size_t)a * N + j] : make_double2(0.0, 0.0);
+      part[(size_t)a * N + j] = make_double2(A[a].r + f.x, A[a].i + f.y);
+    }
+  }
+}
+
+// Adjoint, center side of panels with slots: the slots in list order, plain: after the far
+// sums (fc); four lanes a center, then center_grad_from_sums.
+template <int KIND>
+__global__ __launch_bounds__(256) void k_near_center_sums(FarBlocks B,
+                                                          const double* __restrict__ ro,
+                                                          double* __restrict__ wo) {
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int e = b * 256 + threadIdx.x;
+  const int ci = e >> 2, q = e & 3;
+  if (ci >= it.Mc) return;   // whole groups of four lanes
+  const int si = ci / it.T, t = ci - si * it.T;
+  const int m = t / kQ;
+  const int cnt = near_lists(it, ro).count[m];
+  if (cnt > kNearSlots) return;
+  const int subs = near_subs(it.qs), nc = it.n_sides * kQ;
+  const double* __restrict__ p =
+      ro + it.cpart + ((size_t)m * kNearSlots * subs * nc + si * kQ + (t - m * kQ)) * 4 + q;
+  double s = it.g2 > 0.0 ? 0.0 : ro[it.fc + (size_t)ci * 4 + q];
+  for (int i = 0; i < cnt * subs; ++i) s += p[(size_t)i * nc * 4];
+  const int l0 = threadIdx.x & ~3;
+  const double s0 = __shfl(s, (l0 & 63)), s1 = __shfl(s, (l0 & 63) + 1),
+               s2 = __shfl(s, (l0 & 63) + 2), s3 = __shfl(s, (l0 & 63) + 3);
+  if (q == 0)
+    center_grad_from_sums(ci, it.side, it.T, reinterpret_cast<const CenterRec*>(ro + it.ctr), s0,
+                          s1, s2, s3, wo + it.cg);
+}
+
+// Adjoint, center side of panels without slots, one wave a center: the tape sums over the near
+// sources (K_R, K_theta, grad_v K) contracted with G, plain: plus the far ones (fc).
 template <int P, int KIND>
 __global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double* __restrict__ ro,
                                                       double* __restrict__ wo) {
@@ -230,6 +329,7 @@ __global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double*
   const int Mc = it.Mc;
   if (ci >= Mc) return;
   const int m = (ci % it.T) / kQ;
+  if (near_lists(it, ro).count[m] <= kNearSlots) return;
   const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
   const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
   const CenterRec* ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
@@ -273,72 +373,6 @@ __global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double*
   }
 }
 
-// Adjoint, source side: spart[sp][b][j], b < src_slots(KIND), the plain adjoint's
-// source-side sums over the centers of the target panels near j's panel (every ns-th
-// panel of the chunk's a wave); plain: the first share adds the far sums (fs).
-template <int P, int KIND>
-__global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double* __restrict__ ro,
-                                                      double* __restrict__ wo) {
-  constexpr bool kS = (KIND & 1) != 0;
-  constexpr bool kD = (KIND & 2) != 0;
-  constexpr int NK = kS && kD ? 2 : 1;
-  constexpr int NA = src_slots(KIND);
-  int b;
-  const FarItem& it = *far_item(B, blockIdx.x, &b);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int w = b * 4 + wave;
-  const int ns = it.nsrc;
-  const int c = w / ns, sp = w - c * ns;
-  const int N = it.N, qs = it.qs, T = it.T, Mc = it.Mc, NJ = it.NJ;
-  if (c * kWave >= N) return;
-  const int j = c * kWave + lane;
-  const bool valid = j < N;
-  const int jj = valid ? j : N - 1;
-  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
-  const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
-  const CenterRec* __restrict__ ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
-  const double* __restrict__ jtab = ro + it.jtab;
-  const double2* __restrict__ G = reinterpret_cast<const double2*>(ro + it.G);
-  const int mj = jj / qs;
-  const int pa = (c * kWave) / qs;
-  const int pb = min(c * kWave + kWave - 1, N - 1) / qs;
-  const double4 g = geo[jj];
-  double2 q[2];
-  q[0] = dens[jj];
-  q[1] = dens[(size_t)(NK - 1) * N + jj];
-  const double k = it.k, inv_k = 1.0 / k;
-  const int nj = NJ / 2, n_sides = it.n_sides;
-  const NearRel R = near_rel(it, ro);
-  Cplx A[NA];
-#pragma unroll
-  for (int a = 0; a < NA; ++a) A[a] = {0.0, 0.0};
-  for_near_any(pa, pb, R, it.P, near_lists(it, ro), lane, sp, ns, [&](int m) {
-    if (valid && (pa == pb || is_near(R, m, mj))) {
-      for (int si = 0; si < n_sides; ++si) {
-        for (int a = 0; a < kQ; ++a) {
-          const int ci = si * T + m * kQ + a;
-          const int z0 = opaque_zero();
-          const double2 GS = G[(size_t)ci + z0];
-          const double2 GD = NK == 2 ? G[(size_t)Mc + ci + z0] : GS;
-          adjoint_pair<P, KIND>(g, q, ctr + ci + z0, jtab + (size_t)ci * NJ + z0,
-                                g_seed_table + z0, GS, GD, k, inv_k, nj, A);
-        }
-      }
-    }
-  });
-  if (valid) {
-    double2* part = reinterpret_cast<double2*>(wo + it.spart) + (size_t)sp * NA * N;
-    const double2* fs = reinterpret_cast<const double2*>(ro + it.fs);
-    const bool add = sp == 0 && !(it.g2 > 0.0);
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      const double2 f = add ? fs[(size_t)a * N + j] : make_double2(0.0, 0.0);
-      part[(size_t)a * N + j] = make_double2(A[a].r + f.x, A[a].i + f.y);
-    }
-  }
-}
-
 // Adjoint with respect to the density alone: sum_i G_i K_ij over the near centers, into
 // spart[sp][kk][j]; plain: conjugated and with the far sums (fs), as the source passes
 // keep it.
@@ -352,59 +386,52 @@ __global__ __launch_bounds__(256) void k_near_density(FarBlocks B, const double*
   const FarItem& it = *far_item(B, blockIdx.x, &b);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int w = b * 4 + wave;
-  const int ns = it.nsrc;
-  const int c = w / ns, sp = w - c * ns;
+  const NearChunk c = near_chunk(it, b * 4 + wave);
+  if (!c.on) return;
   const int N = it.N, qs = it.qs, T = it.T, Mc = it.Mc, NJ = it.NJ;
-  if (c * kWave >= N) return;
-  const int j = c * kWave + lane;
-  const bool valid = j < N;
-  const int jj = valid ? j : N - 1;
+  const bool valid = c.sub * kWave + lane < qs;
+  const int j = c.panel * qs + (valid ? c.sub * kWave + lane : qs - 1);
   const CenterRec* __restrict__ ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
   const double* __restrict__ jtab = ro + it.jtab;
   const double2* __restrict__ G = reinterpret_cast<const double2*>(ro + it.G);
-  const int mj = jj / qs;
-  const int pa = (c * kWave) / qs;
-  const int pb = min(c * kWave + kWave - 1, N - 1) / qs;
-  const double4 g = reinterpret_cast<const double4*>(ro + it.geo)[jj];
+  const double4 g = reinterpret_cast<const double4*>(ro + it.geo)[j];
   const double k = it.k, inv_k = 1.0 / k;
   const int n_sides = it.n_sides;
-  const NearRel R = near_rel(it, ro);
   double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
-  for_near_any(pa, pb, R, it.P, near_lists(it, ro), lane, sp, ns, [&](int m) {
-    if (valid && (pa == pb || is_near(R, m, mj))) {
-      for (int si_ = 0; si_ < n_sides; ++si_) {
-        for (int a = 0; a < kQ; ++a) {
-          const int ci = si_ * T + m * kQ + a;
-          const int z0 = opaque_zero();
-          const double* __restrict__ J = jtab + (size_t)ci * NJ + z0;
-          const double* __restrict__ cf = g_seed_table + z0;
-          const CenterRec* C = ctr + ci;
-          const double vx = g.x - C->cx, vy = g.y - C->cy;
-          const double rho2 = fma(vx, vx, vy * vy);
-          const double ir = rsqrt_refined(rho2);
-          const double rho = rho2 * ir;
-          const double cd = (C->ct * vx + C->st * vy) * ir;
-          const double sd = (C->st * vx - C->ct * vy) * ir;
-          double cps = 0.0, sps = 0.0;
-          if (kD) {
-            cps = C->ct * g.z + C->st * g.w;
-            sps = C->st * g.z - C->ct * g.w;
-          }
-          double ks_r, ks_i, kd_r, kd_i;
-          pair_kernel<P, KIND>(k * rho, ir * inv_k, cd, sd, cps, sps, J, cf, ks_r, ks_i, kd_r,
-                               kd_i);
-          int kk = 0;
-          if (kS) {
-            const double2 Gi = G[(size_t)(kk++) * Mc + ci];
-            sr = fma(Gi.x, ks_r, fma(-Gi.y, ks_i, sr));
-            si = fma(Gi.x, ks_i, fma(Gi.y, ks_r, si));
-          }
-          if (kD) {
-            const double2 Gi = G[(size_t)kk * Mc + ci];
-            dr = fma(Gi.x, kd_r, fma(-Gi.y, kd_i, dr));
-            di = fma(Gi.x, kd_i, fma(Gi.y, kd_r, di));
-          }
+  int turn = 0;
+  for_near_panels(c.panel, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int m) {
+    if (turn++ % it.nsrc != c.sp) return;
+    for (int si_ = 0; si_ < n_sides; ++si_) {
+      for (int a = 0; a < kQ; ++a) {
+        const int ci = si_ * T + m * kQ + a;
+        const int z0 = opaque_zero();
+        const double* __restrict__ J = jtab + (size_t)ci * NJ + z0;
+        const double* __restrict__ cf = g_seed_table + z0;
+        const CenterRec* C = ctr + ci;
+        const double vx = g.x - C->cx, vy = g.y - C->cy;
+        const double rho2 = fma(vx, vx, vy * vy);
+        const double ir = rsqrt_refined(rho2);
+        const double rho = rho2 * ir;
+        const double cd = (C->ct * vx + C->st * vy) * ir;
+        const double sd = (C->st * vx - C->ct * vy) * ir;
+        double cps = 0.0, sps = 0.0;
+        if (kD) {
+          cps = C->ct * g.z + C->st * g.w;
+          sps = C->st * g.z - C->ct * g.w;
+        }
+        double ks_r, ks_i, kd_r, kd_i;
+        pair_kernel<P, KIND>(k * rho, ir * inv_k, cd, sd, cps, sps, J, cf, ks_r, ks_i, kd_r,
+                             kd_i);
+        int kk = 0;
+        if (kS) {
+          const double2 Gi = G[(size_t)(kk++) * Mc + ci];
+          sr = fma(Gi.x, ks_r, fma(-Gi.y, ks_i, sr));
+          si = fma(Gi.x, ks_i, fma(Gi.y, ks_r, si));
+        }
+        if (kD) {
+          const double2 Gi = G[(size_t)kk * Mc + ci];
+          dr = fma(Gi.x, kd_r, fma(-Gi.y, kd_i, dr));
+          di = fma(Gi.x, kd_i, fma(Gi.y, kd_r, di));
         }
       }
     }
@@ -413,17 +440,17 @@ __global__ __launch_bounds__(256) void k_near_density(FarBlocks B, const double*
     const bool plain = !(it.g2 > 0.0);
     // the split sums near parts itself, [kk][j]; plain parts lie in the source-pass layout
     double2* part = reinterpret_cast<double2*>(wo + it.spart) +
-                    (size_t)sp * (plain ? NA : (kS && kD ? 2 : 1)) * N;
+                    (size_t)c.sp * (plain ? NA : (kS && kD ? 2 : 1)) * N;
     const double2* fs = reinterpret_cast<const double2*>(ro + it.fs);
     const double sg = plain ? -1.0 : 1.0;
     int kk = 0;
     if (kS) {
-      const double2 f = plain && sp == 0 ? fs[j] : make_double2(0.0, 0.0);
+      const double2 f = plain && c.sp == 0 ? fs[j] : make_double2(0.0, 0.0);
       part[j] = make_double2(sr + f.x, sg * si + f.y);
       ++kk;
     }
     if (kD) {
-      const double2 f = plain && sp == 0 ? fs[(size_t)kk * N + j] : make_double2(0.0, 0.0);
+      const double2 f = plain && c.sp == 0 ? fs[(size_t)kk * N + j] : make_double2(0.0, 0.0);
       part[(size_t)kk * N + j] = make_double2(k * dr + f.x, sg * k * di + f.y);
     }
   }
@@ -442,6 +469,9 @@ static hipError_t launch_near_pk(NearPass pass, const FarBlocks& B, int blocks, 
       break;
     case kNearCenters:
       hipLaunchKernelGGL((k_near_centers<P, KIND>), grid, block, 0, s, B, ws, ws);
+      break;
+    case kNearCenterSums:
+      hipLaunchKernelGGL((k_near_center_sums<KIND>), grid, block, 0, s, B, ws, ws);
       break;
     case kNearSources:
       hipLaunchKernelGGL((k_near_sources<P, KIND>), grid, block, 0, s, B, ws, ws);

@@ -824,6 +824,20 @@ __device__ __forceinline__ void fused_pair(const double4 g, const double2 (&q)[2
   cres[3] = ey;
 }
 
+// Four sums over the wave, reduce-scatter: the xor-32 and xor-16 exchanges leave in lane L
+// a four-lane partial of sum (L >> 4) & 3, the xor 8..1 butterfly completes it across
+// each group of 16 lanes: lanes 0, 16, 32, 48 hold sums 0..3
+__device__ __forceinline__ double wave_sum4(const double (&c)[4], int lane) {
+  const bool h32 = (lane & 32) != 0, h16 = (lane & 16) != 0;
+  const double k0 = h32 ? c[2] : c[0], k1 = h32 ? c[3] : c[1];
+  const double e0 = h32 ? c[0] : c[2], e1 = h32 ? c[1] : c[3];
+  const double p0 = k0 + __shfl_xor(e0, 32), p1 = k1 + __shfl_xor(e1, 32);
+  double v = (h16 ? p1 : p0) + __shfl_xor(h16 ? p0 : p1, 16);
+#pragma unroll
+  for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
 // ---------------------------------------------------------------------------
 // fused adjoint tile: one workgroup of four waves, centers [i0, i0 + nc) x
 // 64-source chunks [ch0, ch1) of one contour, taken in sub-blocks of
@@ -885,16 +899,7 @@ __device__ __forceinline__ void fused_tile(
         Gk[1] = NK == 2 ? G[(size_t)Mc + ci + z0] : Gk[0];
         double cres[4];
         fused_pair<P, KIND>(g, q, C->cx, C->cy, C->ct, C->st, J, nj, cf, k, inv_k, Gk, A, cres);
-        // the four sums over the wave, reduce-scatter: the xor-32 and xor-16
-        // exchanges leave in lane L a four-lane partial of sum (L >> 4) & 3, the
-        // xor 8..1 butterfly completes it across each group of 16 lanes
-        const bool h32 = (lane & 32) != 0, h16 = (lane & 16) != 0;
-        const double k0 = h32 ? cres[2] : cres[0], k1 = h32 ? cres[3] : cres[1];
-        const double e0 = h32 ? cres[0] : cres[2], e1 = h32 ? cres[1] : cres[3];
-        const double p0 = k0 + __shfl_xor(e0, 32), p1 = k1 + __shfl_xor(e1, 32);
-        double v = (h16 ? p1 : p0) + __shfl_xor(h16 ? p0 : p1, 16);
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        const double v = wave_sum4(cres, lane);
         // lanes 0, 16, 32, 48 add sums 0..3 to this wave's slots of the center
         if ((lane & 15) == 0) wacc[c * 4 + (lane >> 4)] += v;
       }
