@@ -182,7 +182,7 @@ Layout make_layout(const Dims& d) {
   L.G = take(sizeof(double2) * (size_t)d.nk * d.Mc);
   L.cg = take(sizeof(double) * (size_t)d.Mc * 8);
   int n_sp = std::max(d.n_csplit, d.n_cb);
-  if (far_applies(d)) n_sp = std::max(n_sp, kFarMaxShares);   // of the near source passes
+  if (d.P >= 3) n_sp = std::max(n_sp, kFarMaxShares);   // of the near source passes
   L.spart = take(sizeof(double2) * (size_t)n_sp * src_slots(d.kind) * d.N);
   L.cpart = take(sizeof(double) * (size_t)d.n_sb * d.Mc * 4);
   L.sg = take(sizeof(double) * (size_t)d.N * 8);
@@ -192,7 +192,6 @@ Layout make_layout(const Dims& d) {
   L.nlist = take(sizeof(int) * (size_t)d.P * kNearCap);
   L.fpart = take(sizeof(double2) * (size_t)d.n_fsplit * d.nk * d.T * 2);
   L.gfar = take(sizeof(double2) * (size_t)d.nk * d.T);
-  L.aacc = take(sizeof(double2) * (size_t)d.nk * d.N);
   L.ngeo = take(sizeof(double4) * (size_t)d.T);
   L.ndens = take(sizeof(double2) * (size_t)d.nk * d.T);
   L.nw = take(sizeof(double) * (size_t)d.T);
@@ -200,7 +199,7 @@ Layout make_layout(const Dims& d) {
   L.gtw = take(sizeof(double) * (size_t)d.T * 2);
   L.gde = take(sizeof(double2) * (size_t)d.nk * d.T);
   L.far = 0;
-  if (far_applies(d)) {
+  if (d.P >= 3) {   // contours (the near/far split's near passes use the item at any size)
     L.far = take(sizeof(FarItem));
     FarItem it;
     far_layout(d, true, take, &it);
@@ -436,7 +435,7 @@ static int run_forward_far(const Dims& d, const Layout& L, const double* nodes,
 
 int run_forward(const Dims& d, const Layout& L, const double* nodes, const double* density,
                 double* out, void* ws, hipStream_t stream, bool timed) {
-  if (L.far) return run_forward_far(d, L, nodes, density, out, ws, stream, timed);
+  if (L.far && far_applies(d)) return run_forward_far(d, L, nodes, density, out, ws, stream, timed);
   int rc = prepare(d, L, nodes, density, ws, stream);
   if (rc) return rc;
   if (timed) timer_begin(0, stream);
@@ -525,23 +524,47 @@ int qbx_layer_potential_ext(const qbx_geometry* g, const double* density, double
 
 }  // extern "C"
 
-// the split's panel records, near lists and far sources (every split entry
-// point, after prepare)
-static int split_geometry(const Dims& d, const Layout& L, const qbx_geometry* g,
-                          const double* density, double g2, void* ws, hipStream_t stream,
-                          NearLists* nl, NystromSources* ns) {
+// A split call's common start: source grid and centers, panel records, far sources, gamma
+// near lists and, where they apply, the panel expansions (fwd / bwd, eval, src, geom as
+// in far_fields; the cotangent weights must be in place for bwd, so `before` runs first).
+template <typename Before>
+static int split_start(const Dims& d, const Layout& L, const qbx_geometry* g,
+                       const double* density, double g2, bool fwd, bool bwd, int eval, bool src,
+                       bool geom, void* ws, hipStream_t stream, FarItem* it, SplitCall* c,
+                       Before&& before) {
+  *it = far_item_of(d, L, true, fwd, bwd);
+  it->g2 = g2;
+  it->pt = 1;
+  it->fqs = kQ;
+  it->fgeo = L.ngeo / sizeof(double);
+  it->fdens = L.ndens / sizeof(double);
+  it->fG = L.gfar / sizeof(double);
+  it->ncount = L.ncount / sizeof(double);
+  it->nlist = L.nlist / sizeof(double);
+  int rc = prepare(d, L, g->nodes, density, ws, stream, it);
+  if (rc) return rc;
+  c->far = far_applies_split(d);
+  c->dev = at<FarItem>(ws, L.far);
+  c->ws = static_cast<double*>(ws);
+  c->nodes = g->nodes;
+  c->bnd = at<double4>(ws, L.bnd);
+  c->g2 = g2;
   hipError_t e = launch_panel_bounds(d, g->nodes, at<double4>(ws, L.bnd), stream);
   if (e != hipSuccess) return device_fail(e, "panel bounds kernel");
-  ns->geo = at<double4>(ws, L.ngeo);
-  ns->dens = at<double2>(ws, L.ndens);
-  ns->w = at<double>(ws, L.nw);
-  e = launch_nystrom_sources(d, g->nodes, density, at<double>(ws, L.tables), *ns, stream);
+  c->ns.geo = at<double4>(ws, L.ngeo);
+  c->ns.dens = at<double2>(ws, L.ndens);
+  c->ns.w = at<double>(ws, L.nw);
+  e = launch_nystrom_sources(d, g->nodes, density, at<double>(ws, L.tables), c->ns, stream);
   if (e != hipSuccess) return device_fail(e, "far source kernel");
   e = launch_near_lists(d, at<double4>(ws, L.bnd), g2, at<int>(ws, L.ncount), at<int>(ws, L.nlist),
                         stream);
   if (e != hipSuccess) return device_fail(e, "near list kernel");
-  nl->count = at<int>(ws, L.ncount);
-  nl->list = at<int>(ws, L.nlist);
+  if ((rc = before())) return rc;
+  if (c->far) {
+    e = far_fields(far_single(*it, c->dev), g->nodes, c->ws, fwd, bwd, eval, src, geom, true,
+                   stream);
+    if (e != hipSuccess) return device_fail(e, "panel expansion kernels");
+  }
   return QBX_OK;
 }
 
@@ -560,25 +583,21 @@ int qbx_layer_potential_split(const qbx_geometry* g, const double* density, doub
   const Layout L = make_layout(d);
   if (ws_bytes < L.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
-  rc = prepare(d, L, g->nodes, density, ws, stream);
+  FarItem it;
+  SplitCall c{d};
+  rc = split_start(d, L, g, density, gamma * gamma, true, false, 0, false, false, ws, stream, &it,
+                   &c, [] { return QBX_OK; });
   if (rc) return rc;
-  const double g2 = gamma * gamma;
-  NearLists nl;
-  NystromSources ns;
-  if ((rc = split_geometry(d, L, g, density, g2, ws, stream, &nl, &ns))) return rc;
   timer_begin(6, stream);
-  hipError_t e = launch_split_near(d, at<double4>(ws, L.geo), at<double2>(ws, L.dens),
-                                   at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab),
-                                   at<double4>(ws, L.bnd), g2, nl, at<double2>(ws, L.partial),
-                                   stream);
+  hipError_t e = launch_near(kNearForward, d.p, d.kind, FarBlocks{c.dev, nullptr, 1},
+                             far_blocks(it, kStepCenters), c.ws, nullptr, stream);
   timer_end(6, stream);
   if (e != hipSuccess) return device_fail(e, "split near kernel");
   timer_begin(7, stream);
-  e = launch_split_far(d, ns, g->nodes, at<double4>(ws, L.bnd), g2, at<double2>(ws, L.fpart),
-                       stream);
+  e = launch_split_far(c, at<double2>(ws, L.fpart), stream);
   timer_end(7, stream);
   if (e != hipSuccess) return device_fail(e, "split far kernel");
-  e = launch_split_finalize(d, at<double2>(ws, L.partial), at<double2>(ws, L.fpart), out, stream);
+  e = launch_split_finalize(c, at<double2>(ws, L.partial), at<double2>(ws, L.fpart), out, stream);
   if (e != hipSuccess) return device_fail(e, "split finalize kernel");
   return QBX_OK;
 }
@@ -597,18 +616,19 @@ int qbx_layer_potential_split_gradient(const qbx_geometry* g, const double* dens
   const Layout L = make_layout(d);
   if (ws_bytes < L.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
-  rc = prepare(d, L, g->nodes, density, ws, stream);
+  FarItem it;
+  SplitCall c{d};
+  rc = split_start(d, L, g, density, gamma * gamma, true, false, 1, false, false, ws, stream, &it,
+                   &c, [] { return QBX_OK; });
   if (rc) return rc;
-  NearLists nl;
-  NystromSources ns;
-  if ((rc = split_geometry(d, L, g, density, gamma * gamma, ws, stream, &nl, &ns))) return rc;
   hipError_t e = launch_order_weighted(d, at<double>(ws, L.jtab), stream);
   if (e != hipSuccess) return device_fail(e, "order-weighted table kernel");
-  e = launch_split_gradient(d, g->nodes, at<double4>(ws, L.geo), at<double2>(ws, L.dens), ns,
-                            at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab),
-                            at<double4>(ws, L.bnd), gamma * gamma, nl,
-                            at<double2>(ws, L.partial), at<double2>(ws, L.fpart), grad, dn,
-                            stream);
+  e = launch_near(kNearGradient, d.p, d.kind, FarBlocks{c.dev, nullptr, 1},
+                  far_blocks(it, kStepCenters), c.ws, nullptr, stream);
+  if (e == hipSuccess) e = launch_split_far_grad(c, at<double2>(ws, L.fpart), stream);
+  if (e == hipSuccess)
+    e = launch_split_finalize_gradient(c, at<CenterRec>(ws, L.ctr), at<double2>(ws, L.partial),
+                                       at<double2>(ws, L.fpart), grad, dn, stream);
   if (e != hipSuccess) return device_fail(e, "split gradient kernels");
   return QBX_OK;
 }
@@ -630,38 +650,55 @@ int qbx_layer_potential_split_adjoint(const qbx_geometry* g, const double* densi
   const Layout L = make_layout(d);
   if (ws_bytes < L.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
-  rc = prepare(d, L, g->nodes, density, ws, stream);
+  const bool geom = grad_nodes != nullptr;
+  double2* Gf = at<double2>(ws, L.gfar);
+  FarItem it;
+  SplitCall c{d};
+  rc = split_start(d, L, g, density, gamma * gamma, geom, true, geom ? 1 : -1, true, geom, ws,
+                   stream, &it, &c, [&] {
+                     hipError_t e = launch_make_G(d, cotangent, at<double2>(ws, L.G), stream);
+                     if (e == hipSuccess) e = launch_split_gfar(d, at<double2>(ws, L.G), Gf, stream);
+                     return e == hipSuccess ? QBX_OK : device_fail(e, "cotangent kernels");
+                   });
   if (rc) return rc;
-  NearLists nl;
-  NystromSources ns;
-  if ((rc = split_geometry(d, L, g, density, gamma * gamma, ws, stream, &nl, &ns))) return rc;
-  hipError_t e = launch_make_G(d, cotangent, at<double2>(ws, L.G), stream);
-  if (e != hipSuccess) return device_fail(e, "cotangent kernel");
-  if (grad_nodes) {
-    SplitNodeScratch w;
-    w.Gf = at<double2>(ws, L.gfar);
-    w.cg = at<double>(ws, L.cg);
-    w.spart = at<double2>(ws, L.spart);
-    w.fpart = at<double2>(ws, L.fpart);
-    w.apart = at<double2>(ws, L.apart);
-    w.sg = at<double>(ws, L.sg);
-    w.gtw = at<double>(ws, L.gtw);
-    w.gde = at<double2>(ws, L.gde);
-    e = launch_split_adjoint_nodes(d, g->nodes, density, at<double>(ws, L.tables),
-                                   at<double4>(ws, L.geo), at<double2>(ws, L.dens), ns,
-                                   at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab),
-                                   at<double4>(ws, L.bnd), gamma * gamma, nl,
-                                   at<double2>(ws, L.G), w, grad_density, grad_nodes, stream);
-  } else {
-    e = launch_split_adjoint_density(d, g->nodes, at<double>(ws, L.tables), at<double4>(ws, L.geo),
-                                     at<double>(ws, L.wgt), ns, at<CenterRec>(ws, L.ctr),
-                                     at<double>(ws, L.jtab), at<double4>(ws, L.bnd), gamma * gamma,
-                                     nl, at<double2>(ws, L.G), at<double2>(ws, L.gfar),
-                                     at<double2>(ws, L.aacc), at<double2>(ws, L.apart),
-                                     grad_density, stream);
+  const FarBlocks one{c.dev, nullptr, 1};
+  hipError_t e;
+  if (!geom) {
+    // (the item's source parts lie where the density step reads them)
+    e = launch_near(kNearDensity, d.p, d.kind, one, far_blocks(it, kStepChunks), c.ws, nullptr,
+                    stream);
+    timer_begin(8, stream);
+    if (e == hipSuccess) e = launch_split_far_adj(c, false, Gf, at<double2>(ws, L.apart), stream);
+    timer_end(8, stream);
+    if (e == hipSuccess)
+      e = launch_split_density_grad(c, at<double>(ws, L.tables), at<double>(ws, L.wgt), it.nsrc,
+                                    at<double2>(ws, L.spart), at<double2>(ws, L.apart),
+                                    grad_density, stream);
+    return e == hipSuccess ? QBX_OK : device_fail(e, "split adjoint kernels");
   }
-  if (e != hipSuccess) return device_fail(e, "split adjoint kernels");
-  return QBX_OK;
+  e = launch_near(kNearSources, d.p, d.kind, one, far_blocks(it, kStepChunks), c.ws, nullptr,
+                  stream);
+  if (e == hipSuccess)
+    e = launch_near(kNearCenterSums, d.p, d.kind, one, far_blocks(it, kStepCenterSums), c.ws,
+                    nullptr, stream);
+  if (e == hipSuccess)
+    e = launch_near(kNearCenters, d.p, d.kind, one, far_blocks(it, kStepCenters), c.ws, nullptr,
+                    stream);
+  if (e == hipSuccess) e = launch_split_far_grad(c, at<double2>(ws, L.fpart), stream);
+  if (e == hipSuccess) e = launch_split_far_adj(c, true, Gf, at<double2>(ws, L.apart), stream);
+  if (e == hipSuccess)
+    e = launch_split_nystrom_grad(c, density, at<double>(ws, L.tables), Gf,
+                                  at<double2>(ws, L.fpart), at<double2>(ws, L.apart),
+                                  at<double>(ws, L.cg), at<double>(ws, L.gtw),
+                                  at<double2>(ws, L.gde), stream);
+  if (e == hipSuccess)
+    e = launch_source_finalize(d, it.nsrc, at<double4>(ws, L.geo), at<double2>(ws, L.spart),
+                               at<double>(ws, L.sg), stream);
+  if (e == hipSuccess)
+    e = launch_chain(d, g->nodes, density, at<double>(ws, L.tables), at<double>(ws, L.sg),
+                     at<double>(ws, L.cg), at<double>(ws, L.gtw), at<double>(ws, L.gde),
+                     grad_density, grad_nodes, stream);
+  return e == hipSuccess ? QBX_OK : device_fail(e, "split adjoint kernels");
 }
 
 int qbx_layer_potential_gradient(const qbx_geometry* g, const double* density, double k, int p,
@@ -676,7 +713,7 @@ int qbx_layer_potential_gradient(const qbx_geometry* g, const double* density, d
   const Layout L = make_layout(d);
   if (ws_bytes < L.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
-  if (L.far) {
+  if (far_applies(d)) {
     const FarItem it = far_item_of(d, L, true, true, false);
     rc = prepare(d, L, g->nodes, density, ws, stream, &it);
     if (rc) return rc;
@@ -728,7 +765,7 @@ int qbx_layer_potential_adjoint(const qbx_geometry* g, const double* density, do
   if (ws_bytes < L.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
   if (!grad_density && !grad_nodes) return QBX_OK;
-  if (L.far && !tape)
+  if (far_applies(d) && !tape)
     return run_adjoint_far(d, L, g->nodes, density, cotangent, grad_density, grad_nodes, ws,
                            stream);
   rc = prepare(d, L, g->nodes, density, ws, stream);

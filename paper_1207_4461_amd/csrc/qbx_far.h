@@ -96,7 +96,8 @@ struct FarItem {
   size_t geo, dens, ctr, jtab, G;      // pair sources, centers, cotangent weights
   size_t fgeo, fdens, fG;              // far sources and far targets' weights
   size_t bnd, rec0, rec1;
-  size_t ncount, nlist;                // int arrays (still offsets in doubles)
+  size_t ncount, nlist;                // near lists: int arrays (still offsets in doubles)
+  size_t mcount, mlist;                // lists of the panels no expansion takes (plain: the same)
   size_t rows0, rows1;                 // double2 [V][2][C][kFarW]
   size_t lp0, lp1;                     // double2 [n][V][2][kFarQ + 1][C]
   size_t ls0, ls1;                     // double2 [V][C][kFarW]
@@ -202,6 +203,8 @@ constexpr int kFarGroup8Panels = 2048;
 inline bool far_applies(const Dims& d) {
   return d.P >= kFarMinPanels && d.center_rule == 0 && d.r <= 1.0;
 }
+// the near/far split's far targets are points: no disk to look at
+inline bool far_applies_split(const Dims& d) { return d.P >= kFarMinPanels; }
 // blocks of the translation aimed for (256 compute units, three blocks each resident), and
 // the most shares of the sources a panel-level block takes when groups serve the rest
 // (about 110 sources are left per 64 target panels)
@@ -249,8 +252,8 @@ inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_
   const size_t C0 = d.P, C1 = it->C1;
   it->rec0 = at(sizeof(FarRec) / sizeof(double) * C0);
   it->rec1 = at(sizeof(FarRec) / sizeof(double) * C1);
-  it->ncount = at((C0 + 1) / 2);
-  it->nlist = at(C0 * kNearCap / 2);
+  it->ncount = it->mcount = at((C0 + 1) / 2);
+  it->nlist = it->mlist = at(C0 * kNearCap / 2);
   it->rows0 = at((size_t)Vmax * 2 * C0 * kFarW * 2);
   it->rows1 = at((size_t)Vmax * 2 * C1 * kFarW * 2);
   // a batch's items share the GPU: four times a single item's blocks between them

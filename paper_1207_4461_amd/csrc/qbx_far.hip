@@ -1049,8 +1049,8 @@ __global__ __launch_bounds__(64) void k_far_src(FarBlocks B, const double* __res
   }
 }
 
-// Near lists: one wave per panel scans all panels (64 per ballot) and writes the near
-// ones in ascending order, at most kNearCap of them, and their count.
+// Lists of the panels that no expansion takes: one wave per panel scans all panels (64 per
+// ballot) and writes them in ascending order, at most kNearCap, and their count.
 __global__ __launch_bounds__(256) void k_far_lists(FarBlocks B, const double* __restrict__ ro,
                                                    double* __restrict__ wo) {
   int b;
@@ -1063,10 +1063,10 @@ __global__ __launch_bounds__(256) void k_far_lists(FarBlocks B, const double* __
   R.r0 = reinterpret_cast<const FarRec*>(ro + it.rec0);
   R.r1 = it.C1 > 0 ? reinterpret_cast<const FarRec*>(ro + it.rec1) : nullptr;
   R.g = it.g;
-  R.bnd = nullptr;
-  R.g2 = 0.0;
-  int* count = reinterpret_cast<int*>(wo + it.ncount);
-  int* list = reinterpret_cast<int*>(wo + it.nlist);
+  R.bnd = it.g2 > 0.0 ? reinterpret_cast<const double4*>(ro + it.bnd) : nullptr;
+  R.g2 = it.g2;
+  int* count = reinterpret_cast<int*>(wo + it.mcount);
+  int* list = reinterpret_cast<int*>(wo + it.mlist);
   int n = 0;
   for (int w0 = 0; w0 < it.P; w0 += kWave) {
     const int mp = w0 + lane;

@@ -102,7 +102,6 @@ struct Layout {
   size_t nlist;    // int[P][kNearCap] split: near-panel lists
   size_t fpart;    // double2[n_fsplit][nk][T][2] split: far sums (forward: first half)
   size_t gfar;     // double2[nk][T] split adjoint: cotangent weights of both sides
-  size_t aacc;     // double2[nk][N] split adjoint: near sums per source
   size_t ngeo;     // double4[T] split: the far sources (Nystrom grid) {x, y, nx, ny}
   size_t ndens;    // double2[nk][T] split: their weighted densities
   size_t nw;       // double[T] split: their 16-point weights
@@ -187,53 +186,43 @@ hipError_t launch_panel_bounds(const Dims& d, const double* nodes, double4* bnd,
 // the Nystrom grid's far sources from the nodes, node densities and tables
 hipError_t launch_nystrom_sources(const Dims& d, const double* nodes, const double* density,
                                   const double* tables, NystromSources ns, hipStream_t s);
-// partial [nk][Mc]: QBX sums over the sources of near panels
-hipError_t launch_split_near(const Dims& d, const double4* geo, const double2* dens,
-                             const CenterRec* ctr, const double* jtab, const double4* bnd,
-                             double g2, NearLists nl, double2* partial, hipStream_t s);
-// the near lists of every panel (count, list: NearLists' arrays)
+// the gamma near lists of every panel (count, list: NearLists' arrays)
 hipError_t launch_near_lists(const Dims& d, const double4* bnd, double g2, int* count, int* list,
                              hipStream_t s);
-// partial [n_fsplit][nk][T]: direct sums over the far sources (ns) of far panels
-hipError_t launch_split_far(const Dims& d, NystromSources ns, const double* nodes,
-                            const double4* bnd, double g2, double2* partial, hipStream_t s);
-hipError_t launch_split_finalize(const Dims& d, const double2* nearp, const double2* farp,
-                                 double* out, hipStream_t s);
-// the split's target derivatives: near sums [nk][Mc][2], far sums
-// [n_fsplit][nk][T][2], then grad and n . grad (either may be NULL)
-hipError_t launch_split_gradient(const Dims& d, const double* nodes, const double4* geo,
-                                 const double2* dens, NystromSources ns, const CenterRec* ctr,
-                                 const double* jtab, const double4* bnd, double g2, NearLists nl,
-                                 double2* nearp, double2* farp, double* grad, double* dn,
-                                 hipStream_t s);
-// the split's adjoint with respect to the density (G from launch_make_G)
-hipError_t launch_split_adjoint_density(const Dims& d, const double* nodes, const double* tables,
-                                        const double4* geo, const double* wgt, NystromSources ns,
-                                        const CenterRec* ctr, const double* jtab,
-                                        const double4* bnd, double g2, NearLists nl,
-                                        const double2* G, double2* Gf, double2* acc,
-                                        double2* partial, double* grad_density, hipStream_t s);
-// the split's adjoint with respect to the nodes (and the density, through the
-// chain rule; either output may be NULL): cg [Mc][8], spart [src_slots][N], fpart
-// [n_fsplit][nk][T][2], apart [n_asplit][nk + 2][T], sg [N][8], gtw [T][2],
-// gde [nk][T]
-struct SplitNodeScratch {
-  double2* Gf;
-  double* cg;
-  double2* spart;
-  double2* fpart;
-  double2* apart;
-  double* sg;
-  double* gtw;
-  double2* gde;
+// One split call.  far: panel expansions take the far pairs they reach (their sums lie in
+// the item's fu and fs) and the far passes the rest; otherwise the far passes take every
+// far pair, in n_fsplit / n_asplit parts.
+struct SplitCall {
+  const Dims& d;
+  const double* nodes;
+  NystromSources ns;
+  const double4* bnd;
+  double g2;
+  bool far;
+  const FarItem* dev;
+  double* ws;
 };
-hipError_t launch_split_adjoint_nodes(const Dims& d, const double* nodes, const double* density,
-                                      const double* tables, const double4* geo,
-                                      const double2* dens, NystromSources ns,
-                                      const CenterRec* ctr, const double* jtab,
-                                      const double4* bnd, double g2, NearLists nl,
-                                      const double2* G, SplitNodeScratch w,
-                                      double* grad_density, double* grad_nodes, hipStream_t s);
+// direct sums over the far sources: values [parts][nk][T], target gradients
+// [parts][nk][T][2], the adjoint's source side [parts][nk (+ 2)][T]
+hipError_t launch_split_far(const SplitCall& c, double2* out, hipStream_t s);
+hipError_t launch_split_far_grad(const SplitCall& c, double2* out, hipStream_t s);
+hipError_t launch_split_far_adj(const SplitCall& c, bool geo, const double2* Gf, double2* out,
+                                hipStream_t s);
+// both sides' cotangent weights per target
+hipError_t launch_split_gfar(const Dims& d, const double2* G, double2* Gf, hipStream_t s);
+hipError_t launch_split_finalize(const SplitCall& c, const double2* nearp, const double2* farp,
+                                 double* out, hipStream_t s);
+hipError_t launch_split_finalize_gradient(const SplitCall& c, const CenterRec* ctr,
+                                          const double2* nearp, const double2* farp, double* grad,
+                                          double* dn, hipStream_t s);
+hipError_t launch_split_density_grad(const SplitCall& c, const double* tables, const double* wgt,
+                                     int n_acc, const double2* acc, const double2* partial,
+                                     double* grad_density, hipStream_t s);
+// the far pairs' terms of the node gradient (cg [Mc][8], gtw [T][2], gde [nk][T])
+hipError_t launch_split_nystrom_grad(const SplitCall& c, const double* density,
+                                     const double* tables, const double2* Gf,
+                                     const double2* fpart, const double2* apart, double* cg,
+                                     double* gtw, double2* gde, hipStream_t s);
 // ---- adjoint (qbx_adjoint.hip) ----
 // the chain rule to the nodes and node densities from the per-source (sg) and
 // per-center (cg) gradients; one block per panel

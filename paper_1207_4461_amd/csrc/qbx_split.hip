@@ -51,67 +51,6 @@ __global__ __launch_bounds__(256) void k_near_lists(int NP, const double4* __res
   if (lane == 0) count[m] = n;
 }
 
-// f(pan) for every panel near panel m (wave-uniform), in ascending order: from
-// m's list when it fits, else by the wave's scan of all NP panels
-template <typename F>
-__device__ __forceinline__ void for_near_panels(int m, const double4* __restrict__ bnd, int NP,
-                                                double g2, NearLists nl, int lane, F&& f) {
-  const int cnt = nl.count[m];
-  if (cnt <= kNearCap) {
-    const int* __restrict__ L = nl.list + (size_t)m * kNearCap;
-    for (int i = 0; i < cnt; ++i) f(L[i]);
-    return;
-  }
-  const double4 bm = bnd[m];
-  for (int w0 = 0; w0 < NP; w0 += kWave) {
-    const int mp = w0 + lane;
-    const bool nr = mp < NP && panels_near(bm, bnd[mp], g2);
-    unsigned long long mask = __ballot(nr);
-    while (mask) {
-      const int pan = w0 + __builtin_ctzll(mask);
-      mask &= mask - 1;
-      f(pan);
-    }
-  }
-}
-
-// f(m) once for every panel m near any of the panels pa..pb (a 64-source chunk's
-// panels; the relation is symmetric): from their lists, each m at the first list
-// that holds it, when every list fits; else by the wave's scan (ascending)
-template <typename F>
-__device__ __forceinline__ void for_near_any(int pa, int pb, const double4* __restrict__ bnd,
-                                             int NP, double g2, NearLists nl, int lane, F&& f) {
-  bool fits = true;
-  for (int ps = pa; ps <= pb; ++ps) fits = fits && nl.count[ps] <= kNearCap;
-  if (fits) {
-    for (int ps = pa; ps <= pb; ++ps) {
-      const int* __restrict__ L = nl.list + (size_t)ps * kNearCap;
-      const int cnt = nl.count[ps];
-      for (int i = 0; i < cnt; ++i) {
-        const int m = L[i];
-        bool seen = false;
-        for (int pq = pa; pq < ps; ++pq) seen = seen || panels_near(bnd[m], bnd[pq], g2);
-        if (!seen) f(m);
-      }
-    }
-    return;
-  }
-  for (int w0 = 0; w0 < NP; w0 += kWave) {
-    const int mt = w0 + lane;
-    bool any = false;
-    if (mt < NP) {
-      const double4 bt = bnd[mt];
-      for (int ps = pa; ps <= pb; ++ps) any = any || panels_near(bt, bnd[ps], g2);
-    }
-    unsigned long long mask = __ballot(any);
-    while (mask) {
-      const int m = w0 + __builtin_ctzll(mask);
-      mask &= mask - 1;
-      f(m);
-    }
-  }
-}
-
 // bnd[m] = {b_x, b_y, rad2, 0}
 __global__ __launch_bounds__(256) void k_panel_bounds(int NP, const double* __restrict__ nodes,
                                                       double4* __restrict__ bnd) {
@@ -169,44 +108,6 @@ __global__ __launch_bounds__(256) void k_nystrom_sources(int T, int nk,
   }
 }
 
-// partial[kk][ci]: QBX sums of center ci over the sources of near panels
-template <int P, int KIND>
-__global__ __launch_bounds__(256) void k_split_near(const double4* __restrict__ geo,
-                                                    const double2* __restrict__ dens, int N,
-                                                    int qs, const CenterRec* __restrict__ ctr,
-                                                    const double* __restrict__ jtab, int NJ,
-                                                    int Mc, int T, const double4* __restrict__ bnd,
-                                                    int NP, double g2, NearLists nl, double k,
-                                                    double2* __restrict__ partial) {
-  constexpr bool kS = (KIND & 1) != 0;
-  constexpr bool kD = (KIND & 2) != 0;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int ci = blockIdx.x * 4 + wave;
-  if (ci >= Mc) return;
-  const int m = (ci % T) / kQ;                 // the target's panel
-  const CenterRec* C = ctr + ci;
-  const double cx = C->cx, cy = C->cy, ct = C->ct, st = C->st;
-  const double inv_k = 1.0 / k;
-  const double* Jtab = jtab + (size_t)ci * NJ;
-  double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
-  for_near_panels(m, bnd, NP, g2, nl, lane, [&](int pan) {
-    for (int s0 = 0; s0 < qs; s0 += kWave) {
-      if (s0 + lane < qs)
-        forward_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k,
-                                Jtab, sr, si, dr, di);
-    }
-  });
-  Cplx S = {sr, si}, Dd = {dr, di};
-  if (kS) wave_sum(S);
-  if (kD) wave_sum(Dd);
-  if (lane == 0) {
-    int kk = 0;
-    if (kS) partial[(size_t)(kk++) * Mc + ci] = make_double2(S.r, S.i);
-    if (kD) partial[(size_t)kk * Mc + ci] = make_double2(k * Dd.r, k * Dd.i);
-  }
-}
-
 // one far pair: w sigma H_0 (S) and w mu H_1 (x - x').n' / rho (D; the factor k is
 // applied once per sum), with the pair's weighted densities wS (S) and wD (D)
 template <bool kS, bool kD>
@@ -223,6 +124,75 @@ __device__ __forceinline__ void far_accumulate_q(const double2& wS, const double
     const double wr = wD.x * f, wi = wD.y * f;
     dr = fma(wr, h.h1r, fma(-wi, h.h1i, dr));
     di = fma(wr, h.h1i, fma(wi, h.h1r, di));
+  }
+}
+
+// one far pair of the target derivatives: the gradient's sums (x, y; complex), without
+// the factors -k (S) and k (D)
+template <bool kS, bool kD>
+__device__ __forceinline__ void grad_accumulate(const double2& wS, const double2& wD,
+                                                const double4& g, double dx, double dy, double ir,
+                                                double k, const H01& h, double (&S)[4],
+                                                double (&D)[4]) {
+  const double ux = dx * ir, uy = dy * ir;
+  if (kS) {
+    const double hr = fma(wS.x, h.h1r, -wS.y * h.h1i), hi = fma(wS.x, h.h1i, wS.y * h.h1r);
+    S[0] = fma(hr, ux, S[0]);
+    S[1] = fma(hi, ux, S[1]);
+    S[2] = fma(hr, uy, S[2]);
+    S[3] = fma(hi, uy, S[3]);
+  }
+  if (kD) {
+    const double f = fma(ux, g.z, uy * g.w);
+    // k H_0 f u + (H_1 / rho)(n' - 2 f u), times w mu
+    const double a_r = k * f * h.h0r, a_i = k * f * h.h0i;
+    const double b_r = h.h1r * ir, b_i = h.h1i * ir;
+    const double vx = fma(-2.0 * f, ux, g.z), vy = fma(-2.0 * f, uy, g.w);
+    const double cxr = fma(a_r, ux, b_r * vx), cxi = fma(a_i, ux, b_i * vx);
+    const double cyr = fma(a_r, uy, b_r * vy), cyi = fma(a_i, uy, b_i * vy);
+    D[0] = fma(wD.x, cxr, fma(-wD.y, cxi, D[0]));
+    D[1] = fma(wD.x, cxi, fma(wD.y, cxr, D[1]));
+    D[2] = fma(wD.x, cyr, fma(-wD.y, cyi, D[2]));
+    D[3] = fma(wD.x, cyi, fma(wD.y, cyr, D[3]));
+  }
+}
+
+// one far pair of the adjoint, source side: the cotangent weights GS, GD of the target
+// times H_0 (S) and H_1 (x - x').n' / rho (D) into v; GEO: the gradients for the
+// source's position and normal, contracted with its weighted densities, into e (without
+// the factor k)
+template <bool kS, bool kD, bool GEO>
+__device__ __forceinline__ void adj_accumulate(const double2& GS, const double2& GD,
+                                               const double2& qS, const double2& qD,
+                                               const double4& g, double dx, double dy, double ir,
+                                               double k, const H01& h, double (&v)[4],
+                                               double (&e)[4]) {
+  if (kS) {
+    v[0] = fma(GS.x, h.h0r, fma(-GS.y, h.h0i, v[0]));
+    v[1] = fma(GS.x, h.h0i, fma(GS.y, h.h0r, v[1]));
+    if (GEO) {
+      const double cr = qS.x * GS.x - qS.y * GS.y, cim = qS.x * GS.y + qS.y * GS.x;
+      const double a1 = cr * h.h1r - cim * h.h1i;   // Re(q G H_1)
+      e[0] = fma(a1 * ir, dx, e[0]);
+      e[1] = fma(a1 * ir, dy, e[1]);
+    }
+  }
+  if (kD) {
+    const double f = fma(dx, g.z, dy * g.w) * ir;   // (x - x').n' / rho
+    const double wr = GD.x * f, wi = GD.y * f;
+    v[2] = fma(wr, h.h1r, fma(-wi, h.h1i, v[2]));
+    v[3] = fma(wr, h.h1i, fma(wi, h.h1r, v[3]));
+    if (GEO) {
+      const double cr = qD.x * GD.x - qD.y * GD.y, cim = qD.x * GD.y + qD.y * GD.x;
+      const double a0 = cr * h.h0r - cim * h.h0i;   // Re(q G H_0)
+      const double a1 = cr * h.h1r - cim * h.h1i;   // Re(q G H_1)
+      const double ux = dx * ir, uy = dy * ir;
+      const double b = (k * a0 - 2.0 * a1 * ir) * f;
+      e[0] -= fma(b, ux, a1 * ir * g.z);
+      e[1] -= fma(b, uy, a1 * ir * g.w);
+      e[2] = fma(a1, ux, e[2]);
+      e[3] = fma(a1, uy, e[3]);
+    }
   }
 }
 
@@ -355,76 +325,6 @@ __global__ __launch_bounds__(256) void k_split_finalize(int Mc, int T, int nk, i
 // interpolation of w_j conj(...) (PyTorch's convention, A^H g).
 // ---------------------------------------------------------------------------
 
-// acc[kk][j] = sum over the centers i of target panels near j's panel of G_i K_ij
-// (QBX pairs).  One wave per 64-source chunk: the wave scans the target panels
-// near any of its chunk's source panels, and each lane adds the centers of a
-// scanned panel only when that panel is near its own source panel.
-template <int P, int KIND>
-__global__ __launch_bounds__(256) void k_split_near_adj(
-    const double4* __restrict__ geo, int N, int qs, const CenterRec* __restrict__ ctr,
-    const double* __restrict__ jtab, int NJ, int Mc, int T, int n_sides,
-    const double4* __restrict__ bnd, int NP, double g2, NearLists nl, double k,
-    const double2* __restrict__ G, double2* __restrict__ acc) {
-  constexpr bool kS = (KIND & 1) != 0;
-  constexpr bool kD = (KIND & 2) != 0;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int c = blockIdx.x * 4 + wave;
-  if (c * kWave >= N) return;
-  const int j = c * kWave + lane;
-  const bool valid = j < N;
-  const int jj = valid ? j : N - 1;
-  const double4 bj = bnd[jj / qs];
-  const int pa = (c * kWave) / qs;
-  const int pb = min(c * kWave + kWave - 1, N - 1) / qs;
-  const double4 g = geo[jj];
-  const double inv_k = 1.0 / k;
-  double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
-  for_near_any(pa, pb, bnd, NP, g2, nl, lane, [&](int m) {
-    if (valid && panels_near(bnd[m], bj, g2)) {
-      for (int si_ = 0; si_ < n_sides; ++si_) {
-        for (int a = 0; a < kQ; ++a) {
-          const int ci = si_ * T + m * kQ + a;
-          const int z0 = opaque_zero();
-          const double* __restrict__ J = jtab + (size_t)ci * NJ + z0;
-          const double* __restrict__ cf = g_seed_table + z0;
-          const CenterRec* C = ctr + ci;
-          const double vx = g.x - C->cx, vy = g.y - C->cy;
-          const double rho2 = fma(vx, vx, vy * vy);
-          const double ir = rsqrt_refined(rho2);
-          const double rho = rho2 * ir;
-          const double cd = (C->ct * vx + C->st * vy) * ir;
-          const double sd = (C->st * vx - C->ct * vy) * ir;
-          double cps = 0.0, sps = 0.0;
-          if (kD) {
-            cps = C->ct * g.z + C->st * g.w;
-            sps = C->st * g.z - C->ct * g.w;
-          }
-          double ks_r, ks_i, kd_r, kd_i;
-          pair_kernel<P, KIND>(k * rho, ir * inv_k, cd, sd, cps, sps, J, cf, ks_r, ks_i, kd_r,
-                               kd_i);
-          int kk = 0;
-          if (kS) {
-            const double2 Gi = G[(size_t)(kk++) * Mc + ci];
-            sr = fma(Gi.x, ks_r, fma(-Gi.y, ks_i, sr));
-            si = fma(Gi.x, ks_i, fma(Gi.y, ks_r, si));
-          }
-          if (kD) {
-            const double2 Gi = G[(size_t)kk * Mc + ci];
-            dr = fma(Gi.x, kd_r, fma(-Gi.y, kd_i, dr));
-            di = fma(Gi.x, kd_i, fma(Gi.y, kd_r, di));
-          }
-        }
-      }
-    }
-  });
-  if (valid) {
-    int kk = 0;
-    if (kS) acc[(size_t)(kk++) * N + j] = make_double2(sr, si);
-    if (kD) acc[(size_t)kk * N + j] = make_double2(k * dr, k * di);
-  }
-}
-
 // Gf[kk][t] = sum over the sides of G[kk][si T + t]: the far sums do not depend on
 // the side, so their transpose takes the two sides' cotangents together
 __global__ __launch_bounds__(256) void k_split_gfar(int T, int nk, int n_sides,
@@ -477,46 +377,16 @@ __global__ __launch_bounds__(256) void k_split_far_adj(
   const double inv_k = 1.0 / k;
   const double zv = seed::kZV * (1.0 + 1e-12), zu = seed::kZU * (1.0 + 1e-12);
   const double zf = seed::kZF * (1.0 + 1e-12);
-  double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
   double2 qS = make_double2(0.0, 0.0), qD = qS;
   if (GEO) {
     qS = dens[jj];
     qD = dens[(size_t)(NK - 1) * N + jj];
   }
-  double gxp = 0.0, gyp = 0.0, gnx = 0.0, gny = 0.0;   // GEO: without the factor k
-  // one far pair: the cotangent weights of target t times H_0 (S) and
-  // H_1 (x - x').n' / rho (D)
+  double e[4] = {0.0, 0.0, 0.0, 0.0};   // GEO: position and normal, without the factor k
   auto add = [&](int t, double dx, double dy, double ir, const H01& h) {
-    int kk = 0;
-    if (kS) {
-      const double2 Gt = Gf[(size_t)(kk++) * T + t];
-      sr = fma(Gt.x, h.h0r, fma(-Gt.y, h.h0i, sr));
-      si = fma(Gt.x, h.h0i, fma(Gt.y, h.h0r, si));
-      if (GEO) {
-        const double cr = qS.x * Gt.x - qS.y * Gt.y, cim = qS.x * Gt.y + qS.y * Gt.x;
-        const double a1 = cr * h.h1r - cim * h.h1i;   // Re(q G H_1)
-        gxp = fma(a1 * ir, dx, gxp);
-        gyp = fma(a1 * ir, dy, gyp);
-      }
-    }
-    if (kD) {
-      const double2 Gt = Gf[(size_t)kk * T + t];
-      const double f = fma(dx, g.z, dy * g.w) * ir;   // (x - x').n' / rho
-      const double wr = Gt.x * f, wi = Gt.y * f;
-      dr = fma(wr, h.h1r, fma(-wi, h.h1i, dr));
-      di = fma(wr, h.h1i, fma(wi, h.h1r, di));
-      if (GEO) {
-        const double cr = qD.x * Gt.x - qD.y * Gt.y, cim = qD.x * Gt.y + qD.y * Gt.x;
-        const double a0 = cr * h.h0r - cim * h.h0i;   // Re(q G H_0)
-        const double a1 = cr * h.h1r - cim * h.h1i;   // Re(q G H_1)
-        const double ux = dx * ir, uy = dy * ir;
-        const double b = (k * a0 - 2.0 * a1 * ir) * f;
-        gxp -= fma(b, ux, a1 * ir * g.z);
-        gyp -= fma(b, uy, a1 * ir * g.w);
-        gnx = fma(a1, ux, gnx);
-        gny = fma(a1, uy, gny);
-      }
-    }
+    adj_accumulate<kS, kD, GEO>(Gf[t], Gf[(size_t)(NK - 1) * T + t], qS, qD, g, dx, dy, ir, k, h, v,
+                                e);
   };
   for (int mt = sp; mt < NP; mt += n_asplit) {
     const double4 bt = bnd[mt];
@@ -570,20 +440,20 @@ __global__ __launch_bounds__(256) void k_split_far_adj(
   }
   if (valid) {
     int kk = 0;
-    if (kS) partial[((size_t)sp * NS + kk++) * N + j] = make_double2(sr, si);
-    if (kD) partial[((size_t)sp * NS + kk) * N + j] = make_double2(k * dr, k * di);
+    if (kS) partial[((size_t)sp * NS + kk++) * N + j] = make_double2(v[0], v[1]);
+    if (kD) partial[((size_t)sp * NS + kk) * N + j] = make_double2(k * v[2], k * v[3]);
     if (GEO) {
-      partial[((size_t)sp * NS + NK) * N + j] = make_double2(k * gxp, k * gyp);
-      partial[((size_t)sp * NS + NK + 1) * N + j] = make_double2(k * gnx, k * gny);
+      partial[((size_t)sp * NS + NK) * N + j] = make_double2(k * e[0], k * e[1]);
+      partial[((size_t)sp * NS + NK + 1) * N + j] = make_double2(k * e[2], k * e[3]);
     }
   }
 }
 
-// grad_density[kk][t] = sum_b V[b][a] w_j conj(acc[kk][j]) (j = m qs + b, the
+// grad_density[kk][t] = sum_b V[b][a] w_j conj(acc[kk][j]) (acc in n_acc parts, j = m qs + b, the
 // near sources of panel m) + w_t conj(sum_sp partial[sp][kk][t]) (the far source
 // at node t = 16 m + a, weight w_t): one thread per node and kind
 __global__ __launch_bounds__(256) void k_split_density_grad(
-    int T, int N, int qs, int nk, int n_asplit, const double* __restrict__ tab,
+    int T, int N, int qs, int nk, int n_acc, int n_asplit, const double* __restrict__ tab,
     const double* __restrict__ wgt, const double* __restrict__ nw,
     const double2* __restrict__ acc, const double2* __restrict__ partial,
     double* __restrict__ grad_density) {
@@ -595,7 +465,11 @@ __global__ __launch_bounds__(256) void k_split_density_grad(
   double gr = 0.0, gi = 0.0;
   for (int b = 0; b < qs; ++b) {
     const size_t j = (size_t)m * qs + b;
-    const double2 v = acc[(size_t)kk * N + j];
+    double2 v = make_double2(0.0, 0.0);
+    for (int p = 0; p < n_acc; ++p) {
+      const double2 x = acc[((size_t)p * nk + kk) * N + j];
+      v = make_double2(v.x + x.x, v.y + x.y);
+    }
     const double c = tab[L.V + b * kQ + a] * wgt[j];
     gr = fma(c, v.x, gr);
     gi = fma(-c, v.y, gi);      // conj
@@ -609,60 +483,6 @@ __global__ __launch_bounds__(256) void k_split_density_grad(
   const double w = nw[t];
   grad_density[2 * (size_t)e] = fma(w, fr, gr);
   grad_density[2 * (size_t)e + 1] = fma(-w, fi, gi);
-}
-
-template <int P>
-static hipError_t launch_split_near_adj_p(const Dims& d, const double4* geo, const CenterRec* ctr,
-                                          const double* jtab, const double4* bnd, double g2,
-                                          NearLists nl, const double2* G, double2* acc,
-                                          hipStream_t s) {
-  const int chunks = (d.N + kWave - 1) / kWave;
-  const dim3 grid((unsigned)((chunks + 3) / 4)), block(256);
-#define QBX_NADJ_ARGS \
-  geo, d.N, d.qs, ctr, jtab, d.NJ, d.Mc, d.T, d.n_sides, bnd, d.P, g2, nl, d.k, G, acc
-  switch (d.kind) {
-    case 1: hipLaunchKernelGGL((k_split_near_adj<P, 1>), grid, block, 0, s, QBX_NADJ_ARGS); break;
-    case 2: hipLaunchKernelGGL((k_split_near_adj<P, 2>), grid, block, 0, s, QBX_NADJ_ARGS); break;
-    default: hipLaunchKernelGGL((k_split_near_adj<P, 3>), grid, block, 0, s, QBX_NADJ_ARGS); break;
-  }
-#undef QBX_NADJ_ARGS
-  return hipGetLastError();
-}
-
-hipError_t launch_split_adjoint_density(const Dims& d, const double* nodes, const double* tables,
-                                        const double4* geo, const double* wgt, NystromSources ns,
-                                        const CenterRec* ctr, const double* jtab,
-                                        const double4* bnd, double g2, NearLists nl,
-                                        const double2* G, double2* Gf, double2* acc,
-                                        double2* partial, double* grad_density, hipStream_t s) {
-  hipError_t e;
-  {
-    auto launch = [&]() -> hipError_t {
-      QBX_P_SWITCH(d.p, launch_split_near_adj_p, d, geo, ctr, jtab, bnd, g2, nl, G, acc, s)
-    };
-    e = launch();
-    if (e != hipSuccess) return e;
-  }
-  const int nt = d.T * d.nk;
-  hipLaunchKernelGGL(k_split_gfar, dim3((nt + 255) / 256), dim3(256), 0, s, d.T, d.nk, d.n_sides,
-                     G, Gf);
-  const int n_sb = (d.T + kWave - 1) / kWave;
-  const long waves = (long)n_sb * d.n_asplit;
-  const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
-#define QBX_FADJ_ARGS                                                                       \
-  ns.geo, nullptr, d.T, nodes, d.T, bnd, d.P, g2, d.k, Gf, n_sb, d.n_asplit,             \
-      partial
-  timer_begin(8, s);
-  switch (d.kind) {
-    case 1: hipLaunchKernelGGL((k_split_far_adj<1, false>), grid, block, 0, s, QBX_FADJ_ARGS); break;
-    case 2: hipLaunchKernelGGL((k_split_far_adj<2, false>), grid, block, 0, s, QBX_FADJ_ARGS); break;
-    default: hipLaunchKernelGGL((k_split_far_adj<3, false>), grid, block, 0, s, QBX_FADJ_ARGS); break;
-  }
-  timer_end(8, s);
-#undef QBX_FADJ_ARGS
-  hipLaunchKernelGGL(k_split_density_grad, dim3((nt + 255) / 256), dim3(256), 0, s, d.T, d.N, d.qs,
-                     d.nk, d.n_asplit, tables, wgt, ns.w, acc, partial, grad_density);
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -682,55 +502,6 @@ hipError_t launch_split_adjoint_density(const Dims& d, const double* nodes, cons
 //    layout of the plain adjoint, and the plain chain rule (chain_panel) maps
 //    everything to the nodes and node densities.
 // ---------------------------------------------------------------------------
-
-// cg[ci]: center_grad_from_sums of the near sources' tape sums, contracted with G
-template <int P, int KIND>
-__global__ __launch_bounds__(256) void k_split_near_cg(
-    const double4* __restrict__ geo, const double2* __restrict__ dens, int N, int qs,
-    const CenterRec* __restrict__ ctr, const double* __restrict__ jtab, int NJ, int Mc, int T,
-    int side, const double4* __restrict__ bnd, int NP, double g2, NearLists nl, double k,
-    const double2* __restrict__ G, double* __restrict__ cg) {
-  constexpr bool kS = (KIND & 1) != 0;
-  constexpr bool kD = (KIND & 2) != 0;
-  constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int ci = blockIdx.x * 4 + wave;
-  if (ci >= Mc) return;
-  const int m = (ci % T) / kQ;
-  const CenterRec* C = ctr + ci;
-  const double cx = C->cx, cy = C->cy, ct = C->ct, st = C->st;
-  const double inv_k = 1.0 / k;
-  const double* Jtab = jtab + (size_t)ci * NJ;
-  Cplx A[2][5];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 5; ++b) A[a][b] = {0.0, 0.0};
-  for_near_panels(m, bnd, NP, g2, nl, lane, [&](int pan) {
-    for (int s0 = 0; s0 < qs; s0 += kWave) {
-      if (s0 + lane < qs)
-        tape_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k, Jtab,
-                             NJ / 2, A);
-    }
-  });
-#pragma unroll
-  for (int kk = 0; kk < NK; ++kk)
-#pragma unroll
-    for (int b = 1; b < 5; ++b) wave_sum(A[kk][b]);
-  if (lane == 0) {
-    double dR = 0.0, dt = 0.0, gvx = 0.0, gvy = 0.0;
-#pragma unroll
-    for (int kk = 0; kk < NK; ++kk) {
-      const double2 g = G[(size_t)kk * Mc + ci];
-      dR += g.x * A[kk][1].r - g.y * A[kk][1].i;   // Re(G a)
-      dt += g.x * A[kk][2].r - g.y * A[kk][2].i;
-      gvx += g.x * A[kk][3].r - g.y * A[kk][3].i;
-      gvy += g.x * A[kk][4].r - g.y * A[kk][4].i;
-    }
-    center_grad_from_sums(ci, side, T, ctr, dR, dt, gvx, gvy, cg);
-  }
-}
 
 // The far pairs' terms of the node gradient, per node t = 16 m + a (added to
 // the first side's center slot t, which the chain rule sums with the other's):
@@ -794,93 +565,6 @@ __global__ __launch_bounds__(256) void k_split_nystrom_grad(
   gtw[2 * (size_t)t + 1] = gw * om * g.z;
 }
 
-// part[b][j], b < src_slots(KIND): the plain adjoint's source-side sums over the
-// centers of the target panels near j's panel (the scan of k_split_near_adj)
-template <int P, int KIND>
-__global__ __launch_bounds__(256) void k_split_near_adj_nodes(
-    const double4* __restrict__ geo, const double2* __restrict__ dens, int N, int qs,
-    const CenterRec* __restrict__ ctr, const double* __restrict__ jtab, int NJ, int Mc, int T,
-    int n_sides, const double4* __restrict__ bnd, int NP, double g2, NearLists nl, double k,
-    const double2* __restrict__ G, double2* __restrict__ part) {
-  constexpr bool kS = (KIND & 1) != 0;
-  constexpr bool kD = (KIND & 2) != 0;
-  constexpr int NK = kS && kD ? 2 : 1;
-  constexpr int NA = src_slots(KIND);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int c = blockIdx.x * 4 + wave;
-  if (c * kWave >= N) return;
-  const int j = c * kWave + lane;
-  const bool valid = j < N;
-  const int jj = valid ? j : N - 1;
-  const double4 bj = bnd[jj / qs];
-  const int pa = (c * kWave) / qs;
-  const int pb = min(c * kWave + kWave - 1, N - 1) / qs;
-  const double4 g = geo[jj];
-  double2 q[2];
-  q[0] = dens[jj];
-  q[1] = dens[(size_t)(NK - 1) * N + jj];
-  const double inv_k = 1.0 / k;
-  const int nj = NJ / 2;
-  Cplx A[NA];
-#pragma unroll
-  for (int b = 0; b < NA; ++b) A[b] = {0.0, 0.0};
-  for_near_any(pa, pb, bnd, NP, g2, nl, lane, [&](int m) {
-    if (valid && panels_near(bnd[m], bj, g2)) {
-      for (int si_ = 0; si_ < n_sides; ++si_) {
-        for (int a = 0; a < kQ; ++a) {
-          const int ci = si_ * T + m * kQ + a;
-          const int z0 = opaque_zero();
-          const double2 GS = G[(size_t)ci + z0];
-          const double2 GD = NK == 2 ? G[(size_t)Mc + ci + z0] : GS;
-          adjoint_pair<P, KIND>(g, q, ctr + ci + z0, jtab + (size_t)ci * NJ + z0,
-                                g_seed_table + z0, GS, GD, k, inv_k, nj, A);
-        }
-      }
-    }
-  });
-  if (valid) {
-#pragma unroll
-    for (int b = 0; b < NA; ++b) part[(size_t)b * N + j] = make_double2(A[b].r, A[b].i);
-  }
-}
-
-// sg[j] (the per-source layout of source_finalize_elem) from the near slots:
-// density gradients conj(near), source position, normal psi-projection (the far
-// pairs' source terms sit on the far sources, the nodes: k_split_nystrom_grad)
-__global__ __launch_bounds__(256) void k_split_source_finalize(int N, int kind,
-                                                               const double4* __restrict__ geo,
-                                                               const double2* __restrict__ nearp,
-                                                               double* __restrict__ sg) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
-  const bool hasS = kind & 1, hasD = kind & 2;
-  const int nk = hasS && hasD ? 2 : 1;
-  double o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (hasS) {
-    const double2 a = nearp[j];
-    o[0] = a.x;
-    o[1] = a.y;
-  }
-  if (hasD) {
-    const double2 a = nearp[(size_t)(nk - 1) * N + j];
-    o[2] = a.x;
-    o[3] = a.y;
-  }
-  const double2 x = nearp[(size_t)nk * N + j];
-  o[4] = x.x;
-  o[5] = x.y;
-  if (hasD) {
-    const double rp = nearp[(size_t)(nk + 1) * N + j].x;
-    const double4 g = geo[j];
-    o[6] = rp * g.w;   // Re(w mu Psi) (n_y, -n_x)
-    o[7] = -rp * g.z;
-  }
-  double* q = sg + (size_t)j * 8;
-#pragma unroll
-  for (int b = 0; b < 8; ++b) q[b] = o[b];
-}
-
 // ---------------------------------------------------------------------------
 // Target derivatives with the split (Section 3.2 for the near sources' local
 // expansion, the chain rule for the direct ones).  Near: per center the sums
@@ -890,51 +574,6 @@ __global__ __launch_bounds__(256) void k_split_source_finalize(int N, int kind,
 // u = (x - x')/rho, f = u . n'; the finalize combines them as grad u = (i/4)
 // (F_R w^ + (F_theta/R) theta^ + far) and n . grad u with n = -s w^.
 // ---------------------------------------------------------------------------
-
-// partial[kk][ci][0..1] = F_R, F_theta over the near sources of center ci
-template <int P, int KIND>
-__global__ __launch_bounds__(256) void k_split_near_grad(
-    const double4* __restrict__ geo, const double2* __restrict__ dens, int N, int qs,
-    const CenterRec* __restrict__ ctr, const double* __restrict__ jtab, int NJ, int Mc, int T,
-    const double4* __restrict__ bnd, int NP, double g2, NearLists nl, double k,
-    double2* __restrict__ partial) {
-  constexpr bool kS = (KIND & 1) != 0;
-  constexpr bool kD = (KIND & 2) != 0;
-  constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int ci = blockIdx.x * 4 + wave;
-  if (ci >= Mc) return;
-  const int m = (ci % T) / kQ;
-  const CenterRec* C = ctr + ci;
-  const double cx = C->cx, cy = C->cy, ct = C->ct, st = C->st;
-  const double inv_k = 1.0 / k;
-  const double* Jtab = jtab + (size_t)ci * NJ;
-  const double* Ltab = jtab + (size_t)Mc * NJ + (size_t)ci * (NJ / 2);   // l J_l
-  Cplx A[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a) A[a][0] = A[a][1] = {0.0, 0.0};
-  for_near_panels(m, bnd, NP, g2, nl, lane, [&](int pan) {
-    for (int s0 = 0; s0 < qs; s0 += kWave) {
-      if (s0 + lane < qs)
-        grad_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k, Jtab,
-                             NJ / 2, Ltab, A);
-    }
-  });
-#pragma unroll
-  for (int kk = 0; kk < NK; ++kk) {
-    wave_sum(A[kk][0]);
-    wave_sum(A[kk][1]);
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int kk = 0; kk < NK; ++kk) {
-      double2* q = partial + ((size_t)kk * Mc + ci) * 2;
-      q[0] = make_double2(A[kk][0].r, A[kk][0].i);
-      q[1] = make_double2(A[kk][1].r, A[kk][1].i);
-    }
-  }
-}
 
 // partial[sp][kk][t][0..1]: the direct gradient (x, y) of target t over the far
 // sources of panels sp, sp + n_fsplit, ..., without the factors -k (S), k (D)
@@ -958,8 +597,7 @@ __global__ __launch_bounds__(256) void k_split_far_grad(
   const double tx = nodes[2 * (size_t)tt], ty = nodes[2 * (size_t)tt + 1];
   const double4 bt = bnd[tt / kQ];
   const double inv_k = 1.0 / k;
-  double sxr = 0.0, sxi = 0.0, syr = 0.0, syi = 0.0;
-  double dxr = 0.0, dxi = 0.0, dyr = 0.0, dyi = 0.0;
+  double S[4] = {0.0, 0.0, 0.0, 0.0}, D[4] = {0.0, 0.0, 0.0, 0.0};
   for (int pm = sp; pm < NP; pm += n_fsplit) {
     const bool far = valid && !panels_near(bt, bnd[pm], g2);
     if (far) {
@@ -974,29 +612,8 @@ __global__ __launch_bounds__(256) void k_split_far_grad(
         const double ir = rsqrt_refined(rho2);
         const double z = k * (rho2 * ir), iz = ir * inv_k;
         const H01 h = __all(z >= seed::kZV) ? hankel01_vfar(z, iz, cf) : hankel01(z, iz, cf);
-        const double ux = dx * ir, uy = dy * ir;
-        if (kS) {
-          const double2 w = dens[j];
-          const double hr = fma(w.x, h.h1r, -w.y * h.h1i), hi = fma(w.x, h.h1i, w.y * h.h1r);
-          sxr = fma(hr, ux, sxr);
-          sxi = fma(hi, ux, sxi);
-          syr = fma(hr, uy, syr);
-          syi = fma(hi, uy, syi);
-        }
-        if (kD) {
-          const double2 w = dens[(kS ? (size_t)N : 0) + j];
-          const double f = fma(ux, g.z, uy * g.w);
-          // k H_0 f u + (H_1 / rho)(n' - 2 f u), times w mu
-          const double a_r = k * f * h.h0r, a_i = k * f * h.h0i;
-          const double b_r = h.h1r * ir, b_i = h.h1i * ir;
-          const double vx = fma(-2.0 * f, ux, g.z), vy = fma(-2.0 * f, uy, g.w);
-          const double cxr = fma(a_r, ux, b_r * vx), cxi = fma(a_i, ux, b_i * vx);
-          const double cyr = fma(a_r, uy, b_r * vy), cyi = fma(a_i, uy, b_i * vy);
-          dxr = fma(w.x, cxr, fma(-w.y, cxi, dxr));
-          dxi = fma(w.x, cxi, fma(w.y, cxr, dxi));
-          dyr = fma(w.x, cyr, fma(-w.y, cyi, dyr));
-          dyi = fma(w.x, cyi, fma(w.y, cyr, dyi));
-        }
+        grad_accumulate<kS, kD>(dens[j], dens[(kS && kD ? (size_t)N : 0) + j], g, dx, dy, ir, k, h, S,
+                                D);
       }
     }
   }
@@ -1004,13 +621,13 @@ __global__ __launch_bounds__(256) void k_split_far_grad(
     int kk = 0;
     if (kS) {
       double2* q = partial + (((size_t)sp * NK + kk++) * T + t) * 2;
-      q[0] = make_double2(-k * sxr, -k * sxi);
-      q[1] = make_double2(-k * syr, -k * syi);
+      q[0] = make_double2(-k * S[0], -k * S[1]);
+      q[1] = make_double2(-k * S[2], -k * S[3]);
     }
     if (kD) {
       double2* q = partial + (((size_t)sp * NK + kk) * T + t) * 2;
-      q[0] = make_double2(k * dxr, k * dxi);
-      q[1] = make_double2(k * dyr, k * dyi);
+      q[0] = make_double2(k * D[0], k * D[1]);
+      q[1] = make_double2(k * D[2], k * D[3]);
     }
   }
 }
@@ -1054,54 +671,129 @@ __global__ __launch_bounds__(256) void k_split_finalize_gradient(
   }
 }
 
-template <int P>
-static hipError_t launch_split_near_grad_p(const Dims& d, const double4* geo, const double2* dens,
-                                           const CenterRec* ctr, const double* jtab,
-                                           const double4* bnd, double g2, NearLists nl,
-                                           double2* partial, hipStream_t s) {
-  const dim3 grid((unsigned)((d.Mc + 3) / 4)), block(256);
-#define QBX_NGRAD_ARGS \
-  geo, dens, d.N, d.qs, ctr, jtab, d.NJ, d.Mc, d.T, bnd, d.P, g2, nl, d.k, partial
-  switch (d.kind) {
-    case 1: hipLaunchKernelGGL((k_split_near_grad<P, 1>), grid, block, 0, s, QBX_NGRAD_ARGS); break;
-    case 2: hipLaunchKernelGGL((k_split_near_grad<P, 2>), grid, block, 0, s, QBX_NGRAD_ARGS); break;
-    default: hipLaunchKernelGGL((k_split_near_grad<P, 3>), grid, block, 0, s, QBX_NGRAD_ARGS); break;
+// ---------------------------------------------------------------------------
+// Far pairs that panel expansions do not take (qbx_far.hip), with those that they do
+// already summed per target (fu) or per source (fs): one wave per panel walks the panels
+// that are left (few: between gamma panel radii and the expansions' reach), 16 lanes its
+// nodes, the four groups of 16 lanes a quarter of the other panel's nodes each.
+// MODE 0: values, out[kk][t]; 1: target gradients, out[kk][t][0..1]; 2, 3: the adjoint's
+// source side without and with position and normal, out[kk (.. nk + 1)][j].
+// ---------------------------------------------------------------------------
+template <int KIND, int MODE>
+__global__ __launch_bounds__(256) void k_split_mid(FarBlocks B, const double* __restrict__ ro,
+                                                   double2* __restrict__ out) {
+  constexpr bool kS = (KIND & 1) != 0;
+  constexpr bool kD = (KIND & 2) != 0;
+  constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int m = b * 4 + wave;
+  if (m >= it.P) return;
+  const int T = it.T;
+  const int me = m * kQ + (lane & 15), s0 = (lane >> 4) * 4;
+  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.fgeo);
+  const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.fdens);
+  const double2* __restrict__ Gf = reinterpret_cast<const double2*>(ro + it.fG);
+  const double4* __restrict__ bnd = reinterpret_cast<const double4*>(ro + it.bnd);
+  const int* __restrict__ count = reinterpret_cast<const int*>(ro + it.mcount);
+  const int* __restrict__ list = reinterpret_cast<const int*>(ro + it.mlist) + (size_t)m * kNearCap;
+  FarRel R;
+  R.r0 = reinterpret_cast<const FarRec*>(ro + it.rec0);
+  R.r1 = it.C1 > 0 ? reinterpret_cast<const FarRec*>(ro + it.rec1) : nullptr;
+  R.g = it.g;
+  R.bnd = bnd;
+  R.g2 = it.g2;
+  const double k = it.k, inv_k = 1.0 / k;
+  const double4 x = geo[me];
+  const double2 qS = dens[me], qD = dens[(size_t)(NK - 1) * T + me];
+  double u[4] = {0.0, 0.0, 0.0, 0.0}, e[4] = {0.0, 0.0, 0.0, 0.0};
+  auto pairs = [&](int pan) {
+    if (panels_near(bnd[m], bnd[pan], it.g2)) return;   // a near pair (QBX)
+    for (int s = 0; s < 4; ++s) {
+      const int z0 = opaque_zero();
+      const double* __restrict__ cf = g_seed_table + z0;
+      const int j = pan * kQ + s0 + s;
+      const double4 y = geo[j];
+      // MODE 0, 1: x the target, y the source; 2, 3: x the source, y the target
+      const double dx = MODE < 2 ? x.x - y.x : y.x - x.x, dy = MODE < 2 ? x.y - y.y : y.y - x.y;
+      const double rho2 = fma(dx, dx, dy * dy);
+      const double ir = rsqrt_refined(rho2);
+      const H01 h = hankel01(k * (rho2 * ir), ir * inv_k, cf);
+      if (MODE == 0)
+        far_accumulate_q<kS, kD>(dens[j], dens[(size_t)(NK - 1) * T + j], y, dx, dy, ir, h, u[0],
+                                 u[1], u[2], u[3]);
+      else if (MODE == 1)
+        grad_accumulate<kS, kD>(dens[j], dens[(size_t)(NK - 1) * T + j], y, dx, dy, ir, k, h, u, e);
+      else
+        adj_accumulate<kS, kD, MODE == 3>(Gf[j], Gf[(size_t)(NK - 1) * T + j], qS, qD, x, dx, dy,
+                                          ir, k, h, u, e);
+    }
+  };
+  const int cnt = count[m];
+  if (cnt <= kNearCap) {
+    for (int i = 0; i < cnt; ++i) pairs(list[i]);
+  } else {
+    for (int w0 = 0; w0 < it.P; w0 += kWave) {
+      const int mp = w0 + lane;
+      unsigned long long mask = __ballot(mp < it.P && !far_panels(R, m, mp));
+      while (mask) {
+        const int pan = w0 + __builtin_ctzll(mask);
+        mask &= mask - 1;
+        pairs(pan);
+      }
+    }
   }
-#undef QBX_NGRAD_ARGS
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    u[i] += __shfl_xor(u[i], 16);
+    u[i] += __shfl_xor(u[i], 32);
+    if (MODE == 1 || MODE == 3) {
+      e[i] += __shfl_xor(e[i], 16);
+      e[i] += __shfl_xor(e[i], 32);
+    }
+  }
+  if (lane >= kQ) return;
+  const double2* __restrict__ fu = reinterpret_cast<const double2*>(ro + (MODE < 2 ? it.fu : it.fs));
+  auto put = [&](size_t o, double r, double i) {
+    const double2 f = fu[o];
+    out[o] = make_double2(f.x + r, f.y + i);
+  };
+  if (MODE == 1) {
+    if (kS) {
+      put(2 * (size_t)me, -k * u[0], -k * u[1]);
+      put(2 * (size_t)me + 1, -k * u[2], -k * u[3]);
+    }
+    if (kD) {
+      put(2 * ((size_t)(NK - 1) * T + me), k * e[0], k * e[1]);
+      put(2 * ((size_t)(NK - 1) * T + me) + 1, k * e[2], k * e[3]);
+    }
+  } else {
+    if (kS) put(me, u[0], u[1]);
+    if (kD) put((size_t)(NK - 1) * T + me, k * u[2], k * u[3]);
+    if (MODE == 3) {
+      put((size_t)NK * T + me, k * e[0], k * e[1]);
+      put((size_t)(NK + 1) * T + me, k * e[2], k * e[3]);
+    }
+  }
+}
+
+template <int MODE>
+static hipError_t launch_mid(const SplitCall& c, double2* out, hipStream_t s) {
+  const dim3 grid((unsigned)((c.d.P + 3) / 4)), block(256);
+  const FarBlocks B{c.dev, nullptr, 1};
+  switch (c.d.kind) {
+    case 1: hipLaunchKernelGGL((k_split_mid<1, MODE>), grid, block, 0, s, B, c.ws, out); break;
+    case 2: hipLaunchKernelGGL((k_split_mid<2, MODE>), grid, block, 0, s, B, c.ws, out); break;
+    default: hipLaunchKernelGGL((k_split_mid<3, MODE>), grid, block, 0, s, B, c.ws, out); break;
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_split_gradient(const Dims& d, const double* nodes, const double4* geo,
-                                 const double2* dens, NystromSources ns, const CenterRec* ctr,
-                                 const double* jtab, const double4* bnd, double g2, NearLists nl,
-                                 double2* nearp, double2* farp, double* grad, double* dn,
-                                 hipStream_t s) {
-  hipError_t e;
-  {
-    auto launch = [&]() -> hipError_t {
-      QBX_P_SWITCH(d.p, launch_split_near_grad_p, d, geo, dens, ctr, jtab, bnd, g2, nl, nearp, s)
-    };
-    e = launch();
-    if (e != hipSuccess) return e;
-  }
-  const int n_tb = (d.T + kWave - 1) / kWave;
-  const long waves = (long)n_tb * d.n_fsplit;
-  const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
-#define QBX_FGRAD_ARGS \
-  ns.geo, ns.dens, d.T, nodes, d.T, bnd, d.P, g2, d.k, n_tb, d.n_fsplit, \
-      farp
-  switch (d.kind) {
-    case 1: hipLaunchKernelGGL((k_split_far_grad<1>), grid, block, 0, s, QBX_FGRAD_ARGS); break;
-    case 2: hipLaunchKernelGGL((k_split_far_grad<2>), grid, block, 0, s, QBX_FGRAD_ARGS); break;
-    default: hipLaunchKernelGGL((k_split_far_grad<3>), grid, block, 0, s, QBX_FGRAD_ARGS); break;
-  }
-#undef QBX_FGRAD_ARGS
-  const int n = d.Mc * d.nk;
-  hipLaunchKernelGGL(k_split_finalize_gradient, dim3((n + 255) / 256), dim3(256), 0, s, d.Mc, d.T,
-                     d.nk, d.n_fsplit, d.side, ctr, nearp, farp, grad, dn);
-  return hipGetLastError();
-}
-
+// ---------------------------------------------------------------------------
+// launchers
+// ---------------------------------------------------------------------------
 hipError_t launch_panel_bounds(const Dims& d, const double* nodes, double4* bnd, hipStream_t s) {
   hipLaunchKernelGGL(k_panel_bounds, dim3((d.P + 255) / 256), dim3(256), 0, s, d.P, nodes, bnd);
   return hipGetLastError();
@@ -1115,29 +807,6 @@ hipError_t launch_nystrom_sources(const Dims& d, const double* nodes, const doub
   return hipGetLastError();
 }
 
-template <int P>
-static hipError_t launch_split_near_p(const Dims& d, const double4* geo, const double2* dens,
-                                      const CenterRec* ctr, const double* jtab,
-                                      const double4* bnd, double g2, NearLists nl,
-                                      double2* partial, hipStream_t s) {
-  const dim3 grid((unsigned)((d.Mc + 3) / 4)), block(256);
-#define QBX_NEAR_ARGS \
-  geo, dens, d.N, d.qs, ctr, jtab, d.NJ, d.Mc, d.T, bnd, d.P, g2, nl, d.k, partial
-  switch (d.kind) {
-    case 1: hipLaunchKernelGGL((k_split_near<P, 1>), grid, block, 0, s, QBX_NEAR_ARGS); break;
-    case 2: hipLaunchKernelGGL((k_split_near<P, 2>), grid, block, 0, s, QBX_NEAR_ARGS); break;
-    default: hipLaunchKernelGGL((k_split_near<P, 3>), grid, block, 0, s, QBX_NEAR_ARGS); break;
-  }
-#undef QBX_NEAR_ARGS
-  return hipGetLastError();
-}
-
-hipError_t launch_split_near(const Dims& d, const double4* geo, const double2* dens,
-                             const CenterRec* ctr, const double* jtab, const double4* bnd,
-                             double g2, NearLists nl, double2* partial, hipStream_t s) {
-  QBX_P_SWITCH(d.p, launch_split_near_p, d, geo, dens, ctr, jtab, bnd, g2, nl, partial, s)
-}
-
 hipError_t launch_near_lists(const Dims& d, const double4* bnd, double g2, int* count, int* list,
                              hipStream_t s) {
   hipLaunchKernelGGL(k_near_lists, dim3((unsigned)((d.P + 3) / 4)), dim3(256), 0, s, d.P, bnd,
@@ -1145,122 +814,109 @@ hipError_t launch_near_lists(const Dims& d, const double4* bnd, double g2, int* 
   return hipGetLastError();
 }
 
-hipError_t launch_split_far(const Dims& d, NystromSources ns, const double* nodes,
-                            const double4* bnd, double g2, double2* partial, hipStream_t s) {
+hipError_t launch_split_gfar(const Dims& d, const double2* G, double2* Gf, hipStream_t s) {
+  const int nt = d.T * d.nk;
+  hipLaunchKernelGGL(k_split_gfar, dim3((nt + 255) / 256), dim3(256), 0, s, d.T, d.nk, d.n_sides,
+                     G, Gf);
+  return hipGetLastError();
+}
+
+// one wave per 64 points and source (target) split
+static dim3 far_grid(const Dims& d, int splits) {
+  const long waves = (long)((d.T + kWave - 1) / kWave) * splits;
+  return dim3((unsigned)((waves + 3) / 4));
+}
+
+hipError_t launch_split_far(const SplitCall& c, double2* out, hipStream_t s) {
+  if (c.far) return launch_mid<0>(c, out, s);
+  const Dims& d = c.d;
   const int n_tb = (d.T + kWave - 1) / kWave;
-  const long waves = (long)n_tb * d.n_fsplit;
-  const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
+  const dim3 grid = far_grid(d, d.n_fsplit), block(256);
 #define QBX_FAR_ARGS \
-  ns.geo, ns.dens, d.T, nodes, d.T, bnd, d.P, g2, d.k, n_tb, d.n_fsplit, \
-      partial
+  c.ns.geo, c.ns.dens, d.T, c.nodes, d.T, c.bnd, d.P, c.g2, d.k, n_tb, d.n_fsplit, out
   switch (d.kind) {
     case 1: hipLaunchKernelGGL((k_split_far<1>), grid, block, 0, s, QBX_FAR_ARGS); break;
     case 2: hipLaunchKernelGGL((k_split_far<2>), grid, block, 0, s, QBX_FAR_ARGS); break;
     default: hipLaunchKernelGGL((k_split_far<3>), grid, block, 0, s, QBX_FAR_ARGS); break;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_split_far_grad(const SplitCall& c, double2* out, hipStream_t s) {
+  if (c.far) return launch_mid<1>(c, out, s);
+  const Dims& d = c.d;
+  const int n_tb = (d.T + kWave - 1) / kWave;
+  const dim3 grid = far_grid(d, d.n_fsplit), block(256);
+  switch (d.kind) {
+    case 1: hipLaunchKernelGGL((k_split_far_grad<1>), grid, block, 0, s, QBX_FAR_ARGS); break;
+    case 2: hipLaunchKernelGGL((k_split_far_grad<2>), grid, block, 0, s, QBX_FAR_ARGS); break;
+    default: hipLaunchKernelGGL((k_split_far_grad<3>), grid, block, 0, s, QBX_FAR_ARGS); break;
+  }
 #undef QBX_FAR_ARGS
   return hipGetLastError();
 }
 
-hipError_t launch_split_finalize(const Dims& d, const double2* nearp, const double2* farp,
+hipError_t launch_split_far_adj(const SplitCall& c, bool geo, const double2* Gf, double2* out,
+                                hipStream_t s) {
+  if (c.far) return geo ? launch_mid<3>(c, out, s) : launch_mid<2>(c, out, s);
+  const Dims& d = c.d;
+  const int n_sb = (d.T + kWave - 1) / kWave;
+  const dim3 grid = far_grid(d, d.n_asplit), block(256);
+#define QBX_FADJ(KD, GEO)                                                                       \
+  hipLaunchKernelGGL((k_split_far_adj<KD, GEO>), grid, block, 0, s, c.ns.geo, c.ns.dens, d.T,    \
+                     c.nodes, d.T, c.bnd, d.P, c.g2, d.k, Gf, n_sb, d.n_asplit, out)
+  switch (d.kind + (geo ? 4 : 0)) {
+    case 1: QBX_FADJ(1, false); break;
+    case 2: QBX_FADJ(2, false); break;
+    case 3: QBX_FADJ(3, false); break;
+    case 5: QBX_FADJ(1, true); break;
+    case 6: QBX_FADJ(2, true); break;
+    default: QBX_FADJ(3, true); break;
+  }
+#undef QBX_FADJ
+  return hipGetLastError();
+}
+
+hipError_t launch_split_finalize(const SplitCall& c, const double2* nearp, const double2* farp,
                                  double* out, hipStream_t s) {
+  const Dims& d = c.d;
   const int n = d.Mc * d.nk;
   hipLaunchKernelGGL(k_split_finalize, dim3((n + 255) / 256), dim3(256), 0, s, d.Mc, d.T, d.nk,
-                     d.n_fsplit, nearp, farp, out);
+                     c.far ? 1 : d.n_fsplit, nearp, farp, out);
   return hipGetLastError();
 }
 
-template <int P>
-static hipError_t launch_split_nodes_near_p(const Dims& d, const double4* geo,
-                                            const double2* dens, const CenterRec* ctr,
-                                            const double* jtab, const double4* bnd, double g2,
-                                            NearLists nl, const double2* G, double* cg,
-                                            double2* spart, hipStream_t s) {
-  const dim3 gc((unsigned)((d.Mc + 3) / 4)), block(256);
-  const int chunks = (d.N + kWave - 1) / kWave;
-  const dim3 gs((unsigned)((chunks + 3) / 4));
-#define QBX_NCG_ARGS \
-  geo, dens, d.N, d.qs, ctr, jtab, d.NJ, d.Mc, d.T, d.side, bnd, d.P, g2, nl, d.k, G, cg
-#define QBX_NSRC_ARGS \
-  geo, dens, d.N, d.qs, ctr, jtab, d.NJ, d.Mc, d.T, d.n_sides, bnd, d.P, g2, nl, d.k, G, spart
-  switch (d.kind) {
-    case 1:
-      hipLaunchKernelGGL((k_split_near_cg<P, 1>), gc, block, 0, s, QBX_NCG_ARGS);
-      hipLaunchKernelGGL((k_split_near_adj_nodes<P, 1>), gs, block, 0, s, QBX_NSRC_ARGS);
-      break;
-    case 2:
-      hipLaunchKernelGGL((k_split_near_cg<P, 2>), gc, block, 0, s, QBX_NCG_ARGS);
-      hipLaunchKernelGGL((k_split_near_adj_nodes<P, 2>), gs, block, 0, s, QBX_NSRC_ARGS);
-      break;
-    default:
-      hipLaunchKernelGGL((k_split_near_cg<P, 3>), gc, block, 0, s, QBX_NCG_ARGS);
-      hipLaunchKernelGGL((k_split_near_adj_nodes<P, 3>), gs, block, 0, s, QBX_NSRC_ARGS);
-      break;
-  }
-#undef QBX_NCG_ARGS
-#undef QBX_NSRC_ARGS
+hipError_t launch_split_finalize_gradient(const SplitCall& c, const CenterRec* ctr,
+                                          const double2* nearp, const double2* farp, double* grad,
+                                          double* dn, hipStream_t s) {
+  const Dims& d = c.d;
+  const int n = d.Mc * d.nk;
+  hipLaunchKernelGGL(k_split_finalize_gradient, dim3((n + 255) / 256), dim3(256), 0, s, d.Mc, d.T,
+                     d.nk, c.far ? 1 : d.n_fsplit, d.side, ctr, nearp, farp, grad, dn);
   return hipGetLastError();
 }
 
-hipError_t launch_split_adjoint_nodes(const Dims& d, const double* nodes, const double* density,
-                                      const double* tables, const double4* geo,
-                                      const double2* dens, NystromSources ns,
-                                      const CenterRec* ctr, const double* jtab,
-                                      const double4* bnd, double g2, NearLists nl,
-                                      const double2* G, SplitNodeScratch w,
-                                      double* grad_density, double* grad_nodes, hipStream_t s) {
-  hipError_t e;
-  {
-    auto launch = [&]() -> hipError_t {
-      QBX_P_SWITCH(d.p, launch_split_nodes_near_p, d, geo, dens, ctr, jtab, bnd, g2, nl, G, w.cg,
-                   w.spart, s)
-    };
-    e = launch();
-    if (e != hipSuccess) return e;
-  }
+hipError_t launch_split_density_grad(const SplitCall& c, const double* tables, const double* wgt,
+                                     int n_acc, const double2* acc, const double2* partial,
+                                     double* grad_density, hipStream_t s) {
+  const Dims& d = c.d;
   const int nt = d.T * d.nk;
-  hipLaunchKernelGGL(k_split_gfar, dim3((nt + 255) / 256), dim3(256), 0, s, d.T, d.nk, d.n_sides,
-                     G, w.Gf);
-  // far, target side: the split's far target gradients
-  {
-    const int n_tb = (d.T + kWave - 1) / kWave;
-    const long waves = (long)n_tb * d.n_fsplit;
-    const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
-#define QBX_FGRAD_ARGS                                                                          \
-  ns.geo, ns.dens, d.T, nodes, d.T, bnd, d.P, g2, d.k, n_tb, d.n_fsplit, \
-      w.fpart
-    switch (d.kind) {
-      case 1: hipLaunchKernelGGL((k_split_far_grad<1>), grid, block, 0, s, QBX_FGRAD_ARGS); break;
-      case 2: hipLaunchKernelGGL((k_split_far_grad<2>), grid, block, 0, s, QBX_FGRAD_ARGS); break;
-      default: hipLaunchKernelGGL((k_split_far_grad<3>), grid, block, 0, s, QBX_FGRAD_ARGS); break;
-    }
-#undef QBX_FGRAD_ARGS
-  }
-  // far, source side (the far sources at the nodes)
-  {
-    const int n_sb = (d.T + kWave - 1) / kWave;
-    const long waves = (long)n_sb * d.n_asplit;
-    const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
-#define QBX_FADJ_ARGS                                                                       \
-  ns.geo, ns.dens, d.T, nodes, d.T, bnd, d.P, g2, d.k, w.Gf, n_sb, d.n_asplit,          \
-      w.apart
-    switch (d.kind) {
-      case 1: hipLaunchKernelGGL((k_split_far_adj<1, true>), grid, block, 0, s, QBX_FADJ_ARGS); break;
-      case 2: hipLaunchKernelGGL((k_split_far_adj<2, true>), grid, block, 0, s, QBX_FADJ_ARGS); break;
-      default: hipLaunchKernelGGL((k_split_far_adj<3, true>), grid, block, 0, s, QBX_FADJ_ARGS); break;
-    }
-#undef QBX_FADJ_ARGS
-  }
+  hipLaunchKernelGGL(k_split_density_grad, dim3((nt + 255) / 256), dim3(256), 0, s, d.T, d.N, d.qs,
+                     d.nk, n_acc, c.far ? 1 : d.n_asplit, tables, wgt, c.ns.w, acc, partial,
+                     grad_density);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_nystrom_grad(const SplitCall& c, const double* density,
+                                     const double* tables, const double2* Gf,
+                                     const double2* fpart, const double2* apart, double* cg,
+                                     double* gtw, double2* gde, hipStream_t s) {
+  const Dims& d = c.d;
   const TableLayout L = table_layout(d.qs);
   hipLaunchKernelGGL(k_split_nystrom_grad, dim3((d.T + 255) / 256), dim3(256), 0, s, d.T, d.nk,
-                     d.n_fsplit, d.n_asplit, density, ns.geo, ns.w, tables + L.w16, w.Gf, w.fpart,
-                     w.apart, w.cg, w.gtw, w.gde);
-  hipLaunchKernelGGL(k_split_source_finalize, dim3((d.N + 255) / 256), dim3(256), 0, s, d.N,
-                     d.kind, geo, w.spart, w.sg);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_chain(d, nodes, density, tables, w.sg, w.cg, w.gtw,
-                      reinterpret_cast<const double*>(w.gde), grad_density, grad_nodes, s);
+                     c.far ? 1 : d.n_fsplit, c.far ? 1 : d.n_asplit, density, c.ns.geo, c.ns.w,
+                     tables + L.w16, Gf, fpart, apart, cg, gtw, gde);
+  return hipGetLastError();
 }
 
 }  // namespace qbx

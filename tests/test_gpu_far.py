@@ -70,3 +70,53 @@ def test_far_nan_density_reaches_every_target():
     dens[0, 40] = float("nan")
     u = qbx.layer_potential(torch.from_numpy(pb.nodes).cuda(), dens, pb.k, pb.p)
     assert bool(torch.isnan(u.real).all())
+
+
+# the near/far split over its expansions: against the oracle's split, at the project's bars (1e-11
+# values and densities, 1e-10 nodes).  gamma small: far pairs that no expansion reaches are
+# summed directly; k = 150: no pair of panels is reached at all
+SPLIT = [
+    dict(P=95, k=5.0, p=6, side=1, kind=1, os=2, gamma=6.0),
+    dict(P=97, k=9.0, p=8, side=0, kind=3, os=3, gamma=6.0),
+    dict(P=98, k=9.0, p=5, side=0, kind=3, os=1, gamma=0.5),
+    dict(P=96, k=150.0, p=4, side=-1, kind=2, os=4, gamma=2.0),
+    dict(P=99, k=0.01, p=7, side=1, kind=1, os=5, gamma=9.0),
+]
+
+
+@pytest.mark.parametrize("c", SPLIT, ids=lambda c: "P{P}-k{k}-p{p}-g{gamma}-o{os}".format(**c))
+def test_split_matches_oracle(c):
+    from oracle import qbx_oracle as O
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), c["P"], c["k"], c["p"], c["side"],
+                        c["kind"], 19, oversample=c["os"], with_cotangent=True)
+    args = (pb.k, pb.p, pb.r, pb.oversample, pb.side, pb.kind)
+    nodes, dens, cot = (torch.from_numpy(np.ascontiguousarray(a)).cuda()
+                        for a in (pb.nodes, pb.density, pb.cotangent))
+    nrel = lambda a, b: float(np.abs(a.cpu().numpy() - np.asarray(b)).max() / np.abs(np.asarray(b)).max())
+    u = qbx.layer_potential_split(nodes, dens, *args, gamma=c["gamma"])
+    assert nrel(u, O.layer_potential_split(pb.nodes, pb.density, *args, gamma=c["gamma"])) < 1e-11
+    grad, dn = qbx.layer_potential_split_gradient(nodes, dens, *args, gamma=c["gamma"])
+    og, od = O.layer_potential_split_gradient(pb.nodes, pb.density, *args, gamma=c["gamma"])
+    assert nrel(grad, og) < 1e-11 and nrel(dn, od) < 1e-11
+    gd, gn = qbx.layer_potential_split_vjp(nodes, dens, cot, *args, gamma=c["gamma"],
+                                           want_nodes=True)
+    only = qbx.layer_potential_split_vjp(nodes, dens, cot, *args, gamma=c["gamma"])
+    rd, rn = O.split_vjp(pb.nodes, pb.density, *args, pb.cotangent, gamma=c["gamma"])
+    assert nrel(gd, rd) < 1e-11 and nrel(only, rd) < 1e-11 and nrel(gn, rn) < 1e-10
+
+
+def test_split_groups_match_oracle():
+    """Groups of panels in the split (321 panels, 16 sampled targets)."""
+    from oracle import qbx_oracle as O
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), 321, 20.0, 10, 0, 3, 23, oversample=2)
+    args = (pb.k, pb.p, pb.r, pb.oversample, pb.side, pb.kind)
+    idx = np.linspace(0, pb.n_targets - 1, 16).astype(int)
+    u = qbx.layer_potential_split(torch.from_numpy(pb.nodes).cuda(),
+                                  torch.from_numpy(pb.density).cuda(), *args, gamma=6.0)
+    ref = np.asarray(O.layer_potential_split(pb.nodes, pb.density, *args, gamma=6.0, targets=idx))
+    got = u.cpu().numpy()[:, :, idx]
+    assert np.abs(got - ref).max() / np.abs(ref).max() < 1e-11
