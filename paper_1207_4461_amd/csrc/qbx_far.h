@@ -205,19 +205,36 @@ inline bool far_applies(const Dims& d) {
 }
 // the near/far split's far targets are points: no disk to look at
 inline bool far_applies_split(const Dims& d) { return d.P >= kFarMinPanels; }
-// blocks of the translation aimed for (256 compute units, three blocks each resident), and
-// the most shares of the sources a panel-level block takes when groups serve the rest
-// (about 110 sources are left per 64 target panels)
-constexpr int kFarM2LBlocks = 1024;
+// Blocks of the translation that are resident at once (256 compute units, three each), and the
+// most shares of the sources a panel-level block takes when groups serve the rest (about 110
+// sources are left per 64 target panels).
+constexpr int kFarM2LBlocks = 768;
+constexpr int kFarMaxPanelShares = 16;
 // waves of the near source passes aimed for
 constexpr int kFarSourceWaves = 8192;
 constexpr int kFarMaxShares = 8;   // parts of a chunk's near source sums at most
-constexpr int kFarMaxPanelShares = 16;
+// Shares of the sources per (target block, vector, half): as many as `rounds` rounds of
+// resident blocks hold, for the number of rounds that gives the least time (a partly
+// filled last round costs a whole one); a batch's item: its part of four rounds.
 inline int far_share(int C, int V, int blocks, bool inner) {
-  const int tb = (C + kWave - 1) / kWave;
-  int n = (blocks + tb * V * 2 - 1) / (tb * V * 2);
-  int most = (C + 3) / 4;
+  const int base = (C + kWave - 1) / kWave * V * 2;
+  int most = (C + 3) / 4, n = 1;
   if (inner && most > kFarMaxPanelShares) most = kFarMaxPanelShares;
+  if (blocks < kFarM2LBlocks) {
+    n = (blocks + base - 1) / base;
+  } else {
+    double best = 1e300;
+    for (int rounds = 1; rounds <= 3; ++rounds) {
+      int c = rounds * blocks / base;
+      if (c < 1) continue;
+      if (c > most) c = most;
+      const int r = (c * base + blocks - 1) / blocks;
+      if ((double)r / c < best * 0.999) {
+        best = (double)r / c;
+        n = c;
+      }
+    }
+  }
   if (n > most) n = most;
   return n < 1 ? 1 : n;
 }

@@ -511,6 +511,7 @@ __global__ __launch_bounds__(256) void k_far_lsum(FarBlocks B, const double* __r
   const double2* lp = reinterpret_cast<const double2*>(ro + (group ? it.lp1 : it.lp0));
   const size_t stride = (size_t)it.V * 2 * (kFarQ + 1) * C;
   double sr = 0.0, si = 0.0;
+#pragma unroll 8
   for (int s = 0; s < ns; ++s) {
     const double2 x = lp[s * stride + e];
     sr += x.x;

@@ -10,6 +10,7 @@
 //  * Section 3.3 step 4(a): c = x + s r h_m n with h_m the panel length,
 //    radius R = r h_m, and theta = arg(x - c) = arg(-s n).
 #include "qbx_far.h"
+#include "qbx_gl_table.h"
 #include "qbx_internal.h"
 #include "qbx_panel.h"
 #include "qbx_special.h"
@@ -19,13 +20,26 @@ namespace qbx {
 // ---------------------------------------------------------------------------
 // tables: GL rules (16 and q_s points), Lagrange value / derivative maps from
 // the 16 nodes to the q_s source nodes, and the 16x16 differentiation matrix.
+// The rules come from constants (correctly rounded): Newton's method on P_n, a serial
+// chain of some 600 steps with a division each, took 31 to 49 us of every call.
 // ---------------------------------------------------------------------------
+static __constant__ double g_gl_nodes[gltab::kLen] = {QBX_GL_NODES};
+static __constant__ double g_gl_weights[gltab::kLen] = {QBX_GL_WEIGHTS};
+
+// node i (ascending) of the n-point rule (n a multiple of 16) and its weight
+__device__ __forceinline__ void gl_rule(int n, int i, double* node, double* weight) {
+  const int k = n / kQ, half = n / 2;
+  const int at = (k - 1) * k / 2 * (kQ / 2) + (i < half ? half - 1 - i : i - half);
+  *node = i < half ? -g_gl_nodes[at] : g_gl_nodes[at];
+  *weight = g_gl_weights[at];
+}
+
 __global__ __launch_bounds__(256) void k_tables(int qs, double* __restrict__ tab) {
   const TableLayout L = table_layout(qs);
-  __shared__ double t16[kQ], w16[kQ], tq[128], wq[128], bw[kQ];
+  __shared__ double t16[kQ], bw[kQ];
   const int t = threadIdx.x;
-  if (t < kQ) gauss_legendre_node(kQ, t, &t16[t], &w16[t]);
-  if (t < qs) gauss_legendre_node(qs, t, &tq[t], &wq[t]);
+  double w;
+  if (t < kQ) gl_rule(kQ, t, &t16[t], &w);
   __syncthreads();
   if (t < kQ) {  // barycentric weights 1 / prod_{c != a} (tau_a - tau_c)
     double prod = 1.0;
@@ -34,17 +48,21 @@ __global__ __launch_bounds__(256) void k_tables(int qs, double* __restrict__ tab
     bw[t] = 1.0 / prod;
   }
   __syncthreads();
-  if (t < kQ) {
-    tab[L.tau16 + t] = t16[t];
-    tab[L.w16 + t] = w16[t];
+  const int e = blockIdx.x * 256 + t;
+  if (e < kQ) {
+    tab[L.tau16 + e] = t16[e];
+    tab[L.w16 + e] = w;
   }
-  if (t < qs) {
-    tab[L.taus + t] = tq[t];
-    tab[L.ws + t] = wq[t];
+  if (e < qs) {
+    double x, ws;
+    gl_rule(qs, e, &x, &ws);
+    tab[L.taus + e] = x;
+    tab[L.ws + e] = ws;
   }
-  for (int e = t; e < qs * kQ; e += blockDim.x) {
+  if (e < qs * kQ) {
     const int b = e / kQ, a = e % kQ;
-    const double tau = tq[b];
+    double tau, ws;
+    gl_rule(qs, b, &tau, &ws);
     double val = 1.0;
     for (int c = 0; c < kQ; ++c)
       if (c != a) val *= (tau - t16[c]);
@@ -59,7 +77,7 @@ __global__ __launch_bounds__(256) void k_tables(int qs, double* __restrict__ tab
     tab[L.V + e] = bw[a] * val;
     tab[L.Vd + e] = bw[a] * der;
   }
-  for (int e = t; e < kQ * kQ; e += blockDim.x) {
+  if (e < kQ * kQ) {
     const int b = e / kQ, a = e % kQ;  // row: node b, column: basis a
     double v;
     if (a != b) {
@@ -74,7 +92,7 @@ __global__ __launch_bounds__(256) void k_tables(int qs, double* __restrict__ tab
 }
 
 hipError_t launch_tables(const Dims& d, double* tables, hipStream_t s) {
-  hipLaunchKernelGGL(k_tables, dim3(1), dim3(256), 0, s, d.qs, tables);
+  hipLaunchKernelGGL(k_tables, dim3((d.qs * kQ + 255) / 256), dim3(256), 0, s, d.qs, tables);
   return hipGetLastError();
 }
 

@@ -44,6 +44,7 @@ __device__ __forceinline__ void upsample_panel(const Dims& d, int m, const doubl
   __shared__ double X[kQ][2];
   __shared__ double2 S[2][kQ];
   __shared__ double red[128];
+  __shared__ double J[2 * (kPMax + 4)];
   if (t < 2 * kQ) X[t >> 1][t & 1] = nodes[(size_t)m * 2 * kQ + t];
   if (t < d.nk * kQ) {
     const int kk = t / kQ, a = t % kQ;
@@ -92,6 +93,12 @@ __device__ __forceinline__ void upsample_panel(const Dims& d, int m, const doubl
   }
   const double hm = red[0];
   if (t == 0) hpan[m] = hm;
+  // every center of the panel has the radius r h_m: one Bessel table, by one thread into LDS
+  // (of the second wave, the first has the centers), then copied to all of them.  A table
+  // per center, each written and rescaled in global memory by its own thread, took most of
+  // this kernel's time.
+  const double R = d.center_rule ? d.r * sqrt(hm) : d.r * hm;
+  if (t == 64) center_bessel_table(d.k * R, d.NJ / 2, J);
   if (t < kQ * d.n_sides) {
     const int a = t % kQ, si = t / kQ;
     const double sgn = side_sign(d.side, si);
@@ -104,7 +111,6 @@ __device__ __forceinline__ void upsample_panel(const Dims& d, int m, const doubl
     }
     const double inv = 1.0 / sqrt(tx * tx + ty * ty);
     const double nx = ty * inv, ny = -tx * inv;
-    const double R = d.center_rule ? d.r * sqrt(hm) : d.r * hm;
     CenterRec c;
     c.x = X[a][0];
     c.y = X[a][1];
@@ -116,7 +122,11 @@ __device__ __forceinline__ void upsample_panel(const Dims& d, int m, const doubl
     c.pad = 0.0;
     const size_t ci = (size_t)si * d.T + (size_t)m * kQ + a;
     ctr[ci] = c;
-    center_bessel_table(d.k * R, d.NJ / 2, jtab + ci * d.NJ);
+  }
+  __syncthreads();
+  for (int e = t; e < kQ * d.n_sides * d.NJ; e += blockDim.x) {
+    const int si = e / (kQ * d.NJ), q = e - si * kQ * d.NJ;
+    jtab[((size_t)si * d.T + (size_t)m * kQ) * d.NJ + q] = J[q % d.NJ];
   }
 }
 
