@@ -30,7 +30,6 @@
 namespace qbx {
 
 using cplx = std::complex<double>;
-constexpr int kDotBlocks = 256;      // first-stage blocks of the multi-dot
 constexpr int kMaxRestart = 1000;   // Krylov vectors kept (16 B x nodes each)
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
@@ -93,48 +92,66 @@ __global__ __launch_bounds__(256) void k_combine(int T, const double2* __restric
   y[t] = make_double2(fma(half, v[t].x, sw[t] * (a.x - dx)), fma(half, v[t].y, sw[t] * (a.y - dy)));
 }
 
-// partial[b][i] = sum over block b's slice of conj(V_i[t]) w[t], i < nv
+// Inner products h[i] = V_i^H w, i < nv, in two steps with fixed orders: a block per
+// (slice of kDotSlice entries, vector), then a wave per vector over the slices.  (One block
+// per slice of all vectors in turn and one thread per vector over 256 slices took 18 and
+// 48 us at 4096 unknowns; together these take about 8.)
+constexpr int kDotSlice = 2048;
 __global__ __launch_bounds__(256) void k_dots_partial(int T, const double2* __restrict__ V, int nv,
                                                       const double2* __restrict__ w,
                                                       double2* __restrict__ partial) {
-  __shared__ double red[2][256];
-  const int tid = threadIdx.x;
-  for (int i = 0; i < nv; ++i) {
-    const double2* vi = V + (size_t)i * T;
-    double re = 0.0, im = 0.0;
-    for (int t = blockIdx.x * 256 + tid; t < T; t += gridDim.x * 256) {
-      const double2 a = vi[t], b = w[t];
-      re = fma(a.x, b.x, fma(a.y, b.y, re));     // conj(a) b
-      im = fma(a.x, b.y, fma(-a.y, b.x, im));
-    }
-    red[0][tid] = re;
-    red[1][tid] = im;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-      if (tid < off) {
-        red[0][tid] += red[0][tid + off];
-        red[1][tid] += red[1][tid + off];
-      }
-      __syncthreads();
-    }
-    if (tid == 0) partial[(size_t)blockIdx.x * nv + i] = make_double2(red[0][0], red[1][0]);
-    __syncthreads();
+  __shared__ double red[4][2];
+  const int tid = threadIdx.x, i = blockIdx.y;
+  const double2* vi = V + (size_t)i * T;
+  const int t0 = blockIdx.x * kDotSlice, t1 = min(t0 + kDotSlice, T);
+  double re = 0.0, im = 0.0;
+  for (int t = t0 + tid; t < t1; t += 256) {
+    const double2 a = vi[t], b = w[t];
+    re = fma(a.x, b.x, fma(a.y, b.y, re));     // conj(a) b
+    im = fma(a.x, b.y, fma(-a.y, b.x, im));
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    re += __shfl_xor(re, off);
+    im += __shfl_xor(im, off);
+  }
+  if ((tid & 63) == 0) {
+    red[tid >> 6][0] = re;
+    red[tid >> 6][1] = im;
+  }
+  __syncthreads();
+  if (tid == 0)
+    partial[(size_t)blockIdx.x * nv + i] =
+        make_double2((red[0][0] + red[1][0]) + (red[2][0] + red[3][0]),
+                     (red[0][1] + red[1][1]) + (red[2][1] + red[3][1]));
 }
 
-// h[i] = sum over blocks, in block order
-__global__ __launch_bounds__(256) void k_dots_final(int nblk, int nv,
-                                                    const double2* __restrict__ partial,
-                                                    double2* __restrict__ h) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nv) return;
+__global__ __launch_bounds__(64) void k_dots_final(int nblk, int nv,
+                                                   const double2* __restrict__ partial,
+                                                   double2* __restrict__ h) {
+  const int i = blockIdx.x;
   double re = 0.0, im = 0.0;
-  for (int b = 0; b < nblk; ++b) {
+  for (int b = threadIdx.x; b < nblk; b += 64) {
     const double2 v = partial[(size_t)b * nv + i];
     re += v.x;
     im += v.y;
   }
-  h[i] = make_double2(re, im);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    re += __shfl_xor(re, off);
+    im += __shfl_xor(im, off);
+  }
+  if (threadIdx.x == 0) h[i] = make_double2(re, im);
+}
+
+// y = x / sqrt(n2), n2 = x^H x on the device
+__global__ __launch_bounds__(256) void k_normalize(int T, const double2* __restrict__ x,
+                                                   const double2* __restrict__ n2,
+                                                   double2* __restrict__ y) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= T) return;
+  const double s = 1.0 / sqrt(n2->x);
+  y[t] = make_double2(s * x[t].x, s * x[t].y);
 }
 
 // w -= sum_i h[i] V_i
@@ -238,8 +255,8 @@ static SolveLayout make_solve_layout(const Dims& d, int restart) {
   L.w = take(sizeof(double2) * T);
   L.b = take(sizeof(double2) * T);
   L.x = take(sizeof(double2) * T);
-  L.partial = take(sizeof(double2) * kDotBlocks * (size_t)(restart + 1));
-  L.h = take(sizeof(double2) * (size_t)(restart + 1));
+  L.partial = take(sizeof(double2) * ((T + kDotSlice - 1) / kDotSlice) * (size_t)(restart + 1));
+  L.h = take(sizeof(double2) * (2 * (size_t)restart + 3));
   L.total = o;
   return L;
 }
@@ -305,28 +322,51 @@ struct Gmres {
                        at<double2>(L.out), half, alpha, y);
     return check(hipGetLastError(), "solve adjoint combine kernel");
   }
-  // h[0..nv) = V_i^H w on the device, and a host copy
-  int dots(const double2* Vb, int nv, const double2* w, cplx* host) const {
-    hipLaunchKernelGGL(k_dots_partial, dim3(kDotBlocks), dim3(256), 0, s, T, Vb, nv, w,
+  // h[0..nv) = V_i^H w on the device
+  int dots(const double2* Vb, int nv, const double2* w, double2* h) const {
+    const int nblk = (T + kDotSlice - 1) / kDotSlice;
+    hipLaunchKernelGGL(k_dots_partial, dim3(nblk, nv), dim3(256), 0, s, T, Vb, nv, w,
                        at<double2>(L.partial));
-    hipLaunchKernelGGL(k_dots_final, dim3((nv + 255) / 256), dim3(256), 0, s, kDotBlocks, nv,
-                       at<double2>(L.partial), at<double2>(L.h));
-    int rc = check(hipGetLastError(), "solve dot kernels");
-    if (rc) return rc;
-    rc = check(hipMemcpyAsync(host, at<double2>(L.h), sizeof(double2) * nv,
-                              hipMemcpyDeviceToHost, s), "solve dot copy");
-    if (rc) return rc;
-    return check(hipStreamSynchronize(s), "solve dot sync");
+    hipLaunchKernelGGL(k_dots_final, dim3(nv), dim3(64), 0, s, nblk, nv, at<double2>(L.partial), h);
+    return check(hipGetLastError(), "solve dot kernels");
   }
-  // w -= sum_i h_i V_i with h already on the device
-  int subtract(int nv, double2* w) const {
-    hipLaunchKernelGGL(k_subtract, dim3(grid), dim3(256), 0, s, T, at<double2>(L.V), nv,
-                       at<double2>(L.h), w);
+  // n device values on the host (synchronous)
+  int fetch(const double2* dev, int n, cplx* host) const {
+    const int rc = check(hipMemcpyAsync(host, dev, sizeof(double2) * n, hipMemcpyDeviceToHost, s),
+                         "solve dot copy");
+    return rc ? rc : check(hipStreamSynchronize(s), "solve dot sync");
+  }
+  // w -= sum_i h_i V_i with h on the device
+  int subtract(int nv, const double2* h, double2* w) const {
+    hipLaunchKernelGGL(k_subtract, dim3(grid), dim3(256), 0, s, T, at<double2>(L.V), nv, h, w);
     return check(hipGetLastError(), "solve update kernel");
+  }
+  // One Arnoldi step on w = A V_j: classical Gram-Schmidt twice against V_0..V_j, the norm
+  // and V_{j+1} = w / |w|, all on the device; h1, h2 (j + 1 each) and |w|^2 come to the
+  // host in one copy.  (V_{j+1} is not read when |w| = 0.)
+  int arnoldi(int j, double2* w, cplx* h1, cplx* h2, double* hn, cplx* buf) const {
+    const int nv = j + 1;
+    double2* h = at<double2>(L.h);
+    int rc;
+    if ((rc = dots(V(0), nv, w, h))) return rc;
+    if ((rc = subtract(nv, h, w))) return rc;
+    if ((rc = dots(V(0), nv, w, h + nv))) return rc;
+    if ((rc = subtract(nv, h + nv, w))) return rc;
+    if ((rc = dots(w, 1, w, h + 2 * nv))) return rc;
+    hipLaunchKernelGGL(k_normalize, dim3(grid), dim3(256), 0, s, T, w, h + 2 * nv, V(j + 1));
+    if ((rc = check(hipGetLastError(), "solve vector kernel"))) return rc;
+    if ((rc = fetch(h, 2 * nv + 1, buf))) return rc;
+    for (int i = 0; i < nv; ++i) {
+      h1[i] = buf[i];
+      h2[i] = buf[nv + i];
+    }
+    *hn = std::sqrt(std::max(buf[2 * nv].real(), 0.0));
+    return QBX_OK;
   }
   int norm(const double2* w, double* n) const {
     cplx h;
-    const int rc = dots(w, 1, w, &h);
+    int rc = dots(w, 1, w, at<double2>(L.h));
+    if (!rc) rc = fetch(at<double2>(L.h), 1, &h);
     *n = std::sqrt(std::max(h.real(), 0.0));
     return rc;
   }
@@ -405,7 +445,8 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
   int it = 0;
   double res = 0.0;
   if (bnorm > 0.0) {
-    std::vector<cplx> H((size_t)(m + 1) * m), gv(m + 1), cs(m), sn(m), y(m), h1(m + 1), h2(m + 1);
+    std::vector<cplx> H((size_t)(m + 1) * m), gv(m + 1), cs(m), sn(m), y(m), h1(m + 1), h2(m + 1),
+        buf(2 * m + 1);
     auto Hs = [&](int i, int j) -> cplx& { return H[(size_t)i * m + j]; };
     bool done = false;
     while (!done) {
@@ -427,14 +468,9 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
       int jj = 0;
       for (int j = 0; j < m; ++j) {
         if ((rc = G.matvec(G.V(j), w))) return rc;
-        // classical Gram-Schmidt, twice
-        if ((rc = G.dots(G.V(0), j + 1, w, h1.data()))) return rc;
-        if ((rc = G.subtract(j + 1, w))) return rc;
-        if ((rc = G.dots(G.V(0), j + 1, w, h2.data()))) return rc;
-        if ((rc = G.subtract(j + 1, w))) return rc;
-        for (int i = 0; i <= j; ++i) Hs(i, j) = h1[i] + h2[i];
         double hn;
-        if ((rc = G.norm(w, &hn))) return rc;
+        if ((rc = G.arnoldi(j, w, h1.data(), h2.data(), &hn, buf.data()))) return rc;
+        for (int i = 0; i <= j; ++i) Hs(i, j) = h1[i] + h2[i];
         // previous rotations, then the new one
         for (int i = 0; i < j; ++i) {
           const cplx a = Hs(i, j), bb = Hs(i + 1, j);
@@ -463,7 +499,6 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
           done = true;
           break;
         }
-        if ((rc = G.axpby(1.0 / hn, w, 0, nullptr, G.V(j + 1)))) return rc;
       }
       // x += V y, H y = g (upper triangular).  A zero pivot (the operator
       // singular on the Krylov space: w = 0 with nothing left to rotate) takes
@@ -477,7 +512,7 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
       for (int i = 0; i < jj; ++i) ny[i] = make_double2(-y[i].real(), -y[i].imag());
       if ((rc = G.check(hipMemcpyAsync(G.at<double2>(L.h), ny.data(), sizeof(double2) * jj,
                                        hipMemcpyHostToDevice, stream), "solve copy"))) return rc;
-      if ((rc = G.subtract(jj, x))) return rc;
+      if ((rc = G.subtract(jj, G.at<double2>(L.h), x))) return rc;
       if ((rc = G.check(hipStreamSynchronize(stream), "solve sync"))) return rc;
     }
     // the true residual of the returned solution
