@@ -383,14 +383,9 @@ static hipError_t launch_adjoint_fused_p(const Dims& d, const double4* geo, cons
   return hipGetLastError();
 }
 
-hipError_t launch_adjoint_fused(const Dims& d, const double* nodes, const double* density,
-                                const double* tables, const double4* geo, const double2* dens,
-                                const CenterRec* ctr, const double* jtab, const double* cot,
-                                double2* G, double* cpart, double* cg, double2* spartial,
-                                double* sg, double* grad_density, double* grad_nodes,
-                                hipStream_t s) {
-  const int n = d.Mc * d.nk;
-  hipLaunchKernelGGL(k_make_G, dim3((n + 255) / 256), dim3(256), 0, s, d.Mc, d.T, d.nk, cot, G);
+hipError_t launch_fused_tiles(const Dims& d, const double4* geo, const double2* dens,
+                              const CenterRec* ctr, const double* jtab, const double2* G,
+                              double2* spartial, double* cpart, hipStream_t s) {
   timer_begin(4, s);
   hipError_t e;
   switch (d.p) {
@@ -407,6 +402,18 @@ hipError_t launch_adjoint_fused(const Dims& d, const double* nodes, const double
       e = hipErrorInvalidValue;
   }
   timer_end(4, s);
+  return e;
+}
+
+hipError_t launch_adjoint_fused(const Dims& d, const double* nodes, const double* density,
+                                const double* tables, const double4* geo, const double2* dens,
+                                const CenterRec* ctr, const double* jtab, const double* cot,
+                                double2* G, double* cpart, double* cg, double2* spartial,
+                                double* sg, double* grad_density, double* grad_nodes,
+                                hipStream_t s) {
+  const int n = d.Mc * d.nk;
+  hipLaunchKernelGGL(k_make_G, dim3((n + 255) / 256), dim3(256), 0, s, d.Mc, d.T, d.nk, cot, G);
+  const hipError_t e = launch_fused_tiles(d, geo, dens, ctr, jtab, G, spartial, cpart, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_fused_center_grads, dim3((d.Mc + 255) / 256), dim3(256), 0, s, d.Mc,
                      d.n_sb, d.side, d.T, ctr, cpart, cg);

@@ -312,7 +312,7 @@ static void timer_clear() {
 
 // the item of a call's far sums: the offsets of layout L (full: make_layout's, else
 // make_forward_layout's), for plain pairs
-static FarItem far_item_of(const Dims& d, const Layout& L, bool full, bool fwd, bool bwd) {
+FarItem far_item_of(const Dims& d, const Layout& L, bool full, bool fwd, bool bwd) {
   size_t o = align256(L.far + sizeof(FarItem));
   auto take = [&](size_t bytes) {
     const size_t a = o;

@@ -4,47 +4,132 @@
 // kept; any target inside a center's disk is then evaluated from them by Section
 // 3.3 step 4(c), with its own distance and angle from the center.
 //
-//  * k_coef<M>: lanes are 64 centers, the sources of a source split are
-//    wave-uniform (scalar loads).  Per pair, with v = x' - c, rho = |v| and
-//    E = e^{-i arg v}, the source factors f_m = H_m(k rho) E^m and
-//    f_{-m} = (-1)^m H_m(k rho) conj(E)^m, |m| <= M, are added with a complex
-//    weight q_j into 2M + 1 complex sums per lane, all in registers (one
-//    template instance per M).  One launch per weight.
-//  * The single layer takes q = w sigma and M = p.  The double layer uses the
-//    ladder d/dn' f_l = (k/2)(conj(nu) f_{l-1} - nu f_{l+1}), nu = n_x + i n_y:
-//    two launches with q = w mu conj(nu) and q = w mu nu at M = p + 1 give sums
-//    alpha_m, beta_m, and a^D_l = (k/2)(alpha_{l-1} - beta_{l+1}) (k_coef_finalize).
+//  * A pair (center c, source x') with v = x' - c, rho = |v| and E = e^{-i arg v} has the
+//    factors f_m = H_m(k rho) E^m and f_{-m} = (-1)^m H_m(k rho) conj(E)^m.  The single layer
+//    adds q f_l to a_l, q = w sigma; the double layer's ladder d/dn' f_l =
+//    (k/2)(conj(nu) f_{l-1} - nu f_{l+1}), nu = n_x + i n_y, adds the f_m to its two
+//    neighbours with the weights w mu conj(nu) and w mu nu (coef_pair, k/2 in
+//    k_coef_finalize).  A wave takes one sign of the orders: f_{-m} follows f_m's recurrences
+//    with the signs of H_1, of 1/z and of E's imaginary part turned, so one code has both, the
+//    sums of both kinds stay in registers up to p = 24, and a pair's H and E serve both kinds.
+//  * k_coef: lanes are 64 centers, the sources of a source split are wave-uniform (scalar
+//    loads): contours below the panel expansions' sizes.
+//  * k_coef_near: the sources of near panels only, where panel expansions take the far ones
+//    (qbx_far.hip: the coefficients are the local expansions that those end in).
+//    256 panels (4 x 16 sources each), S + D, both sides, p = 12, all coefficient kernels:
+//    8.4 ms as three passes over every pair (one per weight), 0.49 ms now, 0.34 of it
+//    k_coef_near.
 //  * k_evaluate_expansions: one thread per target,
 //    u = (i/4) sum_l a_l J_l(k|x - c|) e^{i l arg(x - c)} with J_l by Miller's
 //    recurrence (J_{-l} = (-1)^l J_l).
-//  * k_assign_centers: one wave per target, the nearest center whose disk holds
-//    it (ties to the lower index), or -1.
+//  * k_assign_centers: per target, the nearest center whose disk holds it (ties to the
+//    lower index), or -1.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "../../include/qbx.h"
 #include "qbx_internal.h"
+#include "qbx_near.h"
 #include "qbx_panel.h"
 #include "qbx_special.h"
 
 namespace qbx {
 
-// the D weights w mu conj(nu) and w mu nu per source: qd[0][j], qd[1][j]
-__global__ __launch_bounds__(256) void k_dlp_weights(int N, const double4* __restrict__ geo,
-                                                     const double2* __restrict__ densD,
-                                                     double2* __restrict__ qd) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
-  const double4 g = geo[j];
-  const double2 w = densD[j];
-  // (w_r + i w_i)(n_x -+ i n_y)
-  qd[j] = make_double2(fma(w.x, g.z, w.y * g.w), fma(w.y, g.z, -w.x * g.w));
-  qd[(size_t)N + j] = make_double2(fma(w.x, g.z, -w.y * g.w), fma(w.y, g.z, w.x * g.w));
+// sums of one sign of the orders: S[l] = a^S_{sg l}, D[l] = (2/k) a^D_{sg l}, 0 <= l <= P (the
+// order-0 sums are in parts: S's in the positive sign's, D's in both)
+template <int P, int KIND>
+struct CoefSums {
+  double sr[KIND & 1 ? P + 1 : 1], si[KIND & 1 ? P + 1 : 1];
+  double dr[KIND & 2 ? P + 1 : 1], di[KIND & 2 ? P + 1 : 1];
+};
+
+// adds one pair; q the weighted densities (S, D), sg the sign of the orders
+template <int P, int KIND>
+__device__ __forceinline__ void coef_pair(const double4 g, const double2 qS, const double2 w,
+                                          double cx, double cy, double k, double inv_k, double sg,
+                                          CoefSums<P, KIND>& A) {
+  constexpr bool kS = (KIND & 1) != 0, kD = (KIND & 2) != 0;
+  constexpr int M = kD ? P + 1 : P;
+  const int z0 = opaque_zero();
+  const double* __restrict__ cf = g_seed_table + z0;
+  // D: f_m's weight in order m + 1 and, negative, in order m - 1: w conj(nu) and w nu, for the
+  // negative orders -w nu and -w conj(nu)
+  const double ny = sg * g.w, wx = sg * w.x, wy = sg * w.y;
+  const double ur = fma(wx, g.z, wy * ny), ui = fma(wy, g.z, -wx * ny);
+  const double lr = fma(wx, g.z, -wy * ny), li = fma(wy, g.z, wx * ny);
+  const double vx = g.x - cx, vy = g.y - cy;
+  const double rho2 = fma(vx, vx, vy * vy);
+  const double ir = rsqrt_refined(rho2);
+  const double z = k * (rho2 * ir), iz = ir * inv_k;
+  const H01 h = hankel01(z, iz, cf);
+  const double e1r = vx * ir, e1i = -sg * (vy * ir);
+  const double tz = 2.0 * sg * iz;
+  double hpr = h.h0r, hpi = h.h0i, hr = sg * h.h1r, hi = sg * h.h1i;   // H_{m-1}, H_m
+  double er = e1r, ei = e1i;                                         // E^m
+  if (kS && sg > 0.0) {
+    A.sr[0] = fma(qS.x, hpr, fma(-qS.y, hpi, A.sr[0]));
+    A.si[0] = fma(qS.x, hpi, fma(qS.y, hpr, A.si[0]));
+  }
+  if (kD && P >= 1) {
+    A.dr[1] = fma(ur, hpr, fma(-ui, hpi, A.dr[1]));
+    A.di[1] = fma(ur, hpi, fma(ui, hpr, A.di[1]));
+  }
+#pragma unroll
+  for (int m = 1; m <= M; ++m) {
+    const double fr = fma(hr, er, -hi * ei), fi = fma(hr, ei, hi * er);
+    if (kS && m <= P) {
+      A.sr[m] = fma(qS.x, fr, fma(-qS.y, fi, A.sr[m]));
+      A.si[m] = fma(qS.x, fi, fma(qS.y, fr, A.si[m]));
+    }
+    if (kD) {
+      A.dr[m - 1] = fma(-lr, fr, fma(li, fi, A.dr[m - 1]));
+      A.di[m - 1] = fma(-lr, fi, fma(-li, fr, A.di[m - 1]));
+      if (m + 1 <= P) {
+        A.dr[m + 1] = fma(ur, fr, fma(-ui, fi, A.dr[m + 1]));
+        A.di[m + 1] = fma(ur, fi, fma(ui, fr, A.di[m + 1]));
+      }
+    }
+    if (m < M) {
+      // H_{m+1} = (2m/z) H_m - H_{m-1};  E^{m+1} = E^m E
+      const double t = m * tz;
+      const double nr = fma(t, hr, -hpr), ni = fma(t, hi, -hpi);
+      hpr = hr;
+      hpi = hi;
+      hr = nr;
+      hi = ni;
+      const double tr = fma(er, e1r, -ei * e1i);
+      ei = fma(er, e1i, ei * e1r);
+      er = tr;
+    }
+  }
 }
 
-// partial[sp][m + M][ci]: sum over the sources of split sp of q_j f_m(x'_j - c_ci)
-template <int M>
+template <int P, int KIND>
+__device__ __forceinline__ void coef_zero(CoefSums<P, KIND>& A) {
+#pragma unroll
+  for (int l = 0; l <= P; ++l) {
+    if (KIND & 1) A.sr[l] = A.si[l] = 0.0;
+    if (KIND & 2) A.dr[l] = A.di[l] = 0.0;
+  }
+}
+
+// partial[sp][half][kind][l][ci]
+template <int P, int KIND>
+__device__ __forceinline__ void coef_store(const CoefSums<P, KIND>& A, int sp, int half, int ci,
+                                           int Mc, double2* __restrict__ partial) {
+  constexpr int NK = KIND == 3 ? 2 : 1;
+  double2* o = partial + ((size_t)(sp * 2 + half) * NK * (P + 1)) * Mc + ci;
+#pragma unroll
+  for (int l = 0; l <= P; ++l) {
+    if (KIND & 1) o[(size_t)l * Mc] = make_double2(A.sr[l], A.si[l]);
+    if (KIND & 2) o[(size_t)((NK - 1) * (P + 1) + l) * Mc] = make_double2(A.dr[l], A.di[l]);
+  }
+}
+
+// the sums over the sources of split sp; q: [n kinds][N] weighted densities
+template <int P, int KIND>
 __global__ __launch_bounds__(256) void k_coef(const double4* __restrict__ geo,
                                               const double2* __restrict__ q, int N,
                                               const CenterRec* __restrict__ ctr, int Mc,
@@ -53,108 +138,102 @@ __global__ __launch_bounds__(256) void k_coef(const double4* __restrict__ geo,
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int gw = blockIdx.x * 4 + wave;
-  const int sp = gw / n_cb;
-  const int cb = gw - sp * n_cb;
+  const int half = gw & 1;
+  const int sp = (gw >> 1) / n_cb;
+  const int cb = (gw >> 1) - sp * n_cb;
   const int ci = cb * kWave + lane;
   if (sp >= n_sp) return;   // past the last split (whole waves); an empty split writes zeros
   const int j0 = sp * src_per_split;
   const int j1 = min(N, j0 + src_per_split);
   const bool valid = ci < Mc;
   const CenterRec c = ctr[valid ? ci : Mc - 1];
-  const double inv_k = 1.0 / k;
-  double ar[2 * M + 1], ai[2 * M + 1];
-#pragma unroll
-  for (int m = 0; m <= 2 * M; ++m) ar[m] = ai[m] = 0.0;
-  for (int j = j0; j < j1; ++j) {
-    const int z0 = opaque_zero();
-    const double* __restrict__ cf = g_seed_table + z0;
-    const double4 g = geo[j];
-    const double2 w = q[j];
-    const double vx = g.x - c.cx, vy = g.y - c.cy;
-    const double rho2 = fma(vx, vx, vy * vy);
-    const double ir = rsqrt_refined(rho2);
-    const double z = k * (rho2 * ir), iz = ir * inv_k;
-    const H01 h = hankel01(z, iz, cf);
-    const double e1r = vx * ir, e1i = -vy * ir;   // E = e^{-i theta'}
-    // m = 0
-    ar[M] = fma(w.x, h.h0r, fma(-w.y, h.h0i, ar[M]));
-    ai[M] = fma(w.x, h.h0i, fma(w.y, h.h0r, ai[M]));
-    double hpr = h.h0r, hpi = h.h0i, hr = h.h1r, hi = h.h1i;   // H_{m-1}, H_m
-    double er = e1r, ei = e1i;                                 // E^m
-#pragma unroll
-    for (int m = 1; m <= M; ++m) {
-      // f = H_m E^m, g = H_m conj(E)^m from the four shared products
-      const double rr = hr * er, ii = hi * ei, ri = hr * ei, ir2 = hi * er;
-      const double fr = rr - ii, fi = ri + ir2;
-      const double gr = rr + ii, gi = ir2 - ri;
-      ar[M + m] = fma(w.x, fr, fma(-w.y, fi, ar[M + m]));
-      ai[M + m] = fma(w.x, fi, fma(w.y, fr, ai[M + m]));
-      // f_{-m} = (-1)^m H_m conj(E)^m
-      const double s = (m & 1) ? -1.0 : 1.0;
-      ar[M - m] = fma(s * w.x, gr, fma(-s * w.y, gi, ar[M - m]));
-      ai[M - m] = fma(s * w.x, gi, fma(s * w.y, gr, ai[M - m]));
-      if (m < M) {
-        // H_{m+1} = (2m/z) H_m - H_{m-1};  E^{m+1} = E^m E
-        const double t = 2.0 * m * iz;
-        const double nr = fma(t, hr, -hpr), ni = fma(t, hi, -hpi);
-        hpr = hr;
-        hpi = hi;
-        hr = nr;
-        hi = ni;
-        const double tr = fma(er, e1r, -ei * e1i);
-        ei = fma(er, e1i, ei * e1r);
-        er = tr;
-      }
-    }
-  }
-  if (valid) {
-#pragma unroll
-    for (int m = 0; m <= 2 * M; ++m)
-      partial[((size_t)sp * (2 * M + 1) + m) * Mc + ci] = make_double2(ar[m], ai[m]);
-  }
+  const double inv_k = 1.0 / k, sg = half ? -1.0 : 1.0;
+  const double2* __restrict__ qD = q + (KIND == 3 ? (size_t)N : 0);
+  CoefSums<P, KIND> A;
+  coef_zero<P, KIND>(A);
+  for (int j = j0; j < j1; ++j)
+    coef_pair<P, KIND>(geo[j], q[j], qD[j], c.cx, c.cy, k, inv_k, sg, A);
+  if (valid) coef_store<P, KIND>(A, sp, half, ci, Mc, partial);
 }
 
-// coef[kk][ci][l + p] from the split sums: S straight (a_l), D by the ladder
-// (k/2)(alpha_{l-1} - beta_{l+1}); pS: [n_sp][2p+1][Mc], pa, pb: [n_sp][2p+3][Mc]
+// The sums over the sources of panels near the center's; a wave has the 16 centers of one panel
+// and side, four lanes each, and of each near panel the sources 4 sp + (0..3) + 4 n_sp i (whole
+// panels dealt to the splits left some with twice the work).  Bound by FP64 issue and its
+// latency at two waves a SIMD: 213 VGPRs at p = 12, S + D; 335 us for 256 panels, 370 + 184 us
+// as one pass per weight over both signs.
+template <int P, int KIND>
+__global__ __launch_bounds__(256) void k_coef_near(FarBlocks B, const double* __restrict__ ro,
+                                                   int n_sp, double2* __restrict__ partial) {
+  int b;
+  const FarItem& it = *far_item(B, blockIdx.x, &b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int gw = b * 4 + wave;
+  const int half = gw & 1;
+  const int sp = (gw >> 1) % n_sp, row = (gw >> 1) / n_sp;
+  const int si = row / it.P, m = row - si * it.P;
+  if (si >= it.n_sides) return;
+  const int ci = si * it.T + m * kQ + (lane & 15);
+  const CenterRec c = reinterpret_cast<const CenterRec*>(ro + it.ctr)[ci];
+  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
+  const double2* __restrict__ q = reinterpret_cast<const double2*>(ro + it.dens);
+  const double2* __restrict__ qD = q + (KIND == 3 ? (size_t)it.N : 0);
+  const double k = it.k, inv_k = 1.0 / k, sg = half ? -1.0 : 1.0;
+  const int qs = it.qs;
+  CoefSums<P, KIND> A;
+  coef_zero<P, KIND>(A);
+  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
+    for (int s = 4 * sp + (lane >> 4); s < qs; s += 4 * n_sp) {
+      const int j = pan * qs + s;
+      coef_pair<P, KIND>(geo[j], q[j], qD[j], c.cx, c.cy, k, inv_k, sg, A);
+    }
+  });
+#pragma unroll
+  for (int l = 0; l <= P; ++l)
+#pragma unroll
+    for (int off = 16; off <= 32; off *= 2) {
+      if (KIND & 1) {
+        A.sr[l] += __shfl_xor(A.sr[l], off);
+        A.si[l] += __shfl_xor(A.si[l], off);
+      }
+      if (KIND & 2) {
+        A.dr[l] += __shfl_xor(A.dr[l], off);
+        A.di[l] += __shfl_xor(A.di[l], off);
+      }
+    }
+  if (lane < kQ) coef_store<P, KIND>(A, sp, half, ci, it.Mc, partial);
+}
+
+// coef[kk][ci][l + p] from the split sums; far: added to the far sums that coef holds already.
+// A block has 16 centers of one kind: read by runs of centers, written by runs of orders.
 __global__ __launch_bounds__(256) void k_coef_finalize(int Mc, int p, int kind, int n_sp,
-                                                       double k,
-                                                       const double2* __restrict__ pS,
-                                                       const double2* __restrict__ pa,
-                                                       const double2* __restrict__ pb,
-                                                       double* __restrict__ coef) {
-  const int L = 2 * p + 1;
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int nk = kind == 3 ? 2 : 1;
-  if (e >= (long long)nk * Mc * L) return;
-  const int kk = (int)(e / ((long long)Mc * L));
-  const int rem = (int)(e - (long long)kk * Mc * L);
-  const int ci = rem / L, li = rem - ci * L;   // li = l + p
-  const bool isD = (kind == 2) || (kind == 3 && kk == 1);
-  double r = 0.0, im = 0.0;
-  if (!isD) {
-    for (int sp = 0; sp < n_sp; ++sp) {
-      const double2 v = pS[((size_t)sp * L + li) * Mc + ci];
-      r += v.x;
-      im += v.y;
-    }
-  } else {
-    const int LD = L + 2;   // orders -(p+1)..(p+1)
-    double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0;
-    for (int sp = 0; sp < n_sp; ++sp) {
-      // alpha_{l-1} at index (l - 1) + (p + 1) = li; beta_{l+1} at li + 2
-      const double2 a = pa[((size_t)sp * LD + li) * Mc + ci];
-      const double2 b = pb[((size_t)sp * LD + li + 2) * Mc + ci];
-      ar += a.x;
-      ai += a.y;
-      br += b.x;
-      bi += b.y;
-    }
-    r = 0.5 * k * (ar - br);
-    im = 0.5 * k * (ai - bi);
+                                                       double k, int far,
+                                                       const double2* __restrict__ partial,
+                                                       double2* __restrict__ coef) {
+  __shared__ double2 a[(2 * kPMax + 1) * 16];
+  const int nk = kind == 3 ? 2 : 1, L = 2 * p + 1;
+  const int kk = blockIdx.y, c0 = blockIdx.x * 16;
+  const double f = (kind & 2) && kk == nk - 1 ? 0.5 * k : 1.0;
+  for (int t = threadIdx.x; t < L * 16; t += blockDim.x) {
+    const int l = t / 16 - p, ci = c0 + t % 16;
+    double r = 0.0, im = 0.0;
+    if (ci < Mc)
+      for (int sp = 0; sp < n_sp; ++sp)
+        for (int half = l < 0 ? 1 : 0; half <= (l <= 0 ? 1 : 0); ++half) {
+          const double2 v =
+              partial[(((size_t)(sp * 2 + half) * nk + kk) * (p + 1) + abs(l)) * Mc + ci];
+          r += v.x;
+          im += v.y;
+        }
+    a[t % 16 * L + t / 16] = make_double2(f * r, f * im);
   }
-  const size_t o = ((size_t)kk * Mc + ci) * L + li;
-  coef[2 * o] = r;
-  coef[2 * o + 1] = im;
+  __syncthreads();
+  double2* o = coef + ((size_t)kk * Mc + c0) * L;
+  const int n = min(16, Mc - c0) * L;
+  for (int t = threadIdx.x; t < n; t += blockDim.x) {
+    const double2 v = a[t], w = far ? o[t] : make_double2(0.0, 0.0);
+    o[t] = make_double2(w.x + v.x, w.y + v.y);
+  }
 }
 
 // ctr_xy [Mc][2], ctr_r [Mc] from the center records (either may be NULL)
@@ -213,6 +292,10 @@ __global__ __launch_bounds__(256) void k_evaluate_expansions(
 // the nearest center with |x_t - c| <= slack R_c, ties to the lower index; -1 if none.
 // Every product and sum is rounded on its own (no contraction), so any IEEE double
 // evaluation of the same formula takes the same decisions.
+// A wave has NT targets: each center that it reads serves all of them.  Bound by those reads
+// (24 bytes a center and wave): 20001 targets and 8192 centers take 77 us, 182 us with one
+// target a wave.
+template <int NT>
 __global__ __launch_bounds__(256) void k_assign_centers(int Mc, const double* __restrict__ ctr_xy,
                                                         const double* __restrict__ ctr_r,
                                                         double slack, int n_t,
@@ -221,93 +304,113 @@ __global__ __launch_bounds__(256) void k_assign_centers(int Mc, const double* __
 #pragma clang fp contract(off)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 4 + wave;
-  if (t >= n_t) return;
-  const double tx = tgt[2 * (size_t)t], ty = tgt[2 * (size_t)t + 1];
-  double best = INFINITY;
-  int bi = -1;
+  const int t0 = (blockIdx.x * 4 + wave) * NT;
+  if (t0 >= n_t) return;
+  double tx[NT], ty[NT], best[NT];
+  int bi[NT];
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    const size_t t = min(t0 + u, n_t - 1);
+    tx[u] = tgt[2 * t];
+    ty[u] = tgt[2 * t + 1];
+    best[u] = INFINITY;
+    bi[u] = -1;
+  }
   for (int i = lane; i < Mc; i += kWave) {
-    const double dx = tx - ctr_xy[2 * (size_t)i], dy = ty - ctr_xy[2 * (size_t)i + 1];
-    const double d2 = dx * dx + dy * dy;
+    const double cx = ctr_xy[2 * (size_t)i], cy = ctr_xy[2 * (size_t)i + 1];
     const double rr = slack * ctr_r[i];
-    if (d2 <= rr * rr && d2 < best) {   // lanes visit their centers in increasing order
-      best = d2;
-      bi = i;
+    const double r2 = rr * rr;
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      const double dx = tx[u] - cx, dy = ty[u] - cy;
+      const double d2 = dx * dx + dy * dy;
+      if (d2 <= r2 && d2 < best[u]) {   // lanes visit their centers in increasing order
+        best[u] = d2;
+        bi[u] = i;
+      }
     }
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    const double ob = __shfl_xor(best, off);
-    const int oi = __shfl_xor(bi, off);
-    if (ob < best || (ob == best && oi >= 0 && (bi < 0 || oi < bi))) {
-      best = ob;
-      bi = oi;
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    for (int off = 32; off > 0; off >>= 1) {
+      const double ob = __shfl_xor(best[u], off);
+      const int oi = __shfl_xor(bi[u], off);
+      if (ob < best[u] || (ob == best[u] && oi >= 0 && (bi[u] < 0 || oi < bi[u]))) {
+        best[u] = ob;
+        bi[u] = oi;
+      }
     }
+    if (lane == 0 && t0 + u < n_t) idx[t0 + u] = bi[u];
   }
-  if (lane == 0) idx[t] = bi;
 }
 
 namespace {
 
-template <int M>
-hipError_t launch_coef_m(const double4* geo, const double2* q, int N, const CenterRec* ctr,
-                         int Mc, int n_cb, int n_sp, int src_per_split, double k,
+template <int P, int KIND>
+hipError_t launch_coef_k(const Dims& d, bool far, const FarItem* dev, const double* ws,
+                         const double4* geo, const double2* q, const CenterRec* ctr, int n_sp,
                          double2* partial, hipStream_t s) {
-  const long waves = (long)n_cb * n_sp;
-  hipLaunchKernelGGL((k_coef<M>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, geo, q, N,
-                     ctr, Mc, n_cb, n_sp, src_per_split, k, partial);
+  if (far) {
+    const long waves = 2L * d.P * d.n_sides * n_sp;
+    hipLaunchKernelGGL((k_coef_near<P, KIND>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s,
+                       FarBlocks{dev, nullptr, 1}, ws, n_sp, partial);
+  } else {
+    const int n_cb = (d.Mc + kWave - 1) / kWave;
+    const long waves = 2L * n_cb * n_sp;
+    hipLaunchKernelGGL((k_coef<P, KIND>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, geo,
+                       q, d.N, ctr, d.Mc, n_cb, n_sp, (d.N + n_sp - 1) / n_sp, d.k, partial);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_coef(int M, const double4* geo, const double2* q, int N, const CenterRec* ctr,
-                       int Mc, int n_cb, int n_sp, int src_per_split, double k,
+template <int P>
+hipError_t launch_coef_p(const Dims& d, bool far, const FarItem* dev, const double* ws,
+                         const double4* geo, const double2* q, const CenterRec* ctr, int n_sp,
+                         double2* partial, hipStream_t s) {
+  if (d.kind == 1) return launch_coef_k<P, 1>(d, far, dev, ws, geo, q, ctr, n_sp, partial, s);
+  if (d.kind == 2) return launch_coef_k<P, 2>(d, far, dev, ws, geo, q, ctr, n_sp, partial, s);
+  return launch_coef_k<P, 3>(d, far, dev, ws, geo, q, ctr, n_sp, partial, s);
+}
+
+hipError_t launch_coef(const Dims& d, bool far, const FarItem* dev, const double* ws,
+                       const double4* geo, const double2* q, const CenterRec* ctr, int n_sp,
                        double2* partial, hipStream_t s) {
-  switch (M) {
-#define QBX_CASE(MM) \
-  case MM:           \
-    return launch_coef_m<MM>(geo, q, N, ctr, Mc, n_cb, n_sp, src_per_split, k, partial, s);
+  switch (d.p) {
+#define QBX_CASE(PP) \
+  case PP:           \
+    return launch_coef_p<PP>(d, far, dev, ws, geo, q, ctr, n_sp, partial, s);
     QBX_CASE(0) QBX_CASE(1) QBX_CASE(2) QBX_CASE(3) QBX_CASE(4) QBX_CASE(5) QBX_CASE(6)
     QBX_CASE(7) QBX_CASE(8) QBX_CASE(9) QBX_CASE(10) QBX_CASE(11) QBX_CASE(12) QBX_CASE(13)
     QBX_CASE(14) QBX_CASE(15) QBX_CASE(16) QBX_CASE(17) QBX_CASE(18) QBX_CASE(19) QBX_CASE(20)
-    QBX_CASE(21) QBX_CASE(22) QBX_CASE(23) QBX_CASE(24) QBX_CASE(25)
+    QBX_CASE(21) QBX_CASE(22) QBX_CASE(23) QBX_CASE(24)
 #undef QBX_CASE
     default:
       return hipErrorInvalidValue;
   }
 }
 
-// source splits of the coefficient pass: enough waves (64 centers each) to fill
-// the device about four times, at most 8 splits (the split sums take
-// n_sp x (2M + 1) x Mc x 16 bytes per weight)
-int coef_splits(const Dims& d) {
-  const int n_cb = (d.Mc + kWave - 1) / kWave;
-  int n_sp = (4096 + n_cb - 1) / n_cb;
-  if (n_sp > 8) n_sp = 8;
-  const int chunks = (d.N + kWave - 1) / kWave;
-  if (n_sp > chunks) n_sp = chunks;
-  return n_sp < 1 ? 1 : n_sp;
+// splits of the coefficient sums: enough waves (two signs; 64 centers each, or far a panel
+// and side) to fill the device about four times, at most 8 (the split sums take
+// n_sp x 2 x (p + 1) x Mc x 16 bytes per kind)
+int coef_splits(const Dims& d, bool far) {
+  const int n_cb = far ? d.P * d.n_sides : (d.Mc + kWave - 1) / kWave;
+  int n_sp = std::min(8, (2048 + n_cb - 1) / n_cb);
+  const int most = far ? (d.qs + 3) / 4 : (d.N + kWave - 1) / kWave;
+  return std::max(1, std::min(n_sp, most));
 }
 
 struct ExpLayout {
   Layout base;          // tables .. partial of make_forward_layout (partial unused)
-  size_t qd, pS, pa, pb, total;
+  size_t part, total;
 };
 
 ExpLayout make_expansion_layout(const Dims& d) {
   ExpLayout E;
-  E.base = make_forward_layout(d, false);
-  size_t o = E.base.total;
-  auto take = [&](size_t bytes) {
-    size_t at = o;
-    o = align256(o + bytes);
-    return at;
-  };
-  const size_t n_sp = (size_t)coef_splits(d);
-  const bool hasS = d.kind & 1, hasD = d.kind & 2;
-  E.qd = take(hasD ? sizeof(double2) * 2 * (size_t)d.N : 0);
-  E.pS = take(hasS ? sizeof(double2) * n_sp * (2 * d.p + 1) * d.Mc : 0);
-  E.pa = take(hasD ? sizeof(double2) * n_sp * (2 * d.p + 3) * d.Mc : 0);
-  E.pb = take(hasD ? sizeof(double2) * n_sp * (2 * d.p + 3) * d.Mc : 0);
-  E.total = o;
+  E.base = make_forward_layout(d, true);
+  // at any r and k, whichever way the sums are formed then
+  const size_t n_sp = std::max(coef_splits(d, false), coef_splits(d, true));
+  E.part = E.base.total;
+  E.total = align256(E.part + sizeof(double2) * n_sp * 2 * d.nk * (d.p + 1) * d.Mc);
   return E;
 }
 
@@ -344,41 +447,30 @@ int qbx_expansion_coefficients(const qbx_geometry* g, const double* density, dou
   if (ws_bytes < E.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, E.total);
   const Layout& L = E.base;
+  const bool far = far_applies(d);
+  FarItem it{};
+  if (far) it = far_item_of(d, L, false, true, false);
+  FarItem* dev = far ? at<FarItem>(ws, L.far) : nullptr;
   hipError_t e = launch_tables(d, at<double>(ws, L.tables), stream);
   if (e != hipSuccess) return device_fail(e, "tables kernel");
   e = launch_upsample(d, g->nodes, density, at<double>(ws, L.tables), at<double4>(ws, L.geo),
                       at<double2>(ws, L.dens), at<double>(ws, L.wgt), at<double>(ws, L.h),
-                      at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab), stream);
+                      at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab), stream,
+                      far ? &it : nullptr, dev);
   if (e != hipSuccess) return device_fail(e, "upsample kernel");
-  const int n_cb = (d.Mc + kWave - 1) / kWave;
-  const int n_sp = coef_splits(d);
-  const int per = (d.N + n_sp - 1) / n_sp;
-  const double4* geo = at<double4>(ws, L.geo);
+  if (far) {
+    e = far_fields(far_single(it, dev), g->nodes, static_cast<double*>(ws), true, false, 3, false,
+                   false, true, stream, reinterpret_cast<double2*>(coef));
+    if (e != hipSuccess) return device_fail(e, "panel expansion kernels");
+  }
+  const int n_sp = coef_splits(d, far);
   const CenterRec* ctr = at<CenterRec>(ws, L.ctr);
-  const double2* dens = at<double2>(ws, L.dens);
-  if (d.kind & 1) {
-    e = launch_coef(d.p, geo, dens, d.N, ctr, d.Mc, n_cb, n_sp, per, d.k, at<double2>(ws, E.pS),
-                    stream);
-    if (e != hipSuccess) return device_fail(e, "coefficient kernel (S)");
-  }
-  if (d.kind & 2) {
-    const double2* densD = dens + ((d.kind & 1) ? (size_t)d.N : 0);
-    double2* qd = at<double2>(ws, E.qd);
-    hipLaunchKernelGGL(k_dlp_weights, dim3((d.N + 255) / 256), dim3(256), 0, stream, d.N, geo,
-                       densD, qd);
-    e = hipGetLastError();
-    if (e == hipSuccess)
-      e = launch_coef(d.p + 1, geo, qd, d.N, ctr, d.Mc, n_cb, n_sp, per, d.k,
-                      at<double2>(ws, E.pa), stream);
-    if (e == hipSuccess)
-      e = launch_coef(d.p + 1, geo, qd + d.N, d.N, ctr, d.Mc, n_cb, n_sp, per, d.k,
-                      at<double2>(ws, E.pb), stream);
-    if (e != hipSuccess) return device_fail(e, "coefficient kernels (D)");
-  }
-  const long long n = (long long)d.nk * d.Mc * (2 * d.p + 1);
-  hipLaunchKernelGGL(k_coef_finalize, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                     d.Mc, d.p, d.kind, n_sp, d.k, at<double2>(ws, E.pS), at<double2>(ws, E.pa),
-                     at<double2>(ws, E.pb), coef);
+  e = launch_coef(d, far, dev, static_cast<double*>(ws), at<double4>(ws, L.geo),
+                  at<double2>(ws, L.dens), ctr, n_sp, at<double2>(ws, E.part), stream);
+  if (e != hipSuccess) return device_fail(e, "coefficient kernel");
+  hipLaunchKernelGGL(k_coef_finalize, dim3((d.Mc + 15) / 16, d.nk), dim3(256), 0, stream, d.Mc,
+                     d.p, d.kind, n_sp, d.k, far ? 1 : 0, at<double2>(ws, E.part),
+                     reinterpret_cast<double2*>(coef));
   if (ctr_xy || ctr_r)
     hipLaunchKernelGGL(k_center_out, dim3((d.Mc + 255) / 256), dim3(256), 0, stream, d.Mc, ctr,
                        ctr_xy, ctr_r);
@@ -416,8 +508,15 @@ int qbx_assign_centers(int n_ctr, const double* ctr_xy, const double* ctr_r, int
   if (n_targets == 0) return QBX_OK;
   if (!ctr_xy || !ctr_r || !target_xy || !center_index)
     return fail(QBX_EINVAL, "NULL array argument");
-  hipLaunchKernelGGL(k_assign_centers, dim3((unsigned)(((long)n_targets + 3) / 4)), dim3(256), 0,
-                     stream, n_ctr, ctr_xy, ctr_r, slack, n_targets, target_xy, center_index);
+  // four targets a wave once that leaves enough waves to fill the device
+  const int nt = n_targets >= 4096 ? 4 : 1;
+  const dim3 grid((unsigned)(((long)n_targets + 4 * nt - 1) / (4 * nt)));
+  if (nt == 4)
+    hipLaunchKernelGGL(k_assign_centers<4>, grid, dim3(256), 0, stream, n_ctr, ctr_xy, ctr_r,
+                       slack, n_targets, target_xy, center_index);
+  else
+    hipLaunchKernelGGL(k_assign_centers<1>, grid, dim3(256), 0, stream, n_ctr, ctr_xy, ctr_r,
+                       slack, n_targets, target_xy, center_index);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? QBX_OK : device_fail(e, "center assignment kernel");
 }

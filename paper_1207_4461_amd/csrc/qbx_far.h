@@ -162,7 +162,8 @@ FarPlan far_single(const FarItem& it, const FarItem* dev);
 // what the caller wants of them: values or sums at the targets (eval: the mode of
 // launch_far_eval, or -1), gradients at the sources (src; geom: position and normal too)
 hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fwd, bool bwd,
-                      int eval, bool src, bool geom, bool lists, hipStream_t s);
+                      int eval, bool src, bool geom, bool lists, hipStream_t s,
+                      double2* coef = nullptr);
 // the offsets of an item's far arrays from take(bytes) (returning a byte offset), with
 // bwd those of the adjoint too; V, n0, n1 are then set per call (far_shape).  n_items: the
 // items that share the call's launches.
@@ -177,8 +178,10 @@ hipError_t launch_far_lists(const FarBlocks& B, int blocks, double* ws, hipStrea
 hipError_t launch_far_p2m(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
 hipError_t launch_far_m2l(bool groups, const FarBlocks& B, int blocks, double* ws, hipStream_t s);
 hipError_t launch_far_lsum(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
-// mode 0 values, 1 target derivatives, 2 center gradients contracted with G
-hipError_t launch_far_eval(int mode, const FarBlocks& B, int blocks, double* ws, hipStream_t s);
+// mode 0 values, 1 target derivatives, 2 center gradients contracted with G, 3 the coefficients
+// of the centers (into coef)
+hipError_t launch_far_eval(int mode, const FarBlocks& B, int blocks, double* ws, double2* coef,
+                           hipStream_t s);
 hipError_t launch_far_t(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
 hipError_t launch_far_rows(const FarBlocks& B, int blocks, double* ws, hipStream_t s);
 hipError_t launch_far_src(const FarBlocks& B, int blocks, double* ws, bool geom, hipStream_t s);

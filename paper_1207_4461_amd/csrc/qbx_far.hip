@@ -597,14 +597,16 @@ __device__ __forceinline__ double2 cpow_int(double2 z, int n) {   // |z| = 1
 // W_n = J_n(k R) e^{i n theta}, |n| <= p, into fu[kk][ci].  MODE 1: per kind the sums of
 // the target derivatives F_R, F_theta (fu[kk][ci][2]); for points the gradient itself.
 // MODE 2: the four center gradients contracted with G over the kinds (fc[ci]): Re of
-// K_R, K_theta and grad_v K.  With tau = |tau| e^{i beta},
+// K_R, K_theta and grad_v K.  MODE 3: the coefficients themselves, coef[kk][ci][m + p] = a_m,
+// |m| <= p.  With tau = |tau| e^{i beta},
 //   a_m e^{i m beta} = sum_l (L_l e^{i l beta}) J_{l-m}(k |tau|),
 // two real multiply-adds a term: the four waves share the orders m in blocks of kMB,
 // whose J_{l-m} slide through registers as l advances.
 constexpr int kMB = 6;
 template <int MODE>
 __global__ __launch_bounds__(256, 2) void k_far_eval(FarBlocks B, const double* __restrict__ ro,
-                                                  double* __restrict__ wo) {
+                                                     double* __restrict__ wo,
+                                                     double2* __restrict__ coef) {
   __shared__ double Jt[kFarJ + 1][kWave];
   __shared__ double2 LP[kFarW][kWave];
   int b;
@@ -620,7 +622,7 @@ __global__ __launch_bounds__(256, 2) void k_far_eval(FarBlocks B, const double* 
   const int ci = si * it.T + tc;
   const int m = tc / kQ;
   const int p = it.pt ? 0 : it.p;
-  const int pm = MODE == 0 ? p : p + 1;   // orders a_m that enter
+  const int pm = MODE == 0 || MODE == 3 ? p : p + 1;   // orders a_m that enter
   const FarTarget tg = far_target(it, ro, ci);
   constexpr int NO = MODE == 0 ? 1 : MODE == 1 ? 2 : 4;
   double2 o[2][2];            // MODE 0, 1: per kind
@@ -699,11 +701,19 @@ __global__ __launch_bounds__(256, 2) void k_far_eval(FarBlocks B, const double* 
             }
           }
         }
-        double2 zp = cpow_int(zt, m0);
+        const double2 zs = MODE == 3 ? conj2(eb) : zt;
+        double2 zp = cpow_int(zs, m0);
 #pragma unroll
         for (int i = 0; i < kMB; ++i) {
           const int mm = m0 + i;
-          if (mm <= pm) {
+          if (MODE == 3) {
+            if (mm <= pm && valid) {
+              const double2 a = cmul(make_double2(ar[i], ai[i]), zp);   // a_m
+              double2* q = coef + ((size_t)vv * Mt + ci) * (2 * p + 1) + mm + p;
+              const double2 f = lev ? *q : make_double2(0.0, 0.0);
+              *q = make_double2(f.x + a.x, f.y + a.y);
+            }
+          } else if (mm <= pm) {
             const double2 a = cmul(make_double2(ar[i], ai[i]), zp);   // a_m e^{i m theta}
             const double jm = far_tj(tg, mm, p);
             if (MODE == 0) {
@@ -738,11 +748,12 @@ __global__ __launch_bounds__(256, 2) void k_far_eval(FarBlocks B, const double* 
               }
             }
           }
-          zp = cmul(zp, zt);
+          zp = cmul(zp, zs);
         }
       }
     }
   }
+  if (MODE == 3) return;
   // add the four waves (in wave order) through LDS
   __syncthreads();
   double* red = &LP[0][0].x;   // [4][8][64]
@@ -1140,13 +1151,17 @@ hipError_t launch_far_lsum(const FarBlocks& B, int blocks, double* ws, hipStream
   hipLaunchKernelGGL(k_far_lsum, dim3(blocks), dim3(256), 0, s, B, ws, ws);
   return hipGetLastError();
 }
-hipError_t launch_far_eval(int mode, const FarBlocks& B, int blocks, double* ws, hipStream_t s) {
+hipError_t launch_far_eval(int mode, const FarBlocks& B, int blocks, double* ws, double2* coef,
+                           hipStream_t s) {
+  const dim3 grid(blocks), block(256);
   if (mode == 0)
-    hipLaunchKernelGGL(k_far_eval<0>, dim3(blocks), dim3(256), 0, s, B, ws, ws);
+    hipLaunchKernelGGL(k_far_eval<0>, grid, block, 0, s, B, ws, ws, coef);
   else if (mode == 1)
-    hipLaunchKernelGGL(k_far_eval<1>, dim3(blocks), dim3(256), 0, s, B, ws, ws);
+    hipLaunchKernelGGL(k_far_eval<1>, grid, block, 0, s, B, ws, ws, coef);
+  else if (mode == 2)
+    hipLaunchKernelGGL(k_far_eval<2>, grid, block, 0, s, B, ws, ws, coef);
   else
-    hipLaunchKernelGGL(k_far_eval<2>, dim3(blocks), dim3(256), 0, s, B, ws, ws);
+    hipLaunchKernelGGL(k_far_eval<3>, grid, block, 0, s, B, ws, ws, coef);
   return hipGetLastError();
 }
 hipError_t launch_far_t(const FarBlocks& B, int blocks, double* ws, hipStream_t s) {
@@ -1179,7 +1194,7 @@ void far_shape(FarItem* it, bool fwd, bool bwd) {
 }
 
 hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fwd, bool bwd,
-                      int eval, bool src, bool geom, bool lists, hipStream_t s) {
+                      int eval, bool src, bool geom, bool lists, hipStream_t s, double2* coef) {
   hipError_t e = launch_far_recs(P.at[kStepClusters], P.blocks[kStepClusters], nodes, ws, s);
   if (e == hipSuccess && lists) e = launch_far_lists(P.at[kStepLists], P.blocks[kStepLists], ws, s);
   if (e == hipSuccess && fwd)
@@ -1191,7 +1206,7 @@ hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fw
     e = launch_far_m2l(true, P.at[kStepM2LGroups], P.blocks[kStepM2LGroups], ws, s);
   if (e == hipSuccess) e = launch_far_lsum(P.at[kStepSum], P.blocks[kStepSum], ws, s);
   if (e == hipSuccess && eval >= 0)
-    e = launch_far_eval(eval, P.at[kStepTargets], P.blocks[kStepTargets], ws, s);
+    e = launch_far_eval(eval, P.at[kStepTargets], P.blocks[kStepTargets], ws, coef, s);
   if (e == hipSuccess && src)
     e = launch_far_src(P.at[kStepSources], P.blocks[kStepSources], ws, geom, s);
   return e;

@@ -151,6 +151,9 @@ Layout make_forward_layout(const Dims& d, bool far);
 // tables, source grid and centers, then the plain forward and its finalize
 // into out, with the arrays of L (make_layout or make_forward_layout) in ws;
 // timed: bracket the pair kernel with the kernel timer's events when it is on
+// the item of a call's far sums on layout L (full: make_layout's offsets, else
+// make_forward_layout's); fwd, bwd as in far_fields
+FarItem far_item_of(const Dims& d, const Layout& L, bool full, bool fwd, bool bwd);
 int run_forward(const Dims& d, const Layout& L, const double* nodes, const double* density,
                 double* out, void* ws, hipStream_t stream, bool timed = true);
 
@@ -253,6 +256,10 @@ hipError_t launch_adjoint_src(const Dims& d, const double4* geo, const double2* 
                               const CenterRec* ctr, const double* jtab, const double2* G,
                               double2* partial, hipStream_t s);
 hipError_t launch_make_G(const Dims& d, const double* cot, double2* G, hipStream_t s);
+// the fused adjoint's tiles alone: source sums spartial (n_cb parts) and center sums cpart
+hipError_t launch_fused_tiles(const Dims& d, const double4* geo, const double2* dens,
+                              const CenterRec* ctr, const double* jtab, const double2* G,
+                              double2* spartial, double* cpart, hipStream_t s);
 // adjoint without a tape: one pass over the pairs for both gradient sides
 hipError_t launch_adjoint_fused(const Dims& d, const double* nodes, const double* density,
                                 const double* tables, const double4* geo, const double2* dens,

@@ -120,3 +120,83 @@ def test_split_groups_match_oracle():
     ref = np.asarray(O.layer_potential_split(pb.nodes, pb.density, *args, gamma=6.0, targets=idx))
     got = u.cpu().numpy()[:, :, idx]
     assert np.abs(got - ref).max() / np.abs(ref).max() < 1e-11
+
+
+# coefficients: around the threshold, rows that are no multiple of a wave's, a source count that
+# the splits do not divide, smallest and largest order
+EXPANSIONS = [
+    dict(P=95, k=9.0, p=5, side=0, kind=3, os=1),
+    dict(P=96, k=9.0, p=0, side=0, kind=2, os=1),
+    dict(P=97, k=14.0, p=12, side=0, kind=3, os=1),
+    dict(P=98, k=6.0, p=24, side=-1, kind=1, os=1),
+    dict(P=99, k=20.0, p=3, side=1, kind=1, os=3),
+]
+
+
+@pytest.mark.parametrize("c", EXPANSIONS, ids=lambda c: "P{P}-p{p}-s{side}-{kind}-o{os}".format(**c))
+def test_far_coefficients(c):
+    """Stored expansions against the oracle's, to the bars of expansion_bars.py."""
+    from expansion_bars import check_coefficients
+    from oracle import qbx_oracle as O
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), c["P"], c["k"], c["p"], c["side"],
+                        c["kind"], 17, oversample=c["os"])
+    nodes, dens = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (pb.nodes, pb.density))
+    args = (pb.k, pb.p, pb.r, pb.oversample, pb.side, pb.kind)
+    sel = np.unique(np.r_[0, pb.n_centers - 1,
+                          np.random.default_rng(9).choice(pb.n_centers, 96, replace=False)])
+    ra, rC, rR = (t.numpy() for t in O.expansion_coefficients(pb.nodes, pb.density, *args,
+                                                              centers=sel))
+    a, C, _ = (t.cpu().numpy() for t in qbx.expansion_coefficients(nodes, dens, *args))
+    a, C = a[:, sel], C[sel]
+    gap = max(float(np.hypot(*(C - rC).T).max()), 4 * np.spacing(np.abs(rC).max()))
+    check_coefficients(a, ra, pb, rC, rR, gap)
+
+
+def test_far_coefficients_of_groups():
+    """With groups of panels, each center's expansion at its own target is the one-sided limit."""
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), 321, 12.0, 8, 0, 3, 17, oversample=1)
+    nodes, dens = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (pb.nodes, pb.density))
+    args = (pb.k, pb.p, pb.r, pb.oversample, pb.side, pb.kind)
+    a, C, _ = qbx.expansion_coefficients(nodes, dens, *args)
+    t = nodes.reshape(-1, 2).repeat(2, 1)
+    idx = torch.arange(len(t), dtype=torch.int32, device="cuda")
+    u = qbx.evaluate_expansions(a, C, t, idx, pb.k, pb.p, pb.kind)   # [kind][side and target]
+    ref = qbx.layer_potential(nodes, dens, *args).transpose(0, 1).reshape(u.shape)
+    assert rel(u, ref) < 1e-12
+
+
+def test_assignment_of_many_targets():
+    """Four targets a wave (from 4096 on) give what one target a wave does."""
+    from paper_1207_4461_amd import qbx
+
+    rng = np.random.default_rng(3)
+    C = torch.from_numpy(rng.uniform(-1, 1, (777, 2))).cuda()
+    R = torch.from_numpy(rng.uniform(0.01, 0.06, 777)).cuda()
+    t = torch.from_numpy(rng.uniform(-1, 1, (4099, 2))).cuda()
+    t[5] = float("nan")
+    one = torch.cat([qbx.assign_centers(C, R, t[:2000]), qbx.assign_centers(C, R, t[2000:])])
+    assert int(one.max()) > 0 and int(one[5]) == -1
+    assert torch.equal(qbx.assign_centers(C, R, t), one)
+
+
+@pytest.mark.parametrize("n_src,n_ctr,p,kind", [(1, 1, 3, 1), (63, 65, 7, 2), (257, 130, 12, 3),
+                                                (1030, 7, 24, 3)])
+def test_explicit_fused_matches_tape(n_src, n_ctr, p, kind):
+    """Explicit adjoint: one pass for both sides (no tape) against the two passes."""
+    from paper_1207_4461_amd import qbx
+
+    ep = I.explicit_problem(seed=11, n_src=n_src, n_ctr=n_ctr, k=3.0, p=p, kind=kind)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    a = [d(v) for v in (ep.src_xy, ep.src_nu, ep.src_q, ep.ctr_xy, ep.ctr_r,
+                        np.exp(1j * ep.ctr_theta))]
+    cot = d(ep.cotangent)
+    tape = torch.empty(qbx.explicit_tape_bytes(n_ctr, kind), dtype=torch.uint8, device="cuda")
+    qbx.apply_explicit(*a, ep.k, p, kind, tape=tape)
+    two = qbx.apply_explicit_vjp(*a, cot, ep.k, p, kind, tape=tape)
+    one = qbx.apply_explicit_vjp(*a, cot, ep.k, p, kind)
+    for key in two:
+        assert rel(one[key], two[key]) < 1e-11, key
