@@ -72,17 +72,29 @@ __global__ __launch_bounds__(256) void k_explicit_source_grads(
     const double2* __restrict__ dens, const double2* __restrict__ partial,
     double* __restrict__ grad_q, double* __restrict__ grad_src_xy,
     double* __restrict__ grad_src_nu) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
+  // 64 sources a block; the parts are dealt to four waves and joined in order
+  __shared__ double2 joined[3][4][kWave];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = blockIdx.x * kWave + lane;
   const bool hasS = kind & 1, hasD = kind & 2;
   const int nk = hasS && hasD ? 2 : 1;
   const int NA = src_slots(kind);
   double s[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
-  for (int cs = 0; cs < n_csplit; ++cs)
+  if (j < N)
+    for (int cs = wave; cs < n_csplit; cs += 4)
+      for (int b = 0; b < NA; ++b) {
+        const double2 v = partial[((size_t)cs * NA + b) * N + j];
+        s[b][0] += v.x;
+        s[b][1] += v.y;
+      }
+  if (wave > 0)
+    for (int b = 0; b < NA; ++b) joined[wave - 1][b][lane] = make_double2(s[b][0], s[b][1]);
+  __syncthreads();
+  if (wave > 0 || j >= N) return;
+  for (int w = 0; w < 3; ++w)
     for (int b = 0; b < NA; ++b) {
-      const double2 v = partial[((size_t)cs * NA + b) * N + j];
-      s[b][0] += v.x;
-      s[b][1] += v.y;
+      s[b][0] += joined[w][b][lane].x;
+      s[b][1] += joined[w][b][lane].y;
     }
   if (grad_q) {
     for (int kk = 0; kk < nk; ++kk) {
@@ -133,6 +145,25 @@ __global__ __launch_bounds__(256) void k_explicit_center_grads(
   }
   if (grad_ctr_r) grad_ctr_r[i] = dR;
   if (grad_ctr_theta) grad_ctr_theta[i] = dt;
+}
+
+// the same from the fused tiles' sums over the n_sb source blocks, Re G sum q of (dK/dR,
+// dK/dtheta, grad_v K): cpart[sb][i][4]
+__global__ __launch_bounds__(256) void k_explicit_fused_center_grads(
+    int Mc, int n_sb, const double* __restrict__ cpart, double* __restrict__ grad_ctr_xy,
+    double* __restrict__ grad_ctr_r, double* __restrict__ grad_ctr_theta) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= Mc) return;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int sb = 0; sb < n_sb; ++sb)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) s[b] += cpart[((size_t)sb * Mc + i) * 4 + b];
+  if (grad_ctr_xy) {
+    grad_ctr_xy[2 * (size_t)i] = -s[2];
+    grad_ctr_xy[2 * (size_t)i + 1] = -s[3];
+  }
+  if (grad_ctr_r) grad_ctr_r[i] = s[0];
+  if (grad_ctr_theta) grad_ctr_theta[i] = s[1];
 }
 
 namespace {
@@ -294,7 +325,21 @@ int qbx_apply_explicit_adjoint(int n_src, const double* src_xy, const double* sr
   if (rc) return rc;
   hipError_t e = launch_make_G(d, cotangent, at<double2>(ws, L.G), stream);
   if (e != hipSuccess) return device_fail(e, "explicit cotangent kernel");
-  if (want_ctr) {
+  // both sides and no tape: one evaluation per pair serves both (10007 sources, 5003 centers,
+  // p = 12, S + D: the tape's pass 1.47 ms and the source pass 1.06 ms before)
+  const bool fused = want_src && want_ctr && !tape;
+  if (fused) {
+    e = launch_fused_tiles(d, at<double4>(ws, L.geo), at<double2>(ws, L.dens),
+                           at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab),
+                           at<double2>(ws, L.G), at<double2>(ws, L.spart),
+                           at<double>(ws, L.cpart), stream);
+    if (e != hipSuccess) return device_fail(e, "explicit fused adjoint pass");
+    hipLaunchKernelGGL(k_explicit_fused_center_grads, dim3((d.Mc + 255) / 256), dim3(256), 0,
+                       stream, d.Mc, d.n_sb, at<double>(ws, L.cpart), grad_ctr_xy, grad_ctr_r,
+                       grad_ctr_theta);
+    e = hipGetLastError();
+    if (e != hipSuccess) return device_fail(e, "explicit center gradient kernel");
+  } else if (want_ctr) {
     const double2* tp = reinterpret_cast<const double2*>(tape);
     if (!tp) {
       timer_begin(3, stream);
@@ -315,14 +360,16 @@ int qbx_apply_explicit_adjoint(int n_src, const double* src_xy, const double* sr
     if (e != hipSuccess) return device_fail(e, "explicit center gradient kernel");
   }
   if (want_src) {
-    timer_begin(1, stream);
-    e = launch_adjoint_src(d, at<double4>(ws, L.geo), at<double2>(ws, L.dens),
-                           at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab),
-                           at<double2>(ws, L.G), at<double2>(ws, L.spart), stream);
-    timer_end(1, stream);
-    if (e != hipSuccess) return device_fail(e, "explicit adjoint source pass");
-    hipLaunchKernelGGL(k_explicit_source_grads, dim3((d.N + 255) / 256), dim3(256), 0, stream,
-                       d.N, d.kind, d.n_csplit, at<double4>(ws, L.geo),
+    if (!fused) {
+      timer_begin(1, stream);
+      e = launch_adjoint_src(d, at<double4>(ws, L.geo), at<double2>(ws, L.dens),
+                             at<CenterRec>(ws, L.ctr), at<double>(ws, L.jtab),
+                             at<double2>(ws, L.G), at<double2>(ws, L.spart), stream);
+      timer_end(1, stream);
+      if (e != hipSuccess) return device_fail(e, "explicit adjoint source pass");
+    }
+    hipLaunchKernelGGL(k_explicit_source_grads, dim3((d.N + kWave - 1) / kWave), dim3(256), 0,
+                       stream, d.N, d.kind, fused ? d.n_cb : d.n_csplit, at<double4>(ws, L.geo),
                        at<double2>(ws, L.dens), at<double2>(ws, L.spart), grad_q, grad_src_xy,
                        grad_src_nu);
     e = hipGetLastError();
