@@ -147,6 +147,11 @@ int far_blocks(const FarItem& it, FarStep step);
 enum NearPass {
   kNearForward, kNearGradient, kNearSources, kNearCenterSums, kNearCenters, kNearDensity
 };
+// the near pairs of alpha S - D (two-sided averages) as matrices over the nodes of near
+// panels, mat[P][cap][16 nodes][16 targets]; item dev with near lists, both sides and kinds
+hipError_t launch_near_matrix(int p, const FarItem* dev, int n_panels, int cap, const double* V,
+                              const double* wgt, double2 alpha, double* ws, double2* mat,
+                              hipStream_t s);
 hipError_t launch_near(NearPass pass, int p, int kind, const FarBlocks& B, int blocks,
                        double* ws, double* out, hipStream_t s);
 

@@ -403,6 +403,91 @@ __global__ __launch_bounds__(256) void k_near_density(FarBlocks B, const double*
   }
 }
 
+#if QBX_NEAR_KIND == 3
+// Stored near pairs of the combined field alpha S - D, each the average of the two one-sided
+// limits: mat[(m cap + slot) 256 + 16 a + t], the weight of node a of the slot-th panel near
+// panel m in the potential at target t of m.  A block per (m, slot): the waves evaluate 4
+// targets each against 64 sources at a time, both sides' centers, then a thread per (t, a)
+// folds in the source weights and the interpolation V from the nodes.  Formed once per solve
+// (about 1.5 forward near passes), it turns a product's near pass into a read of 4 KB per
+// pair of near panels.
+template <int P>
+__global__ __launch_bounds__(256) void k_near_matrix(FarBlocks B, const double* __restrict__ ro,
+                                                     int cap, const double* __restrict__ V,
+                                                     const double* __restrict__ wgt, double2 alpha,
+                                                     double2* __restrict__ mat) {
+  __shared__ double2 c[kQ][kWave + 1];
+  const FarItem& it = *B.items;
+  const int m = blockIdx.x / cap, slot = blockIdx.x - m * cap;
+  const NearLists nl = near_lists(it, ro);
+  if (slot >= nl.count[m]) return;
+  const int pan = nl.list[(size_t)m * kNearCap + slot];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int t = threadIdx.x & 15, a = threadIdx.x >> 4;
+  const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
+  const CenterRec* __restrict__ ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
+  const double k = it.k, inv_k = 1.0 / k;
+  double2 acc = make_double2(0.0, 0.0);
+  for (int s0 = 0; s0 < it.qs; s0 += kWave) {
+    const int ns = min(kWave, it.qs - s0);
+    const int j = pan * it.qs + s0 + min(lane, ns - 1);
+    const double4 g = geo[j];
+    const double w = 0.125 * wgt[j];
+    for (int tt = 4 * wave; tt < 4 * wave + 4; ++tt) {
+      double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
+      for (int side = 0; side < 2; ++side) {
+        const int ci = side * it.T + m * kQ + tt;
+        const int z0 = opaque_zero();
+        const CenterRec* __restrict__ C = ctr + ci + z0;
+        const double ct = C->ct, st = C->st;
+        const double vx = g.x - C->cx, vy = g.y - C->cy;
+        const double rho2 = fma(vx, vx, vy * vy);
+        const double ir = rsqrt_refined(rho2);
+        const double cd = (ct * vx + st * vy) * ir;
+        const double sd = (st * vx - ct * vy) * ir;
+        const double cps = ct * g.z + st * g.w;
+        const double sps = st * g.z - ct * g.w;
+        double ar, ai, br, bi;
+        pair_kernel<P, 3>(k * (rho2 * ir), ir * inv_k, cd, sd, cps, sps,
+                          ro + it.jtab + (size_t)ci * it.NJ + z0, g_seed_table + z0, ar, ai, br,
+                          bi);
+        sr += ar;
+        si += ai;
+        dr += br;
+        di += bi;
+      }
+      // (i/8) w (alpha S - k D)
+      const double ur = fma(alpha.x, sr, fma(-alpha.y, si, -k * dr));
+      const double ui = fma(alpha.x, si, fma(alpha.y, sr, -k * di));
+      c[tt][lane] = make_double2(-w * ui, w * ur);
+    }
+    __syncthreads();
+    for (int q = 0; q < ns; ++q) {
+      const double v = V[(s0 + q) * kQ + a];
+      acc.x = fma(v, c[t][q].x, acc.x);
+      acc.y = fma(v, c[t][q].y, acc.y);
+    }
+    __syncthreads();
+  }
+  mat[(size_t)blockIdx.x * (kQ * kQ) + threadIdx.x] = acc;
+}
+
+template <int P>
+static hipError_t launch_near_matrix_p(const FarItem* dev, int n_panels, int cap, const double* V,
+                                       const double* wgt, double2 alpha, double* ws, double2* mat,
+                                       hipStream_t s) {
+  hipLaunchKernelGGL(k_near_matrix<P>, dim3((unsigned)n_panels * cap), dim3(256), 0, s,
+                     FarBlocks{dev, nullptr, 1}, ws, cap, V, wgt, alpha, mat);
+  return hipGetLastError();
+}
+hipError_t launch_near_matrix(int p, const FarItem* dev, int n_panels, int cap, const double* V,
+                              const double* wgt, double2 alpha, double* ws, double2* mat,
+                              hipStream_t s) {
+  QBX_P_SWITCH(p, launch_near_matrix_p, dev, n_panels, cap, V, wgt, alpha, ws, mat, s)
+}
+#endif
+
 template <int P, int KIND>
 static hipError_t launch_near_pk(NearPass pass, const FarBlocks& B, int blocks, double* ws,
                                  double* out, hipStream_t s) {

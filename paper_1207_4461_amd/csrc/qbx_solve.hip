@@ -9,7 +9,8 @@
 // error, while the average keeps it.  One matrix-vector product is therefore
 // one S+D call of the forward (qbx_layer_potential, or
 // qbx_layer_potential_split) for both sides, with the density sigma for both
-// kinds.
+// kinds; or, where panel expansions take the far pairs, its parts with what
+// does not change between the products of a solve formed once (store_near).
 //
 // As the paper does (after Bremer), the unknowns are tau = sqrt(w) sigma, w the
 // 16-point rule's weight at the node, so that the l2 product of the iteration
@@ -20,11 +21,13 @@
 // below, every reduction in a fixed order (the solve is deterministic).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <complex>
 #include <vector>
 
 #include "../../include/qbx.h"
+#include "qbx_far.h"
 #include "qbx_internal.h"
 
 namespace qbx {
@@ -232,7 +235,97 @@ __global__ __launch_bounds__(256) void k_zero(int n, double2* __restrict__ y) {
   if (t < n) y[t] = make_double2(0.0, 0.0);
 }
 
+// Products of a solve with the near pairs stored (plain call, panel expansions for the far
+// pairs).  Geometry, centers, near lists and the near pairs' weights depend on the contour
+// alone, so a solve forms them once; a product interpolates the density (k_stored_density),
+// forms the multipoles of S and D, joins them to those of alpha S - D (k_stored_rows: the two
+// averages share the density and are only needed in that combination), translates and
+// evaluates one field instead of two, and reads the near weights (k_stored_product).
+// 256 panels, p = 12: a product took 0.25 ms through the forward, 0.10 ms so.
+constexpr int kStoredNear = 24;   // near panels of a panel at most (13 at most shapes)
+
+// sigma = v / sw and, per source, w_j sigma interpolated from its panel's nodes (both kinds)
+__global__ __launch_bounds__(64) void k_stored_density(int N, int qs, const double2* __restrict__ v,
+                                                       const double* __restrict__ sw,
+                                                       const double* __restrict__ V,
+                                                       const double* __restrict__ wgt,
+                                                       double2* __restrict__ sigma,
+                                                       double2* __restrict__ dens) {
+  __shared__ double2 S[kQ];
+  const int m = blockIdx.x, tid = threadIdx.x;
+  if (tid < kQ) {
+    const int t = m * kQ + tid;
+    const double s = 1.0 / sw[t];
+    S[tid] = make_double2(v[t].x * s, v[t].y * s);
+    sigma[t] = S[tid];
+  }
+  __syncthreads();
+  for (int b = tid; b < qs; b += kWave) {
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int a = 0; a < kQ; ++a) {
+      const double c = V[b * kQ + a];
+      re = fma(c, S[a].x, re);
+      im = fma(c, S[a].y, im);
+    }
+    const size_t j = (size_t)m * qs + b;
+    const double w = wgt[j];
+    dens[j] = dens[N + j] = make_double2(w * re, w * im);
+  }
+}
+
+// rows[0][i] = alpha rows[0][i] - rows[1][i], panels then groups
+__global__ __launch_bounds__(256) void k_stored_rows(int n0, int n1, double2 alpha,
+                                                     double2* __restrict__ rows0,
+                                                     double2* __restrict__ rows1) {
+  int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n0 + n1) return;
+  double2* r = i < n0 ? rows0 : rows1;
+  const int n = i < n0 ? n0 : n1;
+  if (i >= n0) i -= n0;
+  const double2 a = cmul(alpha, r[i]), b = r[(size_t)n + i];
+  r[i] = make_double2(a.x - b.x, a.y - b.y);
+}
+
+// y = half v + sw (near + far): a block per panel, thread (t, a) sums node a's share of target
+// t over the near panels; far from the two sides' sums fu.  Bound by the weights' read (54 KB
+// a panel at 13 near panels).
+__global__ __launch_bounds__(256) void k_stored_product(
+    int T, const int* __restrict__ ncount, const int* __restrict__ nlist,
+    const double2* __restrict__ mat, const double2* __restrict__ sigma,
+    const double2* __restrict__ fu, const double2* __restrict__ v, const double* __restrict__ sw,
+    double half, double2* __restrict__ y) {
+  __shared__ int list[kStoredNear];
+  __shared__ double2 part[kQ][kQ];
+  const int m = blockIdx.x, tid = threadIdx.x, a = tid >> 4;
+  const int cnt = min(ncount[m], kStoredNear);
+  if (tid < cnt) list[tid] = nlist[(size_t)m * kNearCap + tid];
+  __syncthreads();
+  const double2* __restrict__ M = mat + (size_t)m * kStoredNear * (kQ * kQ) + tid;
+  double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+  for (int i = 0; i < cnt; ++i) {
+    const double2 w = M[(size_t)i * (kQ * kQ)], d = sigma[list[i] * kQ + a];
+    s.x = fma(w.x, d.x, fma(-w.y, d.y, s.x));
+    s.y = fma(w.x, d.y, fma(w.y, d.x, s.y));
+  }
+  part[a][tid & 15] = s;
+  __syncthreads();
+  if (tid < kQ) {
+    s = part[0][tid];
+    for (int b = 1; b < kQ; ++b) {
+      s.x += part[b][tid].x;
+      s.y += part[b][tid].y;
+    }
+    const int t = m * kQ + tid;
+    const double2 f = fu[t], g = fu[T + t];   // (i/8)(both sides)
+    const double ur = fma(-0.125, f.y + g.y, s.x), ui = fma(0.125, f.x + g.x, s.y);
+    y[t] = make_double2(fma(half, v[t].x, sw[t] * ur), fma(half, v[t].y, sw[t] * ui));
+  }
+}
+
 struct SolveLayout {
+  size_t item, mat;   // the stored products' item and near weights
   size_t fws, fws_bytes, tables, sw, dens, out, V, w, b, x, partial, h, total;
 };
 
@@ -257,6 +350,9 @@ static SolveLayout make_solve_layout(const Dims& d, int restart) {
   L.x = take(sizeof(double2) * T);
   L.partial = take(sizeof(double2) * ((T + kDotSlice - 1) / kDotSlice) * (size_t)(restart + 1));
   L.h = take(sizeof(double2) * (2 * (size_t)restart + 3));
+  const bool stored = d.P >= kFarMinPanels;
+  L.item = take(stored ? sizeof(FarItem) : 0);
+  L.mat = take(stored ? sizeof(double2) * kQ * kQ * kStoredNear * (size_t)d.P : 0);
   L.total = o;
   return L;
 }
@@ -274,6 +370,9 @@ struct Gmres {
   double2 alpha;
   bool adjoint;    // products by A^H instead of A
   int T, grid;
+  bool stored = false;    // products by stored_product
+  Layout fl;              // the forward's workspace
+  FarItem sd, joined;     // its item, and the one with the single field alpha S - D
 
   template <typename X>
   X* at(size_t off) const { return reinterpret_cast<X*>(ws + off); }
@@ -284,7 +383,78 @@ struct Gmres {
   }
   // y = W^{1/2} (-+ 1/2 + alpha S - D) W^{-1/2} v, or for the adjoint system
   // y = W^{-1/2} (-+ 1/2 + conj(alpha) S^H - D^H) W^{1/2} v
+  // Forms what stored products need, unless a panel has too many near panels for it (then
+  // the products stay with the forward).
+  int store_near() {
+    char* fw = ws + L.fws;
+    double* w = reinterpret_cast<double*>(fw);
+    fl = make_layout(d);
+    sd = far_item_of(d, fl, true, true, false);
+    joined = sd;
+    joined.nk = joined.kind = 1;
+    far_shape(&joined, true, false);
+    FarItem* dev = reinterpret_cast<FarItem*>(fw + fl.far);
+    hipLaunchKernelGGL(k_zero, dim3((2 * T + 255) / 256), dim3(256), 0, s, 2 * T,
+                       at<double2>(L.dens));
+    double* tab = reinterpret_cast<double*>(fw + fl.tables);
+    hipError_t e = launch_tables(d, tab, s);
+    if (e == hipSuccess)
+      e = launch_upsample(d, g->nodes, at<double>(L.dens), tab,
+                          reinterpret_cast<double4*>(fw + fl.geo),
+                          reinterpret_cast<double2*>(fw + fl.dens),
+                          reinterpret_cast<double*>(fw + fl.wgt),
+                          reinterpret_cast<double*>(fw + fl.h),
+                          reinterpret_cast<CenterRec*>(fw + fl.ctr),
+                          reinterpret_cast<double*>(fw + fl.jtab), s, &sd, dev);
+    const FarPlan P = far_single(sd, dev);
+    if (e == hipSuccess)
+      e = launch_far_recs(P.at[kStepClusters], P.blocks[kStepClusters], g->nodes, w, s);
+    if (e == hipSuccess) e = launch_far_lists(P.at[kStepLists], P.blocks[kStepLists], w, s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(at<FarItem>(L.item), &joined, sizeof(FarItem), hipMemcpyHostToDevice, s);
+    std::vector<int> count(d.P);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(count.data(), w + sd.ncount, sizeof(int) * d.P, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return check(e, "solve near lists");
+    for (int c : count)
+      if (c > kStoredNear) return QBX_OK;
+    stored = true;
+    return check(launch_near_matrix(p, dev, d.P, kStoredNear, tab + table_layout(d.qs).V,
+                                    reinterpret_cast<double*>(fw + fl.wgt), alpha, w,
+                                    at<double2>(L.mat), s),
+                 "solve near weights");
+  }
+  int stored_product(const double2* v, double2* y) const {
+    char* fw = ws + L.fws;
+    double* w = reinterpret_cast<double*>(fw);
+    const double* V = w + fl.tables / sizeof(double) + table_layout(d.qs).V;
+    hipLaunchKernelGGL(k_stored_density, dim3(d.P), dim3(kWave), 0, s, d.N, d.qs, v,
+                       at<double>(L.sw), V, w + fl.wgt / sizeof(double), at<double2>(L.dens),
+                       reinterpret_cast<double2*>(fw + fl.dens));
+    const FarPlan P = far_single(sd, reinterpret_cast<FarItem*>(fw + fl.far));
+    const FarPlan J = far_single(joined, at<FarItem>(L.item));
+    hipError_t e = launch_far_p2m(P.at[kStepClusters], P.blocks[kStepClusters], w, s);
+    const int n0 = 2 * kFarW * sd.P, n1 = 2 * kFarW * sd.C1;
+    hipLaunchKernelGGL(k_stored_rows, dim3((n0 + n1 + 255) / 256), dim3(256), 0, s, n0, n1, alpha,
+                       reinterpret_cast<double2*>(w + sd.rows0),
+                       reinterpret_cast<double2*>(w + sd.rows1));
+    if (e == hipSuccess) e = launch_far_m2l(false, J.at[kStepM2L], J.blocks[kStepM2L], w, s);
+    if (e == hipSuccess && J.blocks[kStepM2LGroups] > 0)
+      e = launch_far_m2l(true, J.at[kStepM2LGroups], J.blocks[kStepM2LGroups], w, s);
+    if (e == hipSuccess) e = launch_far_lsum(J.at[kStepSum], J.blocks[kStepSum], w, s);
+    if (e == hipSuccess)
+      e = launch_far_eval(0, J.at[kStepTargets], J.blocks[kStepTargets], w, nullptr, s);
+    hipLaunchKernelGGL(k_stored_product, dim3(d.P), dim3(256), 0, s, T,
+                       reinterpret_cast<const int*>(w + sd.ncount),
+                       reinterpret_cast<const int*>(w + sd.nlist), at<double2>(L.mat),
+                       at<double2>(L.dens), reinterpret_cast<const double2*>(w + sd.fu), v,
+                       at<double>(L.sw), half, y);
+    if (e == hipSuccess) e = hipGetLastError();
+    return check(e, "solve product kernels");
+  }
   int matvec(const double2* v, double2* y) const {
+    if (stored) return stored_product(v, y);
     if (adjoint) return matvec_adjoint(v, y);
     hipLaunchKernelGGL(k_to_density, dim3(grid), dim3(256), 0, s, T, v, at<double>(L.sw),
                        at<double2>(L.dens));
@@ -422,7 +592,7 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
   Gmres G{g, d, L, static_cast<char*>(ws), stream, k, r, gamma, p, oversample,
           side == QBX_EXTERIOR ? -0.5 : 0.5, make_double2(alpha_re, alpha_im), adjoint, d.T,
-          (d.T + 255) / 256};
+          (d.T + 255) / 256, false, Layout{}, FarItem{}, FarItem{}};
   const int T = d.T, m = restart;
   double2* b = G.at<double2>(L.b);
   double2* x = G.at<double2>(L.x);
@@ -445,6 +615,7 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
   int it = 0;
   double res = 0.0;
   if (bnorm > 0.0) {
+    if (!adjoint && gamma == 0.0 && far_applies(d) && (rc = G.store_near())) return rc;
     std::vector<cplx> H((size_t)(m + 1) * m), gv(m + 1), cs(m), sn(m), y(m), h1(m + 1), h2(m + 1),
         buf(2 * m + 1);
     auto Hs = [&](int i, int j) -> cplx& { return H[(size_t)i * m + j]; };

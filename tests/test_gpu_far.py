@@ -200,3 +200,41 @@ def test_explicit_fused_matches_tape(n_src, n_ctr, p, kind):
     one = qbx.apply_explicit_vjp(*a, cot, ep.k, p, kind)
     for key in two:
         assert rel(one[key], two[key]) < 1e-11, key
+
+
+# stored products of the solve: around the threshold, groups, source counts past a wave's and
+# with a remainder, a complex coupling; k = 400 leaves every panel near (products by the forward)
+SOLVES = [
+    dict(P=95, k=5.0, p=8, side=1, os=2),
+    dict(P=96, k=5.0, p=8, side=-1, os=2),
+    dict(P=101, k=400.0, p=6, side=1, os=1),
+    dict(P=129, k=11.0, p=12, side=1, os=5, alpha=0.4 - 2.0j),
+    dict(P=321, k=30.0, p=4, side=-1, os=1),
+]
+
+
+@pytest.mark.parametrize("c", SOLVES, ids=lambda c: "P{P}-k{k}-s{side}-o{os}".format(**c))
+def test_solve_products(c):
+    """After a few iterations, the residual of the returned density, formed with the forward,
+    is the one reported; its terms cancel to about 1e-3 of the largest (bar 1e-9 of it)."""
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), c["P"], c["k"], c["p"], 0, 3, 17,
+                        oversample=c["os"])
+    nodes = torch.from_numpy(np.ascontiguousarray(pb.nodes)).cuda()
+    f = torch.from_numpy(np.ascontiguousarray(pb.density)).cuda()[0].contiguous()
+    alpha = c.get("alpha", 1j * c["k"])
+    kw = dict(oversample=c["os"])
+    sig, it, res = qbx.solve_dirichlet(nodes, f, c["k"], c["p"], side=c["side"], alpha=alpha,
+                                       tol=1e-14, restart=6, max_iter=6, **kw)
+    u = qbx.layer_potential(nodes, torch.stack([sig, sig]), c["k"], c["p"], side=0, kind=3, **kw)
+    S, D = 0.5 * (u[0, 0] + u[1, 0]), 0.5 * (u[0, 1] + u[1, 1])
+    r = f - (-0.5 * c["side"] * sig + alpha * S - D)
+    # the solve's norm: the 16-point rule's weights, here from the panels' own tangents
+    x, w = np.polynomial.legendre.leggauss(16)
+    Dm = np.stack([np.polynomial.legendre.legval(x, np.polynomial.legendre.legder(np.eye(16)[n]))
+                   for n in range(16)], 1) @ np.linalg.inv(np.polynomial.legendre.legvander(x, 15))
+    t = np.einsum("ab,mbc->mac", Dm, pb.nodes.reshape(c["P"], 16, 2))
+    wt = torch.from_numpy((w * np.hypot(t[..., 0], t[..., 1])).reshape(-1)).cuda()
+    true = float((wt * r.abs() ** 2).sum().sqrt() / (wt * f.abs() ** 2).sum().sqrt())
+    assert it == 6 and abs(true - res) < 1e-9 * true
