@@ -248,13 +248,15 @@ __global__ __launch_bounds__(256) void k_fused_center_grads(int Mc, int n_sb, in
   center_grad_from_sums(ci, side, T, ctr, s[0], s[1], s[2], s[3], cg);
 }
 
-// per source: sg[j] = {grad(w sigma) re, im, grad(w mu) re, im, g_x', g_y', g_nx, g_ny}
+// 64 sources a block: the parts joined, then the gradients of source_grads_from_sums
 __global__ __launch_bounds__(256) void k_source_finalize(int N, int kind, int n_csplit,
                                                          const double4* __restrict__ geo,
                                                          const double2* __restrict__ partial,
                                                          double* __restrict__ sg) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < N) source_finalize_elem(j, N, kind, n_csplit, geo, partial, sg);
+  double s[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+  int j;
+  if (join_source_parts(N, kind, n_csplit, partial, &j, s))
+    source_grads_from_sums(j, kind, geo, s, sg);
 }
 
 __global__ __launch_bounds__(128) void k_chain(Dims d, const double* __restrict__ nodes,
@@ -417,7 +419,7 @@ hipError_t launch_adjoint_fused(const Dims& d, const double* nodes, const double
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_fused_center_grads, dim3((d.Mc + 255) / 256), dim3(256), 0, s, d.Mc,
                      d.n_sb, d.side, d.T, ctr, cpart, cg);
-  hipLaunchKernelGGL(k_source_finalize, dim3((d.N + 255) / 256), dim3(256), 0, s, d.N, d.kind,
+  hipLaunchKernelGGL(k_source_finalize, dim3((d.N + kWave - 1) / kWave), dim3(256), 0, s, d.N, d.kind,
                      d.n_cb, geo, spartial, sg);
   hipLaunchKernelGGL(k_chain, dim3(d.P), dim3(128), 0, s, d, nodes, density, tables, sg, cg,
                      nullptr, nullptr, grad_density, grad_nodes);
@@ -435,7 +437,7 @@ hipError_t launch_chain(const Dims& d, const double* nodes, const double* densit
 
 hipError_t launch_source_finalize(const Dims& d, int parts, const double4* geo,
                                   const double2* spart, double* sg, hipStream_t s) {
-  hipLaunchKernelGGL(k_source_finalize, dim3((d.N + 255) / 256), dim3(256), 0, s, d.N, d.kind,
+  hipLaunchKernelGGL(k_source_finalize, dim3((d.N + kWave - 1) / kWave), dim3(256), 0, s, d.N, d.kind,
                      parts, geo, spart, sg);
   return hipGetLastError();
 }
@@ -463,7 +465,7 @@ hipError_t launch_adjoint_rest(const Dims& d, const double* nodes, const double*
   hipError_t e = launch_adjoint_src(d, geo, dens, ctr, jtab, G, spartial, s);
   timer_end(1, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_source_finalize, dim3((d.N + 255) / 256), dim3(256), 0, s, d.N, d.kind,
+  hipLaunchKernelGGL(k_source_finalize, dim3((d.N + kWave - 1) / kWave), dim3(256), 0, s, d.N, d.kind,
                      d.n_csplit, geo, spartial, sg);
   hipLaunchKernelGGL(k_chain, dim3(d.P), dim3(128), 0, s, d, nodes, density, tables, sg, cg,
                      nullptr, nullptr, grad_density, grad_nodes);

@@ -44,6 +44,7 @@ static int g_adjoint_waves = 16384;
 static int g_fused_tiles = 16384;  // fused adjoint workgroups aimed for
 static const int kSplitFarWaves = 65536;  // far-pass wavefronts aimed for
 static const int kFusedMinTile = 32;      // fewest centers a fused adjoint tile takes
+static const int kFusedLeastTile = 8;     // where those do not fill the chip
 static double g_fused_part_bytes = 2147483648.0;  // fused adjoint partial-sum bound
 
 double fused_part_budget() { return g_fused_part_bytes; }
@@ -101,7 +102,11 @@ void set_launch_shape(Dims* d) {
   // within the partial-sum bound
   if ((long)d->n_cb * max_sb < g_fused_tiles && d->fused_cblock > kFusedMinTile) {
     const long want_cb = ((long)g_fused_tiles + max_sb - 1) / max_sb;
-    const long h = std::max((long)kFusedMinTile, ((long)d->Mc + want_cb - 1) / want_cb);
+    long h = std::max((long)kFusedMinTile, ((long)d->Mc + want_cb - 1) / want_cb);
+    // a tile's waves take its centers in turn, so where tiles of 32 do not fill the chip
+    // once (1024 blocks) they get shorter still: 32 panels, order 8, S: 77 us in 128 tiles of
+    // 32 centers, 27 us in 512 of 8
+    h = std::min(h, std::max((long)kFusedLeastTile, (long)d->Mc * max_sb / 1024));
     const long n_cb = ((long)d->Mc + h - 1) / h;
     if (h < d->fused_cblock &&
         (double)n_cb * src_slots(d->kind) * (double)d->N * 16.0 <= fused_part_budget()) {

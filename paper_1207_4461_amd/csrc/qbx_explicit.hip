@@ -72,30 +72,11 @@ __global__ __launch_bounds__(256) void k_explicit_source_grads(
     const double2* __restrict__ dens, const double2* __restrict__ partial,
     double* __restrict__ grad_q, double* __restrict__ grad_src_xy,
     double* __restrict__ grad_src_nu) {
-  // 64 sources a block; the parts are dealt to four waves and joined in order
-  __shared__ double2 joined[3][4][kWave];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = blockIdx.x * kWave + lane;
   const bool hasS = kind & 1, hasD = kind & 2;
   const int nk = hasS && hasD ? 2 : 1;
-  const int NA = src_slots(kind);
   double s[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
-  if (j < N)
-    for (int cs = wave; cs < n_csplit; cs += 4)
-      for (int b = 0; b < NA; ++b) {
-        const double2 v = partial[((size_t)cs * NA + b) * N + j];
-        s[b][0] += v.x;
-        s[b][1] += v.y;
-      }
-  if (wave > 0)
-    for (int b = 0; b < NA; ++b) joined[wave - 1][b][lane] = make_double2(s[b][0], s[b][1]);
-  __syncthreads();
-  if (wave > 0 || j >= N) return;
-  for (int w = 0; w < 3; ++w)
-    for (int b = 0; b < NA; ++b) {
-      s[b][0] += joined[w][b][lane].x;
-      s[b][1] += joined[w][b][lane].y;
-    }
+  int j;
+  if (!join_source_parts(N, kind, n_csplit, partial, &j, s)) return;
   if (grad_q) {
     for (int kk = 0; kk < nk; ++kk) {
       const size_t o = (size_t)kk * N + j;
