@@ -4,12 +4,13 @@
 python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload star4096] [--mode fwdbwd]
 
 A step is one pass of the whole hot path over one batch of synthetic input that
-already sits in HBM: source grid and centers (upsampling), the pair kernels,
-evaluation, and (mode fwdbwd) the adjoint for the density and node gradients.
-Prints ONE JSON line: interactions/s (centers x sources x operators per second,
-forward and forward+backward), the dominant kernel's achieved FP64 rate against
-MI355X's vector FP64 peak (its launch durations timed with HIP events on the
-launch stream), and the CPU oracle timed on a bounded sample of the same workload.
+already sits in HBM: source grid and centers (upsampling), the panel expansions, the pair
+kernels, evaluation, and (mode fwdbwd) the adjoint for the density and node gradients.
+Prints ONE JSON line: interactions/s (centers x sources x operators of the workload per
+second, forward and forward+backward: every pair counts, whether it is evaluated by
+itself or, as most are, carried by expansions), the dominant pair kernel's achieved
+FP64 rate against MI355X's vector FP64 peak (its launch durations timed with HIP events
+on the launch stream, the pairs that it evaluates itself), and the CPU oracle timed on a bounded sample of the same workload.
 """
 from __future__ import annotations
 
@@ -358,20 +359,20 @@ def main():
     value = inter / (dt / args.steps)
 
     # per pair-kernel class: algorithmic flops per launch / average launch time
+    # (the tape's passes take every pair; the others the near ones, panel expansions the rest)
     pairs = pb.n_centers * pb.n_sources
+    near = flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides, pb.side)
     names = ["forward pair kernel", "adjoint source pass", "batched persistent kernel",
              "forward-with-tape pair kernel", "fused adjoint pair kernel",
-             "target-derivative pair kernel", "split near pass", "split far pass",
-             "split far-pass adjoint"]
+             "target-derivative pair kernel", "split near pass", "", ""]
     per_pair = [flops.flops_forward_pair(pb.p, pb.kind), flops.flops_adjoint_pair(pb.p, pb.kind),
                 0, flops.flops_tape_pair(pb.p, pb.kind), flops.flops_fused_pair(pb.p, pb.kind),
                 flops.flops_grad_pair(pb.p, pb.kind), flops.flops_forward_pair(pb.p, pb.kind),
-                flops.flops_far_pair(pb.kind), flops.flops_far_pair(pb.kind)]
-    pairs_of = [pairs] * 6 + [0, 0, 0]
+                0, 0]   # the split's direct far pairs: the few that no expansion takes
+    taped = mode == "fwdbwd" and args.backward == "tape"
+    pairs_of = [near, pairs if taped else near, 0, pairs, near, near, 0, 0, 0]
     if mode in ("split", "splitbwd"):
-        pairs_of[6], pairs_of[7] = flops.split_pairs(pb.nodes, pb.oversample, pb.n_sides,
-                                                     args.gamma)
-        pairs_of[8] = pairs_of[7]
+        pairs_of[6] = flops.split_pairs(pb.nodes, pb.oversample, pb.n_sides, args.gamma)[0]
     kernels = {}
     for c in range(NC):
         if nl[c] == 0 or per_pair[c] == 0:
@@ -384,8 +385,8 @@ def main():
     dom = kernels[names[cls]]
     achieved = dom["tflops"]
     avg_ms = dom["avg_ms"]
-    kernel_names = ["k_forward", "k_adjoint_src", "", "k_forward_tape", "k_adjoint_fused",
-                    "k_forward_grad", "k_split_near", "k_split_far", "k_split_far_adj"]
+    kernel_names = ["k_near_forward", "k_adjoint_src", "", "k_forward_tape", "k_near_sources",
+                    "k_near_grad", "k_near_forward", "", ""]
     roof = {"bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
             "frac": round(achieved / PEAK_FP64_TFLOPS, 4),
             "traffic": measured_traffic(kernel_names[cls], args.workload),
@@ -518,17 +519,19 @@ def bench_solve(args):
     nl = (C.c_int * NC)()
     _lib.check(lib.qbx_kernel_timer_read(ms, nl))
     lib.qbx_kernel_timer(0)
-    cls = 7 if gamma > 0 else 0
+    cls = 6 if gamma > 0 else 0
     products = nl[cls] // args.steps
     n_ctr = 2 * pb.n_targets
     inter = flops.interactions(n_ctr, pb.n_sources, 3) * products
     if gamma > 0:
-        pairs = flops.split_pairs(pb.nodes, pb.oversample, 2, gamma)[1]
-        fl = flops.flops_far_pair(3) * pairs
-        kname = "split far pass"
-    else:
+        fl = flops.flops_forward_pair(p, 3) * flops.split_pairs(pb.nodes, pb.oversample, 2, gamma)[0]
+        kname = "split near pass"
+    elif P < 96:
         fl = flops.flops_forward_pair(p, 3) * n_ctr * pb.n_sources
         kname = "forward pair kernel"
+    else:   # a complex multiply-add per stored weight: 16 x 16 of each pair of near panels
+        fl = 8 * flops.near_pairs(pb.nodes, k, pb.r, pb.oversample, 2, 0) // (2 * pb.oversample)
+        kname = "stored near product (bound by the read of its weights)"
     avg = ms[cls] / nl[cls]
     achieved = fl / (avg * 1e-3) / 1e12
     # the field off the curve: the nodes' own 16-point rule as explicit sources
@@ -669,12 +672,14 @@ def measure_random64(args, mode: str, backward: str, steps: int, warmup: int, au
     nl = (C.c_int * NC)()
     _lib.check(lib.qbx_kernel_timer_read(ms, nl))
     lib.qbx_kernel_timer(0)
-    # algorithmic flops of the persistent launches of one step
+    # algorithmic flops of the pair launches of one step (without a tape: of the near pairs)
+    near = [flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides, pb.side, True)
+            for pb in pbs]
     if mode == "fwd":
-        fl = sum(flops.flops_forward_pair(pb.p, pb.kind) * pb.n_centers * pb.n_sources for pb in pbs)
+        fl = sum(flops.flops_forward_pair(pb.p, pb.kind) * n for pb, n in zip(pbs, near))
     elif fused:
         fl = sum((flops.flops_forward_pair(pb.p, pb.kind) + flops.flops_fused_pair(pb.p, pb.kind))
-                 * pb.n_centers * pb.n_sources for pb in pbs)
+                 * n for pb, n in zip(pbs, near))
     else:
         fl = sum((flops.flops_tape_pair(pb.p, pb.kind) + flops.flops_adjoint_pair(pb.p, pb.kind))
                  * pb.n_centers * pb.n_sources for pb in pbs)

@@ -445,11 +445,13 @@ struct Gmres {
     if (e == hipSuccess) e = launch_far_lsum(J.at[kStepSum], J.blocks[kStepSum], w, s);
     if (e == hipSuccess)
       e = launch_far_eval(0, J.at[kStepTargets], J.blocks[kStepTargets], w, nullptr, s);
+    timer_begin(0, s);
     hipLaunchKernelGGL(k_stored_product, dim3(d.P), dim3(256), 0, s, T,
                        reinterpret_cast<const int*>(w + sd.ncount),
                        reinterpret_cast<const int*>(w + sd.nlist), at<double2>(L.mat),
                        at<double2>(L.dens), reinterpret_cast<const double2*>(w + sd.fu), v,
                        at<double>(L.sw), half, y);
+    timer_end(0, s);
     if (e == hipSuccess) e = hipGetLastError();
     return check(e, "solve product kernels");
   }

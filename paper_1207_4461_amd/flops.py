@@ -228,3 +228,64 @@ def split_pairs(nodes, oversample: int, n_sides: int, gamma: float):
     near = int(cnt.sum()) * 16 * n_sides * qs
     far = int((P - cnt).sum()) * 16 * 16
     return near, far
+
+
+def _far_zmin(x):
+    """The distance (times k) from which expansions of order 24 resolve a cluster of radius x
+    / k: csrc/qbx_far_table.h, rounded up to the table's next entry."""
+    import os
+    import re
+
+    import numpy as np
+
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "qbx_far_table.h")
+    txt = open(path).read()
+    i0, steps = (int(v) for v in re.search(r"kI0 = (-?\d+), kSteps = (\d+)", txt).groups())
+    body = txt.split("#define QBX_FAR_ZMIN_24")[1].split("#define")[0]
+    tab = np.array([float(v) for v in re.findall(r"[0-9][0-9.e+-]*", body)] + [1e300])
+    i = np.ceil((np.log2(np.maximum(x, 1e-300)) - i0) * steps).astype(int)
+    return tab[np.clip(i, 0, len(tab) - 1)]
+
+
+def near_pairs(nodes, k: float, r: float, oversample: int, n_sides: int, side: int,
+               batched: bool = False) -> int:
+    """Center-source pairs of a plain pass that are evaluated one by one; panel expansions take
+    the others (csrc/qbx_far.h).  Contours below 96 panels: all pairs."""
+    import numpy as np
+
+    X = np.asarray(nodes, dtype=np.float64).reshape(-1, 16, 2)
+    P, qs = len(X), 16 * oversample
+    per_panel_pair = 16 * n_sides * qs
+    if P < 96 or r > 1.0:
+        return P * P * per_panel_pair
+    leg = np.polynomial.legendre
+    x16, _ = leg.leggauss(16)
+    xs, ws = leg.leggauss(qs)
+    coef = np.einsum("na,mac->mnc", np.linalg.inv(leg.legvander(x16, 15)), X)
+    der = leg.legder(np.moveaxis(coef, 1, 0))                      # [15][P][2]
+    Y = np.einsum("sn,mnc->msc", leg.legvander(xs, 15), coef)
+    dY = np.einsum("sn,nmc->msc", leg.legvander(xs, 14), der)
+    dX = np.einsum("sn,nmc->msc", leg.legvander(x16, 14), der)
+    R = r * (ws * np.hypot(dY[..., 0], dY[..., 1])).sum(1)
+    nrm = np.stack([dX[..., 1], -dX[..., 0]], -1) / np.hypot(dX[..., 0], dX[..., 1])[..., None]
+    signs = (1, -1) if n_sides == 2 else (side,)
+    C = np.concatenate([X + sg * R[:, None, None] * nrm for sg in signs], 1)
+
+    def far(g):   # [clusters of g panels]^2: taken by expansions
+        n = (P + g - 1) // g
+        cut = [slice(c * g, min(P, c * g + g)) for c in range(n)]
+        b = np.stack([X[c].reshape(-1, 2).mean(0) for c in cut])
+        rs = np.array([np.hypot(*(Y[c].reshape(-1, 2) - b[i]).T).max() for i, c in enumerate(cut)])
+        rt = np.array([(np.hypot(*np.moveaxis(C[c] - b[i], -1, 0)) + R[c, None]).max()
+                       for i, c in enumerate(cut)])
+        ds, dt = _far_zmin(k * rs) / k, _far_zmin(k * rt) / k
+        t = np.maximum.reduce([ds[:, None] + rt, rt[:, None] + ds, dt[:, None] + rs,
+                               rs[:, None] + dt])
+        d = b[:, None] - b[None]
+        return (d ** 2).sum(-1) >= t * t
+
+    taken = far(1)
+    if P >= (128 if batched else 320):
+        g = 8 if P >= 2048 else 4
+        taken |= np.repeat(np.repeat(far(g), g, 0), g, 1)[:P, :P]
+    return int((~taken).sum()) * per_panel_pair

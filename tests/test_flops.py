@@ -42,3 +42,14 @@ def test_split_pair_counts_at_the_extremes():
     near, far = F.split_pairs(nodes, os_, 2, 1e-9)
     # far panels lend their 16 nodes, whatever the oversampling
     assert (near, far) == (2 * 16 * qs * P, (P - 1) * 16 * 16 * P)
+
+
+def test_near_pairs():
+    """Every pair below 96 panels; above, a bounded number of panels per panel, also with groups."""
+    from paper_1207_4461_amd import inputs as I
+
+    for P in (95, 96, 320, 640):
+        pb = I.make_problem("near", I.star((5, 0.25, 0.3)), P, 10.0, 6, 0, 3, 1, oversample=2)
+        per = F.near_pairs(pb.nodes, pb.k, pb.r, 2, 2, 0) / (P * 16 * 2 * 32)
+        assert per == 95 if P == 95 else 3 <= per <= 24
+    assert F.near_pairs(pb.nodes, 1e5, pb.r, 2, 2, 0) == (640 * 16) ** 2 * 4
