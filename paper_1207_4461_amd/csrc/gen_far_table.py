@@ -16,7 +16,7 @@ import mpmath as mp
 
 TOL = 1e-17
 I0, I1, STEPS = -12, 5, 8      # x from 2^-12 to 2^5
-ORDERS = (12, 24)
+ORDERS = (24,)
 Z_MIN, Z_MAX = 1e-3, 2000.0    # below Z_MIN the high orders of H would overflow
 
 mp.mp.dps = 30

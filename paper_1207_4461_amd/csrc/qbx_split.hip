@@ -9,10 +9,10 @@
 // the near pass, the far pass and any IEEE double evaluation of the same formula
 // take the same decisions.  A panel is always near itself (gamma > 0).
 //
-// Near pass (k_split_near): one wave per center, as the plain forward, but the
-// wave first tests 64 source panels at a time against its target's panel and
-// runs the QBX pair kernel (forward_source) over the sources of the near ones
-// only.  Far pass (k_split_far): the 64 lanes are 64 consecutive targets and the
+// Near pass (k_near_forward of qbx_near.hip): one wave per center over the sources of
+// its panel's near list.  Far pairs: from 96 panels on through panel expansions
+// (qbx_far.hip), and the few that none reaches by k_split_mid; below that by
+// k_split_far: the 64 lanes are 64 consecutive targets and the
 // sources of a run of panels are wave-uniform (scalar loads); a far pair adds
 //     S: w sigma H_0(k rho),    D: w mu k H_1(k rho) (x - x').n' / rho,
 // rho = |x - x'|, the normal derivative of H_0(k|x - x'|) at the source (the
@@ -489,18 +489,15 @@ __global__ __launch_bounds__(256) void k_split_density_grad(
 // Node gradient of the split.  The loss L = Re sum_i conj(g_i) u_i is a sum over
 // pairs, each taken by one rule, so its gradient is the plain adjoint's per-pair
 // terms over the near pairs plus the direct rule's over the far ones:
-//  * center side, near pairs (k_split_near_cg): the tape sums of the near sources
-//    (K_R, K_theta, grad_v K; tape_source) contracted with G_i, then the per-center
-//    gradients of center_grad_from_sums (target, radius, normal);
-//  * source side, near pairs (k_split_near_adj_nodes): the plain adjoint's pair
-//    body (adjoint_pair) over the centers of near target panels;
-//  * far pairs, source side: k_split_far_adj<KIND, true> over the far sources
-//    (the nodes); target side: the far target gradients of the split's
-//    derivative pass (k_split_far_grad); k_split_nystrom_grad puts both on the
+//  * both sides, near pairs (k_near_sources of qbx_near.hip, as the plain adjoint): one
+//    evaluation per pair, then the per-center gradients of center_grad_from_sums (target,
+//    radius, normal);
+//  * far pairs: expansions and their transpose from 96 panels on, with k_split_mid;
+//    below, source side k_split_far_adj<KIND, true> over the far sources (the nodes),
+//    target side the far target gradients of k_split_far_grad; k_split_nystrom_grad puts both on the
 //    nodes (position, normal, the weight's tangent term, the density);
-//  * k_split_source_finalize puts the near source terms into the per-source
-//    layout of the plain adjoint, and the plain chain rule (chain_panel) maps
-//    everything to the nodes and node densities.
+//  * the plain adjoint's k_source_finalize and chain rule (chain_panel) map everything to
+//    the nodes and node densities.
 // ---------------------------------------------------------------------------
 
 // The far pairs' terms of the node gradient, per node t = 16 m + a (added to

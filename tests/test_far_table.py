@@ -1,8 +1,8 @@
 """CPU check of the distances from which panel expansions stand for their pairs.
 
 For random clusters as close as the committed table (csrc/qbx_far_table.h) lets them come, the
-translated expansion (sources -> multipole -> local -> target) of order 24, or 12 from its own
-table, is compared with the Hankel function of the distance: the terms left out are below
+translated expansion (sources -> multipole -> local -> target) of order 24
+is compared with the Hankel function of the distance: the terms left out are below
 1e-17 of the leading one, so in double precision only rounding remains: 2e-14 of |H_0| at the nearest point of the two
 disks (some 50 terms of either index, each rounded to 1e-16 of at most that).
 """
@@ -22,7 +22,7 @@ def tables():
     i0, steps, n = (int(v) for v in re.search(r"kI0 = (-?\d+), kSteps = (\d+), kLen = (\d+)",
                                               txt).groups())
     out = {}
-    for order in (12, 24):
+    for order in (24,):
         body = txt.split("#define QBX_FAR_ZMIN_%d" % order)[1].split("#define")[0]
         vals = [float(v) for v in re.findall(r"[0-9][0-9.e+-]*", body)]
         assert len(vals) == n
@@ -50,9 +50,8 @@ def translated(order, k, src, b_a, b_b, y):
     return np.sum(L * sps.jv(l, k * abs(t)) * np.exp(1j * l * np.angle(t)))
 
 
-@pytest.mark.parametrize("order, x", [(12, x) for x in (2.0 ** -11, 0.01, 0.1, 0.2, 0.26)] +
-                         [(24, x) for x in (2.0 ** -11, 0.01, 0.1, 0.5, 0.9, 2.0, 3.3)])
-def test_order_resolves_the_distance(order, x):
+@pytest.mark.parametrize("x", (2.0 ** -11, 0.01, 0.1, 0.5, 0.9, 2.0, 3.3))
+def test_order_resolves_the_distance(x, order=24):
     rng = np.random.default_rng(int(1000 * x) + order)
     k = 1.0
     rt = x
@@ -76,7 +75,5 @@ def test_order_resolves_the_distance(order, x):
 
 def test_tables_grow_with_the_radius():
     _, _, tab = tables()
-    for order in (12, 24):
-        assert all(b >= a for a, b in zip(tab[order], tab[order][1:]))
-        assert min(tab[order]) >= 1e-3                # higher orders of H stay finite
-    assert all(b <= a for a, b in zip(tab[12], tab[24]))
+    assert all(b >= a for a, b in zip(tab[24], tab[24][1:]))
+    assert min(tab[24]) >= 1e-3                       # higher orders of H stay finite
