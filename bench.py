@@ -361,7 +361,9 @@ def main():
     # per pair-kernel class: algorithmic flops per launch / average launch time
     # (the tape's passes take every pair; the others the near ones, panel expansions the rest)
     pairs = pb.n_centers * pb.n_sources
-    near = flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides, pb.side)
+    near = pairs
+    if flops.expansions_apply(pb.n_panels, pb.oversample, pb.n_sides, pb.p, pb.kind):
+        near = flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides, pb.side)
     names = ["forward pair kernel", "adjoint source pass", "batched persistent kernel",
              "forward-with-tape pair kernel", "fused adjoint pair kernel",
              "target-derivative pair kernel", "split near pass", "", ""]
@@ -526,7 +528,7 @@ def bench_solve(args):
     if gamma > 0:
         fl = flops.flops_forward_pair(p, 3) * flops.split_pairs(pb.nodes, pb.oversample, 2, gamma)[0]
         kname = "split near pass"
-    elif P < 96:
+    elif P < 64:
         fl = flops.flops_forward_pair(p, 3) * n_ctr * pb.n_sources
         kname = "forward pair kernel"
     else:   # a complex multiply-add per stored weight: 16 x 16 of each pair of near panels
@@ -674,7 +676,8 @@ def measure_random64(args, mode: str, backward: str, steps: int, warmup: int, au
     lib.qbx_kernel_timer(0)
     # algorithmic flops of the pair launches of one step (without a tape: of the near pairs)
     near = [flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides, pb.side, True)
-            for pb in pbs]
+            if flops.expansions_apply(pb.n_panels, pb.oversample, pb.n_sides, pb.p, pb.kind, True)
+            else pb.n_centers * pb.n_sources for pb in pbs]
     if mode == "fwd":
         fl = sum(flops.flops_forward_pair(pb.p, pb.kind) * n for pb, n in zip(pbs, near))
     elif fused:

@@ -232,7 +232,7 @@ Layout make_forward_layout(const Dims& d, bool far) {
   L.ctr = take(sizeof(CenterRec) * (size_t)d.Mc);
   L.jtab = take(sizeof(double) * (size_t)d.Mc * d.NJ);
   L.partial = take(sizeof(double2) * (size_t)d.n_split * d.nk * d.Mc);
-  if (far && far_applies(d)) {
+  if (far) {
     L.far = take(sizeof(FarItem));
     FarItem it;
     far_layout(d, false, take, &it);

@@ -16,7 +16,7 @@
 // per-center and per-source steps run as ordinary grids over all contours'
 // panels, centers or sources.
 //
-// Contours that panel expansions apply to (far_applies) take their far pairs that way
+// Contours that panel expansions apply to (far_applies_batch) take their far pairs that way
 // (qbx_far.hip, one grid per step over all of them) and their near pairs in one ordinary
 // grid per class (qbx_near.hip); the persistent kernels keep the small contours, and every
 // contour of a call with a tape.
@@ -155,8 +155,8 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     for (int i : sorted_members[c]) {
       BatchItemDev& B = P->items[i];
       B.far_parts = 0;
-      if (far_applies(B.d)) far_members[c].push_back(i);
-      if (!use_far || !far_applies(B.d)) mem.push_back(i);
+      if (far_applies_batch(B.d)) far_members[c].push_back(i);
+      if (!use_far || !far_applies_batch(B.d)) mem.push_back(i);
     }
     n_far += (int)far_members[c].size();
     C.n = (int)mem.size();
@@ -216,7 +216,7 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     BatchItemDev& B = P->items[i];
     B.spart_off = P->n_spart;
     const int parts = std::max(std::max(B.d.n_csplit, B.d.n_cb),
-                               far_applies(B.d) ? kFarMaxShares : 1);
+                               far_applies_batch(B.d) ? kFarMaxShares : 1);
     P->n_spart += (long long)parts * src_slots(B.d.kind) * B.d.N;
     B.cpart_off = P->n_cpart;
     P->n_cpart += (long long)B.d.n_sb * B.d.Mc * 4;

@@ -406,7 +406,7 @@ struct ExpLayout {
 
 ExpLayout make_expansion_layout(const Dims& d) {
   ExpLayout E;
-  E.base = make_forward_layout(d, true);
+  E.base = make_forward_layout(d, d.P >= kFarMinCoefPanels);
   // at any r and k, whichever way the sums are formed then
   const size_t n_sp = std::max(coef_splits(d, false), coef_splits(d, true));
   E.part = E.base.total;
@@ -447,7 +447,7 @@ int qbx_expansion_coefficients(const qbx_geometry* g, const double* density, dou
   if (ws_bytes < E.total)
     return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, E.total);
   const Layout& L = E.base;
-  const bool far = far_applies(d);
+  const bool far = far_applies_coef(d);
   FarItem it{};
   if (far) it = far_item_of(d, L, false, true, false);
   FarItem* dev = far ? at<FarItem>(ws, L.far) : nullptr;

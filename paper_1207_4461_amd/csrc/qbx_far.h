@@ -198,9 +198,21 @@ hipError_t launch_far_src(const FarBlocks& B, int blocks, double* ws, bool geom,
 constexpr int kNearSlots = 32;
 __host__ __device__ inline int near_subs(int qs) { return (qs + kWave - 1) / kWave; }
 
-// fewest panels that are worth the expansions, largest center distance r taken (a disk
-// that reaches over many panels leaves every panel near)
-constexpr int kFarMinPanels = 96;
+// Where expansions take the far pairs.  A center distance r over 1 (a disk that reaches over
+// many panels) leaves every panel near; below that what they save has to pay for their six
+// launches and short chains (about 100 us in a forward, 220 in an adjoint, with both kinds
+// 125 and 290), so a plain pass takes them from kFarMinPanels panels and from a forward pair
+// count of kFarMinFlops (1 + kinds) on.  Forward, far / pair by pair in us: 96 panels, S,
+// p = 4, q_s = 48: 104 / 68, 160 panels: 108 / 127; S, p = 8, q_s = 64, 112 panels: 109 / 108;
+// S + D, p = 8, one side, 96 and 112 panels: 125 / 111, 126 / 143; both sides, p = 12, 96
+// panels: 149 / 220.  Adjoint of the same: 220 / 131, 236 / 238, 239 / 211, 288 / 256,
+// 285 / 322, 437 / 494.
+// Others: a batch's contours share the launches; the split's direct far pairs are cheap, but its
+// near passes came to the same walk (forward, S, p = 4: 64 panels 77, 96 panels 102, 128
+// panels 106 us); the expansion coefficients cost 140 us at any small size against 764 at 96
+// panels; a solve forms what it stores once.
+constexpr int kFarMinPanels = 96, kFarMinCoefPanels = 16, kFarMinSolvePanels = 64;
+constexpr double kFarMinFlops = 1.4e9;
 // From kFarGroupPanels panels on groups of four too, from kFarGroup8Panels on of eight.  The
 // second level costs its own multipoles, sums and evaluation (about 70 us at 256 panels,
 // where it saves less: forward 289 us without, 354 us with groups; at 333 panels 449 and
@@ -208,9 +220,16 @@ constexpr int kFarMinPanels = 96;
 // GPU together (64 contours of 16..512 panels: translations 9.9 ms without, 2.6 ms with).
 constexpr int kFarGroupPanels = 320, kFarGroupPanelsBatch = 128;
 constexpr int kFarGroup8Panels = 2048;
+inline bool far_fits(const Dims& d) { return d.center_rule == 0 && d.r <= 1.0; }
 inline bool far_applies(const Dims& d) {
-  return d.P >= kFarMinPanels && d.center_rule == 0 && d.r <= 1.0;
+  // the forward's flops per pair
+  const double pair = d.kind == 1 ? 95 + 12 * d.p : d.kind == 2 ? 114 + 16 * d.p : 128 + 23 * d.p;
+  return d.P >= kFarMinPanels && far_fits(d) &&
+         pair * d.Mc * d.N >= kFarMinFlops * (1 + d.nk);
 }
+inline bool far_applies_batch(const Dims& d) { return d.P >= kFarMinPanels && far_fits(d); }
+inline bool far_applies_coef(const Dims& d) { return d.P >= kFarMinCoefPanels && far_fits(d); }
+inline bool far_applies_solve(const Dims& d) { return d.P >= kFarMinSolvePanels && far_fits(d); }
 // the near/far split's far targets are points: no disk to look at
 inline bool far_applies_split(const Dims& d) { return d.P >= kFarMinPanels; }
 // Blocks of the translation that are resident at once (256 compute units, three each), and the

@@ -19,6 +19,7 @@
 #include <mutex>
 
 #include "../../include/qbx.h"
+#include "qbx_far.h"
 #include "qbx_internal.h"
 
 static __device__ __align__(256) unsigned char scratch[QBX_STATIC_SCRATCH_BYTES];
@@ -64,7 +65,7 @@ extern "C" int qbx_layer_potential_noalloc(const qbx_geometry* g, const double* 
   if (!density) return fail(QBX_EINVAL, "density is NULL");
   if (!out) return fail(QBX_EINVAL, "out is NULL");
   // the expansions where their arrays fit too (they add rounding differences only)
-  Layout L = make_forward_layout(d, true);
+  Layout L = make_forward_layout(d, far_applies(d));
   if (L.total > (size_t)QBX_STATIC_SCRATCH_BYTES) L = make_forward_layout(d, false);
   if (L.total > (size_t)QBX_STATIC_SCRATCH_BYTES)
     return fail(QBX_EWORKSPACE,

@@ -350,7 +350,7 @@ static SolveLayout make_solve_layout(const Dims& d, int restart) {
   L.x = take(sizeof(double2) * T);
   L.partial = take(sizeof(double2) * ((T + kDotSlice - 1) / kDotSlice) * (size_t)(restart + 1));
   L.h = take(sizeof(double2) * (2 * (size_t)restart + 3));
-  const bool stored = d.P >= kFarMinPanels;
+  const bool stored = d.P >= kFarMinSolvePanels;
   L.item = take(stored ? sizeof(FarItem) : 0);
   L.mat = take(stored ? sizeof(double2) * kQ * kQ * kStoredNear * (size_t)d.P : 0);
   L.total = o;
@@ -617,7 +617,7 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
   int it = 0;
   double res = 0.0;
   if (bnorm > 0.0) {
-    if (!adjoint && gamma == 0.0 && far_applies(d) && (rc = G.store_near())) return rc;
+    if (!adjoint && gamma == 0.0 && far_applies_solve(d) && (rc = G.store_near())) return rc;
     std::vector<cplx> H((size_t)(m + 1) * m), gv(m + 1), cs(m), sn(m), y(m), h1(m + 1), h2(m + 1),
         buf(2 * m + 1);
     auto Hs = [&](int i, int j) -> cplx& { return H[(size_t)i * m + j]; };

@@ -247,16 +247,24 @@ def _far_zmin(x):
     return tab[np.clip(i, 0, len(tab) - 1)]
 
 
+def expansions_apply(n_panels: int, oversample: int, n_sides: int, p: int, kind: int,
+                     batched: bool = False) -> bool:
+    """Whether a plain pass (r <= 1, centers at r h) takes its far pairs by panel expansions."""
+    pairs = (16 * n_panels) ** 2 * oversample * n_sides
+    work = pairs * flops_forward_pair(p, kind)
+    return n_panels >= 96 and (batched or work >= 1.4e9 * (1 + (2 if kind == 3 else 1)))
+
+
 def near_pairs(nodes, k: float, r: float, oversample: int, n_sides: int, side: int,
                batched: bool = False) -> int:
-    """Center-source pairs of a plain pass that are evaluated one by one; panel expansions take
-    the others (csrc/qbx_far.h).  Contours below 96 panels: all pairs."""
+    """Center-source pairs that are evaluated one by one where panel expansions take the others
+    (csrc/qbx_far.h; expansions_apply: whether a plain pass does)."""
     import numpy as np
 
     X = np.asarray(nodes, dtype=np.float64).reshape(-1, 16, 2)
     P, qs = len(X), 16 * oversample
     per_panel_pair = 16 * n_sides * qs
-    if P < 96 or r > 1.0:
+    if r > 1.0:
         return P * P * per_panel_pair
     leg = np.polynomial.legendre
     x16, _ = leg.leggauss(16)

@@ -15,14 +15,15 @@ from paper_1207_4461_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-# panels around the threshold (96), the 64-cluster blocks, the groups of eight (from 512 on) and
+# panels around the least count (96) and pairs around the least work, the 64-cluster blocks, the groups of eight (from 512 on) and
 # their remainders; every kind and side; smallest and largest order and oversampling;
 # wavenumbers that no distance resolves (every pair near) and that reach the table's lower end
 CASES = [
     dict(P=95, k=5.0, p=8, side=1, kind=1, os=4),
     dict(P=96, k=5.0, p=8, side=1, kind=1, os=4),
-    dict(P=97, k=20.0, p=12, side=0, kind=3, os=1),
-    dict(P=128, k=0.003, p=4, side=-1, kind=2, os=3),
+    dict(P=96, k=20.0, p=12, side=0, kind=3, os=4),
+    dict(P=97, k=20.0, p=20, side=0, kind=3, os=3),
+    dict(P=192, k=0.003, p=4, side=-1, kind=2, os=3),
     dict(P=129, k=150.0, p=10, side=0, kind=2, os=2),
     dict(P=193, k=12.0, p=0, side=0, kind=3, os=8),
     dict(P=511, k=30.0, p=24, side=1, kind=3, os=1),
@@ -125,8 +126,9 @@ def test_split_groups_match_oracle():
 # coefficients: around the threshold, rows that are no multiple of a wave's, a source count that
 # the splits do not divide, smallest and largest order
 EXPANSIONS = [
-    dict(P=95, k=9.0, p=5, side=0, kind=3, os=1),
-    dict(P=96, k=9.0, p=0, side=0, kind=2, os=1),
+    dict(P=15, k=3.0, p=5, side=0, kind=3, os=1),
+    dict(P=16, k=3.0, p=5, side=0, kind=3, os=2),
+    dict(P=50, k=9.0, p=0, side=0, kind=2, os=1),
     dict(P=97, k=14.0, p=12, side=0, kind=3, os=1),
     dict(P=98, k=6.0, p=24, side=-1, kind=1, os=1),
     dict(P=99, k=20.0, p=3, side=1, kind=1, os=3),
@@ -205,8 +207,8 @@ def test_explicit_fused_matches_tape(n_src, n_ctr, p, kind):
 # stored products of the solve: around the threshold, groups, source counts past a wave's and
 # with a remainder, a complex coupling; k = 400 leaves every panel near (products by the forward)
 SOLVES = [
-    dict(P=95, k=5.0, p=8, side=1, os=2),
-    dict(P=96, k=5.0, p=8, side=-1, os=2),
+    dict(P=63, k=5.0, p=8, side=1, os=2),
+    dict(P=64, k=5.0, p=8, side=-1, os=2),
     dict(P=101, k=400.0, p=6, side=1, os=1),
     dict(P=129, k=11.0, p=12, side=1, os=5, alpha=0.4 - 2.0j),
     dict(P=321, k=30.0, p=4, side=-1, os=1),
