@@ -237,9 +237,12 @@ inline bool far_applies_split(const Dims& d) { return d.P >= kFarMinPanels; }
 // sources are left per 64 target panels).
 constexpr int kFarM2LBlocks = 768;
 constexpr int kFarMaxPanelShares = 16;
-// waves of the near source passes aimed for
-constexpr int kFarSourceWaves = 8192;
-constexpr int kFarMaxShares = 8;   // parts of a chunk's near source sums at most
+// Waves of the near source passes aimed for, and parts of a chunk's near source sums at most; half
+// of both in a batch, whose items fill the GPU together.  (8192 and 8, 16384 and 16: 1024
+// panels, p = 16, S: near adjoint 307 and 288 us; 4096 panels, S + D: 3.97 and 3.87 ms; the
+// batch of 64 contours: 12.5 and 12.7 ms.)
+constexpr int kFarSourceWaves = 16384;
+constexpr int kFarMaxShares = 16;
 // Shares of the sources per (target block, vector, half): as many as `rounds` rounds of
 // resident blocks hold, for the number of rounds that gives the least time (a partly
 // filled last round costs a whole one); a batch's item: its part of four rounds.
@@ -316,8 +319,10 @@ inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_
   }
   // a chunk's list is cut into at most kFarMaxShares
   const long long chunks = (long long)d.P * near_subs(d.qs) * n_items;
-  const int ns = (int)((kFarSourceWaves + chunks - 1) / chunks);
-  it->nsrc = ns > kFarMaxShares ? kFarMaxShares : ns;
+  const int waves = n_items > 1 ? kFarSourceWaves / 2 : kFarSourceWaves;
+  const int most = n_items > 1 ? kFarMaxShares / 2 : kFarMaxShares;
+  const int ns = (int)((waves + chunks - 1) / chunks);
+  it->nsrc = ns > most ? most : ns;
 }
 
 }  // namespace qbx
