@@ -87,6 +87,7 @@ struct FarItem {
   int pt;               // far targets are points (the split: the nodes)
   int V;                // vectors translated: kinds forward, then kinds backward
   int vf;               // of them forward (0 or nk)
+  int slots;            // longest near list whose panel's center sums go through cpart
   int nsrc;             // waves per 64-source chunk in the near source passes
   int n0, n1;           // blocks of sources per 64 target panels / groups
   int m2l_blocks;       // translation blocks aimed for
@@ -105,7 +106,7 @@ struct FarItem {
   size_t fu;                           // double2 [nk][Mc][2] far sums per center
   size_t fc;                           // double [Mc][4] far center gradients
   size_t fs;                           // double2 [nk + 2][far sources]
-  size_t cpart;                        // double [P][kNearSlots subs][n_sides kQ][4]: near center sums
+  size_t cpart;                        // double [P][slots subs][n_sides kQ][4]: near center sums
   size_t partial, cg, spart;           // near outputs: gradient sums, center / source gradients
 };
 
@@ -193,9 +194,12 @@ hipError_t launch_far_src(const FarBlocks& B, int blocks, double* ws, bool geom,
 
 
 // Near adjoint: a source panel's chunks of 64 (one partial), and the near lists up to which the
-// fused pass also forms the center side (13 panels are near at most sizes; past kNearSlots the
-// centers of a panel are summed by a wave each)
-constexpr int kNearSlots = 32;
+// fused pass also forms the center side (13 panels are near at most sizes; past them the centers
+// of a panel are summed by a wave each, a second evaluation of every pair).  Small contours
+// have room for more: at a few panels a wavelength, up to all 100 panels are near, and the
+// second evaluation made batches of a few such contours slower than the pair tiles.
+constexpr int kNearSlots = 32, kNearSlotsSmall = 128, kNearSlotsSmallPanels = 256;
+static_assert(kNearSlotsSmall <= kNearCap, "slots are positions in the near lists");
 __host__ __device__ inline int near_subs(int qs) { return (qs + kWave - 1) / kWave; }
 
 // Where expansions take the far pairs.  A center distance r over 1 (a disk that reaches over
@@ -314,7 +318,8 @@ inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_
     it->tp0 = at((size_t)d.n_sides * d.nk * C0 * kFarW * 2);
     it->tp1 = at((size_t)(it->g / 4) * d.n_sides * d.nk * C1 * kFarW * 2);
     it->fc = at((size_t)d.Mc * 4);
-    it->cpart = at((size_t)kNearSlots * near_subs(d.qs) * d.Mc * 4);
+    it->slots = d.P <= kNearSlotsSmallPanels ? kNearSlotsSmall : kNearSlots;
+    it->cpart = at((size_t)it->slots * near_subs(d.qs) * d.Mc * 4);
     it->fs = at((size_t)(d.nk + 2) * d.N * 2);
   }
   // a chunk's list is cut into at most kFarMaxShares

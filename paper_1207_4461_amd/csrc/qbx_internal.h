@@ -14,7 +14,7 @@ constexpr int kQ = 16;      // nodes per panel
 constexpr int kWave = 64;   // CDNA wavefront
 // near/far split: capacity of a panel's near list; a panel with more near panels
 // is served by the scan of all panels instead
-constexpr int kNearCap = 64;
+constexpr int kNearCap = 128;
 
 // per-panel near lists of the split: count[m] and, when count[m] <= kNearCap,
 // list[m * kNearCap + i], i < count[m], the panels near m in ascending order

@@ -173,7 +173,7 @@ struct CenterShare {
 //    fused_tile) into LDS and from there into the chunk's slot of the target panel,
 //    cpart[panel][slot][center][4], slot = position of the chunk's panel in the target
 //    panel's list (times the chunks of a panel).  Panels whose list is longer than
-//    kNearSlots have no slots: k_near_centers sums their centers.
+//    the item's slots have none: k_near_centers sums their centers.
 // Replaces a pass per side (1758 and 1259 flops a pair at p = 20, S + D) by one of 1432.
 template <int P, int KIND>
 __global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double* __restrict__ ro,
@@ -228,13 +228,18 @@ __global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double*
       const double v = wave_sum4(cres, lane);
       if ((lane & 15) == 0) cs[cc * 4 + (lane >> 4)] = v;
     }
-    if (cnt <= kNearSlots) {
+    if (cnt <= it.slots) {
       const int* __restrict__ L = nl.list + (size_t)m * kNearCap;
-      const unsigned long long at = __ballot(lane < cnt && L[lane < cnt ? lane : 0] == c.panel);
       // (the relation is symmetric, so the panel is on the list)
-      const int slot = (at ? __builtin_ctzll(at) : 0) * subs + c.sub;
+      int pos = 0;
+      for (int i = 0; i < cnt; i += kWave) {
+        const unsigned long long at =
+            __ballot(i + lane < cnt && L[i + lane < cnt ? i + lane : 0] == c.panel);
+        if (at) pos = i + __builtin_ctzll(at);
+      }
+      const int slot = pos * subs + c.sub;
       double* __restrict__ o =
-          wo + it.cpart + (((size_t)m * kNearSlots * subs + slot) * nc) * 4;
+          wo + it.cpart + (((size_t)m * it.slots * subs + slot) * nc) * 4;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       for (int t = 4 * c0 + lane; t < 4 * c1; t += kWave) o[t] = cs[t];
@@ -268,10 +273,10 @@ __global__ __launch_bounds__(256) void k_near_center_sums(FarBlocks B,
   const int si = ci / it.T, t = ci - si * it.T;
   const int m = t / kQ;
   const int cnt = near_lists(it, ro).count[m];
-  if (cnt > kNearSlots) return;
+  if (cnt > it.slots) return;
   const int subs = near_subs(it.qs), nc = it.n_sides * kQ;
   const double* __restrict__ p =
-      ro + it.cpart + ((size_t)m * kNearSlots * subs * nc + si * kQ + (t - m * kQ)) * 4 + q;
+      ro + it.cpart + ((size_t)m * it.slots * subs * nc + si * kQ + (t - m * kQ)) * 4 + q;
   double s = it.g2 > 0.0 ? 0.0 : ro[it.fc + (size_t)ci * 4 + q];
   for (int i = 0; i < cnt * subs; ++i) s += p[(size_t)i * nc * 4];
   const int l0 = threadIdx.x & ~3;
@@ -298,7 +303,7 @@ __global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double*
   const int Mc = it.Mc;
   if (ci >= Mc) return;
   const int m = (ci % it.T) / kQ;
-  if (near_lists(it, ro).count[m] <= kNearSlots) return;
+  if (near_lists(it, ro).count[m] <= it.slots) return;
   const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
   const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
   const CenterRec* ctr = reinterpret_cast<const CenterRec*>(ro + it.ctr);
