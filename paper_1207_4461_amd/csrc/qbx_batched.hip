@@ -148,6 +148,8 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
   P->pre_f.clear();
   P->pre_a.clear();
   std::vector<std::vector<int>> far_members(P->cls.size());
+  double work = 0.0;
+  for (int i = 0; i < n; ++i) work += pair_work(P->items[i].d);
   int n_far = 0;
   for (size_t c = 0; c < P->cls.size(); ++c) {
     BatchClass& C = P->cls[c];
@@ -155,8 +157,8 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     for (int i : sorted_members[c]) {
       BatchItemDev& B = P->items[i];
       B.far_parts = 0;
-      if (far_applies_batch(B.d)) far_members[c].push_back(i);
-      if (!use_far || !far_applies_batch(B.d)) mem.push_back(i);
+      if (far_applies_batch(B.d, work)) far_members[c].push_back(i);
+      if (!use_far || !far_applies_batch(B.d, work)) mem.push_back(i);
     }
     n_far += (int)far_members[c].size();
     C.n = (int)mem.size();
@@ -216,7 +218,7 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     BatchItemDev& B = P->items[i];
     B.spart_off = P->n_spart;
     const int parts = std::max(std::max(B.d.n_csplit, B.d.n_cb),
-                               far_applies_batch(B.d) ? kFarMaxShares : 1);
+                               far_applies_batch(B.d, work) ? kFarMaxShares : 1);
     P->n_spart += (long long)parts * src_slots(B.d.kind) * B.d.N;
     B.cpart_off = P->n_cpart;
     P->n_cpart += (long long)B.d.n_sb * B.d.Mc * 4;

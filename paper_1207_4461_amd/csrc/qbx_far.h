@@ -225,13 +225,22 @@ constexpr double kFarMinFlops = 1.4e9;
 constexpr int kFarGroupPanels = 320, kFarGroupPanelsBatch = 128;
 constexpr int kFarGroup8Panels = 2048;
 inline bool far_fits(const Dims& d) { return d.center_rule == 0 && d.r <= 1.0; }
-inline bool far_applies(const Dims& d) {
-  // the forward's flops per pair
+// flops of a forward over every pair
+inline double pair_work(const Dims& d) {
   const double pair = d.kind == 1 ? 95 + 12 * d.p : d.kind == 2 ? 114 + 16 * d.p : 128 + 23 * d.p;
-  return d.P >= kFarMinPanels && far_fits(d) &&
-         pair * d.Mc * d.N >= kFarMinFlops * (1 + d.nk);
+  return pair * d.Mc * d.N;
 }
-inline bool far_applies_batch(const Dims& d) { return d.P >= kFarMinPanels && far_fits(d); }
+inline bool far_applies(const Dims& d) {
+  return d.P >= kFarMinPanels && far_fits(d) && pair_work(d) >= kFarMinFlops * (1 + d.nk);
+}
+// A contour of a batch whose forward over every pair takes `work` flops.  Small batches do not
+// fill the GPU, and the chain of launches and the few waves of a contour of 100 to 160 panels
+// take longer than its pair tiles beside the others (forward and adjoint of 7 contours of up
+// to 120 panels, 10 GFLOP: up to 2.7 ms by expansions, 2.2 ms without).
+constexpr double kFarBatchFlops = 2e10;
+inline bool far_applies_batch(const Dims& d, double work) {
+  return d.P >= (work < kFarBatchFlops ? 160 : kFarMinPanels) && far_fits(d);
+}
 inline bool far_applies_coef(const Dims& d) { return d.P >= kFarMinCoefPanels && far_fits(d); }
 inline bool far_applies_solve(const Dims& d) { return d.P >= kFarMinSolvePanels && far_fits(d); }
 // the near/far split's far targets are points: no disk to look at
