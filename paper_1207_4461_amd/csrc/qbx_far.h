@@ -84,14 +84,15 @@ struct FarItem {
   int P, C1, g;         // panels, groups (0: none), panels of a group (4 or 8)
   int T, N, qs, Mc, n_sides, nk, kind, p, NJ, side;
   int fqs;              // far sources per panel (qs; the split: 16, the nodes)
-  int pt;               // far targets are points (the split: the nodes)
+  int pt;               // the near/far split's item: far targets are points (its nodes), near
+                        // pairs those of the gamma relation (at any gamma: g2 may underflow to 0)
   int V;                // vectors translated: kinds forward, then kinds backward
   int vf;               // of them forward (0 or nk)
   int slots;            // longest near list whose panel's center sums go through cpart
   int nsrc;             // waves per 64-source chunk in the near source passes
   int n0, n1;           // blocks of sources per 64 target panels / groups
   int m2l_blocks;       // translation blocks aimed for
-  double k, g2;         // g2: the split's gamma squared, or 0
+  double k, g2;         // g2: the split's gamma squared
   size_t node_off;      // doubles into the nodes
   size_t out_off;       // doubles into out
   size_t geo, dens, ctr, jtab, G;      // pair sources, centers, cotangent weights

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(64) void k_far_recs(FarBlocks B, const double* __re
         rt = fmax(rt, sqrt(dx * dx + dy * dy) + C.R);
       }
   }
-  if (group && it.g2 > 0.0) {
+  if (group && it.pt) {
     const double4* bnd = reinterpret_cast<const double4*>(ro + it.bnd);
     if (m0 + lane < m1) {
       const double4 q = bnd[m0 + lane];
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256, 3) void k_far_m2l(FarBlocks B, const double* _
       reinterpret_cast<const double2*>(ro + (GROUP ? it.rows1 : it.rows0)) +
       (size_t)(v * 2 + half) * C * kFarW + kFarQ;
   const bool inner = !GROUP && it.C1 > 0;
-  const bool gam = !GROUP && it.g2 > 0.0;
+  const bool gam = !GROUP && it.pt != 0;
   const int g = it.g;
   double Lr[kFarQ + 1], Li[kFarQ + 1];
 #pragma unroll
@@ -1075,7 +1075,7 @@ __global__ __launch_bounds__(256) void k_far_lists(FarBlocks B, const double* __
   R.r0 = reinterpret_cast<const FarRec*>(ro + it.rec0);
   R.r1 = it.C1 > 0 ? reinterpret_cast<const FarRec*>(ro + it.rec1) : nullptr;
   R.g = it.g;
-  R.bnd = it.g2 > 0.0 ? reinterpret_cast<const double4*>(ro + it.bnd) : nullptr;
+  R.bnd = it.pt ? reinterpret_cast<const double4*>(ro + it.bnd) : nullptr;
   R.g2 = it.g2;
   int* count = reinterpret_cast<int*>(wo + it.mcount);
   int* list = reinterpret_cast<int*>(wo + it.mlist);

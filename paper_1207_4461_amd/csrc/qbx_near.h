@@ -14,7 +14,7 @@ struct NearRel {
 };
 __device__ __forceinline__ NearRel near_rel(const FarItem& it, const double* ro) {
   NearRel n;
-  n.gamma = it.g2 > 0.0;
+  n.gamma = it.pt != 0;
   n.R.r0 = reinterpret_cast<const FarRec*>(ro + it.rec0);
   n.R.r1 = it.C1 > 0 ? reinterpret_cast<const FarRec*>(ro + it.rec1) : nullptr;
   n.R.g = it.g;

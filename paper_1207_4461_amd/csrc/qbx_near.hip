@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void k_near_forward(FarBlocks B, const double*
     Cplx v[2];
     v[0] = kS ? S : Dd;
     v[1] = Dd;
-    if (it.g2 > 0.0) {
+    if (it.pt) {
       double2* partial = reinterpret_cast<double2*>(wo + it.partial);
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk)
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void k_near_grad(FarBlocks B, const double* __
     wave_sum(A[kk][1]);
   }
   if (lane == 0) {
-    const bool add = !(it.g2 > 0.0);
+    const bool add = !it.pt;
     const double2* fu = reinterpret_cast<const double2*>(ro + it.fu);
     double2* partial = reinterpret_cast<double2*>(wo + it.partial);
 #pragma unroll
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double*
   if (valid) {
     double2* part = reinterpret_cast<double2*>(wo + it.spart) + (size_t)c.sp * NA * N;
     const double2* fs = reinterpret_cast<const double2*>(ro + it.fs);
-    const bool add = c.sp == 0 && !(it.g2 > 0.0);
+    const bool add = c.sp == 0 && !it.pt;
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
       const double2 f = add ? fs[(size_t)a * N + j] : make_double2(0.0, 0.0);
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(256) void k_near_center_sums(FarBlocks B,
   const int subs = near_subs(it.qs), nc = it.n_sides * kQ;
   const double* __restrict__ p =
       ro + it.cpart + ((size_t)m * it.slots * subs * nc + si * kQ + (t - m * kQ)) * 4 + q;
-  double s = it.g2 > 0.0 ? 0.0 : ro[it.fc + (size_t)ci * 4 + q];
+  double s = it.pt ? 0.0 : ro[it.fc + (size_t)ci * 4 + q];
   for (int i = 0; i < cnt * subs; ++i) s += p[(size_t)i * nc * 4];
   const int l0 = threadIdx.x & ~3;
   const double s0 = __shfl(s, (l0 & 63)), s1 = __shfl(s, (l0 & 63) + 1),
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double*
   if (lane == 0) {
     const double2* G = reinterpret_cast<const double2*>(ro + it.G);
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    if (!(it.g2 > 0.0)) {
+    if (!it.pt) {
       const double* fc = ro + it.fc + (size_t)ci * 4;
 #pragma unroll
       for (int q = 0; q < 4; ++q) s[q] = fc[q];
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(256) void k_near_density(FarBlocks B, const double*
     }
   });
   if (valid) {
-    const bool plain = !(it.g2 > 0.0);
+    const bool plain = !it.pt;
     // the split sums near parts itself, [kk][j]; plain parts lie in the source-pass layout
     double2* part = reinterpret_cast<double2*>(wo + it.spart) +
                     (size_t)c.sp * (plain ? NA : (kS && kD ? 2 : 1)) * N;

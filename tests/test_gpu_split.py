@@ -376,3 +376,28 @@ def test_split_gradient_star4096(Q):
     gap = max(rel(g, g0.cpu().numpy()), rel(dn, dn0.cpu().numpy()))
     say(f"  star4096: vs plain QBX derivatives {gap:.3e}")
     assert gap < 1e-10
+
+
+@pytest.mark.parametrize("P", (24, 98))
+def test_smallest_gammas(Q, P):
+    """gamma^2 below the least positive double leaves no pair near, not even a panel with itself,
+    whose direct terms are infinite: every output is NaN, as from any other entry of the split.
+    The least gamma whose square (times a panel's) is representable keeps each panel near itself
+    alone, as a moderate small one does."""
+    pb = I.make_problem("gamma", I.star((5, 0.25, 0.3)), P, 5.0, 4, 0, 3, 29, oversample=2,
+                        with_cotangent=True)
+    nodes, dens, cot = dev(pb.nodes), dev(pb.density), dev(pb.cotangent)
+    args = (pb.k, pb.p, pb.r, pb.oversample, pb.side, pb.kind)
+
+    def every(gamma):
+        u = Q.layer_potential_split(nodes, dens, *args, gamma=gamma)
+        grad, dn = Q.layer_potential_split_gradient(nodes, dens, *args, gamma=gamma)
+        gd, gn = Q.layer_potential_split_vjp(nodes, dens, cot, *args, gamma=gamma, want_nodes=True)
+        only = Q.layer_potential_split_vjp(nodes, dens, cot, *args, gamma=gamma)
+        return [torch.view_as_real(t) if t.is_complex() else t for t in (u, grad, dn, gd, gn, only)]
+
+    assert (1e-170) ** 2 == 0.0
+    for t in every(1e-170):
+        assert bool(torch.isnan(t).all())
+    for a, b in zip(every(1e-150), every(1e-3)):
+        assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
