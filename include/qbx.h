@@ -623,13 +623,16 @@ size_t qbx_autotune_workspace_bytes(int n_panels, int q, int p, int oversample, 
  * timed once) -- it times its pass with hipEvents on `stream`, the minimum
  * over `passes` runs (1..20) after one warm-up, keeps the fastest, installs
  * the result with qbx_set_tuning and writes it to *best (nullable).  Other
- * fields are left as they were.  On error the previous tuning is restored.
+ * fields are left as they were, and so are forward_waves and fused_tiles where
+ * panel expansions take the problem's far pairs (from about 100 panels on at
+ * r <= 1): they do not shape the passes that run there.  On error the previous
+ * tuning is restored.
  *   ws, ws_bytes  device workspace of qbx_autotune_workspace_bytes() bytes: all
  *                 device memory the timing uses (nothing is allocated)
  *   cache_path    host path of a text cache file, or NULL.  A line
  *                 "<key> => <value>" per result, the key naming the device
  *                 (architecture, compute units) and the problem (P, p,
- *                 oversample, side, kind, fields).  On a hit the stored fields
+ *                 oversample, side, kind, the fields tuned).  On a hit the stored fields
  *                 are installed untimed (ws may then be NULL); on a miss the
  *                 result is timed and written back (the file is rewritten
  *                 through a temporary file and a rename).  QBX_EIO for an
@@ -651,7 +654,9 @@ size_t qbx_autotune_batched_workspace_bytes(const qbx_batch_item* items, int n_i
  * batch_adjoint_tasks in 2048 .. 262144 (doubling) on the batched adjoint
  * with the tape and batch_fused_chunks in {4, 8, 16, 32} on the batched
  * adjoint without it (QBX_TUNE_TAPE selects nothing here), keeps the fastest
- * of each and installs them.  ws, cache_path: as qbx_autotune, with
+ * of each and installs them.  batch_grid_scale and batch_fused_chunks are left
+ * as they were when every contour takes its far pairs through panel expansions.
+ * ws, cache_path: as qbx_autotune, with
  * qbx_autotune_batched_workspace_bytes() and a key naming the device, the
  * item count, oversample, fields and a 64-bit signature of the items'
  * (n_panels, p, kind, side). */

@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "../../include/qbx.h"
+#include "qbx_far.h"
 #include "qbx_internal.h"
 
 namespace qbx {
@@ -269,6 +270,9 @@ int qbx_autotune(const qbx_geometry* g, const double* density, double k, int p, 
   if (rc) return rc;
   if (!density) return fail(QBX_EINVAL, "density is NULL");
   if ((rc = valid_passes_fields(passes, fields))) return rc;
+  // where panel expansions take the far pairs, the passes without a tape do not run the kernels
+  // that these two shape: times would differ by noise alone
+  if (far_applies(d)) fields &= ~(QBX_TUNE_FORWARD | QBX_TUNE_FUSED);
   qbx_tuning saved;
   qbx_get_tuning(&saved);
   std::string key;
@@ -310,7 +314,8 @@ int qbx_autotune(const qbx_geometry* g, const double* density, double k, int p, 
   double* gn = static_cast<double*>(c.take(z.gn));
   Events ev;
   hipError_t e;
-  if ((e = hipEventCreate(&ev.a)) != hipSuccess || (e = hipEventCreate(&ev.b)) != hipSuccess)
+  if (fields && ((e = hipEventCreate(&ev.a)) != hipSuccess ||
+                 (e = hipEventCreate(&ev.b)) != hipSuccess))
     return device_fail(e, "autotuner events");
   auto fwd = [&] {
     return qbx_layer_potential(g, density, k, p, r, oversample, side, kind, o, nullptr, wsc, z.ws,
@@ -398,6 +403,8 @@ int qbx_autotune_batched(const qbx_batch_item* items, int n_items, const double*
   if (rc) return rc;
   if (qbx_batched_workspace_bytes(items, n_items, oversample) == 0)
     return fail(QBX_EINVAL, "invalid batch (an item's parameters, offsets or oversample)");
+  if (!batch_has_pair_tasks(items, n_items, oversample))   // as for one contour
+    fields &= ~(QBX_TUNE_FORWARD | QBX_TUNE_FUSED);
   qbx_tuning saved;
   qbx_get_tuning(&saved);
   std::string key;
@@ -439,10 +446,11 @@ int qbx_autotune_batched(const qbx_batch_item* items, int n_items, const double*
   double* gd = static_cast<double*>(c.take(z.gd));
   double* gn = static_cast<double*>(c.take(z.gn));
   // the output serves as the adjoint's cotangent: give it defined values
-  hipError_t e = hipMemsetAsync(o, 0, z.out, stream);
+  hipError_t e = fields ? hipMemsetAsync(o, 0, z.out, stream) : hipSuccess;
   if (e != hipSuccess) return device_fail(e, "autotuner buffers");
   Events ev;
-  if ((e = hipEventCreate(&ev.a)) != hipSuccess || (e = hipEventCreate(&ev.b)) != hipSuccess)
+  if (fields && ((e = hipEventCreate(&ev.a)) != hipSuccess ||
+                 (e = hipEventCreate(&ev.b)) != hipSuccess))
     return device_fail(e, "autotuner events");
   auto fwd = [&] {
     return qbx_layer_potential_batched(items, n_items, nodes, density, o, nullptr, oversample, wsc,

@@ -310,6 +310,20 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
   return true;
 }
 
+bool batch_has_pair_tasks(const qbx_batch_item* items, int n, int oversample) {
+  Dims d;
+  auto dims = [&](int i) {
+    const qbx_batch_item& it = items[i];
+    return make_dims(it.n_panels, kQ, it.p, oversample, it.side, it.kind, it.k, it.r, &d);
+  };
+  double work = 0.0;
+  for (int i = 0; i < n; ++i)
+    if (dims(i)) work += pair_work(d);
+  for (int i = 0; i < n; ++i)
+    if (dims(i) && !far_applies_batch(d, work)) return true;
+  return false;
+}
+
 template <typename T>
 static T* wsp(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);

@@ -317,6 +317,8 @@ void get_contour_tuning(int* forward_waves, int* tape_waves, int* adjoint_waves,
                         int* fused_tiles);
 void set_batch_tuning(double grid_scale, double adjoint_tasks, int fused_chunks);
 void get_batch_tuning(double* grid_scale, double* adjoint_tasks, int* fused_chunks);
+// whether a call without a tape leaves some contour of a valid batch to the persistent kernels
+bool batch_has_pair_tasks(const qbx_batch_item* items, int n, int oversample);
 int validate(const qbx_geometry* g, int p, double k, double r, int oversample, int side,
              int kind, Dims* d);
 }  // namespace qbx

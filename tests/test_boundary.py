@@ -337,6 +337,31 @@ def test_autotune_validation(lib):
     assert lib.qbx_autotune_batched_workspace_bytes(its, 3, 4) == 0
 
 
+def test_autotune_leaves_shapes_that_do_not_act(lib):
+    """With panel expansions (512 panels, r = 1/2) the passes without a tape run no kernel that
+    forward_waves or fused_tiles shapes: nothing is timed (no device is needed) and the fields
+    keep their values, which are none of the candidates."""
+    fields = [n for n, _ in _lib.Tuning._fields_]
+    t0, best = _lib.Tuning(), _lib.Tuning()
+    assert lib.qbx_get_tuning(C.byref(t0)) == _lib.QBX_OK
+    try:
+        t = _lib.Tuning(*[getattr(t0, f) for f in fields])
+        t.forward_waves, t.fused_tiles, t.batch_grid_scale, t.batch_fused_chunks = 5000, 3000, 1.5, 5
+        assert lib.qbx_set_tuning(C.byref(t)) == _lib.QBX_OK
+        what = _lib.QBX_TUNE_FORWARD | _lib.QBX_TUNE_FUSED
+        g = _lib.Geometry(512, 16, BAD)
+        assert lib.qbx_autotune(C.byref(g), BAD, 1.0, 8, 0.5, 4, 1, 1, 2, what, None, C.byref(best),
+                                BAD, 1 << 40, None) == _lib.QBX_OK
+        assert all(getattr(best, f) == getattr(t, f) for f in fields)
+        its = (_lib.BatchItem * 2)(*[_lib.BatchItem(512 * i, 8192 * i, 8192 * i, 512, 8, 1, 1, 3.0,
+                                                    0.5) for i in range(2)])
+        assert lib.qbx_autotune_batched(its, 2, BAD, BAD, 4, 2, what, None, C.byref(best), BAD,
+                                        1 << 40, None) == _lib.QBX_OK
+        assert all(getattr(best, f) == getattr(t, f) for f in fields)
+    finally:
+        assert lib.qbx_set_tuning(C.byref(t0)) == _lib.QBX_OK
+
+
 def test_autotune_workspace_covers_every_candidate(lib):
     """The autotuner's workspace query holds the library workspace of every
     candidate shape (the library's own size depends on the tuning)."""
