@@ -33,7 +33,7 @@ namespace qbx {
 //  * z < Z0: Y_nu = (2/pi)(ln(z/2) + gamma) J_nu - nu 2/(pi z) + R_nu with J_nu, R_nu
 //    entire (DLMF 10.8.1, 10.8.2): for z < Z1 = 4 their ascending series in
 //    w = z^2/4 (DLMF 10.2.2), for Z1 <= z < Z0 polynomial fits in (z - 5).  When every
-//    active lane has z < 2 the series end at w^11, when every one has z < 1/2 at w^7 (the
+//    active lane has |z| < 2 the series end at w^11, when every one has |z| < 1/2 at w^7 (the
 //    next terms are below 1e-17 and 1e-18); the logarithm is log_half_gamma's.
 // Error <~ 2e-15 |H| for every z in (0, 4e5) (the reduction's first part is
 // exact for n < 2^26).
@@ -127,20 +127,22 @@ static __constant__ __align__(16) double g_phase_table[2 * seed::kPhaseN] = {
 
 static __constant__ __align__(16) double g_log_table[2 * logtab::kN] = {QBX_LOG_TABLE_VALUES};
 
-// ln(z/2) + gamma for a normal positive z = 2^e m: e ln 2 + t_i + ln(1 + r), r = m c_i - 1, from
-// the table entry of m's leading bits (gathered per lane) and ln(1 + r) to r^5 (|r| < 2^-9: the
-// next term is below 1e-17).  Absolute error about one ulp of the larger of the sum and 1/2.
+// ln(z/2) + gamma for positive z = 2^e m (subnormal ones too), -infinity for 0:
+// e ln 2 + t_i + ln(1 + r), r = m c_i - 1, from the table entry of m's leading bits (gathered per
+// lane) and ln(1 + r) to r^5 (|r| < 2^-9: the next term is below 1e-17).  Absolute error about
+// one ulp of the larger of the sum and 1/2.
 // The library's log took 110 instructions of the 400 to 900 of a near pair; this takes about 20.
 __device__ __forceinline__ double log_half_gamma(double z) {
-  const int hi = __double2hiint(z);
-  const double e = (double)((hi >> 20) - 1023);
-  const double m = __hiloint2double((hi & 0xfffff) | 0x3ff00000, __double2loint(z));
-  const double* __restrict__ T = g_log_table + 2 * ((hi >> 12) & (logtab::kN - 1));
+  const double h = __builtin_amdgcn_frexp_mant(z);   // m / 2
+  const double e = (double)(__builtin_amdgcn_frexp_exp(z) - 1);
+  const double m = h + h;
+  const double* __restrict__ T = g_log_table + 2 * ((__double2hiint(h) >> 12) & (logtab::kN - 1));
   const double r = fma(m, T[0], -1.0);
   double q = fma(r, 0.2, -0.25);
   q = fma(r, q, 1.0 / 3.0);
   q = fma(r, q, -0.5);
-  return fma(e, 0.69314718055994530942, T[1]) + fma(r * r, q, r);
+  const double L = fma(e, 0.69314718055994530942, T[1]) + fma(r * r, q, r);
+  return z > 0.0 ? L : -INFINITY;
 }
 
 // H_0, H_1 from the amplitude functions P0, Q0, P1, Q1 of the asymptotic form:
@@ -270,9 +272,9 @@ __device__ __forceinline__ H01 hankel01(double z, double iz, const double* __res
     } else {
       const double w = 0.25 * z * z;
       D4 f;
-      if (__all(z < 0.5))
+      if (__all(fabs(z) < 0.5))
         f = horner4<8>(cf + seed::kSEROff, w);
-      else if (__all(z < 2.0))
+      else if (__all(fabs(z) < 2.0))
         f = horner4<12>(cf + seed::kSEROff, w);
       else
         f = horner4<seed::kSERLen>(cf + seed::kSEROff, w);

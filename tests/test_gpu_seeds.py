@@ -27,3 +27,20 @@ def test_seeds(lo, hi):
             ref = [mp.hankel1(n, mp.mpf(float(x))) for x in z]
             err = [float(abs(mp.mpc(v.real, v.imag) - r) / abs(r)) for v, r in zip(h[n], ref)]
             assert max(err) < 2e-15
+
+
+def test_seeds_at_the_ends_of_the_range():
+    """z = 0, subnormal and negative: the logarithm's limits, as the library's has them."""
+    from paper_1207_4461_amd import qbx
+
+    z = np.array([0.0, 5e-324, 1e-310, 2.3e-308, -1e-310, -0.3, -1.5, -3.9, float("nan"), 0.7])
+    h0, h1 = (t.cpu().numpy() for t in qbx.hankel01(torch.from_numpy(z).cuda()))
+    assert h0[0].real == 1.0 and h0[0].imag == -np.inf and h1[0].real == 0.0
+    for i in (1, 2, 3, 9):
+        ref = mp.hankel1(0, mp.mpf(float(z[i])))
+        assert abs(h0[i].imag - float(ref.imag)) < 2e-15 * abs(ref)
+    assert np.isnan(h0[4:9].imag).all() and np.isnan(h1[4:9].imag).all()
+    for i in (5, 6, 7):   # the series of J are even and odd; Y has no real value
+        assert abs(h0[i].real - float(mp.besselj(0, float(z[i])))) < 4e-15
+        assert abs(h1[i].real - float(mp.besselj(1, float(z[i])))) < 4e-15
+    assert np.isnan(h0[8].real) and np.isnan(h1[8].real)
