@@ -9,16 +9,15 @@
 //    adds q f_l to a_l, q = w sigma; the double layer's ladder d/dn' f_l =
 //    (k/2)(conj(nu) f_{l-1} - nu f_{l+1}), nu = n_x + i n_y, adds the f_m to its two
 //    neighbours with the weights w mu conj(nu) and w mu nu (coef_pair, k/2 in
-//    k_coef_finalize).  A wave takes one sign of the orders: f_{-m} follows f_m's recurrences
-//    with the signs of H_1, of 1/z and of E's imaginary part turned, so one code has both, the
-//    sums of both kinds stay in registers up to p = 24, and a pair's H and E serve both kinds.
+//    k_coef_finalize).  With D a wave takes one sign of the orders: f_{-m} follows f_m's
+//    recurrences with the signs of H_1, of 1/z and of E's imaginary part turned, so one code has
+//    both, the sums of both kinds stay in registers up to p = 24, and a pair's H and E serve both
+//    kinds.  S alone has room for both signs in one wave, which share f_m's four products.
 //  * k_coef: lanes are 64 centers, the sources of a source split are wave-uniform (scalar
-//    loads): contours below the panel expansions' sizes.
+//    loads): every pair, where panel expansions do not apply (far_applies_coef).
 //  * k_coef_near: the sources of near panels only, where panel expansions take the far ones
-//    (qbx_far.hip: the coefficients are the local expansions that those end in).
-//    256 panels (4 x 16 sources each), S + D, both sides, p = 12, all coefficient kernels:
-//    8.4 ms as three passes over every pair (one per weight), 0.49 ms now, 0.34 of it
-//    k_coef_near.
+//    (qbx_far.hip: the coefficients are the local expansions that those end in).  Near is what
+//    keeps each order right by itself (qbx_coef_table.h), which is wider than for potentials.
 //  * k_evaluate_expansions: one thread per target,
 //    u = (i/4) sum_l a_l J_l(k|x - c|) e^{i l arg(x - c)} with J_l by Miller's
 //    recurrence (J_{-l} = (-1)^l J_l).
@@ -38,14 +37,17 @@
 namespace qbx {
 
 // sums of one sign of the orders: S[l] = a^S_{sg l}, D[l] = (2/k) a^D_{sg l}, 0 <= l <= P (the
-// order-0 sums are in parts: S's in the positive sign's, D's in both)
+// order-0 sums are in parts: S's in the positive sign's, D's in both); S alone: M[l] = a^S_{-l}
 template <int P, int KIND>
 struct CoefSums {
   double sr[KIND & 1 ? P + 1 : 1], si[KIND & 1 ? P + 1 : 1];
   double dr[KIND & 2 ? P + 1 : 1], di[KIND & 2 ? P + 1 : 1];
+  double mr[KIND == 1 ? P + 1 : 1], mi[KIND == 1 ? P + 1 : 1];
 };
+// waves that share a center's orders
+constexpr int coef_halves(int kind) { return kind == 1 ? 1 : 2; }
 
-// adds one pair; q the weighted densities (S, D), sg the sign of the orders
+// adds one pair; q the weighted densities (S, D), sg the sign of the orders (S alone: 1)
 template <int P, int KIND>
 __device__ __forceinline__ void coef_pair(const double4 g, const double2 qS, const double2 w,
                                           double cx, double cy, double k, double inv_k, double sg,
@@ -78,7 +80,14 @@ __device__ __forceinline__ void coef_pair(const double4 g, const double2 qS, con
   }
 #pragma unroll
   for (int m = 1; m <= M; ++m) {
-    const double fr = fma(hr, er, -hi * ei), fi = fma(hr, ei, hi * er);
+    const double rr = hr * er, ii = hi * ei, ri = hr * ei, im = hi * er;
+    const double fr = rr - ii, fi = ri + im;
+    if (KIND == 1) {   // f_{-m} = (-1)^m H_m conj(E)^m
+      const double qx = (m & 1) ? -qS.x : qS.x, qy = (m & 1) ? -qS.y : qS.y;
+      const double gr = rr + ii, gi = im - ri;
+      A.mr[m] = fma(qx, gr, fma(-qy, gi, A.mr[m]));
+      A.mi[m] = fma(qx, gi, fma(qy, gr, A.mi[m]));
+    }
     if (kS && m <= P) {
       A.sr[m] = fma(qS.x, fr, fma(-qS.y, fi, A.sr[m]));
       A.si[m] = fma(qS.x, fi, fma(qS.y, fr, A.si[m]));
@@ -112,6 +121,7 @@ __device__ __forceinline__ void coef_zero(CoefSums<P, KIND>& A) {
   for (int l = 0; l <= P; ++l) {
     if (KIND & 1) A.sr[l] = A.si[l] = 0.0;
     if (KIND & 2) A.dr[l] = A.di[l] = 0.0;
+    if (KIND == 1) A.mr[l] = A.mi[l] = 0.0;
   }
 }
 
@@ -124,6 +134,7 @@ __device__ __forceinline__ void coef_store(const CoefSums<P, KIND>& A, int sp, i
 #pragma unroll
   for (int l = 0; l <= P; ++l) {
     if (KIND & 1) o[(size_t)l * Mc] = make_double2(A.sr[l], A.si[l]);
+    if (KIND == 1) o[(size_t)(P + 1 + l) * Mc] = make_double2(A.mr[l], A.mi[l]);
     if (KIND & 2) o[(size_t)((NK - 1) * (P + 1) + l) * Mc] = make_double2(A.dr[l], A.di[l]);
   }
 }
@@ -138,9 +149,10 @@ __global__ __launch_bounds__(256) void k_coef(const double4* __restrict__ geo,
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int gw = blockIdx.x * 4 + wave;
-  const int half = gw & 1;
-  const int sp = (gw >> 1) / n_cb;
-  const int cb = (gw >> 1) - sp * n_cb;
+  constexpr int kH = coef_halves(KIND);
+  const int half = gw % kH;
+  const int sp = gw / kH / n_cb;
+  const int cb = gw / kH - sp * n_cb;
   const int ci = cb * kWave + lane;
   if (sp >= n_sp) return;   // past the last split (whole waves); an empty split writes zeros
   const int j0 = sp * src_per_split;
@@ -159,8 +171,9 @@ __global__ __launch_bounds__(256) void k_coef(const double4* __restrict__ geo,
 // The sums over the sources of panels near the center's; a wave has the 16 centers of one panel
 // and side, four lanes each, and of each near panel the sources 4 sp + (0..3) + 4 n_sp i (whole
 // panels dealt to the splits left some with twice the work).  Bound by FP64 issue and its
-// latency at two waves a SIMD: 213 VGPRs at p = 12, S + D; 335 us for 256 panels, 370 + 184 us
-// as one pass per weight over both signs.
+// latency at two waves a SIMD: 213 VGPRs at p = 12, S + D.  256 panels, k = 20, both sides, all
+// kernels: 1.75 ms with the 73 panels of p = 12 near, 4.4 over every pair (k_coef), 8.0 as three
+// passes over every pair (one per weight).
 template <int P, int KIND>
 __global__ __launch_bounds__(256) void k_coef_near(FarBlocks B, const double* __restrict__ ro,
                                                    int n_sp, double2* __restrict__ partial) {
@@ -169,8 +182,9 @@ __global__ __launch_bounds__(256) void k_coef_near(FarBlocks B, const double* __
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int gw = b * 4 + wave;
-  const int half = gw & 1;
-  const int sp = (gw >> 1) % n_sp, row = (gw >> 1) / n_sp;
+  constexpr int kH = coef_halves(KIND);
+  const int half = gw % kH;
+  const int sp = gw / kH % n_sp, row = gw / kH / n_sp;
   const int si = row / it.P, m = row - si * it.P;
   if (si >= it.n_sides) return;
   const int ci = si * it.T + m * kQ + (lane & 15);
@@ -199,6 +213,10 @@ __global__ __launch_bounds__(256) void k_coef_near(FarBlocks B, const double* __
       if (KIND & 2) {
         A.dr[l] += __shfl_xor(A.dr[l], off);
         A.di[l] += __shfl_xor(A.di[l], off);
+      }
+      if (KIND == 1) {
+        A.mr[l] += __shfl_xor(A.mr[l], off);
+        A.mi[l] += __shfl_xor(A.mi[l], off);
       }
     }
   if (lane < kQ) coef_store<P, KIND>(A, sp, half, ci, it.Mc, partial);
@@ -351,12 +369,12 @@ hipError_t launch_coef_k(const Dims& d, bool far, const FarItem* dev, const doub
                          const double4* geo, const double2* q, const CenterRec* ctr, int n_sp,
                          double2* partial, hipStream_t s) {
   if (far) {
-    const long waves = 2L * d.P * d.n_sides * n_sp;
+    const long waves = (long)coef_halves(KIND) * d.P * d.n_sides * n_sp;
     hipLaunchKernelGGL((k_coef_near<P, KIND>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s,
                        FarBlocks{dev, nullptr, 1}, ws, n_sp, partial);
   } else {
     const int n_cb = (d.Mc + kWave - 1) / kWave;
-    const long waves = 2L * n_cb * n_sp;
+    const long waves = (long)coef_halves(KIND) * n_cb * n_sp;
     hipLaunchKernelGGL((k_coef<P, KIND>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, geo,
                        q, d.N, ctr, d.Mc, n_cb, n_sp, (d.N + n_sp - 1) / n_sp, d.k, partial);
   }
@@ -389,12 +407,12 @@ hipError_t launch_coef(const Dims& d, bool far, const FarItem* dev, const double
   }
 }
 
-// splits of the coefficient sums: enough waves (two signs; 64 centers each, or far a panel
-// and side) to fill the device about four times, at most 8 (the split sums take
+// splits of the coefficient sums: enough waves (64 centers each, or far a panel and side; with
+// D one per sign) to fill the device about four times, at most 8 (the split sums take
 // n_sp x 2 x (p + 1) x Mc x 16 bytes per kind)
 int coef_splits(const Dims& d, bool far) {
-  const int n_cb = far ? d.P * d.n_sides : (d.Mc + kWave - 1) / kWave;
-  int n_sp = std::min(8, (2048 + n_cb - 1) / n_cb);
+  const int n_cb = coef_halves(d.kind) * (far ? d.P * d.n_sides : (d.Mc + kWave - 1) / kWave);
+  int n_sp = std::min(8, (4096 + n_cb - 1) / n_cb);
   const int most = far ? (d.qs + 3) / 4 : (d.N + kWave - 1) / kWave;
   return std::max(1, std::min(n_sp, most));
 }
@@ -406,7 +424,7 @@ struct ExpLayout {
 
 ExpLayout make_expansion_layout(const Dims& d) {
   ExpLayout E;
-  E.base = make_forward_layout(d, d.P >= kFarMinCoefPanels);
+  E.base = make_forward_layout(d, far_coef_size(d));
   // at any r and k, whichever way the sums are formed then
   const size_t n_sp = std::max(coef_splits(d, false), coef_splits(d, true));
   E.part = E.base.total;
@@ -449,7 +467,10 @@ int qbx_expansion_coefficients(const qbx_geometry* g, const double* density, dou
   const Layout& L = E.base;
   const bool far = far_applies_coef(d);
   FarItem it{};
-  if (far) it = far_item_of(d, L, false, true, false);
+  if (far) {
+    it = far_item_of(d, L, false, true, false);
+    it.coef = d.p;
+  }
   FarItem* dev = far ? at<FarItem>(ws, L.far) : nullptr;
   hipError_t e = launch_tables(d, at<double>(ws, L.tables), stream);
   if (e != hipSuccess) return device_fail(e, "tables kernel");

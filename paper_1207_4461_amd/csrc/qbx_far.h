@@ -38,6 +38,8 @@ constexpr int kFarW = 2 * kFarQ + 1;
 // kFarQ resolves them (ds, dt), and, for the near/far split's
 // groups, the radius of the panel means (rb) and gamma times the largest node radius
 // (gr): groups at least that far hold no pair of panels within gamma radii.
+// Where the coefficients are the result, the distances are those that keep every order right
+// (qbx_coef_table.h) and rt is the radius of the centers alone.
 struct FarRec {
   double bx, by, rs, rt, ds, dt, rb, gr;
 };
@@ -86,6 +88,7 @@ struct FarItem {
   int fqs;              // far sources per panel (qs; the split: 16, the nodes)
   int pt;               // the near/far split's item: far targets are points (its nodes), near
                         // pairs those of the gamma relation (at any gamma: g2 may underflow to 0)
+  int coef;             // order of the coefficients that the call returns, or -1 (it sums them)
   int V;                // vectors translated: kinds forward, then kinds backward
   int vf;               // of them forward (0 or nk)
   int slots;            // longest near list whose panel's center sums go through cpart
@@ -214,9 +217,10 @@ __host__ __device__ inline int near_subs(int qs) { return (qs + kWave - 1) / kWa
 // 285 / 322, 437 / 494.
 // Others: a batch's contours share the launches; the split's direct far pairs are cheap, but its
 // near passes came to the same walk (forward, S, p = 4: 64 panels 77, 96 panels 102, 128
-// panels 106 us); the expansion coefficients cost 140 us at any small size against 764 at 96
-// panels; a solve forms what it stores once.
+// panels 106 us); the coefficients have a rule of
+// their own (far_coef_size); a solve forms what it stores once.
 constexpr int kFarMinPanels = 96, kFarMinCoefPanels = 16, kFarMinSolvePanels = 64;
+constexpr int kFarMaxCoefOrder = 12;   // rows of qbx_coef_table.h
 constexpr double kFarMinFlops = 1.4e9;
 // From kFarGroupPanels panels on groups of four too, from kFarGroup8Panels on of eight.  The
 // second level costs its own multipoles, sums and evaluation (about 70 us at 256 panels,
@@ -242,7 +246,18 @@ constexpr double kFarBatchFlops = 2e10;
 inline bool far_applies_batch(const Dims& d, double work) {
   return d.P >= (work < kFarBatchFlops ? 160 : kFarMinPanels) && far_fits(d);
 }
-inline bool far_applies_coef(const Dims& d) { return d.P >= kFarMinCoefPanels && far_fits(d); }
+// Coefficients: near are 11 panels at p = 0, 23 at 6, 72 at 12 (qbx_coef_table.h), every one past
+// that.  The near pass splits its pairs over more waves than the one over all pairs: 8 panels,
+// S, p = 12: 139 us near, 103 all; 16 panels 113, 252; 256 panels 501, 2484; S + D, both sides,
+// 256 panels 1754, 4365.  Where every panel is near that ends with the size: p = 24, one side,
+// 256 panels 1732, 3396, 512 panels 6605, 6442; both sides 150 panels 3568, 4513, 256 panels
+// 7428, 7377.
+constexpr int kFarMaxAllNear = 320;    // panels times sides
+inline bool far_coef_size(const Dims& d) {
+  return d.P >= kFarMinCoefPanels &&
+         (d.p <= kFarMaxCoefOrder || d.P * d.n_sides <= kFarMaxAllNear);
+}
+inline bool far_applies_coef(const Dims& d) { return far_coef_size(d) && far_fits(d); }
 inline bool far_applies_solve(const Dims& d) { return d.P >= kFarMinSolvePanels && far_fits(d); }
 // the near/far split's far targets are points: no disk to look at
 inline bool far_applies_split(const Dims& d) { return d.P >= kFarMinPanels; }
@@ -295,6 +310,7 @@ template <typename Take>
 inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_items) {
   auto at = [&](size_t doubles) { return take(sizeof(double) * doubles) / sizeof(double); };
   *it = FarItem{};
+  it->coef = -1;
   it->P = d.P;
   it->g = d.P >= kFarGroup8Panels ? 8 : 4;
   it->C1 = d.P >= (n_items > 1 ? kFarGroupPanelsBatch : kFarGroupPanels) ? (d.P + it->g - 1) / it->g : 0;

@@ -1,18 +1,32 @@
 // Panel expansions: the far sums of the pair kernels (derivation in qbx_far.h).
 #include "qbx_far.h"
+#include "qbx_coef_table.h"
 #include "qbx_far_table.h"
 #include "qbx_special.h"
 
 namespace qbx {
 
 static __constant__ double g_zmin[fartab::kLen] = {QBX_FAR_ZMIN_24};
-static_assert(kFarQ == 24, "the table is for this order");
+static __constant__ double g_coef_zmin[2][coeftab::kP + 1][coeftab::kLen] = {
+    {QBX_COEF_ZMIN_SOURCE}, {QBX_COEF_ZMIN_TARGET}};
+static_assert(kFarQ == 24, "the tables are for this order");
+static_assert(kFarMaxCoefOrder == coeftab::kP, "a row for every order");
 
-// smallest k d that resolves a cluster of k radius x (rounded up to a table entry)
+// the entry of k radius x (rounded up), or infinity past the table
+__device__ __forceinline__ double far_entry(const double* tab, int i0, int steps, int len,
+                                            double x) {
+  const double s = ceil((log2(fmax(x, 1e-30)) - i0) * steps);
+  if (!(s < (double)len)) return 1e300;
+  return tab[s > 0.0 ? (int)s : 0];
+}
+// smallest k d that resolves a cluster of k radius x for the sums at the targets, and as
+// sources (side 0) or centers (side 1) for the coefficients up to order p (none past the table)
 __device__ __forceinline__ double far_zmin(double x) {
-  const double s = ceil((log2(fmax(x, 1e-30)) - fartab::kI0) * fartab::kSteps);
-  if (!(s < (double)fartab::kLen)) return 1e300;
-  return g_zmin[s > 0.0 ? (int)s : 0];
+  return far_entry(g_zmin, fartab::kI0, fartab::kSteps, fartab::kLen, x);
+}
+__device__ __forceinline__ double far_coef_zmin(int side, int p, double x) {
+  if (p > coeftab::kP) return 1e300;
+  return far_entry(g_coef_zmin[side][p], coeftab::kI0, coeftab::kSteps, coeftab::kLen, x);
 }
 
 __device__ __forceinline__ double wave_max(double v) {
@@ -59,7 +73,7 @@ __global__ __launch_bounds__(64) void k_far_recs(FarBlocks B, const double* __re
       for (int t = m0 * kQ + lane; t < m1 * kQ; t += kWave) {
         const CenterRec& C = ctr[(size_t)si * it.T + t];
         const double dx = C.cx - bx, dy = C.cy - by;
-        rt = fmax(rt, sqrt(dx * dx + dy * dy) + C.R);
+        rt = fmax(rt, sqrt(dx * dx + dy * dy) + (it.coef < 0 ? C.R : 0.0));
       }
   }
   if (group && it.pt) {
@@ -82,8 +96,8 @@ __global__ __launch_bounds__(64) void k_far_recs(FarBlocks B, const double* __re
     r.by = by;
     r.rs = rs;
     r.rt = rt;
-    r.ds = far_zmin(it.k * rs) / it.k;
-    r.dt = far_zmin(it.k * rt) / it.k;
+    r.ds = (it.coef < 0 ? far_zmin(it.k * rs) : far_coef_zmin(0, it.coef, it.k * rs)) / it.k;
+    r.dt = (it.coef < 0 ? far_zmin(it.k * rt) : far_coef_zmin(1, it.coef, it.k * rt)) / it.k;
     r.rb = rb;
     r.gr = gr;
     reinterpret_cast<FarRec*>(wo + (group ? it.rec1 : it.rec0))[c] = r;

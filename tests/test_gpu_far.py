@@ -240,3 +240,41 @@ def test_solve_products(c):
     wt = torch.from_numpy((w * np.hypot(t[..., 0], t[..., 1])).reshape(-1)).cuda()
     true = float((wt * r.abs() ** 2).sum().sqrt() / (wt * f.abs() ** 2).sum().sqrt())
     assert it == 6 and abs(true - res) < 1e-9 * true
+
+
+# a density on one panel: every center's coefficients come from far sources alone (or near ones
+# alone), so no near term hides an order that the expansions cut short.  Around the sizes from
+# which they take part, groups, the smallest and largest order with and without them
+LOCAL = [
+    dict(P=97, k=14.0, p=8, side=1, kind=3, os=1),
+    dict(P=232, k=20.0, p=12, side=0, kind=3, os=2),
+    dict(P=400, k=9.0, p=5, side=-1, kind=1, os=1),
+    dict(P=321, k=30.0, p=10, side=1, kind=2, os=3),
+    dict(P=40, k=12.0, p=0, side=0, kind=3, os=1),
+    dict(P=240, k=20.0, p=13, side=1, kind=1, os=1),
+    dict(P=161, k=20.0, p=13, side=0, kind=2, os=1),
+    dict(P=120, k=5.0, p=24, side=-1, kind=3, os=1),
+    dict(P=15, k=3.0, p=24, side=1, kind=1, os=1),
+]
+
+
+@pytest.mark.parametrize("c", LOCAL, ids=lambda c: "P{P}-p{p}-s{side}-{kind}-o{os}".format(**c))
+def test_coefficients_of_a_local_density(c):
+    """Every order of every center to the bars of expansion_bars.py."""
+    from expansion_bars import check_coefficients
+    from oracle import qbx_oracle as O
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), c["P"], c["k"], c["p"], c["side"],
+                        c["kind"], 29, oversample=c["os"])
+    local = np.zeros_like(pb.density)
+    local[:, 16 * 7:16 * 8] = pb.density[:, 16 * 7:16 * 8]
+    pb.density = local
+    nodes, dens = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (pb.nodes, local))
+    args = (pb.k, pb.p, pb.r, pb.oversample, pb.side, pb.kind)
+    sel = np.unique(np.linspace(0, pb.n_centers - 1, 97).astype(int))
+    ra, rC, rR = (t.numpy() for t in O.expansion_coefficients(pb.nodes, local, *args, centers=sel))
+    a, C, _ = (t.cpu().numpy() for t in qbx.expansion_coefficients(nodes, dens, *args))
+    a, C = a[:, sel], C[sel]
+    gap = max(float(np.hypot(*(C - rC).T).max()), 4 * np.spacing(np.abs(rC).max()))
+    check_coefficients(a, ra, pb, rC, rR, gap)
