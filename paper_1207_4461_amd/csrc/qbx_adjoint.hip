@@ -1,6 +1,7 @@
 // Adjoint kernels of libqbx: the forward-with-tape and source-major pair
 // loops (bodies and derivations in qbx_pair.h), the per-center gradients from
 // the tape, and the chain rule back to the 16-node panels.
+#include "qbx_far.h"
 #include "qbx_pair.h"
 #include "qbx_panel.h"
 
@@ -250,11 +251,13 @@ __global__ __launch_bounds__(256) void k_fused_center_grads(int Mc, int n_sb, in
 
 // 64 sources a block: the parts joined, then the gradients of source_grads_from_sums
 __global__ __launch_bounds__(256) void k_source_finalize(int N, int kind, int n_csplit,
+                                                         const FarItem* __restrict__ item,
                                                          const double4* __restrict__ geo,
                                                          const double2* __restrict__ partial,
                                                          double* __restrict__ sg) {
   double s[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
   int j;
+  if (item && far_off(*item)) n_csplit = item->n_cb;
   if (join_source_parts(N, kind, n_csplit, partial, &j, s))
     source_grads_from_sums(j, kind, geo, s, sg);
 }
@@ -420,7 +423,7 @@ hipError_t launch_adjoint_fused(const Dims& d, const double* nodes, const double
   hipLaunchKernelGGL(k_fused_center_grads, dim3((d.Mc + 255) / 256), dim3(256), 0, s, d.Mc,
                      d.n_sb, d.side, d.T, ctr, cpart, cg);
   hipLaunchKernelGGL(k_source_finalize, dim3((d.N + kWave - 1) / kWave), dim3(256), 0, s, d.N, d.kind,
-                     d.n_cb, geo, spartial, sg);
+                     d.n_cb, nullptr, geo, spartial, sg);
   hipLaunchKernelGGL(k_chain, dim3(d.P), dim3(128), 0, s, d, nodes, density, tables, sg, cg,
                      nullptr, nullptr, grad_density, grad_nodes);
   return hipGetLastError();
@@ -435,10 +438,11 @@ hipError_t launch_chain(const Dims& d, const double* nodes, const double* densit
   return hipGetLastError();
 }
 
-hipError_t launch_source_finalize(const Dims& d, int parts, const double4* geo,
-                                  const double2* spart, double* sg, hipStream_t s) {
+hipError_t launch_source_finalize(const Dims& d, int parts, const FarItem* item,
+                                  const double4* geo, const double2* spart, double* sg,
+                                  hipStream_t s) {
   hipLaunchKernelGGL(k_source_finalize, dim3((d.N + kWave - 1) / kWave), dim3(256), 0, s, d.N, d.kind,
-                     parts, geo, spart, sg);
+                     parts, item, geo, spart, sg);
   return hipGetLastError();
 }
 
@@ -466,7 +470,7 @@ hipError_t launch_adjoint_rest(const Dims& d, const double* nodes, const double*
   timer_end(1, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_source_finalize, dim3((d.N + kWave - 1) / kWave), dim3(256), 0, s, d.N, d.kind,
-                     d.n_csplit, geo, spartial, sg);
+                     d.n_csplit, nullptr, geo, spartial, sg);
   hipLaunchKernelGGL(k_chain, dim3(d.P), dim3(128), 0, s, d, nodes, density, tables, sg, cg,
                      nullptr, nullptr, grad_density, grad_nodes);
   return hipGetLastError();

@@ -336,6 +336,7 @@ FarItem far_item_of(const Dims& d, const Layout& L, bool full, bool fwd, bool bw
   it.partial = L.partial / sizeof(double);
   it.cg = L.cg / sizeof(double);
   it.spart = L.spart / sizeof(double);
+  it.tpart = L.cpart / sizeof(double);
   far_shape(&it, fwd, bwd);
   return it;
 }
@@ -392,7 +393,7 @@ static int run_adjoint_far(const Dims& d, const Layout& L, const double* nodes,
   int rc = prepare(d, L, nodes, density, ws, stream, &it);
   if (rc) return rc;
   double* w = static_cast<double*>(ws);
-  const FarItem* dev = at<FarItem>(ws, L.far);
+  FarItem* dev = at<FarItem>(ws, L.far);
   const FarBlocks one{dev, nullptr, 1};
   hipError_t e = launch_make_G(d, cotangent, at<double2>(ws, L.G), stream);
   if (e != hipSuccess) return device_fail(e, "cotangent kernel");
@@ -403,6 +404,9 @@ static int run_adjoint_far(const Dims& d, const Layout& L, const double* nodes,
   e = launch_near(geom ? kNearSources : kNearDensity, d.p, d.kind, one,
                   far_blocks(it, kStepChunks), w, nullptr, stream);
   if (geom && e == hipSuccess)
+    e = launch_near_tiles(d.p, d.kind, dev, 1, std::min(it.n_cb * it.n_sb, kFarTileBlocks), w,
+                          stream);
+  if (geom && e == hipSuccess)
     e = launch_near(kNearCenterSums, d.p, d.kind, one, far_blocks(it, kStepCenterSums), w, nullptr,
                     stream);
   if (geom && e == hipSuccess)
@@ -410,8 +414,8 @@ static int run_adjoint_far(const Dims& d, const Layout& L, const double* nodes,
                     stream);
   timer_end(geom ? 4 : 1, stream);
   if (e != hipSuccess) return device_fail(e, "near adjoint kernels");
-  e = launch_source_finalize(d, it.nsrc, at<double4>(ws, L.geo), at<double2>(ws, L.spart),
-                             at<double>(ws, L.sg), stream);
+  e = launch_source_finalize(d, it.nsrc, geom ? dev : nullptr, at<double4>(ws, L.geo),
+                             at<double2>(ws, L.spart), at<double>(ws, L.sg), stream);
   if (e == hipSuccess)
     e = launch_chain(d, nodes, density, at<double>(ws, L.tables), at<double>(ws, L.sg),
                      at<double>(ws, L.cg), nullptr, nullptr, grad_density, grad_nodes, stream);
@@ -539,6 +543,7 @@ static int split_start(const Dims& d, const Layout& L, const qbx_geometry* g,
                        Before&& before) {
   *it = far_item_of(d, L, true, fwd, bwd);
   it->g2 = g2;
+  it->off_pairs = kFarOffSplit * d.P * d.P;
   it->pt = 1;
   it->fqs = kQ;
   it->fgeo = L.ngeo / sizeof(double);
@@ -554,13 +559,12 @@ static int split_start(const Dims& d, const Layout& L, const qbx_geometry* g,
   c->nodes = g->nodes;
   c->bnd = at<double4>(ws, L.bnd);
   c->g2 = g2;
-  hipError_t e = launch_panel_bounds(d, g->nodes, at<double4>(ws, L.bnd), stream);
-  if (e != hipSuccess) return device_fail(e, "panel bounds kernel");
   c->ns.geo = at<double4>(ws, L.ngeo);
   c->ns.dens = at<double2>(ws, L.ndens);
   c->ns.w = at<double>(ws, L.nw);
-  e = launch_nystrom_sources(d, g->nodes, density, at<double>(ws, L.tables), c->ns, stream);
-  if (e != hipSuccess) return device_fail(e, "far source kernel");
+  hipError_t e = launch_nystrom_sources(d, g->nodes, density, at<double>(ws, L.tables),
+                                        at<double4>(ws, L.bnd), c->ns, stream);
+  if (e != hipSuccess) return device_fail(e, "panel bounds and far source kernel");
   e = launch_near_lists(d, at<double4>(ws, L.bnd), g2, at<int>(ws, L.ncount), at<int>(ws, L.nlist),
                         stream);
   if (e != hipSuccess) return device_fail(e, "near list kernel");
@@ -697,8 +701,8 @@ int qbx_layer_potential_split_adjoint(const qbx_geometry* g, const double* densi
                                   at<double>(ws, L.cg), at<double>(ws, L.gtw),
                                   at<double2>(ws, L.gde), stream);
   if (e == hipSuccess)
-    e = launch_source_finalize(d, it.nsrc, at<double4>(ws, L.geo), at<double2>(ws, L.spart),
-                               at<double>(ws, L.sg), stream);
+    e = launch_source_finalize(d, it.nsrc, nullptr, at<double4>(ws, L.geo),
+                               at<double2>(ws, L.spart), at<double>(ws, L.sg), stream);
   if (e == hipSuccess)
     e = launch_chain(d, g->nodes, density, at<double>(ws, L.tables), at<double>(ws, L.sg),
                      at<double>(ws, L.cg), at<double>(ws, L.gtw), at<double>(ws, L.gde),

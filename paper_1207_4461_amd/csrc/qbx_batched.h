@@ -24,6 +24,7 @@ struct BatchItemDev {
   long long cpart_off;   // doubles into the fused adjoint's center-side partial sums
   int far_parts;         // > 0: the call takes this contour's far pairs through panel expansions,
                          // and its source sums come in so many parts
+  int far_at;            // its far item
 };
 
 __device__ __forceinline__ int find_slot(const long long* __restrict__ pre, int n, long long t) {

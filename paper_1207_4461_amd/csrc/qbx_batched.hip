@@ -156,7 +156,7 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
     std::vector<int> mem;
     for (int i : sorted_members[c]) {
       BatchItemDev& B = P->items[i];
-      B.far_parts = 0;
+      B.far_parts = B.far_at = 0;
       if (far_applies_batch(B.d, work)) far_members[c].push_back(i);
       if (!use_far || !far_applies_batch(B.d, work)) mem.push_back(i);
     }
@@ -280,9 +280,11 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
       it.G = it.fG = P->o_G / 8 + 2 * B.G_off;
       it.cg = P->o_cg / 8 + 8 * B.ctr_off;
       it.spart = P->o_spart / 8 + 2 * B.spart_off;
+      it.tpart = P->o_cpart / 8 + B.cpart_off;
       far_shape(&it, fwd, bwd);
       if (use_far) {
         B.far_parts = it.nsrc;
+        B.far_at = (int)P->far.size();
         P->far.push_back(it);
       }
     }
@@ -388,7 +390,7 @@ __global__ __launch_bounds__(256) void k_fused_center_grads_batched(
   if (e >= total) return;
   const int it = find_slot(pre_ctr, n, e);
   const BatchItemDev& B = items[it];
-  if (B.far_parts > 0) return;   // written by k_near_centers
+  if (B.far_parts > 0) return;   // written by k_near_center_sums or k_near_centers
   const Dims& d = B.d;
   const int ci = (int)(e - pre_ctr[it]);
   double s[4] = {0.0, 0.0, 0.0, 0.0};
@@ -403,17 +405,19 @@ __global__ __launch_bounds__(256) void k_fused_center_grads_batched(
 
 __global__ __launch_bounds__(256) void k_source_finalize_batched(
     const BatchItemDev* __restrict__ items, const long long* __restrict__ pre_src, int n,
-    long long total, int fused, const double4* __restrict__ geo,
-    const double2* __restrict__ spart, double* __restrict__ sg) {
+    long long total, int fused, const FarItem* __restrict__ far,
+    const double4* __restrict__ geo, const double2* __restrict__ spart,
+    double* __restrict__ sg) {
   const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int it = find_slot(pre_src, n, e);
   const BatchItemDev& B = items[it];
-  // the source sums come in far_parts parts from the near passes, n_cb from the fused pass,
-  // n_csplit otherwise
+  // the source sums come in far_parts parts from the near passes, n_cb from the fused pass (and
+  // the fused tiles where the item's expansions are off), n_csplit otherwise
+  const bool near = B.far_parts > 0 && !(fused && far_off(far[B.far_at]));
   source_finalize_elem((int)(e - pre_src[it]), B.d.N, B.d.kind,
-                       B.far_parts > 0 ? B.far_parts : fused ? B.d.n_cb : B.d.n_csplit, geo + B.src_off, spart + B.spart_off,
-                       sg + B.src_off * 8);
+                       near ? B.far_parts : fused ? B.d.n_cb : B.d.n_csplit, geo + B.src_off,
+                       spart + B.spart_off, sg + B.src_off * 8);
 }
 
 __global__ __launch_bounds__(128) void k_chain_batched(
@@ -597,6 +601,17 @@ static hipError_t batch_near(const BatchPlan& P, size_t c, NearPass pass, FarSte
                      s);
 }
 
+// the fused tiles of those far items of class c whose expansions are off
+static hipError_t batch_tiles(const BatchPlan& P, size_t c, void* ws, hipStream_t s) {
+  const BatchClass& C = P.cls[c];
+  if (C.far_n == 0) return hipSuccess;
+  int most = 1;
+  for (int i = C.far_at; i < C.far_at + C.far_n; ++i)
+    most = std::max(most, P.far[i].n_cb * P.far[i].n_sb);
+  return launch_near_tiles(C.p, C.kind, wsp<FarItem>(ws, P.o_far) + C.far_at, C.far_n,
+                           std::min(most, kFarTileBlocks), static_cast<double*>(ws), s);
+}
+
 static int batch_forward(const BatchPlan& P, const double* nodes, double* out, double2* tape,
                          void* ws, hipStream_t s) {
   int rc = zero_counters(P, ws, s);
@@ -719,6 +734,7 @@ int qbx_layer_potential_batched_adjoint(const qbx_batch_item* items, int n_items
   for (size_t c = 0; c < P.cls.size() && ea == hipSuccess; ++c) {
     const hipStream_t sc = f.stream(c);
     ea = batch_near(P, c, geom ? kNearSources : kNearDensity, kStepChunks, ws, nullptr, sc);
+    if (geom && ea == hipSuccess) ea = batch_tiles(P, c, ws, sc);
     if (geom && ea == hipSuccess)
       ea = batch_near(P, c, kNearCenterSums, kStepCenterSums, ws, nullptr, sc);
     if (geom && ea == hipSuccess)
@@ -748,6 +764,7 @@ int qbx_layer_potential_batched_adjoint(const qbx_batch_item* items, int n_items
                        wsp<double>(ws, P.o_cpart), wsp<double>(ws, P.o_cg));
   hipLaunchKernelGGL(k_source_finalize_batched, blocks(nS, 256), dim3(256), 0, stream, it,
                      wsp<long long>(ws, P.o_pre_src), P.n, nS, fused ? 1 : 0,
+                     wsp<FarItem>(ws, P.o_far),
                      wsp<double4>(ws, P.o_geo), wsp<double2>(ws, P.o_spart),
                      wsp<double>(ws, P.o_sg));
   hipLaunchKernelGGL(k_chain_batched, dim3((unsigned)P.n_panels), dim3(128), 0, stream, it,

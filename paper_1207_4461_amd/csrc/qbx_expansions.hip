@@ -196,8 +196,8 @@ __global__ __launch_bounds__(256) void k_coef_near(FarBlocks B, const double* __
   const int qs = it.qs;
   CoefSums<P, KIND> A;
   coef_zero<P, KIND>(A);
-  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
-    for (int s = 4 * sp + (lane >> 4); s < qs; s += 4 * n_sp) {
+  for_near_runs(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan, int n) {
+    for (int s = 4 * sp + (lane >> 4); s < n * qs; s += 4 * n_sp) {
       const int j = pan * qs + s;
       coef_pair<P, KIND>(geo[j], q[j], qD[j], c.cx, c.cy, k, inv_k, sg, A);
     }
@@ -222,12 +222,14 @@ __global__ __launch_bounds__(256) void k_coef_near(FarBlocks B, const double* __
   if (lane < kQ) coef_store<P, KIND>(A, sp, half, ci, it.Mc, partial);
 }
 
-// coef[kk][ci][l + p] from the split sums; far: added to the far sums that coef holds already.
+// coef[kk][ci][l + p] from the split sums, added to the far sums that coef holds already where
+// the call has an item and its expansions are on.
 // A block has 16 centers of one kind: read by runs of centers, written by runs of orders.
 __global__ __launch_bounds__(256) void k_coef_finalize(int Mc, int p, int kind, int n_sp,
-                                                       double k, int far,
+                                                       double k, const FarItem* item,
                                                        const double2* __restrict__ partial,
                                                        double2* __restrict__ coef) {
+  const bool far = item && !far_off(*item);
   __shared__ double2 a[(2 * kPMax + 1) * 16];
   const int nk = kind == 3 ? 2 : 1, L = 2 * p + 1;
   const int kk = blockIdx.y, c0 = blockIdx.x * 16;
@@ -490,7 +492,8 @@ int qbx_expansion_coefficients(const qbx_geometry* g, const double* density, dou
                   at<double2>(ws, L.dens), ctr, n_sp, at<double2>(ws, E.part), stream);
   if (e != hipSuccess) return device_fail(e, "coefficient kernel");
   hipLaunchKernelGGL(k_coef_finalize, dim3((d.Mc + 15) / 16, d.nk), dim3(256), 0, stream, d.Mc,
-                     d.p, d.kind, n_sp, d.k, far ? 1 : 0, at<double2>(ws, E.part),
+                     d.p, d.kind, n_sp, d.k, dev,
+                     at<double2>(ws, E.part),
                      reinterpret_cast<double2*>(coef));
   if (ctr_xy || ctr_r)
     hipLaunchKernelGGL(k_center_out, dim3((d.Mc + 255) / 256), dim3(256), 0, stream, d.Mc, ctr,

@@ -81,7 +81,8 @@ __device__ __forceinline__ bool far_panels(const FarRel& R, int a, int b) {
   return far_adm(R.r0[a], R.r0[b]);
 }
 
-// One contour of a call.  Offsets count doubles from the workspace base.
+// One contour of a call.  Offsets count doubles from the workspace base.  Every call writes its
+// items anew; in heavy and next_tile (0 then) its kernels leave what the later ones decide by.
 struct FarItem {
   int P, C1, g;         // panels, groups (0: none), panels of a group (4 or 8)
   int T, N, qs, Mc, n_sides, nk, kind, p, NJ, side;
@@ -91,6 +92,10 @@ struct FarItem {
   int coef;             // order of the coefficients that the call returns, or -1 (it sums them)
   int V;                // vectors translated: kinds forward, then kinds backward
   int vf;               // of them forward (0 or nk)
+  int n_cb, n_sb, cblock, chunks, chunks_per_sb;   // the fused tiles (k_near_tiles)
+  unsigned long long heavy;   // near panels of the panels with many, added up (k_far_lists)
+  int next_tile;        // of the fused tiles
+  double off_pairs;     // the sum from which the expansions are off (far_off)
   int slots;            // longest near list whose panel's center sums go through cpart
   int nsrc;             // waves per 64-source chunk in the near source passes
   int n0, n1;           // blocks of sources per 64 target panels / groups
@@ -112,7 +117,38 @@ struct FarItem {
   size_t fs;                           // double2 [nk + 2][far sources]
   size_t cpart;                        // double [P][slots subs][n_sides kQ][4]: near center sums
   size_t partial, cg, spart;           // near outputs: gradient sums, center / source gradients
+  size_t tpart;                        // double [n_sb][Mc][4]: the fused tiles' center sums
 };
+
+// Expansions of one order do not resolve every contour: past k rt = 3.4 (about k h = 2.8 at
+// r = 0.5), and at the other end where the contour is smaller than 1e-3 / k, every panel is
+// near.  The host does not know the panels' sizes, so the lists decide on the device: where
+// the near lists hold off_pairs pairs of panels, the expansions' kernels return at once, and
+//  * forward, target derivatives, density adjoint and coefficients (from 0.9 P^2: translations
+//    for a few lanes each cost what the pairs do): the near passes take every pair, in one run;
+//  * the adjoint for the nodes, whose near passes evaluate the pairs of a panel twice when its
+//    list is longer than its slots (from 0.4 P^2; 0.5 where the slots hold half the panels):
+//    the fused tiles take every pair (k_near_tiles) and the near passes return too;
+//  * the near/far split (from 0.3 P^2): its direct far passes, which share a panel's pairs out
+//    over many waves, take the far pairs in place of k_split_mid.
+// 1024 panels, S, p = 16, k = 900, in ms, before the expansions / with them and without this
+// rule / now: forward 7.55 / 7.96 / 7.31, adjoint 14.4 / 30.7 / 14.1, split 0.71 / 2.28 /
+// 0.71, split's adjoint 2.08 / 4.59 / 1.88.  What it costs a resolved contour: 1 to 3 us a
+// forward, 5 to 10 an adjoint or a split (launches that return at once).  An unresolved forward
+// of 130 panels waits on the other launches: 0.19 ms before the expansions, 0.27, 0.23 now.
+//
+// Blocks of k_near_tiles, which takes tiles from a counter: what is resident (at most five on each
+// of 256 compute units).  A block per tile costs a resolved contour of 256 panels 16 us of 490,
+// these 6.
+constexpr int kFarTileBlocks = 1280;
+constexpr double kFarOffPass = 0.9, kFarOffAdjoint = 0.4, kFarOffAdjointSmall = 0.5,
+                 kFarOffSplit = 0.3;
+__device__ __forceinline__ bool far_off(const FarItem& it) {
+  return (double)it.heavy >= it.off_pairs;
+}
+// a panel whose list counts towards that: more than a quarter of the panels (13 to 15 are near
+// where the expansions resolve the contour), so that the common case adds nothing
+__device__ __forceinline__ bool far_heavy(int near, int P) { return 4 * (long long)near > P; }
 
 // item of a block: prefix sums of the items' block counts, or a single item
 struct FarBlocks {
@@ -152,6 +188,9 @@ int far_blocks(const FarItem& it, FarStep step);
 enum NearPass {
   kNearForward, kNearGradient, kNearSources, kNearCenterSums, kNearCenters, kNearDensity
 };
+// the fused tiles of those of the n items whose expansions are off, dealt out to `blocks` blocks
+hipError_t launch_near_tiles(int p, int kind, FarItem* items, int n, int blocks, double* ws,
+                             hipStream_t s);
 // the near pairs of alpha S - D (two-sided averages) as matrices over the nodes of near
 // panels, mat[P][cap][16 nodes][16 targets]; item dev with near lists, both sides and kinds
 hipError_t launch_near_matrix(int p, const FarItem* dev, int n_panels, int cap, const double* V,
@@ -179,7 +218,7 @@ hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fw
 // items that share the call's launches.
 template <typename Take>
 inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_items = 1);
-// vectors and translation shares of a call: fwd / bwd as in far_fields
+// vectors, translation shares and off_pairs of a call: fwd / bwd as in far_fields
 void far_shape(FarItem* it, bool fwd, bool bwd);
 
 hipError_t launch_far_recs(const FarBlocks& B, int blocks, const double* nodes, double* ws,
@@ -325,6 +364,11 @@ inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_
   it->p = d.p;
   it->NJ = d.NJ;
   it->side = d.side;
+  it->n_cb = d.n_cb;
+  it->n_sb = d.n_sb;
+  it->cblock = d.fused_cblock;
+  it->chunks = d.chunks;
+  it->chunks_per_sb = d.chunks_per_sb;
   const int Vmax = d.nk * (bwd ? 2 : 1);
   const size_t C0 = d.P, C1 = it->C1;
   it->rec0 = at(sizeof(FarRec) / sizeof(double) * C0);

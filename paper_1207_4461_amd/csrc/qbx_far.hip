@@ -197,6 +197,7 @@ __global__ __launch_bounds__(64) void k_far_p2m(FarBlocks B, const double* __res
   __shared__ double2 val[kFarW][kWave + 1];
   int b;
   const FarItem& it = *far_item(B, blockIdx.x, &b);
+  if (far_off(it)) return;
   const int lane = threadIdx.x;
   const bool group = b >= it.P;
   const int c = group ? b - it.P : b;
@@ -404,6 +405,7 @@ __global__ __launch_bounds__(256, 3) void k_far_m2l(FarBlocks B, const double* _
   __shared__ double2 red[kFarQ + 1][kWave];
   int b;
   const FarItem& it = *far_item(B, blockIdx.x, &b);
+  if (far_off(it)) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int C = GROUP ? it.C1 : it.P;
@@ -511,6 +513,7 @@ __global__ __launch_bounds__(256) void k_far_lsum(FarBlocks B, const double* __r
                                                   double* __restrict__ wo) {
   int b;
   const FarItem& it = *far_item(B, blockIdx.x, &b);
+  if (far_off(it)) return;
   const int per0 = (it.V * 2 * (kFarQ + 1) * it.P + 255) / 256;
   const bool group = b >= per0;
   if (group) b -= per0;
@@ -625,6 +628,7 @@ __global__ __launch_bounds__(256, 2) void k_far_eval(FarBlocks B, const double* 
   __shared__ double2 LP[kFarW][kWave];
   int b;
   const FarItem& it = *far_item(B, blockIdx.x, &b);
+  if (far_off(it)) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int sides = it.pt ? 1 : it.n_sides;
@@ -815,6 +819,7 @@ __global__ __launch_bounds__(256) void k_far_t(FarBlocks B, const double* __rest
   __shared__ double2 Wm[2 * kPMax + 1][kWave];
   int b;
   const FarItem& it = *far_item(B, blockIdx.x, &b);
+  if (far_off(it)) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int sides = it.pt ? 1 : it.n_sides;
@@ -915,6 +920,7 @@ __global__ __launch_bounds__(256) void k_far_rows(FarBlocks B, const double* __r
                                                   double* __restrict__ wo) {
   int b;
   const FarItem& it = *far_item(B, blockIdx.x, &b);
+  if (far_off(it)) return;
   const int per0 = (it.nk * it.P * kFarW + 255) / 256;
   const bool group = b >= per0;
   if (group) b -= per0;
@@ -953,6 +959,7 @@ __global__ __launch_bounds__(64) void k_far_src(FarBlocks B, const double* __res
                                                 double* __restrict__ wo, int geom) {
   int b;
   const FarItem& it = *far_item(B, blockIdx.x, &b);
+  if (far_off(it)) return;
   const int lane = threadIdx.x;
   const int per = (it.fqs + kWave - 1) / kWave;
   const int m = b / per;
@@ -1102,7 +1109,11 @@ __global__ __launch_bounds__(256) void k_far_lists(FarBlocks B, const double* __
     if (nr && pos < kNearCap) list[(size_t)m * kNearCap + pos] = mp;
     n += __popcll(mask);
   }
-  if (lane == 0) count[m] = n;
+  if (lane == 0) {
+    count[m] = n;
+    if (far_heavy(n, it.P))
+      atomicAdd(const_cast<unsigned long long*>(&it.heavy), (unsigned long long)n);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1117,6 +1128,17 @@ hipError_t launch_near(NearPass pass, int p, int kind, const FarBlocks& B, int b
   return kind == 1   ? launch_near_1(pass, p, B, blocks, ws, out, s)
          : kind == 2 ? launch_near_2(pass, p, B, blocks, ws, out, s)
                      : launch_near_3(pass, p, B, blocks, ws, out, s);
+}
+
+hipError_t launch_tiles_1(int, FarItem*, int, int, double*, hipStream_t);
+hipError_t launch_tiles_2(int, FarItem*, int, int, double*, hipStream_t);
+hipError_t launch_tiles_3(int, FarItem*, int, int, double*, hipStream_t);
+
+hipError_t launch_near_tiles(int p, int kind, FarItem* items, int n, int blocks, double* ws,
+                             hipStream_t s) {
+  return kind == 1   ? launch_tiles_1(p, items, n, blocks, ws, s)
+         : kind == 2 ? launch_tiles_2(p, items, n, blocks, ws, s)
+                     : launch_tiles_3(p, items, n, blocks, ws, s);
 }
 
 int far_blocks(const FarItem& it, FarStep step) {
@@ -1205,6 +1227,10 @@ void far_shape(FarItem* it, bool fwd, bool bwd) {
   it->V = it->vf + (bwd ? it->nk : 0);
   it->n0 = far_share(it->P, it->V, it->m2l_blocks, it->C1 > 0);
   it->n1 = it->C1 ? far_share(it->C1, it->V, it->m2l_blocks, false) : 1;
+  it->off_pairs = (!(fwd && bwd)                      ? kFarOffPass
+                   : it->P <= kNearSlotsSmallPanels ? kFarOffAdjointSmall
+                                                    : kFarOffAdjoint) *
+                  it->P * it->P;
 }
 
 hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fwd, bool bwd,

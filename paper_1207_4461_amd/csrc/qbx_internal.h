@@ -183,18 +183,18 @@ hipError_t launch_gradient_principal_value(int T, int nk, int side, int kind, co
                                            const double* grad, const double* dn,
                                            double* grad_pv, double* dn_pv, hipStream_t s);
 // ---- split forward (qbx_split.hip) ----
-// per panel {b_x, b_y, rad2, sqrt(rad2)}: the near relation's mean and squared
-// node radius, and the node radius
-hipError_t launch_panel_bounds(const Dims& d, const double* nodes, double4* bnd, hipStream_t s);
-// the Nystrom grid's far sources from the nodes, node densities and tables
+// bnd, per panel {b_x, b_y, rad2, sqrt(rad2)}: the near relation's mean and squared node
+// radius, and the node radius; ns: the Nystrom grid's far sources from the nodes, node densities
+// and tables
 hipError_t launch_nystrom_sources(const Dims& d, const double* nodes, const double* density,
-                                  const double* tables, NystromSources ns, hipStream_t s);
+                                  const double* tables, double4* bnd, NystromSources ns,
+                                  hipStream_t s);
 // the gamma near lists of every panel (count, list: NearLists' arrays)
 hipError_t launch_near_lists(const Dims& d, const double4* bnd, double g2, int* count, int* list,
                              hipStream_t s);
 // One split call.  far: panel expansions take the far pairs they reach (their sums lie in
-// the item's fu and fs) and the far passes the rest; otherwise the far passes take every
-// far pair, in n_fsplit / n_asplit parts.
+// the item's fu and fs) and the far passes the rest; otherwise, or where the lists turn the
+// expansions off (far_off), the far passes take every far pair, in n_fsplit / n_asplit parts.
 struct SplitCall {
   const Dims& d;
   const double* nodes;
@@ -204,6 +204,7 @@ struct SplitCall {
   bool far;
   const FarItem* dev;
   double* ws;
+  const FarItem* item() const { return far ? dev : nullptr; }
 };
 // direct sums over the far sources: values [parts][nk][T], target gradients
 // [parts][nk][T][2], the adjoint's source side [parts][nk (+ 2)][T]
@@ -234,9 +235,11 @@ hipError_t launch_chain(const Dims& d, const double* nodes, const double* densit
                         const double* tables, const double* sg, const double* cg,
                         const double* gtw, const double* gde, double* grad_density,
                         double* grad_nodes, hipStream_t s);
-// per-source gradients sg from the parts of the source-side sums
-hipError_t launch_source_finalize(const Dims& d, int parts, const double4* geo,
-                                  const double2* spart, double* sg, hipStream_t s);
+// per-source gradients sg from the parts of the source-side sums (item: n_cb where its
+// expansions are off)
+hipError_t launch_source_finalize(const Dims& d, int parts, const FarItem* item,
+                                  const double4* geo, const double2* spart, double* sg,
+                                  hipStream_t s);
 hipError_t launch_forward_tape(const Dims& d, const double4* geo, const double2* dens,
                                const CenterRec* ctr, const double* jtab, double2* partial,
                                hipStream_t s);

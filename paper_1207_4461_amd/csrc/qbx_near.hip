@@ -39,9 +39,9 @@ __global__ __launch_bounds__(256) void k_near_forward(FarBlocks B, const double*
   const int N = it.N, qs = it.qs;
   const double* Jtab = ro + it.jtab + (size_t)ci * it.NJ;
   double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
-  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
-    for (int s0 = 0; s0 < qs; s0 += kWave) {
-      if (s0 + lane < qs)
+  for_near_runs(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan, int n) {
+    for (int s0 = 0; s0 < n * qs; s0 += kWave) {
+      if (s0 + lane < n * qs)
         forward_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k,
                                 Jtab, sr, si, dr, di);
     }
@@ -60,10 +60,11 @@ __global__ __launch_bounds__(256) void k_near_forward(FarBlocks B, const double*
         partial[(size_t)kk * it.Mc + ci] = make_double2(v[kk].r, v[kk].i);
     } else {
       const double2* fu = reinterpret_cast<const double2*>(ro + it.fu);
+      const bool add = !far_off(it);
       const int s = ci / it.T, t = ci - s * it.T;
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) {
-        const double2 f = fu[(size_t)kk * it.Mc + ci];
+        const double2 f = add ? fu[(size_t)kk * it.Mc + ci] : make_double2(0.0, 0.0);
         double* o = out + it.out_off + 2 * (((size_t)s * NK + kk) * it.T + t);
         o[0] = -0.25 * (v[kk].i + f.y);   // (i/4)(near + far)
         o[1] = 0.25 * (v[kk].r + f.x);
@@ -99,9 +100,9 @@ __global__ __launch_bounds__(256) void k_near_grad(FarBlocks B, const double* __
   Cplx A[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a) A[a][0] = A[a][1] = {0.0, 0.0};
-  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
-    for (int s0 = 0; s0 < qs; s0 += kWave) {
-      if (s0 + lane < qs)
+  for_near_runs(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan, int n) {
+    for (int s0 = 0; s0 < n * qs; s0 += kWave) {
+      if (s0 + lane < n * qs)
         grad_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k, Jtab,
                              NJ / 2, Ltab, A);
     }
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(256) void k_near_grad(FarBlocks B, const double* __
     wave_sum(A[kk][1]);
   }
   if (lane == 0) {
-    const bool add = !it.pt;
+    const bool add = !it.pt && !far_off(it);
     const double2* fu = reinterpret_cast<const double2*>(ro + it.fu);
     double2* partial = reinterpret_cast<double2*>(wo + it.partial);
 #pragma unroll
@@ -148,8 +149,8 @@ __device__ __forceinline__ NearChunk near_chunk(const FarItem& it, int w) {
 // shares, left five with twice the work of the others: 1024 panels, p = 16, S: 349 us, 307 so.)
 struct CenterShare {
   int lo, hi, at;
-  __device__ __forceinline__ CenterShare(const NearChunk& c, const FarItem& it, NearLists nl) {
-    const long long units = (long long)nl.count[c.panel] * kQ;
+  __device__ __forceinline__ CenterShare(const NearChunk& c, const FarItem& it, int n_near) {
+    const long long units = (long long)n_near * kQ;
     lo = (int)(units * c.sp / it.nsrc);
     hi = (int)(units * (c.sp + 1) / it.nsrc);
     at = 0;
@@ -187,6 +188,7 @@ __global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double*
   const FarItem& it = *far_item(B, blockIdx.x, &b);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
+  if (!it.pt && far_off(it)) return;   // k_near_tiles
   const NearChunk c = near_chunk(it, b * 4 + wave);
   if (!c.on) return;
   const int N = it.N, qs = it.qs, T = it.T, Mc = it.Mc, NJ = it.NJ;
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double*
   Cplx A[NA];
 #pragma unroll
   for (int a = 0; a < NA; ++a) A[a] = {0.0, 0.0};
-  CenterShare share(c, it, nl);
+  CenterShare share(c, it, nl.count[c.panel]);
   for_near_panels(c.panel, near_rel(it, ro), it.P, nl, lane, [&](int m) {
     int c0, c1;
     if (!share.next(nc, &c0, &c1)) return;
@@ -260,7 +262,8 @@ __global__ __launch_bounds__(256) void k_near_sources(FarBlocks B, const double*
 }
 
 // Adjoint, center side of panels with slots: the slots in list order, plain: after the far
-// sums (fc); four lanes a center, then center_grad_from_sums.
+// sums (fc); four lanes a center, then center_grad_from_sums.  With the expansions off: the
+// fused tiles' sums of every center.
 template <int KIND>
 __global__ __launch_bounds__(256) void k_near_center_sums(FarBlocks B,
                                                           const double* __restrict__ ro,
@@ -272,13 +275,19 @@ __global__ __launch_bounds__(256) void k_near_center_sums(FarBlocks B,
   if (ci >= it.Mc) return;   // whole groups of four lanes
   const int si = ci / it.T, t = ci - si * it.T;
   const int m = t / kQ;
-  const int cnt = near_lists(it, ro).count[m];
-  if (cnt > it.slots) return;
-  const int subs = near_subs(it.qs), nc = it.n_sides * kQ;
-  const double* __restrict__ p =
-      ro + it.cpart + ((size_t)m * it.slots * subs * nc + si * kQ + (t - m * kQ)) * 4 + q;
-  double s = it.pt ? 0.0 : ro[it.fc + (size_t)ci * 4 + q];
-  for (int i = 0; i < cnt * subs; ++i) s += p[(size_t)i * nc * 4];
+  double s = 0.0;
+  if (!it.pt && far_off(it)) {
+    const double* __restrict__ p = ro + it.tpart + (size_t)ci * 4 + q;
+    for (int sb = 0; sb < it.n_sb; ++sb) s += p[(size_t)sb * it.Mc * 4];
+  } else {
+    const int cnt = near_lists(it, ro).count[m];
+    if (cnt > it.slots) return;
+    const int subs = near_subs(it.qs), nc = it.n_sides * kQ;
+    const double* __restrict__ p =
+        ro + it.cpart + ((size_t)m * it.slots * subs * nc + si * kQ + (t - m * kQ)) * 4 + q;
+    if (!it.pt) s = ro[it.fc + (size_t)ci * 4 + q];
+    for (int i = 0; i < cnt * subs; ++i) s += p[(size_t)i * nc * 4];
+  }
   const int l0 = threadIdx.x & ~3;
   const double s0 = __shfl(s, (l0 & 63)), s1 = __shfl(s, (l0 & 63) + 1),
                s2 = __shfl(s, (l0 & 63) + 2), s3 = __shfl(s, (l0 & 63) + 3);
@@ -302,6 +311,7 @@ __global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double*
   const int ci = b * 4 + wave;
   const int Mc = it.Mc;
   if (ci >= Mc) return;
+  if (!it.pt && far_off(it)) return;   // k_near_center_sums
   const int m = (ci % it.T) / kQ;
   if (near_lists(it, ro).count[m] <= it.slots) return;
   const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
@@ -318,9 +328,9 @@ __global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double*
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int q = 0; q < 5; ++q) A[a][q] = {0.0, 0.0};
-  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
-    for (int s0 = 0; s0 < qs; s0 += kWave) {
-      if (s0 + lane < qs)
+  for_near_runs(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan, int n) {
+    for (int s0 = 0; s0 < n * qs; s0 += kWave) {
+      if (s0 + lane < n * qs)
         tape_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k, Jtab,
                              nj, A);
     }
@@ -373,46 +383,49 @@ __global__ __launch_bounds__(256) void k_near_density(FarBlocks B, const double*
   const int n_sides = it.n_sides;
   double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
   const NearLists nl = near_lists(it, ro);
-  CenterShare share(c, it, nl);
-  for_near_panels(c.panel, near_rel(it, ro), it.P, nl, lane, [&](int m) {
-    int c0, c1;
-    if (!share.next(n_sides * kQ, &c0, &c1)) return;
-    for (int cc = c0; cc < c1; ++cc) {
-      const int si_ = cc / kQ;
-      const int ci = si_ * T + m * kQ + (cc - si_ * kQ);
-      const int z0 = opaque_zero();
-      const double* __restrict__ J = jtab + (size_t)ci * NJ + z0;
-      const double* __restrict__ cf = g_seed_table + z0;
-      const CenterRec* C = ctr + ci;
-      const double vx = g.x - C->cx, vy = g.y - C->cy;
-      const double rho2 = fma(vx, vx, vy * vy);
-      const double ir = rsqrt_refined(rho2);
-      const double rho = rho2 * ir;
-      const double cd = (C->ct * vx + C->st * vy) * ir;
-      const double sd = (C->st * vx - C->ct * vy) * ir;
-      double cps = 0.0, sps = 0.0;
-      if (kD) {
-        cps = C->ct * g.z + C->st * g.w;
-        sps = C->st * g.z - C->ct * g.w;
-      }
-      double ks_r, ks_i, kd_r, kd_i;
-      pair_kernel<P, KIND>(k * rho, ir * inv_k, cd, sd, cps, sps, J, cf, ks_r, ks_i, kd_r,
-                           kd_i);
-      int kk = 0;
-      if (kS) {
-        const double2 Gi = G[(size_t)(kk++) * Mc + ci];
-        sr = fma(Gi.x, ks_r, fma(-Gi.y, ks_i, sr));
-        si = fma(Gi.x, ks_i, fma(Gi.y, ks_r, si));
-      }
-      if (kD) {
-        const double2 Gi = G[(size_t)kk * Mc + ci];
-        dr = fma(Gi.x, kd_r, fma(-Gi.y, kd_i, dr));
-        di = fma(Gi.x, kd_i, fma(Gi.y, kd_r, di));
+  const NearRel R = near_rel(it, ro);
+  CenterShare share(c, it, R.all ? it.P : nl.count[c.panel]);
+  for_near_runs(c.panel, R, it.P, nl, lane, [&](int pan, int n) {
+    for (int m = pan; m < pan + n; ++m) {
+      int c0, c1;
+      if (!share.next(n_sides * kQ, &c0, &c1)) continue;
+      for (int cc = c0; cc < c1; ++cc) {
+        const int si_ = cc / kQ;
+        const int ci = si_ * T + m * kQ + (cc - si_ * kQ);
+        const int z0 = opaque_zero();
+        const double* __restrict__ J = jtab + (size_t)ci * NJ + z0;
+        const double* __restrict__ cf = g_seed_table + z0;
+        const CenterRec* C = ctr + ci;
+        const double vx = g.x - C->cx, vy = g.y - C->cy;
+        const double rho2 = fma(vx, vx, vy * vy);
+        const double ir = rsqrt_refined(rho2);
+        const double rho = rho2 * ir;
+        const double cd = (C->ct * vx + C->st * vy) * ir;
+        const double sd = (C->st * vx - C->ct * vy) * ir;
+        double cps = 0.0, sps = 0.0;
+        if (kD) {
+          cps = C->ct * g.z + C->st * g.w;
+          sps = C->st * g.z - C->ct * g.w;
+        }
+        double ks_r, ks_i, kd_r, kd_i;
+        pair_kernel<P, KIND>(k * rho, ir * inv_k, cd, sd, cps, sps, J, cf, ks_r, ks_i, kd_r,
+                             kd_i);
+        int kk = 0;
+        if (kS) {
+          const double2 Gi = G[(size_t)(kk++) * Mc + ci];
+          sr = fma(Gi.x, ks_r, fma(-Gi.y, ks_i, sr));
+          si = fma(Gi.x, ks_i, fma(Gi.y, ks_r, si));
+        }
+        if (kD) {
+          const double2 Gi = G[(size_t)kk * Mc + ci];
+          dr = fma(Gi.x, kd_r, fma(-Gi.y, kd_i, dr));
+          di = fma(Gi.x, kd_i, fma(Gi.y, kd_r, di));
+        }
       }
     }
   });
   if (valid) {
-    const bool plain = !it.pt;
+    const bool plain = !it.pt, add = plain && c.sp == 0 && !far_off(it);
     // the split sums near parts itself, [kk][j]; plain parts lie in the source-pass layout
     double2* part = reinterpret_cast<double2*>(wo + it.spart) +
                     (size_t)c.sp * (plain ? NA : (kS && kD ? 2 : 1)) * N;
@@ -420,13 +433,51 @@ __global__ __launch_bounds__(256) void k_near_density(FarBlocks B, const double*
     const double sg = plain ? -1.0 : 1.0;
     int kk = 0;
     if (kS) {
-      const double2 f = plain && c.sp == 0 ? fs[j] : make_double2(0.0, 0.0);
+      const double2 f = add ? fs[j] : make_double2(0.0, 0.0);
       part[j] = make_double2(sr + f.x, sg * si + f.y);
       ++kk;
     }
     if (kD) {
-      const double2 f = plain && c.sp == 0 ? fs[(size_t)kk * N + j] : make_double2(0.0, 0.0);
+      const double2 f = add ? fs[(size_t)kk * N + j] : make_double2(0.0, 0.0);
       part[(size_t)kk * N + j] = make_double2(k * dr + f.x, sg * k * di + f.y);
+    }
+  }
+}
+
+// Adjoint of items whose expansions are off: the fused tiles over every pair (fused_tile, the
+// parts and center sums of k_adjoint_fused), taken by resident blocks from the item's counter
+// (1024 panels, p = 16, S: 14.1 ms; dealt out in turn 16.7).  One launch beside the near passes;
+// where every item is resolved its blocks return after a look at each.  next: the items'
+// next_tile (apart from the items, which stay readable by scalar loads).
+template <int P, int KIND>
+__global__ __launch_bounds__(256) void k_near_tiles(const FarItem* __restrict__ items, int n,
+                                                    int* __restrict__ next,
+                                                    const double* __restrict__ ro,
+                                                    double* __restrict__ wo) {
+  constexpr int NA = src_slots(KIND);
+  constexpr int kItemInts = sizeof(FarItem) / sizeof(int);
+  __shared__ double acc[4 * fused_centers(KIND) * 4];
+  __shared__ int s_tile;
+  for (int i = 0; i < n; ++i) {
+    const FarItem& it = items[i];
+    if (!far_off(it)) continue;
+    const int tiles = it.n_cb * it.n_sb;
+    for (;;) {   // the counter passes the tile count: every block leaves
+      if (threadIdx.x == 0) s_tile = atomicAdd(next + i * kItemInts, 1);
+      __syncthreads();
+      const int b = s_tile;
+      __syncthreads();   // every thread has read s_tile before the next fetch
+      if (b >= tiles) break;
+      const int cb = b / it.n_sb, sb = b - cb * it.n_sb;
+      const int i0 = cb * it.cblock, ch0 = sb * it.chunks_per_sb;
+      fused_tile<P, KIND>(reinterpret_cast<const double4*>(ro + it.geo),
+                          reinterpret_cast<const double2*>(ro + it.dens), it.N,
+                          reinterpret_cast<const CenterRec*>(ro + it.ctr), ro + it.jtab, it.NJ,
+                          reinterpret_cast<const double2*>(ro + it.G), it.Mc, i0,
+                          min(it.cblock, it.Mc - i0), ch0,
+                          min(ch0 + it.chunks_per_sb, it.chunks), it.k,
+                          reinterpret_cast<double2*>(wo + it.spart) + (size_t)cb * NA * it.N,
+                          wo + it.tpart + (size_t)sb * it.Mc * 4, acc);
     }
   }
 }
@@ -549,12 +600,24 @@ static hipError_t launch_near_p(NearPass pass, const FarBlocks& B, int blocks, d
   return launch_near_pk<P, QBX_NEAR_KIND>(pass, B, blocks, ws, out, s);
 }
 
+template <int P>
+static hipError_t launch_tiles_p(FarItem* items, int n, int blocks, double* ws,
+                                 hipStream_t s) {
+  hipLaunchKernelGGL((k_near_tiles<P, QBX_NEAR_KIND>), dim3((unsigned)blocks), dim3(256), 0, s,
+                     items, n, &items->next_tile, ws, ws);
+  return hipGetLastError();
+}
+
 #define QBX_CAT2(a, b) a##b
 #define QBX_CAT(a, b) QBX_CAT2(a, b)
 hipError_t QBX_CAT(launch_near_, QBX_NEAR_KIND)(NearPass pass, int p, const FarBlocks& B,
                                                 int blocks, double* ws, double* out,
                                                 hipStream_t s) {
   QBX_P_SWITCH(p, launch_near_p, pass, B, blocks, ws, out, s)
+}
+hipError_t QBX_CAT(launch_tiles_, QBX_NEAR_KIND)(int p, FarItem* items, int n, int blocks,
+                                                 double* ws, hipStream_t s) {
+  QBX_P_SWITCH(p, launch_tiles_p, items, n, blocks, ws, s)
 }
 
 }  // namespace qbx

@@ -11,8 +11,8 @@
 //
 // Near pass (k_near_forward of qbx_near.hip): one wave per center over the sources of
 // its panel's near list.  Far pairs: from 96 panels on through panel expansions
-// (qbx_far.hip), and the few that none reaches by k_split_mid; below that by
-// k_split_far: the 64 lanes are 64 consecutive targets and the
+// (qbx_far.hip), and the few that none reaches by k_split_mid; below that, and where none
+// reaches many (far_off), by k_split_far: the 64 lanes are 64 consecutive targets and the
 // sources of a run of panels are wave-uniform (scalar loads); a far pair adds
 //     S: w sigma H_0(k rho),    D: w mu k H_1(k rho) (x - x').n' / rho,
 // rho = |x - x'|, the normal derivative of H_0(k|x - x'|) at the source (the
@@ -51,13 +51,9 @@ __global__ __launch_bounds__(256) void k_near_lists(int NP, const double4* __res
   if (lane == 0) count[m] = n;
 }
 
-// bnd[m] = {b_x, b_y, rad2, 0}
-__global__ __launch_bounds__(256) void k_panel_bounds(int NP, const double* __restrict__ nodes,
-                                                      double4* __restrict__ bnd) {
+// the panel's record {b_x, b_y, rad2, sqrt(rad2)} from its nodes
+__device__ __forceinline__ double4 panel_bounds(const double* __restrict__ X) {
 #pragma clang fp contract(off)
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= NP) return;
-  const double* X = nodes + (size_t)m * 2 * kQ;
   double sx = X[0], sy = X[1];
   for (int a = 1; a < kQ; ++a) {
     sx = sx + X[2 * a];
@@ -72,10 +68,11 @@ __global__ __launch_bounds__(256) void k_panel_bounds(int NP, const double* __re
   }
   // .w: the node radius, which bounds |x - x'| from below for a whole panel of
   // the far sources (the panel's nodes) at once
-  bnd[m] = make_double4(bx, by, r2, sqrt(r2));
+  return make_double4(bx, by, r2, sqrt(r2));
 }
 
-// The Nystrom grid as the far sources (one thread per node t = 16 m + a): the node
+// The panels' records (one thread of each panel's; a launch of their own took as long as this
+// one) and the Nystrom grid as the far sources (one thread per node t = 16 m + a): the node
 // itself, the outward normal n = (y', -x')/|X'| from the 16-node derivative (the
 // table's Dn rows, as for the centers), the 16-point Gauss-Legendre weight
 // w = omega_a |X'(tau_a)| (the table's w16) and the weighted node densities w sigma.
@@ -84,6 +81,7 @@ __global__ __launch_bounds__(256) void k_nystrom_sources(int T, int nk,
                                                          const double* __restrict__ density,
                                                          const double* __restrict__ Dn,
                                                          const double* __restrict__ w16,
+                                                         double4* __restrict__ bnd,
                                                          double4* __restrict__ ngeo,
                                                          double2* __restrict__ ndens,
                                                          double* __restrict__ nw) {
@@ -91,6 +89,7 @@ __global__ __launch_bounds__(256) void k_nystrom_sources(int T, int nk,
   if (t >= T) return;
   const int m = t / kQ, a = t - m * kQ;
   const double* X = nodes + (size_t)m * 2 * kQ;
+  if (a == 0) bnd[m] = panel_bounds(X);
   const double* Dr = Dn + a * kQ;
   double tx = 0.0, ty = 0.0;
   for (int c = 0; c < kQ; ++c) {
@@ -217,7 +216,9 @@ __global__ __launch_bounds__(256) void k_split_far(const double4* __restrict__ g
                                                    const double* __restrict__ nodes, int T,
                                                    const double4* __restrict__ bnd, int NP,
                                                    double g2, double k, int n_tb, int n_fsplit,
+                                                   const FarItem* __restrict__ item,
                                                    double2* __restrict__ partial) {
+  if (item && !far_off(*item)) return;   // k_split_mid
   constexpr bool kS = (KIND & 1) != 0;
   constexpr bool kD = (KIND & 2) != 0;
   constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
@@ -296,11 +297,19 @@ __global__ __launch_bounds__(256) void k_split_far(const double4* __restrict__ g
   }
 }
 
+// parts of the far sums: one with panel expansions (an item), the direct passes' n without or
+// where the expansions are off
+__device__ __forceinline__ int split_parts(int n, const FarItem* item) {
+  return item && !far_off(*item) ? 1 : n;
+}
+
 // out[si][kk][t] = (i/4) (near[kk][ci] + sum over far splits of far[sp][kk][t])
 __global__ __launch_bounds__(256) void k_split_finalize(int Mc, int T, int nk, int n_fsplit,
+                                                        const FarItem* __restrict__ item,
                                                         const double2* __restrict__ nearp,
                                                         const double2* __restrict__ farp,
                                                         double* __restrict__ out) {
+  n_fsplit = split_parts(n_fsplit, item);
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= Mc * nk) return;
   const int kk = e / Mc, ci = e - kk * Mc;
@@ -358,7 +367,8 @@ __global__ __launch_bounds__(256) void k_split_far_adj(
     const double4* __restrict__ geo, const double2* __restrict__ dens, int N,
     const double* __restrict__ nodes, int T, const double4* __restrict__ bnd, int NP, double g2,
     double k, const double2* __restrict__ Gf, int n_sb, int n_asplit,
-    double2* __restrict__ partial) {
+    const FarItem* __restrict__ item, double2* __restrict__ partial) {
+  if (item && !far_off(*item)) return;
   constexpr bool kS = (KIND & 1) != 0;
   constexpr bool kD = (KIND & 2) != 0;
   constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
@@ -453,10 +463,11 @@ __global__ __launch_bounds__(256) void k_split_far_adj(
 // near sources of panel m) + w_t conj(sum_sp partial[sp][kk][t]) (the far source
 // at node t = 16 m + a, weight w_t): one thread per node and kind
 __global__ __launch_bounds__(256) void k_split_density_grad(
-    int T, int N, int qs, int nk, int n_acc, int n_asplit, const double* __restrict__ tab,
-    const double* __restrict__ wgt, const double* __restrict__ nw,
+    int T, int N, int qs, int nk, int n_acc, int n_asplit, const FarItem* __restrict__ item,
+    const double* __restrict__ tab, const double* __restrict__ wgt, const double* __restrict__ nw,
     const double2* __restrict__ acc, const double2* __restrict__ partial,
     double* __restrict__ grad_density) {
+  n_asplit = split_parts(n_asplit, item);
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= T * nk) return;
   const TableLayout L = table_layout(qs);
@@ -511,11 +522,14 @@ __global__ __launch_bounds__(256) void k_split_density_grad(
 //    g_w = sum_kk Re(F_kk sigma_kk), gtw[t] = g_w omega_a X'/|X'| with X'/|X'| =
 //    (-n_y, n_x); gde[kk][t] = w conj(F_kk) joins the node density gradient.
 __global__ __launch_bounds__(256) void k_split_nystrom_grad(
-    int T, int nk, int n_fsplit, int n_asplit, const double* __restrict__ density,
+    int T, int nk, int n_fsplit, int n_asplit, const FarItem* __restrict__ item,
+    const double* __restrict__ density,
     const double4* __restrict__ ngeo, const double* __restrict__ nw,
     const double* __restrict__ w16, const double2* __restrict__ Gf,
     const double2* __restrict__ fpart, const double2* __restrict__ apart,
     double* __restrict__ cg, double* __restrict__ gtw, double2* __restrict__ gde) {
+  n_fsplit = split_parts(n_fsplit, item);
+  n_asplit = split_parts(n_asplit, item);
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= T) return;
   const int ns = nk + 2;
@@ -578,7 +592,9 @@ template <int KIND>
 __global__ __launch_bounds__(256) void k_split_far_grad(
     const double4* __restrict__ geo, const double2* __restrict__ dens, int N,
     const double* __restrict__ nodes, int T, const double4* __restrict__ bnd, int NP, double g2,
-    double k, int n_tb, int n_fsplit, double2* __restrict__ partial) {
+    double k, int n_tb, int n_fsplit, const FarItem* __restrict__ item,
+    double2* __restrict__ partial) {
+  if (item && !far_off(*item)) return;
   constexpr bool kS = (KIND & 1) != 0;
   constexpr bool kD = (KIND & 2) != 0;
   constexpr int NK = (kS ? 1 : 0) + (kD ? 1 : 0);
@@ -632,9 +648,11 @@ __global__ __launch_bounds__(256) void k_split_far_grad(
 // grad[si][kk][t][0..1] and dn[si][kk][t] from the near sums of center ci and the
 // far sums of its target
 __global__ __launch_bounds__(256) void k_split_finalize_gradient(
-    int Mc, int T, int nk, int n_fsplit, int side, const CenterRec* __restrict__ ctr,
+    int Mc, int T, int nk, int n_fsplit, const FarItem* __restrict__ item,
+    int side, const CenterRec* __restrict__ ctr,
     const double2* __restrict__ nearp, const double2* __restrict__ farp, double* __restrict__ grad,
     double* __restrict__ dn) {
+  n_fsplit = split_parts(n_fsplit, item);
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= Mc * nk) return;
   const int kk = e / Mc, ci = e - kk * Mc;
@@ -673,6 +691,7 @@ __global__ __launch_bounds__(256) void k_split_finalize_gradient(
 // already summed per target (fu) or per source (fs): one wave per panel walks the panels
 // that are left (few: between gamma panel radii and the expansions' reach), 16 lanes its
 // nodes, the four groups of 16 lanes a quarter of the other panel's nodes each.
+// Where no expansion reaches many of them (far_off), the direct passes take every far pair.
 // MODE 0: values, out[kk][t]; 1: target gradients, out[kk][t][0..1]; 2, 3: the adjoint's
 // source side without and with position and normal, out[kk (.. nk + 1)][j].
 // ---------------------------------------------------------------------------
@@ -687,7 +706,7 @@ __global__ __launch_bounds__(256) void k_split_mid(FarBlocks B, const double* __
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int m = b * 4 + wave;
-  if (m >= it.P) return;
+  if (m >= it.P || far_off(it)) return;
   const int T = it.T;
   const int me = m * kQ + (lane & 15), s0 = (lane >> 4) * 4;
   const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.fgeo);
@@ -791,16 +810,12 @@ static hipError_t launch_mid(const SplitCall& c, double2* out, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_panel_bounds(const Dims& d, const double* nodes, double4* bnd, hipStream_t s) {
-  hipLaunchKernelGGL(k_panel_bounds, dim3((d.P + 255) / 256), dim3(256), 0, s, d.P, nodes, bnd);
-  return hipGetLastError();
-}
-
 hipError_t launch_nystrom_sources(const Dims& d, const double* nodes, const double* density,
-                                  const double* tables, NystromSources ns, hipStream_t s) {
+                                  const double* tables, double4* bnd, NystromSources ns,
+                                  hipStream_t s) {
   const TableLayout L = table_layout(d.qs);
   hipLaunchKernelGGL(k_nystrom_sources, dim3((d.T + 255) / 256), dim3(256), 0, s, d.T, d.nk,
-                     nodes, density, tables + L.Dn, tables + L.w16, ns.geo, ns.dens, ns.w);
+                     nodes, density, tables + L.Dn, tables + L.w16, bnd, ns.geo, ns.dens, ns.w);
   return hipGetLastError();
 }
 
@@ -825,12 +840,15 @@ static dim3 far_grid(const Dims& d, int splits) {
 }
 
 hipError_t launch_split_far(const SplitCall& c, double2* out, hipStream_t s) {
-  if (c.far) return launch_mid<0>(c, out, s);
+  if (c.far) {
+    const hipError_t e = launch_mid<0>(c, out, s);
+    if (e != hipSuccess) return e;
+  }
   const Dims& d = c.d;
   const int n_tb = (d.T + kWave - 1) / kWave;
   const dim3 grid = far_grid(d, d.n_fsplit), block(256);
 #define QBX_FAR_ARGS \
-  c.ns.geo, c.ns.dens, d.T, c.nodes, d.T, c.bnd, d.P, c.g2, d.k, n_tb, d.n_fsplit, out
+  c.ns.geo, c.ns.dens, d.T, c.nodes, d.T, c.bnd, d.P, c.g2, d.k, n_tb, d.n_fsplit, c.item(), out
   switch (d.kind) {
     case 1: hipLaunchKernelGGL((k_split_far<1>), grid, block, 0, s, QBX_FAR_ARGS); break;
     case 2: hipLaunchKernelGGL((k_split_far<2>), grid, block, 0, s, QBX_FAR_ARGS); break;
@@ -840,7 +858,10 @@ hipError_t launch_split_far(const SplitCall& c, double2* out, hipStream_t s) {
 }
 
 hipError_t launch_split_far_grad(const SplitCall& c, double2* out, hipStream_t s) {
-  if (c.far) return launch_mid<1>(c, out, s);
+  if (c.far) {
+    const hipError_t e = launch_mid<1>(c, out, s);
+    if (e != hipSuccess) return e;
+  }
   const Dims& d = c.d;
   const int n_tb = (d.T + kWave - 1) / kWave;
   const dim3 grid = far_grid(d, d.n_fsplit), block(256);
@@ -855,13 +876,17 @@ hipError_t launch_split_far_grad(const SplitCall& c, double2* out, hipStream_t s
 
 hipError_t launch_split_far_adj(const SplitCall& c, bool geo, const double2* Gf, double2* out,
                                 hipStream_t s) {
-  if (c.far) return geo ? launch_mid<3>(c, out, s) : launch_mid<2>(c, out, s);
+  if (c.far) {
+    const hipError_t e = geo ? launch_mid<3>(c, out, s) : launch_mid<2>(c, out, s);
+    if (e != hipSuccess) return e;
+  }
   const Dims& d = c.d;
   const int n_sb = (d.T + kWave - 1) / kWave;
   const dim3 grid = far_grid(d, d.n_asplit), block(256);
 #define QBX_FADJ(KD, GEO)                                                                       \
   hipLaunchKernelGGL((k_split_far_adj<KD, GEO>), grid, block, 0, s, c.ns.geo, c.ns.dens, d.T,    \
-                     c.nodes, d.T, c.bnd, d.P, c.g2, d.k, Gf, n_sb, d.n_asplit, out)
+                     c.nodes, d.T, c.bnd, d.P, c.g2, d.k, Gf, n_sb, d.n_asplit, c.item(),   \
+                     out)
   switch (d.kind + (geo ? 4 : 0)) {
     case 1: QBX_FADJ(1, false); break;
     case 2: QBX_FADJ(2, false); break;
@@ -879,7 +904,7 @@ hipError_t launch_split_finalize(const SplitCall& c, const double2* nearp, const
   const Dims& d = c.d;
   const int n = d.Mc * d.nk;
   hipLaunchKernelGGL(k_split_finalize, dim3((n + 255) / 256), dim3(256), 0, s, d.Mc, d.T, d.nk,
-                     c.far ? 1 : d.n_fsplit, nearp, farp, out);
+                     d.n_fsplit, c.item(), nearp, farp, out);
   return hipGetLastError();
 }
 
@@ -889,7 +914,7 @@ hipError_t launch_split_finalize_gradient(const SplitCall& c, const CenterRec* c
   const Dims& d = c.d;
   const int n = d.Mc * d.nk;
   hipLaunchKernelGGL(k_split_finalize_gradient, dim3((n + 255) / 256), dim3(256), 0, s, d.Mc, d.T,
-                     d.nk, c.far ? 1 : d.n_fsplit, d.side, ctr, nearp, farp, grad, dn);
+                     d.nk, d.n_fsplit, c.item(), d.side, ctr, nearp, farp, grad, dn);
   return hipGetLastError();
 }
 
@@ -899,7 +924,7 @@ hipError_t launch_split_density_grad(const SplitCall& c, const double* tables, c
   const Dims& d = c.d;
   const int nt = d.T * d.nk;
   hipLaunchKernelGGL(k_split_density_grad, dim3((nt + 255) / 256), dim3(256), 0, s, d.T, d.N, d.qs,
-                     d.nk, n_acc, c.far ? 1 : d.n_asplit, tables, wgt, c.ns.w, acc, partial,
+                     d.nk, n_acc, d.n_asplit, c.item(), tables, wgt, c.ns.w, acc, partial,
                      grad_density);
   return hipGetLastError();
 }
@@ -911,7 +936,7 @@ hipError_t launch_split_nystrom_grad(const SplitCall& c, const double* density,
   const Dims& d = c.d;
   const TableLayout L = table_layout(d.qs);
   hipLaunchKernelGGL(k_split_nystrom_grad, dim3((d.T + 255) / 256), dim3(256), 0, s, d.T, d.nk,
-                     c.far ? 1 : d.n_fsplit, c.far ? 1 : d.n_asplit, density, c.ns.geo, c.ns.w,
+                     d.n_fsplit, d.n_asplit, c.item(), density, c.ns.geo, c.ns.w,
                      tables + L.w16, Gf, fpart, apart, cg, gtw, gde);
   return hipGetLastError();
 }

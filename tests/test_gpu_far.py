@@ -278,3 +278,46 @@ def test_coefficients_of_a_local_density(c):
     a, C = a[:, sel], C[sel]
     gap = max(float(np.hypot(*(C - rC).T).max()), 4 * np.spacing(np.abs(rC).max()))
     check_coefficients(a, ra, pb, rC, rR, gap)
+
+
+# contours that the expansions resolve in part or not at all: the lists turn them off on the
+# device.  Share of near pairs: 0.23 (all on), 0.54 (adjoint off; panels with more than 128 near
+# ones), 0.68 (panels with fewer), 0.84 with groups, 0.95 (all off), 1; both ends of k; P where a
+# run of 64 panels is not the last
+UNRESOLVED = [
+    dict(P=290, k=80.0, p=8, side=1, kind=1, os=4),
+    dict(P=290, k=84.0, p=6, side=0, kind=3, os=3),
+    dict(P=150, k=45.0, p=9, side=-1, kind=2, os=2),
+    dict(P=330, k=110.0, p=3, side=1, kind=3, os=1),
+    dict(P=290, k=110.0, p=5, side=0, kind=1, os=1),
+    dict(P=129, k=200.0, p=24, side=1, kind=1, os=5),
+    dict(P=322, k=1e-4, p=4, side=0, kind=3, os=1),
+]
+
+
+@pytest.mark.parametrize("c", UNRESOLVED,
+                         ids=lambda c: "P{P}-k{k}-p{p}-s{side}-{kind}-o{os}".format(**c))
+def test_unresolved_contours(c):
+    test_far_matches_pairs(c)
+
+
+def test_unresolved_contours_of_a_batch():
+    """Contours that are resolved, in part and not at all beside each other: against the tape path
+    (per order and kind one class; the first class has one of each)."""
+    from paper_1207_4461_amd import qbx
+
+    specs = [(290, 84.0, 6, 0, 3), (170, 5.0, 6, 1, 3), (165, 300.0, 6, -1, 3), (40, 5.0, 6, 0, 3),
+             (200, 111.0, 4, 1, 1), (161, 1e-4, 4, 0, 1)]
+    pbs = [I.make_problem("far", I.star((5, 0.25, 0.3)), P, k, p, side, kind, 41 + i,
+                          with_cotangent=True) for i, (P, k, p, side, kind) in enumerate(specs)]
+    B = qbx.Batch(pbs, oversample=4)
+    cot = B.pack_out([pb.cotangent for pb in pbs])
+    ref = B.split_out(B.forward(with_tape=True).clone())
+    rd, rn = (t.clone() for t in B.adjoint(cot, use_tape=True))
+    for u, r in zip(B.split_out(B.forward()), ref):
+        assert rel(u, r) < 1e-12
+    gd, gn = B.adjoint(cot, use_tape=False)
+    for a, r in zip(B.split_density(gd), B.split_density(rd)):
+        assert rel(a, r) < 1e-12
+    for a, r in zip(B.split_nodes(gn), B.split_nodes(rn)):
+        assert rel(a, r) < 1e-11
