@@ -115,8 +115,13 @@ int qbx_layer_potential(const qbx_geometry* g, const double* density, double k, 
 
 /* For callers that cannot allocate device memory (code under graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the plain forward of
- * qbx_layer_potential (no tape), same arguments and results, with no
- * workspace.  Its scratch arrays live in a file-scope device array of
+ * qbx_layer_potential (no tape), same arguments, with no workspace.  The
+ * results are bit for bit those of qbx_layer_potential as long as its arrays
+ * fit the scratch (for example up to 2300 panels, one side, S, p = 16; 1100
+ * panels, both sides, S+D, p = 20, oversample 4).  Beyond, sums are formed in
+ * another order and differ by rounding: up to about 4600 and 2300 panels the
+ * far pairs' sums in fewer parts (somewhat slower), past that pair by pair
+ * (many times slower).  Its scratch arrays live in a file-scope device array of
  * QBX_STATIC_SCRATCH_BYTES that every GPU the library runs on holds from the
  * module's load until the process ends; the call allocates and frees nothing.
  * The stream must belong to the current device.  All calls on one GPU share

@@ -216,8 +216,9 @@ Layout make_layout(const Dims& d) {
 // The arrays the plain forward alone uses (tables, source grid, centers, J
 // tables without the order-weighted block, forward partial sums), packed; the
 // other offsets are left at 0 and must not be used.
-Layout make_forward_layout(const Dims& d, bool far) {
+Layout make_forward_layout(const Dims& d, bool far, int m2l_blocks) {
   Layout L{};
+  L.m2l_blocks = m2l_blocks > 0 ? m2l_blocks : kFarM2LBlocks;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -235,7 +236,7 @@ Layout make_forward_layout(const Dims& d, bool far) {
   if (far) {
     L.far = take(sizeof(FarItem));
     FarItem it;
-    far_layout(d, false, take, &it);
+    far_layout(d, false, take, &it, 1, L.m2l_blocks);
   }
   L.total = o;
   return L;
@@ -325,7 +326,7 @@ FarItem far_item_of(const Dims& d, const Layout& L, bool full, bool fwd, bool bw
     return a;
   };
   FarItem it;
-  far_layout(d, full, take, &it);
+  far_layout(d, full, take, &it, 1, full ? kFarM2LBlocks : L.m2l_blocks);
   it.k = d.k;
   it.geo = it.fgeo = L.geo / sizeof(double);
   it.dens = it.fdens = L.dens / sizeof(double);

@@ -199,6 +199,12 @@ hipError_t launch_near_matrix(int p, const FarItem* dev, int n_panels, int cap, 
 hipError_t launch_near(NearPass pass, int p, int kind, const FarBlocks& B, int blocks,
                        double* ws, double* out, hipStream_t s);
 
+// Blocks of the translation that are resident at once (256 compute units, three each), and the
+// most shares of the sources a panel-level block takes when groups serve the rest (about 110
+// sources are left per 64 target panels).
+constexpr int kFarM2LBlocks = 768;
+constexpr int kFarMaxPanelShares = 16;
+
 // A call's items on the device and the grids of its steps.  One contour: the item in the
 // workspace and no prefix arrays; a batch: every step's prefix sums of block counts.
 struct FarPlan {
@@ -215,9 +221,11 @@ hipError_t far_fields(const FarPlan& P, const double* nodes, double* ws, bool fw
                       double2* coef = nullptr);
 // the offsets of an item's far arrays from take(bytes) (returning a byte offset), with
 // bwd those of the adjoint too; V, n0, n1 are then set per call (far_shape).  n_items: the
-// items that share the call's launches.
+// items that share the call's launches; m2l_blocks: the translation blocks of a single item, fewer
+// where their partial sums would not fit.
 template <typename Take>
-inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_items = 1);
+inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_items = 1,
+                       int m2l_blocks = kFarM2LBlocks);
 // vectors, translation shares and off_pairs of a call: fwd / bwd as in far_fields
 void far_shape(FarItem* it, bool fwd, bool bwd);
 
@@ -300,11 +308,6 @@ inline bool far_applies_coef(const Dims& d) { return far_coef_size(d) && far_fit
 inline bool far_applies_solve(const Dims& d) { return d.P >= kFarMinSolvePanels && far_fits(d); }
 // the near/far split's far targets are points: no disk to look at
 inline bool far_applies_split(const Dims& d) { return d.P >= kFarMinPanels; }
-// Blocks of the translation that are resident at once (256 compute units, three each), and the
-// most shares of the sources a panel-level block takes when groups serve the rest (about 110
-// sources are left per 64 target panels).
-constexpr int kFarM2LBlocks = 768;
-constexpr int kFarMaxPanelShares = 16;
 // Waves of the near source passes aimed for, and parts of a chunk's near source sums at most; half
 // of both in a batch, whose items fill the GPU together.  (8192 and 8, 16384 and 16: 1024
 // panels, p = 16, S: near adjoint 307 and 288 us; 4096 panels, S + D: 3.97 and 3.87 ms; the
@@ -346,7 +349,8 @@ inline size_t far_lp_doubles(int C, int Vmax, int blocks, bool inner) {
 }
 
 template <typename Take>
-inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_items) {
+inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_items,
+                       int m2l_blocks) {
   auto at = [&](size_t doubles) { return take(sizeof(double) * doubles) / sizeof(double); };
   *it = FarItem{};
   it->coef = -1;
@@ -378,7 +382,7 @@ inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_
   it->rows0 = at((size_t)Vmax * 2 * C0 * kFarW * 2);
   it->rows1 = at((size_t)Vmax * 2 * C1 * kFarW * 2);
   // a batch's items share the GPU: four times a single item's blocks between them
-  it->m2l_blocks = n_items > 1 ? (4 * kFarM2LBlocks + n_items - 1) / n_items : kFarM2LBlocks;
+  it->m2l_blocks = n_items > 1 ? (4 * kFarM2LBlocks + n_items - 1) / n_items : m2l_blocks;
   it->lp0 = at(far_lp_doubles(d.P, Vmax, it->m2l_blocks, it->C1 > 0));
   it->lp1 = at(it->C1 ? far_lp_doubles(it->C1, Vmax, it->m2l_blocks, false) : 0);
   it->ls0 = at((size_t)Vmax * C0 * kFarW * 2);

@@ -110,6 +110,7 @@ struct Layout {
   size_t gtw;      // double[T][2] split node adjoint: far weights' tangent gradients
   size_t gde;      // double2[nk][T] split node adjoint: far node density gradients
   size_t far;      // panel expansions (FarItem, then its arrays), or 0: the pair kernels alone
+  int m2l_blocks;  // their translation blocks (make_forward_layout)
   size_t total;
 };
 
@@ -146,8 +147,9 @@ int device_fail(hipError_t e, const char* where);
 size_t align256(size_t x);
 Layout make_layout(const Dims& d);
 // the plain forward's arrays only (tables ... partial), packed from offset 0; far: with
-// those of the panel expansions where they apply
-Layout make_forward_layout(const Dims& d, bool far);
+// those of the panel expansions where they apply, in m2l_blocks translation blocks (0: as many as
+// are resident)
+Layout make_forward_layout(const Dims& d, bool far, int m2l_blocks = 0);
 // tables, source grid and centers, then the plain forward and its finalize
 // into out, with the arrays of L (make_layout or make_forward_layout) in ws;
 // timed: bracket the pair kernel with the kernel timer's events when it is on

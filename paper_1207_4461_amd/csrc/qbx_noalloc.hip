@@ -64,8 +64,13 @@ extern "C" int qbx_layer_potential_noalloc(const qbx_geometry* g, const double* 
   if (rc) return rc;
   if (!density) return fail(QBX_EINVAL, "density is NULL");
   if (!out) return fail(QBX_EINVAL, "out is NULL");
-  // the expansions where their arrays fit too (they add rounding differences only)
+  // The expansions where their arrays fit too: as qbx_layer_potential forms them, else with
+  // fewer shares of the translations' sources, whose sums take most of it (the last: one share),
+  // else every pair.
   Layout L = make_forward_layout(d, far_applies(d));
+  for (int blocks = kFarM2LBlocks / 2;
+       L.far && L.total > (size_t)QBX_STATIC_SCRATCH_BYTES && blocks > 0; blocks /= 2)
+    L = make_forward_layout(d, true, blocks);
   if (L.total > (size_t)QBX_STATIC_SCRATCH_BYTES) L = make_forward_layout(d, false);
   if (L.total > (size_t)QBX_STATIC_SCRATCH_BYTES)
     return fail(QBX_EWORKSPACE,

@@ -81,3 +81,14 @@ def test_noalloc_rejects_a_problem_beyond_the_scratch(lib):
                                          big.oversample, big.side, big.kind, C.c_void_p(16),
                                          torch.cuda.current_stream(dev).cuda_stream)
     assert rc == _lib.QBX_EWORKSPACE and b"static scratch" in lib.qbx_last_error()
+
+
+@pytest.mark.parametrize("n_panels", [2200, 2600, 4680])
+def test_noalloc_where_the_scratch_is_short(lib, n_panels):
+    """S, one side, p = 16: the far sums as with a workspace (the same bits), in fewer parts, and
+    pair by pair; the last two differ by rounding (the bar of the far pairs' parity tests)."""
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), n_panels, 30.0, 16, 1, 1, 17)
+    say(f"no-alloc P={n_panels}")
+    a, b = _run_both(lib, pb)
+    assert np.abs(a - b).max() <= 1e-12 * np.abs(a).max()
+    assert n_panels > 2300 or np.array_equal(a, b)
