@@ -240,6 +240,14 @@ int qbx_layer_potential_split_adjoint(const qbx_geometry* g, const double* densi
 size_t qbx_solve_workspace_bytes(int n_panels, int q, int p, int oversample, int side,
                                  int restart);
 
+/* The least workspace that the solves accept: without the near pairs' weights
+ * (96 KB a panel from 64 panels on) that plain solves of r <= 1 store between
+ * their products.  With less than qbx_solve_workspace_bytes() each product of
+ * those is a call of the forward (256 panels: 0.25 ms for 0.10).  Split
+ * (gamma > 0), adjoint and r > 1 solves never use more than this. */
+size_t qbx_solve_workspace_bytes_least(int n_panels, int q, int p, int oversample, int side,
+                                       int restart);
+
 /* Nystrom solve of the Dirichlet problem by the combined-field representation
  * u = -D sigma + alpha S sigma (Section 4.3, eq. dirichlet-inteq):
  *   -+ sigma/2 + alpha S sigma - D sigma = f   at the nodes
@@ -261,7 +269,8 @@ size_t qbx_solve_workspace_bytes(int n_panels, int q, int p, int oversample, int
  *          the returned sigma (check it: the call returns QBX_OK also when
  *          max_iter ends the iteration first).
  * SYNCHRONOUS on `stream` (the Arnoldi coefficients come back to the host after
- * every product).  No allocation; the workspace is qbx_solve_workspace_bytes().
+ * every product).  No allocation; the workspace is qbx_solve_workspace_bytes(),
+ * or less (qbx_solve_workspace_bytes_least()).
  * Errors as qbx_layer_potential, plus QBX_EINVAL for side 0, restart, max_iter,
  * tol <= 0, gamma < 0 or a non-finite alpha. */
 int qbx_solve_dirichlet(const qbx_geometry* g, const double* f, double k, int p, double r,

@@ -325,7 +325,8 @@ __global__ __launch_bounds__(256) void k_stored_product(
 }
 
 struct SolveLayout {
-  size_t item, mat;   // the stored products' item and near weights
+  size_t item, mat;   // the stored products' item and near weights (last: a solve can do without)
+  size_t least;       // the total without them
   size_t fws, fws_bytes, tables, sw, dens, out, V, w, b, x, partial, h, total;
 };
 
@@ -350,6 +351,7 @@ static SolveLayout make_solve_layout(const Dims& d, int restart) {
   L.x = take(sizeof(double2) * T);
   L.partial = take(sizeof(double2) * ((T + kDotSlice - 1) / kDotSlice) * (size_t)(restart + 1));
   L.h = take(sizeof(double2) * (2 * (size_t)restart + 3));
+  L.least = o;
   const bool stored = d.P >= kFarMinSolvePanels;
   L.item = take(stored ? sizeof(FarItem) : 0);
   L.mat = take(stored ? sizeof(double2) * kQ * kQ * kStoredNear * (size_t)d.P : 0);
@@ -563,6 +565,14 @@ size_t qbx_solve_workspace_bytes(int n_panels, int q, int p, int oversample, int
   return make_solve_layout(d, restart).total;
 }
 
+size_t qbx_solve_workspace_bytes_least(int n_panels, int q, int p, int oversample, int side,
+                                       int restart) {
+  Dims d;
+  if (!qbx_solve_workspace_bytes(n_panels, q, p, oversample, side, restart)) return 0;
+  if (!make_dims(n_panels, q, p, oversample, QBX_BOTH, 3, 1.0, 0.5, &d)) return 0;
+  return make_solve_layout(d, restart).least;
+}
+
 }  // extern "C"
 
 namespace qbx {
@@ -590,8 +600,8 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
   if (!std::isfinite(alpha_re) || !std::isfinite(alpha_im))
     return fail(QBX_EINVAL, "alpha is not finite");
   const SolveLayout L = make_solve_layout(d, restart);
-  if (ws_bytes < L.total)
-    return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
+  if (ws_bytes < L.least)
+    return fail(QBX_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, L.least);
   Gmres G{g, d, L, static_cast<char*>(ws), stream, k, r, gamma, p, oversample,
           side == QBX_EXTERIOR ? -0.5 : 0.5, make_double2(alpha_re, alpha_im), adjoint, d.T,
           (d.T + 255) / 256, false, Layout{}, FarItem{}, FarItem{}};
@@ -617,7 +627,9 @@ static int solve(const qbx_geometry* g, const double* f, double k, int p, double
   int it = 0;
   double res = 0.0;
   if (bnorm > 0.0) {
-    if (!adjoint && gamma == 0.0 && far_applies_solve(d) && (rc = G.store_near())) return rc;
+    if (!adjoint && gamma == 0.0 && far_applies_solve(d) && ws_bytes >= L.total &&
+        (rc = G.store_near()))
+      return rc;
     std::vector<cplx> H((size_t)(m + 1) * m), gv(m + 1), cs(m), sn(m), y(m), h1(m + 1), h2(m + 1),
         buf(2 * m + 1);
     auto Hs = [&](int i, int j) -> cplx& { return H[(size_t)i * m + j]; };

@@ -307,6 +307,15 @@ def solve_workspace_bytes(n_panels: int, p: int, oversample: int, side: int, res
     return n
 
 
+def solve_workspace_bytes_least(n_panels: int, p: int, oversample: int, side: int,
+                                restart: int) -> int:
+    """The least that a solve accepts: without the near weights that plain solves store."""
+    n = _lib.load().qbx_solve_workspace_bytes_least(n_panels, Q, p, oversample, side, restart)
+    if n == 0:
+        raise ValueError("invalid solve parameters")
+    return n
+
+
 def _solve(fn, nodes, rhs, k, p, r, oversample, side, alpha, gamma, tol, restart, max_iter,
            workspace):
     lib = _lib.load()
@@ -315,7 +324,9 @@ def _solve(fn, nodes, rhs, k, p, r, oversample, side, alpha, gamma, tol, restart
     _need(rhs, "right-hand side", torch.complex128, (P * Q,))
     dev = nodes.device
     x = torch.empty(P * Q, dtype=torch.complex128, device=dev)
-    ws = _workspace(solve_workspace_bytes(P, p, oversample, side, restart), dev, workspace)
+    stores = fn == "qbx_solve_dirichlet" and gamma == 0.0 and r <= 1.0 and workspace is None
+    need = solve_workspace_bytes if stores else solve_workspace_bytes_least
+    ws = _workspace(need(P, p, oversample, side, restart), dev, workspace)
     geo = _lib.Geometry(P, Q, nodes.data_ptr())
     it, res = C.c_int(), C.c_double()
     a = complex(alpha)

@@ -152,6 +152,22 @@ def test_solve_entry_point_validates(lib):
     assert adj(side=0) == _lib.QBX_EINVAL and adj(nbytes=n - 1) == _lib.QBX_EWORKSPACE
 
 
+def test_solve_without_the_stored_weights(lib):
+    """From 64 panels on the least workspace leaves out 24 blocks of 16 x 16 weights a panel (and an
+    item of some hundred bytes); the solves refuse less, the adjoint and the split too."""
+    size = (16, 6, 4, 1, 50)
+    assert lib.qbx_solve_workspace_bytes_least(8, *size) == lib.qbx_solve_workspace_bytes(8, *size)
+    least, full = (f(64, *size) for f in (lib.qbx_solve_workspace_bytes_least,
+                                          lib.qbx_solve_workspace_bytes))
+    assert 0 < full - least - 64 * 24 * 256 * 16 <= 2048
+    assert lib.qbx_solve_workspace_bytes_least(64, 16, 6, 4, 0, 50) == 0
+    g = _lib.Geometry(64, 16, BAD)
+    for fn in (lib.qbx_solve_dirichlet, lib.qbx_solve_dirichlet_adjoint):
+        for gamma in (0.0, 6.0):
+            assert fn(C.byref(g), BAD, 3.0, 6, 0.5, 4, 1, 0.0, 1.0, gamma, 1e-14, 50, 100, BAD,
+                      None, None, BAD, least - 1, None) == _lib.QBX_EWORKSPACE
+
+
 def test_ext_entry_point_validates(lib):
     g = _lib.Geometry(8, 16, BAD)
 

@@ -321,3 +321,22 @@ def test_unresolved_contours_of_a_batch():
         assert rel(a, r) < 1e-12
     for a, r in zip(B.split_nodes(gn), B.split_nodes(rn)):
         assert rel(a, r) < 1e-11
+
+
+@pytest.mark.parametrize("short", [0, 1])
+def test_solve_in_the_least_workspace(short):
+    """A solve whose workspace has no room for the stored weights (by all of them, by one byte)
+    forms its products with the forward: the same density to the solve's tolerance."""
+    from paper_1207_4461_amd import qbx
+
+    P, p = 129, 8
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), P, 11.0, p, 0, 3, 17)
+    nodes, f = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (pb.nodes, pb.density[0]))
+    n = (qbx.solve_workspace_bytes(P, p, 4, 1, 60) - 1 if short else
+         qbx.solve_workspace_bytes_least(P, p, 4, 1, 60))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    kw = dict(tol=1e-12, restart=60, max_iter=60)
+    full, it, _ = qbx.solve_dirichlet(nodes, f, 11.0, p, **kw)
+    less, it2, res = qbx.solve_dirichlet(nodes, f, 11.0, p, workspace=ws, **kw)
+    assert res < 1e-11 and abs(it - it2) <= 1
+    assert rel(less, full) < 1e-9   # condition of a few times the two residuals
