@@ -361,9 +361,10 @@ def main():
     # per pair-kernel class: algorithmic flops per launch / average launch time
     # (the tape's passes take every pair; the others the near ones, panel expansions the rest)
     pairs = pb.n_centers * pb.n_sources
-    near = pairs
+    near = near_adj = pairs
     if flops.expansions_apply(pb.n_panels, pb.oversample, pb.n_sides, pb.p, pb.kind):
-        near = flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides, pb.side)
+        near, near_adj = (flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides,
+                                           pb.side, adjoint=adj) for adj in (False, True))
     names = ["forward pair kernel", "adjoint source pass", "batched persistent kernel",
              "forward-with-tape pair kernel", "fused adjoint pair kernel",
              "target-derivative pair kernel", "split near pass", "", ""]
@@ -372,7 +373,7 @@ def main():
                 flops.flops_grad_pair(pb.p, pb.kind), flops.flops_forward_pair(pb.p, pb.kind),
                 0, 0]   # the split's direct far pairs: the few that no expansion takes
     taped = mode == "fwdbwd" and args.backward == "tape"
-    pairs_of = [near, pairs if taped else near, 0, pairs, near, near, 0, 0, 0]
+    pairs_of = [near, pairs if taped else near, 0, pairs, near_adj, near, 0, 0, 0]
     if mode in ("split", "splitbwd"):
         pairs_of[6] = flops.split_pairs(pb.nodes, pb.oversample, pb.n_sides, args.gamma)[0]
     kernels = {}
@@ -675,14 +676,19 @@ def measure_random64(args, mode: str, backward: str, steps: int, warmup: int, au
     _lib.check(lib.qbx_kernel_timer_read(ms, nl))
     lib.qbx_kernel_timer(0)
     # algorithmic flops of the pair launches of one step (without a tape: of the near pairs)
-    near = [flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides, pb.side, True)
-            if flops.expansions_apply(pb.n_panels, pb.oversample, pb.n_sides, pb.p, pb.kind, True)
-            else pb.n_centers * pb.n_sources for pb in pbs]
+    work = sum(flops.all_pairs_work(pb.n_panels, pb.oversample, pb.n_sides, pb.p, pb.kind)
+               for pb in pbs)
+    near, near_adj = (
+        [flops.near_pairs(pb.nodes, pb.k, pb.r, pb.oversample, pb.n_sides, pb.side, True, adj)
+         if flops.expansions_apply(pb.n_panels, pb.oversample, pb.n_sides, pb.p, pb.kind, True,
+                                   work)
+         else pb.n_centers * pb.n_sources for pb in pbs] for adj in (False, True))
     if mode == "fwd":
         fl = sum(flops.flops_forward_pair(pb.p, pb.kind) * n for pb, n in zip(pbs, near))
     elif fused:
-        fl = sum((flops.flops_forward_pair(pb.p, pb.kind) + flops.flops_fused_pair(pb.p, pb.kind))
-                 * n for pb, n in zip(pbs, near))
+        fl = sum(flops.flops_forward_pair(pb.p, pb.kind) * n
+                 + flops.flops_fused_pair(pb.p, pb.kind) * m
+                 for pb, n, m in zip(pbs, near, near_adj))
     else:
         fl = sum((flops.flops_tape_pair(pb.p, pb.kind) + flops.flops_adjoint_pair(pb.p, pb.kind))
                  * pb.n_centers * pb.n_sources for pb in pbs)

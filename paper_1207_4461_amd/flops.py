@@ -239,7 +239,8 @@ def _far_zmin(x):
     import numpy as np
 
     path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "qbx_far_table.h")
-    txt = open(path).read()
+    with open(path) as f:
+        txt = f.read()
     i0, steps = (int(v) for v in re.search(r"kI0 = (-?\d+), kSteps = (\d+)", txt).groups())
     body = txt.split("#define QBX_FAR_ZMIN_24")[1].split("#define")[0]
     tab = np.array([float(v) for v in re.findall(r"[0-9][0-9.e+-]*", body)] + [1e300])
@@ -248,17 +249,25 @@ def _far_zmin(x):
 
 
 def expansions_apply(n_panels: int, oversample: int, n_sides: int, p: int, kind: int,
-                     batched: bool = False) -> bool:
-    """Whether a plain pass (r <= 1, centers at r h) takes its far pairs by panel expansions."""
-    pairs = (16 * n_panels) ** 2 * oversample * n_sides
-    work = pairs * flops_forward_pair(p, kind)
-    return n_panels >= 96 and (batched or work >= 1.4e9 * (1 + (2 if kind == 3 else 1)))
+                     batched: bool = False, batch_work: float = 2e10) -> bool:
+    """Whether a plain pass (r <= 1, centers at r h) takes its far pairs by panel expansions;
+    batch_work: the flops of a forward over every pair of the batch (all_pairs_work)."""
+    if batched:
+        return n_panels >= (160 if batch_work < 2e10 else 96)
+    work = all_pairs_work(n_panels, oversample, n_sides, p, kind)
+    return n_panels >= 96 and work >= 1.4e9 * (1 + (2 if kind == 3 else 1))
+
+
+def all_pairs_work(n_panels: int, oversample: int, n_sides: int, p: int, kind: int) -> int:
+    """Flops of a forward over every pair."""
+    return (16 * n_panels) ** 2 * oversample * n_sides * flops_forward_pair(p, kind)
 
 
 def near_pairs(nodes, k: float, r: float, oversample: int, n_sides: int, side: int,
-               batched: bool = False) -> int:
+               batched: bool = False, adjoint: bool = False) -> int:
     """Center-source pairs that are evaluated one by one where panel expansions take the others
-    (csrc/qbx_far.h; expansions_apply: whether a plain pass does)."""
+    (csrc/qbx_far.h; expansions_apply: whether a plain pass does): all of them where the lists
+    turn the expansions off (far_off; for the adjoint of the nodes from a smaller share on)."""
     import numpy as np
 
     X = np.asarray(nodes, dtype=np.float64).reshape(-1, 16, 2)
@@ -289,6 +298,7 @@ def near_pairs(nodes, k: float, r: float, oversample: int, n_sides: int, side: i
         ds, dt = _far_zmin(k * rs) / k, _far_zmin(k * rt) / k
         t = np.maximum.reduce([ds[:, None] + rt, rt[:, None] + ds, dt[:, None] + rs,
                                rs[:, None] + dt])
+        t = np.minimum(t, 1e150)   # "none": its square stays finite
         d = b[:, None] - b[None]
         return (d ** 2).sum(-1) >= t * t
 
@@ -296,4 +306,8 @@ def near_pairs(nodes, k: float, r: float, oversample: int, n_sides: int, side: i
     if P >= (128 if batched else 320):
         g = 8 if P >= 2048 else 4
         taken |= np.repeat(np.repeat(far(g), g, 0), g, 1)[:P, :P]
-    return int((~taken).sum()) * per_panel_pair
+    near = (~taken).sum(1)
+    share = 0.9 if not adjoint else 0.5 if P <= 256 else 0.4
+    if near[4 * near > P].sum() >= share * P * P:
+        return P * P * per_panel_pair
+    return int(near.sum()) * per_panel_pair

@@ -58,3 +58,27 @@ def test_expansions_apply():
     assert not F.expansions_apply(95, 8, 2, 24, 3) and F.expansions_apply(96, 4, 2, 12, 3)
     assert not F.expansions_apply(96, 3, 1, 4, 1) and F.expansions_apply(96, 3, 1, 4, 1, True)
     assert F.expansions_apply(4096, 1, 1, 0, 1)
+
+
+def test_expansions_apply_in_a_small_batch():
+    """A batch of less than 20 GFLOP over every pair takes them from 160 panels on."""
+    small = F.all_pairs_work(120, 4, 1, 6, 1)
+    assert small == (16 * 120) ** 2 * 4 * F.flops_forward_pair(6, 1) < 2e10
+    assert not F.expansions_apply(120, 4, 1, 6, 1, True, small)
+    assert F.expansions_apply(160, 4, 1, 6, 1, True, small)
+
+
+def test_near_pairs_where_the_expansions_are_off():
+    """Half of the pairs near: all of them for the adjoint, the near ones for the forward; the
+    distance of unresolved panels squares without a warning."""
+    import warnings
+
+    from paper_1207_4461_amd import inputs as I
+
+    pb = I.make_problem("near", I.star((5, 0.25, 0.3)), 290, 84.0, 6, 1, 1, 17)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        every = (290 * 16) ** 2 * 4
+        assert F.near_pairs(pb.nodes, 84.0, 0.5, 4, 1, 1, adjoint=True) == every
+        assert 0.4 * every < F.near_pairs(pb.nodes, 84.0, 0.5, 4, 1, 1) < 0.9 * every
+        assert F.near_pairs(pb.nodes, 300.0, 0.5, 4, 1, 1) == every
