@@ -271,7 +271,8 @@ int qbx_autotune(const qbx_geometry* g, const double* density, double k, int p, 
   if (!density) return fail(QBX_EINVAL, "density is NULL");
   if ((rc = valid_passes_fields(passes, fields))) return rc;
   // where panel expansions take the far pairs, the passes without a tape do not run the kernels
-  // that these two shape: times would differ by noise alone
+  // that these two shape (the fused tiles only where the contour turns them off): times would
+  // differ by noise alone
   if (far_applies(d)) fields &= ~(QBX_TUNE_FORWARD | QBX_TUNE_FUSED);
   qbx_tuning saved;
   qbx_get_tuning(&saved);

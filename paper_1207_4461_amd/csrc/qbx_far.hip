@@ -107,8 +107,9 @@ __global__ __launch_bounds__(64) void k_far_recs(FarBlocks B, const double* __re
 // J_l(x) = S_l (x/2)^l / l!.  The recurrence of J becomes
 // S_{l-1} = S_l - (x^2/4) / (l (l + 1)) S_{l+1}, which neither over- nor underflows;
 // started well above the orders wanted it gives S up to a factor, fixed by
-// 1 = J_0 + 2 (J_2 + J_4 + ...).  x is at most about 20 for a cluster that any distance
-// resolves at order kFarQ; others are not expanded (far_none).
+// 1 = J_0 + 2 (J_2 + J_4 + ...).  x is at most 2^1.75 = 3.4 for a cluster that
+// any distance resolves at order kFarQ (the table ends there: past it the first term left out is
+// above 1e-17 at every distance); others are not expanded (far_none).
 __device__ __forceinline__ int far_start(double x) {
   x = fmin(x, 64.0);   // bounded work for any argument
   return (int)(x + 16.0 + 4.0 * sqrt(x));

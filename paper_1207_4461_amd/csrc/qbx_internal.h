@@ -12,14 +12,14 @@ namespace qbx {
 
 constexpr int kQ = 16;      // nodes per panel
 constexpr int kWave = 64;   // CDNA wavefront
-// near/far split: capacity of a panel's near list; a panel with more near panels
-// is served by the scan of all panels instead
+// capacity of a panel's near list; a panel with more near panels is served by the scan of all
+// panels instead
 constexpr int kNearCap = 128;
 
-// per-panel near lists of the split: count[m] and, when count[m] <= kNearCap,
-// list[m * kNearCap + i], i < count[m], the panels near m in ascending order
 struct FarItem;   // qbx_far.h
 
+// per-panel near lists: count[m] and, when count[m] <= kNearCap, list[m * kNearCap + i],
+// i < count[m], the panels near m in ascending order
 struct NearLists {
   const int* count;
   const int* list;
@@ -150,12 +150,12 @@ Layout make_layout(const Dims& d);
 // those of the panel expansions where they apply, in m2l_blocks translation blocks (0: as many as
 // are resident)
 Layout make_forward_layout(const Dims& d, bool far, int m2l_blocks = 0);
-// tables, source grid and centers, then the plain forward and its finalize
-// into out, with the arrays of L (make_layout or make_forward_layout) in ws;
-// timed: bracket the pair kernel with the kernel timer's events when it is on
 // the item of a call's far sums on layout L (full: make_layout's offsets, else
 // make_forward_layout's); fwd, bwd as in far_fields
 FarItem far_item_of(const Dims& d, const Layout& L, bool full, bool fwd, bool bwd);
+// tables, source grid and centers, then the plain forward and its finalize
+// into out, with the arrays of L (make_layout or make_forward_layout) in ws;
+// timed: bracket the pair kernel with the kernel timer's events when it is on
 int run_forward(const Dims& d, const Layout& L, const double* nodes, const double* density,
                 double* out, void* ws, hipStream_t stream, bool timed = true);
 
