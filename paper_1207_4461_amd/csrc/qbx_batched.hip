@@ -200,6 +200,15 @@ static bool build_plan(const qbx_batch_item* items, int n, int oversample, Batch
       d.n_sb = (d.chunks + d.chunks_per_sb - 1) / d.chunks_per_sb;
       cost_x[i] = (double)d.fused_cblock;
     }
+    // a contour with expansions takes its tiles only where it turns them off, by itself
+    // (k_near_tiles): as many rows of them as its source sums have parts for the near passes
+    for (int i : far_members[c]) {
+      Dims& d = P->items[i].d;
+      d.fused_cblock = std::max(32, (d.Mc + kFarMaxShares - 1) / kFarMaxShares);
+      d.n_cb = (d.Mc + d.fused_cblock - 1) / d.fused_cblock;
+      d.chunks_per_sb = std::min(d.chunks, 4);
+      d.n_sb = (d.chunks + d.chunks_per_sb - 1) / d.chunks_per_sb;
+    }
     {
       std::vector<int> o = mem;
       std::stable_sort(o.begin(), o.end(), [&](int a, int b) { return cost_x[a] > cost_x[b]; });

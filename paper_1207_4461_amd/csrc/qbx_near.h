@@ -39,15 +39,11 @@ __device__ __forceinline__ NearLists near_lists(const FarItem& it, const double*
 
 // f(pan, n) for runs of n consecutive panels near panel m (wave-uniform), in ascending order:
 // the panels of m's list one by one when it fits, else the wave's scan of all NP panels, up to
-// 64 a run (a copy of f each: with one copy for the three the near passes took 5 to 10% longer)
+// 64 a run (a copy of f each: with one copy for both the near passes took 5 to 10% longer)
 template <typename F>
 __device__ __forceinline__ void for_near_runs(int m, const NearRel& R, int NP, NearLists nl,
                                                 int lane, F&& f) {
-  if (R.all) {
-    f(0, NP);
-    return;
-  }
-  const int cnt = nl.count[m];
+  const int cnt = R.all ? kNearCap + 1 : nl.count[m];
   if (cnt <= kNearCap) {
     const int* __restrict__ L = nl.list + (size_t)m * kNearCap;
     for (int i = 0; i < cnt; ++i) f(L[i], 1);
@@ -55,7 +51,7 @@ __device__ __forceinline__ void for_near_runs(int m, const NearRel& R, int NP, N
   }
   for (int w0 = 0; w0 < NP; w0 += kWave) {
     const int mp = w0 + lane;
-    const bool nr = mp < NP && is_near(R, m, mp);
+    const bool nr = mp < NP && (R.all || is_near(R, m, mp));
     unsigned long long mask = __ballot(nr);
     while (mask) {
       const int b0 = __builtin_ctzll(mask);

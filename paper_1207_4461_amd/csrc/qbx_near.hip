@@ -328,9 +328,9 @@ __global__ __launch_bounds__(256) void k_near_centers(FarBlocks B, const double*
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int q = 0; q < 5; ++q) A[a][q] = {0.0, 0.0};
-  for_near_runs(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan, int n) {
-    for (int s0 = 0; s0 < n * qs; s0 += kWave) {
-      if (s0 + lane < n * qs)
+  for_near_panels(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan) {
+    for (int s0 = 0; s0 < qs; s0 += kWave) {
+      if (s0 + lane < qs)
         tape_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k, Jtab,
                              nj, A);
     }
