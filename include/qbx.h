@@ -639,7 +639,8 @@ size_t qbx_autotune_workspace_bytes(int n_panels, int q, int p, int oversample, 
  * the result with qbx_set_tuning and writes it to *best (nullable).  Other
  * fields are left as they were, and so are forward_waves and fused_tiles where
  * panel expansions take the problem's far pairs (from about 100 panels on at
- * r <= 1): they do not shape the passes that run there.  On error the previous
+ * r <= 1): they do not shape the passes that run there (fused_tiles only
+ * those of a contour that the expansions do not resolve).  On error the previous
  * tuning is restored.
  *   ws, ws_bytes  device workspace of qbx_autotune_workspace_bytes() bytes: all
  *                 device memory the timing uses (nothing is allocated)

@@ -141,9 +141,8 @@ def ulp_sensitivity(Q, pb, gd, gn, **kw):
 
 
 def test_adjoint_star4096_sampled_panels(Q):
-    """The fused adjoint at the bench workload's full size (4096 panels, tile height
-    1024 under the default partial-sum bound, so every tile runs four sub-blocks),
-    element by element on three panels against the oracle (bars: see parity_helpers;
+    """The adjoint at the bench workload's full size (4096 panels: panel expansions and near
+    passes), element by element on three panels against the oracle (bars: see parity_helpers;
     the S density gradient and the node gradient meet the plain bars)."""
     pb = I.star4096()
     say(f"star4096: P={pb.n_panels} p={pb.p} kind={pb.kind} side={pb.side}")

@@ -15,8 +15,8 @@ from paper_1207_4461_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-# panels around the least count (96) and pairs around the least work, the 64-cluster blocks, the groups of eight (from 512 on) and
-# their remainders; every kind and side; smallest and largest order and oversampling;
+# panels around the least count (96) and pairs around the least work, the 64-cluster blocks, groups
+# of four (from 320 on) and their remainders; every kind and side; smallest and largest order and oversampling;
 # wavenumbers that no distance resolves (every pair near) and that reach the table's lower end
 CASES = [
     dict(P=95, k=5.0, p=8, side=1, kind=1, os=4),
