@@ -408,3 +408,32 @@ def test_batched_expansions_of_both_sides_and_kinds():
         assert rel(u, qbx.layer_potential(nodes, dens, *args)) < 1e-12
         rd, rn = qbx.layer_potential_vjp(nodes, dens, cot, *args)
         assert rel(a, rd) < 1e-12 and rel(x, rn) < 1e-11
+
+
+@pytest.mark.parametrize("P,k", [(150, 300.0), (290, 84.0), (128, 5.0)])
+def test_replays_decide_anew(P, k):
+    """Captured calls replayed with other contours in the same buffers: what the lists add up and
+    the tiles' counter start from zero in every replay."""
+    from paper_1207_4461_amd import qbx
+
+    pb = I.make_problem("far", I.star((5, 0.25, 0.3)), P, k, 6, 1, 3, 17, with_cotangent=True)
+    nodes, dens, cot = (torch.from_numpy(np.ascontiguousarray(a)).cuda()
+                        for a in (pb.nodes, pb.density, pb.cotangent))
+    args = (pb.k, pb.p, pb.r, pb.oversample, pb.side, pb.kind)
+
+    def calls(x):
+        return [qbx.layer_potential(x, dens, *args), *qbx.layer_potential_vjp(x, dens, cot, *args),
+                qbx.layer_potential_split(x, dens, *args, gamma=6.0)]
+
+    X = nodes.clone()
+    calls(X)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = calls(X)
+    for scale in (1.0, 1.0, 0.05, 6.0, 1.0):      # k times the panel size with it
+        X.copy_(nodes * scale)
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, calls(nodes * scale)):
+            assert torch.equal(a, b)
