@@ -438,7 +438,7 @@ static int run_forward_far(const Dims& d, const Layout& L, const double* nodes,
   if (e != hipSuccess) return device_fail(e, "panel expansion kernels");
   if (timed) timer_begin(0, stream);
   e = launch_near(kNearForward, d.p, d.kind, FarBlocks{dev, nullptr, 1},
-                  far_blocks(it, kStepCenters), w, out, stream);
+                  far_blocks(it, kStepNear), w, out, stream);
   if (timed) timer_end(0, stream);
   return e == hipSuccess ? QBX_OK : device_fail(e, "near forward kernel");
 }
@@ -546,6 +546,7 @@ static int split_start(const Dims& d, const Layout& L, const qbx_geometry* g,
   it->g2 = g2;
   it->off_pairs = kFarOffSplit * d.P * d.P;
   it->pt = 1;
+  it->quad = 0;
   it->fqs = kQ;
   it->fgeo = L.ngeo / sizeof(double);
   it->fdens = L.ndens / sizeof(double);
@@ -735,7 +736,7 @@ int qbx_layer_potential_gradient(const qbx_geometry* g, const double* density, d
     if (e != hipSuccess) return device_fail(e, "panel expansion kernels");
     timer_begin(5, stream);
     e = launch_near(kNearGradient, d.p, d.kind, FarBlocks{dev, nullptr, 1},
-                    far_blocks(it, kStepCenters), w, nullptr, stream);
+                    far_blocks(it, kStepNear), w, nullptr, stream);
     timer_end(5, stream);
     if (e != hipSuccess) return device_fail(e, "near target-derivative kernel");
     Dims one = d;   // a single partial sum per center

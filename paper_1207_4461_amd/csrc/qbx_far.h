@@ -97,6 +97,8 @@ struct FarItem {
   int next_tile;        // of the fused tiles
   double off_pairs;     // the sum from which the expansions are off (far_off)
   int slots;            // longest near list whose panel's center sums go through cpart
+  int quad;             // with the expansions off, a block per center in the near passes over
+                        // centers (a contour whose waves would not fill the GPU)
   int nsrc;             // waves per 64-source chunk in the near source passes
   int n0, n1;           // blocks of sources per 64 target panels / groups
   int m2l_blocks;       // translation blocks aimed for
@@ -134,9 +136,11 @@ struct FarItem {
 // 1024 panels, S, p = 16, k = 900, in ms, before the expansions / with them and without this
 // rule / now: forward 7.55 / 7.96 / 7.31, adjoint 14.4 / 30.7 / 14.1, split 0.71 / 2.28 /
 // 0.71, split's adjoint 2.08 / 4.59 / 1.88.  What it costs a resolved contour: 1 to 3 us a
-// forward, 5 to 10 an adjoint or a split (launches that return at once).  An unresolved forward
-// of 130 panels waits on the other launches: 0.19 ms before the expansions, 0.27, 0.23 now.
+// forward, 5 to 10 an adjoint or a split (launches that return at once).
 //
+// Contours below kFarQuadCenters centers: one wave a center is too few (130 panels, S + D, p = 8, k =
+// 200: near pass 225 us, a block a center 167, the pair loop's split waves 151).
+constexpr int kFarQuadCenters = 8192;
 // Blocks of k_near_tiles, which takes tiles from a counter: what is resident (at most five on each
 // of 256 compute units).  A block per tile costs a resolved contour of 256 panels 16 us of 490,
 // these 6.
@@ -178,6 +182,7 @@ enum FarStep {
   kStepTargets,    // 64 targets of one side
   kStepRows, kStepSources, kStepLists,
   kStepCenters,    // four centers, one wave each (qbx_near.hip)
+  kStepNear,       // the same, or a block per center (quad)
   kStepChunks,     // four shares of the chunks of 64 sources of a panel (qbx_near.hip)
   kStepCenterSums, // 64 centers, four lanes each (qbx_near.hip)
 };
@@ -396,6 +401,7 @@ inline void far_layout(const Dims& d, bool bwd, Take&& take, FarItem* it, int n_
     it->cpart = at((size_t)it->slots * near_subs(d.qs) * d.Mc * 4);
     it->fs = at((size_t)(d.nk + 2) * d.N * 2);
   }
+  it->quad = n_items == 1 && d.Mc < kFarQuadCenters;
   // a chunk's list is cut into at most kFarMaxShares
   const long long chunks = (long long)d.P * near_subs(d.qs) * n_items;
   const int waves = n_items > 1 ? kFarSourceWaves / 2 : kFarSourceWaves;

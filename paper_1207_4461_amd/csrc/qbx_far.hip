@@ -1157,6 +1157,7 @@ int far_blocks(const FarItem& it, FarStep step) {
     case kStepSources: return it.P * ((it.fqs + kWave - 1) / kWave);
     case kStepLists: return (it.P + 3) / 4;
     case kStepCenters: return (it.Mc + 3) / 4;
+    case kStepNear: return it.quad ? it.Mc : (it.Mc + 3) / 4;
     case kStepChunks: return (it.P * near_subs(it.qs) * it.nsrc + 3) / 4;
     case kStepCenterSums: return (it.Mc + 63) / 64;
   }

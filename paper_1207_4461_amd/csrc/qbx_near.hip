@@ -15,6 +15,19 @@
 
 namespace qbx {
 
+// v[0..2 N) of every wave's lane 0 added in wave order into the first's
+template <int N>
+__device__ __forceinline__ void join_waves(double* v, int wave, int lane) {
+  __shared__ double part[4][2 * N];
+  if (lane == 0)
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i) part[wave][i] = v[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2 * N; ++i)
+    v[i] = ((part[0][i] + part[1][i]) + part[2][i]) + part[3][i];
+}
+
 // Values.  Plain: out = (i/4) (near + far), the far sums of k_far_eval; split: the near
 // sums alone into partial[kk][ci] (its finalize adds the far rule's).
 template <int P, int KIND>
@@ -28,8 +41,10 @@ __global__ __launch_bounds__(256) void k_near_forward(FarBlocks B, const double*
   const FarItem& it = *far_item(B, blockIdx.x, &b);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int ci = b * 4 + wave;
+  const bool quad = it.quad && far_off(it);
+  const int ci = quad ? b : b * 4 + wave;
   if (ci >= it.Mc) return;
+  const int first = quad ? wave * kWave : 0, step = quad ? 4 * kWave : kWave;
   const int m = (ci % it.T) / kQ;                 // the target's panel
   const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
   const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
@@ -40,7 +55,7 @@ __global__ __launch_bounds__(256) void k_near_forward(FarBlocks B, const double*
   const double* Jtab = ro + it.jtab + (size_t)ci * it.NJ;
   double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
   for_near_runs(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan, int n) {
-    for (int s0 = 0; s0 < n * qs; s0 += kWave) {
+    for (int s0 = first; s0 < n * qs; s0 += step) {
       if (s0 + lane < n * qs)
         forward_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k,
                                 Jtab, sr, si, dr, di);
@@ -49,10 +64,11 @@ __global__ __launch_bounds__(256) void k_near_forward(FarBlocks B, const double*
   Cplx S = {sr, si}, Dd = {k * dr, k * di};
   if (kS) wave_sum(S);
   if (kD) wave_sum(Dd);
-  if (lane == 0) {
-    Cplx v[2];
-    v[0] = kS ? S : Dd;
-    v[1] = Dd;
+  Cplx v[2];
+  v[0] = kS ? S : Dd;
+  v[1] = Dd;
+  if (quad) join_waves<2>(&v[0].r, wave, lane);
+  if (lane == 0 && !(quad && wave > 0)) {
     if (it.pt) {
       double2* partial = reinterpret_cast<double2*>(wo + it.partial);
 #pragma unroll
@@ -85,9 +101,11 @@ __global__ __launch_bounds__(256) void k_near_grad(FarBlocks B, const double* __
   const FarItem& it = *far_item(B, blockIdx.x, &b);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int ci = b * 4 + wave;
+  const bool quad = it.quad && far_off(it);
+  const int ci = quad ? b : b * 4 + wave;
   const int Mc = it.Mc, NJ = it.NJ;
   if (ci >= Mc) return;
+  const int first = quad ? wave * kWave : 0, step = quad ? 4 * kWave : kWave;
   const int m = (ci % it.T) / kQ;
   const double4* __restrict__ geo = reinterpret_cast<const double4*>(ro + it.geo);
   const double2* __restrict__ dens = reinterpret_cast<const double2*>(ro + it.dens);
@@ -101,7 +119,7 @@ __global__ __launch_bounds__(256) void k_near_grad(FarBlocks B, const double* __
 #pragma unroll
   for (int a = 0; a < 2; ++a) A[a][0] = A[a][1] = {0.0, 0.0};
   for_near_runs(m, near_rel(it, ro), it.P, near_lists(it, ro), lane, [&](int pan, int n) {
-    for (int s0 = 0; s0 < n * qs; s0 += kWave) {
+    for (int s0 = first; s0 < n * qs; s0 += step) {
       if (s0 + lane < n * qs)
         grad_source<P, KIND>(geo, dens, N, pan * qs + s0 + lane, cx, cy, ct, st, k, inv_k, Jtab,
                              NJ / 2, Ltab, A);
@@ -112,7 +130,8 @@ __global__ __launch_bounds__(256) void k_near_grad(FarBlocks B, const double* __
     wave_sum(A[kk][0]);
     wave_sum(A[kk][1]);
   }
-  if (lane == 0) {
+  if (quad) join_waves<4>(&A[0][0].r, wave, lane);
+  if (lane == 0 && !(quad && wave > 0)) {
     const bool add = !it.pt && !far_off(it);
     const double2* fu = reinterpret_cast<const double2*>(ro + it.fu);
     double2* partial = reinterpret_cast<double2*>(wo + it.partial);
