@@ -138,8 +138,8 @@ struct FarItem {
 // 0.71, split's adjoint 2.08 / 4.59 / 1.88.  What it costs a resolved contour: 1 to 3 us a
 // forward, 5 to 10 an adjoint or a split (launches that return at once).
 //
-// Contours below kFarQuadCenters centers: one wave a center is too few (130 panels, S + D, p = 8, k =
-// 200: near pass 225 us, a block a center 167, the pair loop's split waves 151).
+// Contours below kFarQuadCenters centers: one wave a center is too few (130 panels, S + D, p = 8,
+// k = 200: near pass 225 us, a block a center 167, the pair loop's split waves 151).
 constexpr int kFarQuadCenters = 8192;
 // Blocks of k_near_tiles, which takes tiles from a counter: what is resident (at most five on each
 // of 256 compute units).  A block per tile costs a resolved contour of 256 panels 16 us of 490,
